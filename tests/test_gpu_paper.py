@@ -94,3 +94,38 @@ def test_paper_mode_edges(ctx):
     flags = ctx.paper_search(t, pat, 32)
     pos = ctx.paper_positions(flags).cpu().numpy().astype(np.uint64)
     assert pos.tolist() == oracle.search(text, [pat])[1].tolist()
+
+
+@pytest.mark.parametrize("nf", [1, 15, 16, 17, 4095, 4096, 4097, 16383, 16384, 16385, 16384 * 3 + 4096 + 5])
+def test_positions_of_any_nonzero_bytes(ctx, nf):
+    """The positions of a flag array at the edges of a thread's 16 flags, a
+    round and a block, with flags of any nonzero value, none at all and all
+    set, at every alignment of the array; equal to numpy's."""
+    g = rkgen.rng(72, nf)
+    values = g.integers(1, 256, size=nf, dtype=np.uint8)
+    for density in (0.0, 0.001, 0.3, 1.0):
+        f = np.where(g.random(nf) < density, values, 0).astype(np.uint8)
+        f[-1] = 128
+        for shift in (0, 1, 7):
+            t = torch.zeros(nf + shift, dtype=torch.uint8, device="cuda:0")
+            t[shift:] = torch.from_numpy(f).to("cuda:0")
+            pos = ctx.paper_positions(t[shift:]).cpu().numpy()
+            assert np.array_equal(pos, np.nonzero(f)[0]), (density, shift)
+
+
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 9, 12, 15, 16, 17, 19, 22, 26, 31, 32, 33, 64, 257])
+def test_paper_mode_hash_at_the_text_end(ctx, m):
+    """Hashes of every window of short texts of every length near m, 16 and
+    32, where the 16-byte loads of the last windows would pass the end; the
+    text starts at any byte of its buffer."""
+    g = rkgen.rng(73, m)
+    for n in sorted({m, m + 1, m + 14, m + 15, m + 16, m + 17, m + 31, m + 33, 300 + m}):
+        text = rkgen.iid_text(g, n, rkgen.BYTE256)
+        shift = int(g.integers(0, 16))
+        buf = torch.zeros(n + shift, dtype=torch.uint8, device="cuda:0")
+        buf[shift:] = torch.from_numpy(text).to("cuda:0")
+        pat = text[n - m:].tobytes()
+        flags, hs = ctx.paper_search(buf[shift:], pat, 64, hashes=True)
+        ref = oracle.window_hashes(text, m, np.arange(n - m + 1, dtype=np.uint64), d=2, q=1 << 32)
+        assert np.array_equal(hs.cpu().numpy().astype(np.uint64), ref), n
+        assert np.array_equal(flags.cpu().numpy(), expect_flags(text, pat)), n
