@@ -13,15 +13,18 @@
 namespace rk {
 
 // ---------------------------------------------------------- prefix sums (u64)
-// Exclusive scan of u32 counts into u64 offsets: per-block sums, then
-// per-block local scans that start from the sum of the blocks before them,
-// which up to kScanWG blocks add up themselves and beyond that a single-block
-// scan of the sums (scan_sums_single) hands them.  Every block is kScanWG
-// threads: a scan of one step is not held back until a whole CU is free while
-// another step's scan fills the chip.
+// Exclusive scan of u32 counts into u64 offsets: per-block local scans that
+// start from the sum of the counts before them.  Up to kScanSelf blocks add
+// the counts up themselves (the last one reads 240 KB, about 3 us, less than
+// one more launch), up to kScanWG blocks the per-block sums of a kernel before
+// (scan_block_sums), and beyond that a single-block scan of the sums
+// (scan_sums_single) hands them.  Every block is kScanWG threads: a scan of
+// one step is not held back until a whole CU is free while another step's
+// scan fills the chip.
 constexpr int kScanWG = 256;
 constexpr int kScanPer = 16;
 constexpr int kScanBlock = kScanWG * kScanPer;  // items per block
+constexpr uint64_t kScanSelf = 16;              // most blocks that add up the counts before them
 
 __global__ __launch_bounds__(kScanWG) void scan_block_sums(const uint32_t *in, uint64_t n, uint64_t *bsum) {
   __shared__ uint64_t red[kScanWG / 64];
@@ -77,18 +80,34 @@ __global__ __launch_bounds__(kScanWG) void scan_sums_single(uint64_t *bsum, uint
   }
 }
 
-// RAW: bsum holds the blocks' own sums (at most kScanWG blocks), each block
-// adds those before it, and the last one writes the total (bsum[nb], and
-// *total_out if non-null); else bsum is already scanned.
-template <bool RAW>
+// How a block of scan_local gets the sum before it.
+enum ScanPrefix { kPrefixScanned, kPrefixSums, kPrefixCounts };
+
+// kPrefixScanned: bsum is already scanned; kPrefixSums: bsum holds the blocks'
+// own sums (at most kScanWG blocks), each block adds those before it;
+// kPrefixCounts: each block adds the counts before it (in 16-byte aligned).
+// But for the first, the last block writes the total (*total_out if non-null).
+template <ScanPrefix FROM>
 __global__ __launch_bounds__(kScanWG) void scan_local(const uint32_t *in, uint64_t n, uint64_t *bsum, uint64_t nb,
                                                       uint64_t *out, uint64_t *total_out) {
   __shared__ uint64_t wsum[kScanWG / 64];
   __shared__ uint64_t pre[kScanWG / 64];
   const uint64_t base = (uint64_t)blockIdx.x * kScanBlock;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (RAW) {
-    uint64_t p = threadIdx.x < blockIdx.x ? bsum[threadIdx.x] : 0;
+  if (FROM != kPrefixScanned) {
+    uint64_t p = 0;
+    if (FROM == kPrefixSums) {
+      p = threadIdx.x < blockIdx.x ? bsum[threadIdx.x] : 0;
+    } else {
+      const uint4 *q = (const uint4 *)in + threadIdx.x;
+      for (uint32_t b = 0; b < blockIdx.x; ++b, q += kScanBlock / 4) {
+#pragma unroll
+        for (int j = 0; j < kScanBlock / 4 / kScanWG; ++j) {
+          const uint4 v = q[j * kScanWG];
+          p += (uint64_t)v.x + v.y + v.z + v.w;
+        }
+      }
+    }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) p += __shfl_xor(p, d, 64);
     if (lane == 0) pre[wave] = p;
@@ -111,7 +130,7 @@ __global__ __launch_bounds__(kScanWG) void scan_local(const uint32_t *in, uint64
   if (lane == 63) wsum[wave] = x;
   __syncthreads();
   uint64_t before = 0;
-  if (RAW) {
+  if (FROM != kPrefixScanned) {
 #pragma unroll
     for (int k = 0; k < kScanWG / 64; ++k) before += pre[k];
   } else {
@@ -126,10 +145,7 @@ __global__ __launch_bounds__(kScanWG) void scan_local(const uint32_t *in, uint64
     if (i < n) out[i] = run;
     run += v[j];
   }
-  if (RAW && blockIdx.x == nb - 1 && threadIdx.x == kScanWG - 1) {
-    bsum[nb] = run;
-    if (total_out) *total_out = run;
-  }
+  if (FROM != kPrefixScanned && total_out && blockIdx.x == nb - 1 && threadIdx.x == kScanWG - 1) *total_out = run;
 }
 
 // ------------------------------------------------------------ slab compaction
@@ -555,13 +571,6 @@ hipError_t launch_fill_u32(uint32_t *p, uint64_t words, uint32_t v, hipStream_t 
   return hipGetLastError();
 }
 
-uint32_t scan_lds_bytes(int cfg, uint32_t img_cap) {
-  const TileCfg c = kTileCfgs[cfg];
-  const uint32_t W = c.wg * c.c;
-  const uint32_t tile = (kFront + W + 16 + 15) & ~15u;
-  return 2 * tile + kCandCap * 2 + 64 * 4 + img_cap;  // two tile slots
-}
-
 // exclusive scan of n u32 counts into u64 offsets; tmp holds scan_tmp_words(n)
 // u64; *total_dev (optional) receives the sum.
 uint64_t scan_tmp_words(uint64_t n) { return (n + kScanBlock - 1) / kScanBlock + 2; }
@@ -569,27 +578,21 @@ uint64_t scan_tmp_words(uint64_t n) { return (n + kScanBlock - 1) / kScanBlock +
 hipError_t launch_exclusive_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, uint64_t *total_dev,
                                  hipStream_t s) {
   const uint64_t nb = (n + kScanBlock - 1) / kScanBlock;
+  if (nb > 0 && nb <= kScanSelf && ((uintptr_t)in & 15u) == 0) {
+    hipLaunchKernelGGL((scan_local<kPrefixCounts>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp, nb, out,
+                       total_dev);
+    return hipGetLastError();
+  }
   if (nb > 0) hipLaunchKernelGGL(scan_block_sums, dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp);
   if (nb > 0 && nb <= (uint64_t)kScanWG) {
-    hipLaunchKernelGGL((scan_local<true>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp, nb, out, total_dev);
+    hipLaunchKernelGGL((scan_local<kPrefixSums>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp, nb, out,
+                       total_dev);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(scan_sums_single, dim3(1), dim3(kScanWG), 0, s, tmp, nb, total_dev);
   if (nb > 0)
-    hipLaunchKernelGGL((scan_local<false>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp, nb, out, nullptr);
-  return hipGetLastError();
-}
-
-hipError_t launch_exclusive_scan_summed(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *bsum, hipStream_t s) {
-  static_assert(kScanBlock == (1 << kTileSumLog2), "the count pass sums the scan's blocks");
-  const uint64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  if (nb == 0) return hipSuccess;
-  if (nb <= (uint64_t)kScanWG) {
-    hipLaunchKernelGGL((scan_local<true>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, bsum, nb, out, nullptr);
-  } else {
-    hipLaunchKernelGGL(scan_sums_single, dim3(1), dim3(kScanWG), 0, s, bsum, nb, nullptr);
-    hipLaunchKernelGGL((scan_local<false>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, bsum, nb, out, nullptr);
-  }
+    hipLaunchKernelGGL((scan_local<kPrefixScanned>), dim3((uint32_t)nb), dim3(kScanWG), 0, s, in, n, tmp, nb, out,
+                       nullptr);
   return hipGetLastError();
 }
 
@@ -756,12 +759,12 @@ hipError_t launch_window_hashes(const uint8_t *text, uint64_t n, uint32_t m, con
     default: return hipErrorInvalidValue;                      \
   }
 
-hipError_t scan_occupancy(int cfg, int fam, uint32_t lds_bytes, int *blocks) {
-  RK_SCAN_DISPATCH(fam, cfg, occupancy(lds_bytes, blocks))
+hipError_t scan_fit(int cfg, int fam, uint32_t img_cap, uint32_t block, ScanFit *f) {
+  RK_SCAN_DISPATCH(fam, cfg, fit(img_cap, block, f))
 }
 
-hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uint32_t lds_bytes, hipStream_t s) {
-  RK_SCAN_DISPATCH(fam, cfg, launch(p, grid, lds_bytes, s))
+hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uint32_t block, hipStream_t s) {
+  RK_SCAN_DISPATCH(fam, cfg, launch(p, grid, block, s))
 }
 
 // Launches (p != nullptr) or sizes (occupancy into *blocks) the single-bucket

@@ -67,6 +67,46 @@ static int part_family(int mode, const std::vector<VInst> &vs, const std::vector
   return kFamScreen1;
 }
 
+// Sub-tiles per tile: as many as the geometry's tile holds (wg / 64) once
+// there are kTilesWanted tiles of that size (a full chip of waves), fewer for
+// smaller texts, so that their sub-tiles spread over more waves.
+constexpr uint64_t kTilesWanted = 4096;
+static uint32_t pick_sub(int cfg, uint64_t units) {
+  const uint32_t most = kTileCfgs[cfg].wg / 64;
+  uint32_t s = 1;
+  while (2 * s <= most && units / (2 * s) >= kTilesWanted) s *= 2;
+  return s;
+}
+
+// Threads per block of the general kernel: the waves of a block share the
+// image in LDS, so larger images want larger blocks for as many resident
+// waves; smaller blocks cost no meeting of their waves (meet: several
+// instances), and take the tie.
+static uint32_t pick_block(int cfg, int fam, uint32_t img_cap, bool meet, uint32_t *waves_per_cu = nullptr) {
+  if (waves_per_cu) *waves_per_cu = 0;
+  ScanFit f;
+  if (scan_fit(cfg, fam, 0, 64, &f) != hipSuccess || f.blocks < 1) return 256;
+  const uint32_t wmax = (uint32_t)f.blocks;
+  uint32_t best = 64, best_waves = 0;
+  for (uint32_t nw = 1; nw * 64 <= f.max_block; nw *= 2) {
+    const uint32_t lds = img_cap + 16 + nw * f.wave_lds;
+    const uint32_t blocks = std::min(kLdsPerCU / ((lds + 1279) / 1280 * 1280), wmax / nw);
+    const uint32_t waves = blocks * nw;
+    if (meet ? waves * 4 > best_waves * 5 : waves > best_waves) {
+      best = nw * 64;
+      best_waves = waves;
+    }
+  }
+  if (waves_per_cu) *waves_per_cu = best_waves;
+  return best;
+}
+
+// A pattern set whose image leaves fewer than kFullWaves waves per CU resident
+// scans with the geometry of the shortest lanes (36 windows: the least LDS per
+// wave) if more fit then.
+constexpr uint32_t kFullWaves = 16;
+constexpr int kNarrowCfg = 3;
+
 // Host half of a plan: images, and for batches the instance descriptors and
 // the work-queue order.  P receives everything but device memory; the three
 // byte arrays are what plan_upload copies to the device.
@@ -135,18 +175,11 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     memcpy(&P->list_desc, blob.data() + P->vinsts[0].img_off + sizeof(ImageHeader), sizeof(BucketDesc));
     P->list1 = P->list_desc.kind == kListScreen || P->list_desc.kind == kListExact;
     if (P->list1) {
-      // a key table holding a single key: its record goes to the kernel directly
-      const uint8_t *img = blob.data() + P->vinsts[0].img_off;
-      const uint32_t S = P->list_desc.ht_mask + 1;
-      const uint64_t *keys = (const uint64_t *)(img + P->list_desc.ht_off);
-      uint32_t used = 0;
-      uint64_t rec = 0;
-      for (uint32_t s = 0; s < S; ++s)
-        if (keys[s] != kEmptyKey) {
-          ++used;
-          rec = keys[S + s];
-        }
-      P->list_rec1 = used == 1 ? rec : 0;
+      // its one record and tail go to the kernel directly
+      const uint8_t *tab = blob.data() + P->vinsts[0].img_off + P->list_desc.tab_off;
+      memcpy(P->list_tail, tab, 16);
+      memcpy(&P->list_rec1, tab + 16 * P->list_desc.ntab, 8);
+      P->list_desc.shift &= 0xFFFFu;  // (no image in LDS there)
     }
   }
   if (!batch) {
@@ -156,6 +189,15 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     pt.fam = P->fam;
     pt.img_cap = P->img_cap;
     pt.ninst = (uint32_t)P->vinsts.size();
+    uint32_t waves = 0, waves3 = 0;
+    pt.block = pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1, &waves);
+    if (ctx->tile_cfg < 0 && !P->list1 && waves < kFullWaves) {
+      const uint32_t b3 = pick_block(kNarrowCfg, pt.fam, pt.img_cap, pt.ninst > 1, &waves3);
+      if (waves3 > waves) {
+        P->cfg = pt.cfg = kNarrowCfg;
+        pt.block = b3;
+      }
+    }
     P->parts.assign(1, pt);
     return RK_OK;
   }
@@ -178,7 +220,12 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     pt.inst0 = (uint32_t)descs.size();
     pt.ninst = (uint32_t)members[c].size();
     pt.tile0 = base;
-    const uint32_t W = kTileCfgs[c].wg * kTileCfgs[c].c;
+    const uint32_t SUB = 64 * kTileCfgs[c].c;
+    uint64_t units = 0;
+    for (uint32_t vi : members[c]) units += (P->insts[P->vinsts[vi].src].n + SUB - 1) / SUB;
+    pt.sub = pick_sub(c, units);
+    pt.block = pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1);
+    const uint32_t W = pt.sub * SUB;
     std::vector<uint64_t> first(members[c].size());
     for (size_t q = 0; q < members[c].size(); ++q) {
       const VInst &v = P->vinsts[members[c][q]];
@@ -204,8 +251,16 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
       return x.max_m > y.max_m;
     });
     pt.item0 = items.size();
-    for (uint32_t q : order)
-      for (uint64_t t = 0; t < descs[pt.inst0 + q].ntiles; ++t) items.push_back(first[q] + t);
+    // Tiles per pop: some eight pops per wave (pops of one cursor are served
+    // one after the other), at least two tiles per wave for blocks that meet
+    // at each pop.
+    const uint64_t nw = pt.block / 64, per_wave = std::min<uint64_t>(16, pt.ntiles / (8 * 16 * (uint64_t)ctx->num_cu));
+    const uint64_t run = nw * std::max<uint64_t>(per_wave, nw == 1 ? 1 : 2);
+    for (uint32_t q : order) {
+      const uint64_t nt = descs[pt.inst0 + q].ntiles;
+      for (uint64_t t = 0; t < nt; t += run)
+        items.push_back((first[q] + t) | std::min(run, nt - t) << kItemShift);
+    }
     pt.nitems = items.size() - pt.item0;
     P->parts.push_back(pt);
   }
@@ -269,27 +324,47 @@ rk_status plan_build(rk_ctx *ctx, const rk_instance *inst, uint32_t count, int m
 
 rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
   L = Layout();
-  // staging records per tile: one per 64 text bytes for a single pattern
-  // (hits are rare), one per 16 for pattern sets (sampled patterns hit often);
-  // a tile with more hits is rescanned by the collect pass
-  auto slots = [&](uint32_t W) { return ctx->slab_cap ? ctx->slab_cap : (plan->k_total > 1 ? W / 16 : W / 64); };
+  // Staging records per tile: one per 64 text bytes for a single pattern
+  // (hits are rare), one per 16 for pattern sets (sampled patterns hit often),
+  // of the geometry's whole tile: the smaller tiles of a short text hold as
+  // many, as their hits average over less text (a 1.5 MB text with a hit every
+  // 20 bytes had a tenth of its tiles rescanned with a fourth of the records,
+  // which doubled its time).  A tile with more hits is rescanned by the
+  // collect pass.
+  const uint32_t per = plan->k_total > 1 ? 16 : 64;
+  auto slots = [&](int cfg, uint32_t W) -> uint32_t {
+    if (ctx->slab_cap) return ctx->slab_cap;
+    return (ctx->lean_slabs ? W : kTileCfgs[cfg].wg * kTileCfgs[cfg].c) / per;
+  };
+  // Sizes of one text's tiles: T1 now, but every text up to n fits in the
+  // scratch of n (its tiles are smaller when it is short), so room for Tcap
+  // tiles and their slabs.
+  uint64_t Tcap = 0, Told = 0, slab_recs = 0;
   if (plan->batch) {
     for (const Part &pt : plan->parts) {
       PartRun r;
       r.tile0 = pt.tile0;
       r.ntiles = pt.ntiles;
-      r.W = kTileCfgs[pt.cfg].wg * kTileCfgs[pt.cfg].c;
-      r.S = slots(r.W);
+      r.sub = pt.sub;
+      r.W = 64 * kTileCfgs[pt.cfg].c * pt.sub;
+      r.S = slots(pt.cfg, r.W);
       L.parts.push_back(r);
     }
-    L.T = plan->total_tiles;
+    Tcap = L.T = plan->total_tiles;
+    Told = Tcap;
   } else {
     if (n > RK_MAX_N) return set_err(ctx, RK_EUNSUPPORTED, "text longer than 2^40-1 bytes");
+    const TileCfg g = kTileCfgs[plan->cfg];
+    const uint64_t SUB = 64ull * g.c, most = g.wg / 64, units = (n + SUB - 1) / SUB;
     PartRun r;
-    r.W = kTileCfgs[plan->cfg].wg * kTileCfgs[plan->cfg].c;
-    L.T1 = (n + r.W - 1) / r.W;
+    r.sub = pick_sub(plan->cfg, units);
+    r.W = (uint32_t)SUB * r.sub;
+    L.T1 = (units + r.sub - 1) / r.sub;
     r.ntiles = L.T = L.T1 * plan->vinsts.size();
-    r.S = slots(r.W);
+    r.S = slots(plan->cfg, r.W);
+    Tcap = std::max(L.T1, std::min(units, 2 * kTilesWanted)) * plan->vinsts.size();
+    Told = (units + most - 1) / most * plan->vinsts.size();
+    slab_recs = !ctx->slab_cap && ctx->lean_slabs ? Told * (most * SUB / per) : Tcap * r.S;
     L.parts.push_back(r);
   }
   uint64_t o = 0;
@@ -298,17 +373,29 @@ rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
     o = align_up(o + bytes, 256);
     return r;
   };
-  // the counters and the tiles' block sums are one region, cleared by one
-  // fill before every count pass
-  L.nbsum = (L.T + (1u << kTileSumLog2) - 1) / (1u << kTileSumLog2) + 1;
-  L.ctr = take(256 + L.nbsum * 8);
-  L.bsum = L.ctr + 256;
+  L.ctr = take(kCtrBytes);
+  L.bsum = take(scan_tmp_words(Tcap) * 8);
   L.inst = take(plan->batch ? 0 : plan->vinsts.size() * sizeof(InstDesc));
-  L.counts = take(L.T * 4);
-  L.offsets = take(L.T * 8);
-  L.ovf = take(L.T * 8);
-  for (PartRun &r : L.parts) r.slabs = take(r.ntiles * (uint64_t)r.S * 8);
+  L.counts = take(Tcap * 4);
+  L.offsets = take(Tcap * 8);
+  L.ovf = take(Tcap * 8);
+  for (PartRun &r : L.parts) r.slabs = take((plan->batch ? r.ntiles * (uint64_t)r.S : slab_recs) * 8);
   L.total = o;
+  // what the scratch took with tiles of wg * c bytes alone (the limit of
+  // rk_search_static is held against this)
+  o = 0;
+  take(256 + ((Told + 4095) / 4096 + 1) * 8);
+  take(plan->batch ? 0 : plan->vinsts.size() * sizeof(InstDesc));
+  take(Told * 4);
+  take(Told * 8);
+  take(Told * 8);
+  if (plan->batch) {
+    for (const PartRun &r : L.parts) take(r.ntiles * (uint64_t)r.S * 8);
+  } else {
+    const TileCfg g = kTileCfgs[plan->cfg];
+    take(Told * (ctx->slab_cap ? ctx->slab_cap : (uint64_t)g.wg * g.c / per) * 8);
+  }
+  L.extra = L.total > o ? L.total - o : 0;
   return RK_OK;
 }
 
@@ -372,12 +459,12 @@ hipError_t prof_end(rk_ctx *ctx, hipStream_t s, int slot) {
   return hipEventRecord(ctx->prof_events[slot].b, s);
 }
 
-static uint32_t scan_grid(rk_ctx *ctx, int cfg, int fam, uint32_t lds, uint64_t nitems) {
-  if (ctx->grid) return (uint32_t)std::min<uint64_t>(ctx->grid, std::max<uint64_t>(nitems, 1));
-  int blocks = 0;
-  if (scan_occupancy(cfg, fam, lds, &blocks) != hipSuccess || blocks < 1) blocks = 1;
-  const uint64_t g = (uint64_t)ctx->num_cu * (uint64_t)blocks;
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, nitems));
+static uint32_t scan_grid(rk_ctx *ctx, int cfg, int fam, uint32_t img_cap, uint32_t block, uint64_t nruns) {
+  if (ctx->grid) return (uint32_t)std::min<uint64_t>(ctx->grid, std::max<uint64_t>(nruns, 1));
+  ScanFit f;
+  if (scan_fit(cfg, fam, img_cap, block, &f) != hipSuccess || f.blocks < 1) f.blocks = 1;
+  const uint64_t g = (uint64_t)ctx->num_cu * (uint64_t)f.blocks;
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, nruns));
 }
 
 // Blocks per resident slot of the single-bucket scan's grid.
@@ -394,12 +481,14 @@ static void base_params(const rk_plan *plan, const Layout &L, uint32_t pi, uint8
   p.blob = plan->blob_dev;
   p.tile_counts = (uint32_t *)(sc + L.counts);
   p.slab_cap = r.S;
+  p.sub = r.sub;
+  p.run = pt.block / 64;
+  p.inst_tiles = L.T1;
+  p.inst_runs = (L.T1 + p.run - 1) / p.run;
   p.tile0 = r.tile0;
-  p.total = (unsigned long long *)(sc + L.ctr);
-  p.blk_sums = (unsigned long long *)(sc + L.bsum);
+  p.totals = (unsigned long long *)(sc + L.ctr + kCtrTotals);
   p.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf) + pi;
   p.ovf_list = (uint64_t *)(sc + L.ovf) + r.tile0;  // the part's own overflow list
-  p.grab = 1;
 }
 
 // Instance descriptors of a single-text plan's text (one per virtual
@@ -449,7 +538,7 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     e = upload_insts(plan, L, sc, text, n, s);
     if (e != hipSuccess) return hip_err(ctx, e, "instance upload");
   }
-  e = launch_fill_u32((uint32_t *)(sc + L.ctr), 64 + 2 * L.nbsum, 0u, s);
+  e = launch_fill_u32((uint32_t *)(sc + L.ctr), kCtrBytes / 4, 0u, s);
   if (e != hipSuccess) return hip_err(ctx, e, "counter reset");
   if (counts) {
     e = launch_fill_u32((uint32_t *)counts, 2ull * plan->k_total, 0u, s);
@@ -468,11 +557,12 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     lp.D = plan->list_desc;
     lp.rot = (8u * plan->list_desc.m) % 61u;
     lp.slab_cap = r.S;
+    lp.sub = r.sub;
+    memcpy(lp.tail, plan->list_tail, sizeof lp.tail);
     lp.rec1 = plan->list_rec1;
     lp.tile_counts = (uint32_t *)(sc + L.counts);
     lp.out = (uint64_t *)(sc + r.slabs);
-    lp.total = (unsigned long long *)(sc + L.ctr);
-    lp.blk_sums = (unsigned long long *)(sc + L.bsum);
+    lp.totals = (unsigned long long *)(sc + L.ctr + kCtrTotals);
     lp.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf);
     lp.ovf_list = (uint64_t *)(sc + L.ovf);
     lp.pid_counts = (unsigned long long *)counts;
@@ -485,7 +575,7 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
       if (list_scan(plan->cfg, plan->fam, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
       grid = (uint32_t)ctx->num_cu * (uint32_t)blocks * kListGridMul;
     }
-    grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, L.T));
+    grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, (L.T + kListBlock / 64 - 1) / (kListBlock / 64)));
     e = prof_begin(ctx, s, 0, &slot);
     if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
     e = list_scan(plan->cfg, plan->fam, &lp, grid, s, nullptr);
@@ -501,15 +591,14 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
       ScanParams p;
       base_params(plan, L, pi, sc, p);
       p.items = plan->batch ? plan->items_dev + pt.item0 : nullptr;
-      p.nitems = plan->batch ? pt.nitems : r.ntiles;
+      p.nitems = plan->batch ? pt.nitems : p.inst_runs * pt.ninst;
       p.out = (uint64_t *)(sc + r.slabs);
       p.pid_counts = (unsigned long long *)counts;
       if (use_queue) p.queue = (uint32_t *)(sc + L.ctr + kCtrQueue) + pi;
-      const uint32_t lds = scan_lds_bytes(pt.cfg, pt.img_cap);
-      const uint32_t grid = scan_grid(ctx, pt.cfg, pt.fam, lds, p.nitems);
+      const uint32_t grid = scan_grid(ctx, pt.cfg, pt.fam, pt.img_cap, pt.block, p.nitems);
       e = prof_begin(ctx, s, 0, &slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
-      e = launch_scan(pt.cfg, pt.fam, p, grid, lds, s);
+      e = launch_scan(pt.cfg, pt.fam, p, grid, pt.block, s);
       if (e != hipSuccess) return hip_err(ctx, e, "scan launch");
       e = prof_end(ctx, s, slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
@@ -525,7 +614,7 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
 }
 
 rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total) {
-  hipError_t e = hipMemcpyAsync(ctx->pinned, scratch, 64, hipMemcpyDeviceToHost, s);
+  hipError_t e = hipMemcpyAsync(ctx->pinned, scratch, kCtrBytes, hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return hip_err(ctx, e, "total readback");
   // A count pass of a few GiB takes about a millisecond, less than a blocking
   // wait adds in wake-up latency: the stream is polled for up to kSpinUs,
@@ -541,7 +630,7 @@ rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStrea
     }
   }
   if (e != hipSuccess) return hip_err(ctx, e, "scan");
-  *total = ctx->pinned[0];
+  *total = hit_total(ctx->pinned);
   const uint32_t ovf = ovf_total(ctx->pinned);
   for (auto &mm : ctx->memo)
     if (mm.scratch == scratch && mm.plan == plan) {
@@ -570,10 +659,10 @@ rk_status collect_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text,
       overflow = mm.overflow;
     }
   if (total == ~0ull) {
-    hipError_t e = hipMemcpyAsync(ctx->pinned, sc + L.ctr, 8, hipMemcpyDeviceToHost, s);
+    hipError_t e = hipMemcpyAsync(ctx->pinned, sc + L.ctr, kCtrBytes, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_err(ctx, e, "total readback");
-    total = ctx->pinned[0];
+    total = hit_total(ctx->pinned);
   }
   return collect_enqueue_known(ctx, plan, text, n, scratch, scratch_bytes, work, work_bytes, offsets, positions, capacity,
                                total, overflow, s);
@@ -613,7 +702,7 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
     return hip_err_or_ok(ctx, prof_end(ctx, s, slot));
   }
   uint64_t *tile_off = (uint64_t *)(sc + L.offsets);
-  e = launch_exclusive_scan_summed((const uint32_t *)(sc + L.counts), L.T, tile_off, (uint64_t *)(sc + L.bsum), s);
+  e = launch_exclusive_scan((const uint32_t *)(sc + L.counts), L.T, tile_off, (uint64_t *)(sc + L.bsum), nullptr, s);
   if (e != hipSuccess) return hip_err(ctx, e, "tile scan");
   WorkLayout WL = work_layout(total, k);
   uint64_t *target = k == 1 ? positions : (uint64_t *)((uint8_t *)work + WL.a);
@@ -677,17 +766,18 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
       ScanParams p;
       base_params(plan, L, pi, sc, p);
       p.items = p.ovf_list;
+      p.wave_items = 1;
       p.nitems = r.ntiles;
       p.nitems_dev = p.ovf_count;
       p.out = target;
       p.tile_offsets = tile_off;
       p.direct = 1;
-      const uint32_t lds = scan_lds_bytes(pt.cfg, pt.img_cap);
-      const uint32_t grid =
-          std::min<uint32_t>(scan_grid(ctx, pt.cfg, pt.fam, lds, r.ntiles), (uint32_t)ctx->num_cu);
+      // the waves of a block take tiles of their own: one instance, or one wave
+      const uint32_t block = pt.ninst > 1 ? 64 : pt.block;
+      const uint32_t grid = scan_grid(ctx, pt.cfg, pt.fam, pt.img_cap, block, (r.ntiles * 64 + block - 1) / block);
       e = prof_begin(ctx, s, 1, &slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
-      e = launch_scan(pt.cfg, pt.fam, p, grid, lds, s);
+      e = launch_scan(pt.cfg, pt.fam, p, grid, block, s);
       if (e != hipSuccess) return hip_err(ctx, e, "rescan launch");
       e = prof_end(ctx, s, slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
@@ -747,6 +837,7 @@ extern "C" rk_status rk_scan_dump(rk_ctx *ctx, const uint8_t *text, uint64_t n, 
     lp.text = text;
     lp.n = n;
     lp.ntiles = ntiles;
+    lp.sub = kTileCfgs[cfg].wg / 64;
     lp.D = d;
     lp.rot = (8u * m) % 61u;
     lp.dump_out = out;
@@ -758,7 +849,7 @@ extern "C" rk_status rk_scan_dump(rk_ctx *ctx, const uint8_t *text, uint64_t n, 
       if (list_scan(cfg, kFamExact, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
       grid = (uint32_t)ctx->num_cu * (uint32_t)blocks;
     }
-    grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, ntiles));
+    grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, (ntiles + kListBlock / 64 - 1) / (kListBlock / 64)));
     e = list_scan(cfg, kFamExact, &lp, grid, st, nullptr);
     if (e != hipSuccess) return hip_err(ctx, e, "dump launch");
     e = hipStreamSynchronize(st);
@@ -791,14 +882,15 @@ extern "C" rk_status rk_scan_dump(rk_ctx *ctx, const uint8_t *text, uint64_t n, 
   p.ninst = 1;
   p.img_cap = 128;
   p.blob = (const uint8_t *)ctx->dump_dev;
-  p.nitems = I.ntiles;
+  p.sub = kTileCfgs[cfg].wg / 64;
+  p.run = 1;
+  p.inst_tiles = p.inst_runs = p.nitems = I.ntiles;
   p.direct = 1;
   p.dump_out = out;
   p.dump_stride = stride;
   p.dump_cap = cap;
-  const uint32_t lds = scan_lds_bytes(cfg, 128);
-  const uint32_t grid = scan_grid(ctx, cfg, kFamExact, lds, I.ntiles);
-  e = launch_scan(cfg, kFamExact, p, grid, lds, st);
+  const uint32_t grid = scan_grid(ctx, cfg, kFamExact, p.img_cap, 64, I.ntiles);
+  e = launch_scan(cfg, kFamExact, p, grid, 64, st);
   if (e != hipSuccess) return hip_err(ctx, e, "dump launch");
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_err(ctx, e, "dump");

@@ -34,20 +34,19 @@ uint64_t host_hash(const uint8_t *p, uint64_t m) {
   for (uint64_t i = 0; i < m; ++i) s = h_canon(h_mul256(s) + p[i]);
   return s;
 }
-// screen shift for a pattern length: the smallest power of two s with s*m >= 32
-// and s >= 2 (s = 1 is the paper's shift-and-add form; s = 2 keeps the warm-up
-// at 15 bytes while every byte of a window of length >= 16 still contributes)
-uint32_t screen_shift(uint32_t m) {
+// Screen shift of a group whose shortest pattern has m bytes: the smallest of
+// 2, 3, 4, 8 whose hash covers at most m bytes (ceil(32/s) of them; one to
+// three bytes are masked).  s = 1 is the paper's shift-and-add form.
+static uint32_t screen_shift(uint32_t m) {
   if (m < 8) return 8;
-  if (m < 16) return 4;
+  if (m < 11) return 4;
+  if (m < 16) return 3;
   return 2;
 }
-uint32_t screen_hash(const uint8_t *p, uint32_t m) {
-  const uint32_t s = screen_shift(m);
+static uint32_t screen_hash(const uint8_t *p, uint32_t m, uint32_t s, uint32_t mask) {
   uint32_t h = 0;
   for (uint32_t i = 0; i < m; ++i) h = (h << s) + p[i];
-  if (s == 8 && m < 4) h &= (1u << (8 * m)) - 1u;
-  return h;
+  return h & mask;
 }
 
 // ------------------------------------------------------------------ errors
@@ -82,98 +81,71 @@ static inline uint32_t next_pow2(uint32_t v) {
 
 // ------------------------------------------------------------ image building
 // An instance image holds, per group of patterns, the structures the scan
-// probes for every window (up to 4 register targets or a fingerprint table)
-// and those it walks for candidates only (a key -> entry-run hash table, the
-// entries and the pattern bytes).
+// probes for every window (a register target or a bitmap of keys) and those
+// it reads for candidates only (lookup bitmap, records with pattern tails,
+// entries and pattern bytes).
 //
-// Screen mode groups patterns by the part of the window their shift-add hash
-// covers: s=8 hashes the last 4 bytes, s=4 the last 8, s=2 the last 16, and
-// bytes older than that have shifted out of the 32-bit word.  So every pattern
-// of length >= 16 shares one hash stream (its key is the shift-add hash of
-// its last 16 bytes), likewise 8..15 and 4..7; lengths 1..3 get one group each
-// (the hash is masked to the window).  Exact mode groups by length class, each
-// class keyed on the exact hash of the last l bytes, l its shortest length.
+// Patterns are grouped by length class: their keys are taken from the end of
+// the pattern, over as many bytes as the class's shortest one has (exact mode:
+// the exact hash; screen mode: the shift-add hash, from which bytes older than
+// 32/s positions have shifted out).
 struct PatRef {
   uint32_t pid;
   const uint8_t *p;
   uint32_t m;
   uint64_t key;  // screen hash (screen groups) or exact hash (exact groups)
-  uint64_t hx;   // exact hash
+  uint32_t lk;   // shift-add key of the lookup
+  uint32_t at;   // the lookup bit
 };
 
 struct GroupIn {
   bool screen;
-  uint32_t shift, mask;  // screen groups
+  uint32_t shift, mask;  // of the screen hash (screen groups: tested; all groups: looked up)
   uint32_t m;            // exact groups: the length; screen groups: the shortest length
   std::vector<PatRef> pats;
 };
 
-static uint32_t screen_mask(uint32_t m) { return (screen_shift(m) == 8 && m < 4) ? (1u << (8 * m)) - 1u : 0xFFFFFFFFu; }
+// Length class of a pattern: 1, 2, 3, 4 (4..7 bytes), 5 (8..15), 6 (16 and
+// more).  Screen and exact mode share them: a class is a group with a hash
+// stream of its own, keyed on the last l bytes of each pattern, l the class's
+// shortest length in exact mode (at most kStreamM; a class of one length
+// hashes whole windows), what the shift covers of them in screen mode.
+static uint32_t length_class(uint32_t m) { return m < 4 ? m : m < 8 ? 4 : m < 16 ? 5 : 6; }
 
-// group id for a pattern length under a mode.  Lengths 1..3 get one group
-// each.  Screen mode: one group per shift (the span its hash covers).  Exact
-// mode: one group per length class (4..7, 8..15, 16..31, 32 and longer), whose
-// rolling stream hashes the last l bytes of each window, l the shortest
-// pattern length of the class (at most kStreamM): every pattern of the class
-// is keyed by the exact hash of its last l bytes, so a set of many lengths
-// costs one stream per class instead of one per length, and a class holding
-// one length hashes whole windows.
-static uint32_t group_id(int mode, uint32_t m) {
-  if (m < 4) return m;
-  if (mode == RK_MODE_EXACT) return 200 + (uint32_t)m_class(m);
-  return 100 + screen_shift(m);
+// Classes that join the next shorter one, which saves their own pass over the
+// text (a test of every window, about eight instructions in screen mode and
+// sixteen in exact mode): the shorter keys let more windows pass, which is
+// dear where the text repeats itself.  On word text a copied pattern's last
+// eight bytes occur every 3,000 bytes, its last four every 300, and a
+// candidate costs about 130 instructions: the pass is the dearer of the two up
+// to some 100 long and 15 short patterns; half of each keeps clear of texts
+// that repeat more.
+constexpr size_t kJoinLong = 64, kJoinShort = 8;
+
+// Bytes of a bitmap for nbits set bits: at least 8 bytes a bit (a random
+// window passes at most one time in 64) up to 1,024 bits, 4 bytes beyond,
+// where the image's LDS would otherwise cost the scan more resident waves than
+// the candidates saved are worth; at most kMaxBitmap.
+static uint32_t bitmap_bytes(size_t nbits) {
+  const uint64_t want = nbits <= 1024 ? 8 * nbits : 4 * nbits;
+  return std::min(kMaxBitmap, std::max(kMinBitmap, next_pow2((uint32_t)std::min<uint64_t>(want, kMaxBitmap))));
 }
 
-// Cuckoo table of 32-bit keys for the per-window set test: a key sits in one
-// of its two slots (ck_slot1 / ck_slot2, which the kernel computes the same
-// way), so a window costs two LDS reads and two full 32-bit compares and has
-// no false positives beyond hash equality.  Empty slots hold a value that is
-// no key.  At most 45% of the slots are used.
-static bool build_cuckoo(const std::vector<uint32_t> &keys, uint32_t bits, std::vector<uint32_t> &tab) {
-  const uint32_t S = 1u << bits, sh = 32 - bits;
-  std::vector<uint32_t> sorted(keys);
-  std::sort(sorted.begin(), sorted.end());
-  uint32_t filler = 0;
-  for (uint32_t k : sorted) {
-    if (k == filler) ++filler;
-    else if (k > filler) break;
-  }
-  tab.assign(S, filler);
-  std::vector<uint8_t> used(S, 0);
-  uint32_t rng = 0x2545F491u;
-  for (uint32_t key : keys) {
-    uint32_t cur = key;
-    bool placed = false;
-    for (int kick = 0; kick < 1000 && !placed; ++kick) {
-      const uint32_t a = ck_slot1(cur, sh), b = ck_slot2(cur, sh);
-      if (!used[a]) {
-        tab[a] = cur;
-        used[a] = 1;
-        placed = true;
-      } else if (!used[b]) {
-        tab[b] = cur;
-        used[b] = 1;
-        placed = true;
-      } else {
-        rng = rng * 1103515245u + 12345u;
-        const uint32_t v = ((rng >> 16) & 1u) ? a : b;
-        std::swap(cur, tab[v]);  // the evicted key tries its other slot next
-      }
-    }
-    if (!placed) return false;
-  }
-  return true;
-}
-
-// A group serialised in two parts: what the kernel probes for every window
-// (the cuckoo table, staged in LDS) and what it walks for candidates only
-// (key table, entries, pattern bytes; read from the plan in device memory).
+// A group serialised in two parts: what is staged in LDS (bitmaps, and the
+// records with their tails when they fit) and what the kernel reads from the
+// plan in device memory (entries, pattern bytes, larger record tables).
 // Offsets in the descriptor are relative to the start of each part.
 struct GroupBody {
   std::vector<uint8_t> lds, glob;
   BucketDesc D;
-  std::vector<uint32_t> tab;  // the cuckoo table (table kinds)
+  bool tab_lds = false;  // records and tails are in the LDS part
+  bool ids_lds = false;  // ids are in the LDS part
+  bool pat_lds = false;  // pattern bytes are in the LDS part
+  uint32_t npat = 0, max_m = 0;
 };
+constexpr uint32_t kIdsLds = 8 * 1024;   // most bytes of ids staged in LDS (a load for every hit of a pattern's 2nd id on)
+constexpr uint32_t kTabLds = 24 * 1024 + 512;  // largest record table staged in LDS (some 1,024 records)
+constexpr uint32_t kPatLds = 2 * 1024;   // most pattern bytes staged in LDS
 
 static uint32_t put_bytes(std::vector<uint8_t> &body, const void *p, size_t bytes) {
   const uint32_t off = (uint32_t)align_up(body.size(), 16);
@@ -182,152 +154,147 @@ static uint32_t put_bytes(std::vector<uint8_t> &body, const void *p, size_t byte
   return off;
 }
 
-// Record of the entries [i, j) sharing one key: one entry inline; a run of
-// one pattern under several ids (identical bytes: one comparison, then a hit
-// per id) as such when it fits that encoding; else a plain run.
-static uint64_t key_record(const std::vector<Entry> &ents, size_t i, size_t j) {
-  if (j - i == 1) return slot_inline(ents[i].pid, ents[i].off_m);
-  bool same = j - i <= kSameMaxCount && i < kSameMaxFirst;
-  for (size_t q = i + 1; q < j && same; ++q) same = ents[q].off_m == ents[i].off_m;
-  if (same) return slot_same((uint32_t)i, (uint32_t)(j - i), ents[i].off_m);
-  return slot_run((uint32_t)i, (uint32_t)(j - i));
-}
-
-// Serialises one group.  Returns false if its keys do not fit a cuckoo table
-// of at most 2^kMaxTableBits slots or it has more entries than a run can
-// address (the caller then splits the group).
-static bool emit_group(const GroupIn &G, GroupBody &out) {
+// Serialises one group.  Returns false if it has more entries than a lookup
+// counts or more pattern bytes than an entry addresses (the caller then splits
+// the group).
+static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
   std::vector<PatRef> P = G.pats;
-  // entries sharing the low key word (the table key) side by side
-  std::stable_sort(P.begin(), P.end(), [](const PatRef &a, const PatRef &b) {
-    if ((uint32_t)a.key != (uint32_t)b.key) return (uint32_t)a.key < (uint32_t)b.key;
-    if (a.key != b.key) return a.key < b.key;
-    if (a.m != b.m) return a.m < b.m;
-    const int c = memcmp(a.p, b.p, a.m);  // identical patterns side by side
-    if (c) return c < 0;
-    return a.pid < b.pid;
-  });
   if (P.size() > 0xFFFFu) return false;
   BucketDesc &D = out.D;
   memset(&D, 0, sizeof D);
   D.m = G.m;
-  D.npat = (uint32_t)P.size();
-  D.mask = G.screen ? G.mask : 0xFFFFFFFFu;
+  D.shift = G.shift;
+  D.mask = G.mask;
+  out.npat = (uint32_t)P.size();
+  for (const PatRef &r : P) out.max_m = std::max(out.max_m, r.m);
+  // the keys the stream tests
   std::vector<uint64_t> dist;
-  for (const PatRef &r : P)
-    if (dist.empty() || dist.back() != r.key) dist.push_back(r.key);
+  for (const PatRef &r : P) dist.push_back(r.key);
+  std::sort(dist.begin(), dist.end());
+  dist.erase(std::unique(dist.begin(), dist.end()), dist.end());
   std::vector<uint32_t> tkeys;
-  if (!G.screen) {
-    std::vector<uint32_t> lazy;
+  if (G.screen) {
+    for (uint64_t h : dist) tkeys.push_back((uint32_t)h);
+  } else {
+    // low words of every lazy form the rolling state can take
     for (uint64_t H : dist) {
-      lazy.push_back((uint32_t)H);
-      lazy.push_back((uint32_t)(H + kQ));
-      if (H + 2 * kQ < (1ull << 62) + (1ull << 11)) lazy.push_back((uint32_t)(H + 2 * kQ));
+      tkeys.push_back((uint32_t)H);
+      tkeys.push_back((uint32_t)(H + kQ));
+      if (H + 2 * kQ < (1ull << 62) + (1ull << 11)) tkeys.push_back((uint32_t)(H + 2 * kQ));
     }
-    if (lazy.size() <= 4) {
-      D.kind = kListExact;
-      for (int j = 0; j < 4; ++j) D.tgt[j] = lazy[j < (int)lazy.size() ? j : 0];
-      D.shift = (uint32_t)(lazy.size() <= 2 ? 2u : 4u) << 8;  // compare count the kernel unrolls
-    } else {
-      D.kind = kTableExact;
-      for (uint64_t H : dist) tkeys.push_back((uint32_t)H);  // low word of the canonical hash
-    }
+  }
+  const bool table = dist.size() > 1;
+  if (!table) {
+    D.kind = G.screen ? kListScreen : kListExact;
+    for (size_t j = 0; j < 4; ++j) D.tgt[j] = tkeys[j < tkeys.size() ? j : 0];
+    if (!G.screen) D.shift |= (uint32_t)tkeys.size() << 8;  // compare count the kernel unrolls
+    for (PatRef &r : P) r.at = 0;
   } else {
-    D.shift = G.shift;
-    if (dist.size() <= 4) {
-      D.kind = kListScreen;
-      for (int j = 0; j < 4; ++j) D.tgt[j] = (uint32_t)dist[j < (int)dist.size() ? j : 0];
-      D.shift |= (dist.size() == 1 ? 1u : 4u) << 8;  // compare count the kernel unrolls
-    } else {
-      D.kind = kTableScreen;
-      for (uint64_t h : dist) tkeys.push_back((uint32_t)h);
+    D.kind = G.screen ? kTableScreen : kTableExact;
+    const uint32_t tb = bitmap_bytes(tkeys.size()), lb = G.screen ? tb : bitmap_bytes((P.size() + 3) / 4);
+    std::vector<uint32_t> test(tb / 4, 0), look(lb / 4, 0);
+    D.test_sh = 32 - (uint32_t)__builtin_ctz(tb / 4);
+    D.lk_sh = 32 - (uint32_t)__builtin_ctz(lb / 4);
+    for (uint32_t v : tkeys) {
+      if (G.screen) v *= kMix;
+      test[v >> D.test_sh] |= 1u << (v & 31u);
     }
+    for (PatRef &r : P) {
+      const uint32_t v = r.lk * kMix;
+      r.at = (v >> D.lk_sh) * 32 + (v & 31u);
+      look[r.at / 32] |= 1u << (r.at & 31u);
+    }
+    std::vector<uint16_t> below(lb / 4);
+    uint32_t set = 0;
+    for (size_t i = 0; i < look.size(); ++i) {
+      below[i] = (uint16_t)set;
+      set += (uint32_t)__builtin_popcount(look[i]);
+    }
+    D.lk_off = put_bytes(out.lds, look.data(), lb);
+    put_bytes(out.lds, below.data(), below.size() * 2);  // right behind (lb is a multiple of 16)
+    D.test_off = G.screen ? D.lk_off : put_bytes(out.lds, test.data(), tb);
   }
-  if (D.kind == kTableScreen || D.kind == kTableExact) {
-    std::sort(tkeys.begin(), tkeys.end());
-    tkeys.erase(std::unique(tkeys.begin(), tkeys.end()), tkeys.end());
-    uint32_t bits = 6;
-    while ((1u << bits) * 9u < tkeys.size() * 20u) ++bits;  // load <= 45%
-    std::vector<uint32_t> tab;
-    bool ok = false;
-    for (; bits <= kMaxTableBits; ++bits)
-      if ((ok = build_cuckoo(tkeys, bits, tab))) break;
-    if (!ok) return false;
-    D.fp_mask = 32 - bits;  // the kernel's slot shift
-    D.fp_off = put_bytes(out.lds, tab.data(), tab.size() * 4);
-    out.tab = std::move(tab);
-  }
-  const bool table = D.kind == kTableScreen || D.kind == kTableExact;
-  std::vector<Entry> ents(P.size());
+  // patterns of one lookup bit side by side, identical ones adjacent
+  std::stable_sort(P.begin(), P.end(), [](const PatRef &a, const PatRef &b) {
+    if (a.at != b.at) return a.at < b.at;
+    if (a.m != b.m) return a.m < b.m;
+    const int c = memcmp(a.p, b.p, a.m);
+    if (c) return c < 0;
+    return a.pid < b.pid;
+  });
+  // Pattern bytes, each at a 4-byte aligned offset (the kernel compares
+  // dwords), identical patterns under several ids once; their records, in the
+  // order of the patterns.
+  struct One {
+    uint32_t at;
+    uint64_t rec;
+    const PatRef *p;
+  };
+  std::vector<One> ones;
   std::vector<uint8_t> pb;
-  // pattern bytes, each at a 4-byte aligned offset (the kernel compares
-  // dwords); identical patterns under several ids are stored once
-  uint32_t max_m = 0;
-  std::unordered_map<std::string, uint32_t> stored;
-  for (size_t i = 0; i < P.size(); ++i) {
-    ents[i].hx = P[i].hx;
-    ents[i].pid = P[i].pid;
-    std::string s((const char *)P[i].p, P[i].m);
-    auto it = stored.find(s);
-    uint32_t off;
-    if (it != stored.end()) {
-      off = it->second;
-    } else {
-      off = (uint32_t)pb.size();
-      stored.emplace(std::move(s), off);
-      pb.insert(pb.end(), P[i].p, P[i].p + P[i].m);
-      pb.resize(align_up(pb.size(), 4), 0);
+  std::vector<uint32_t> ids;
+  for (size_t i = 0; i < P.size();) {
+    size_t j = i + 1;
+    while (j < P.size() && P[j].at == P[i].at && P[j].m == P[i].m && memcmp(P[j].p, P[i].p, P[i].m) == 0) ++j;
+    const uint32_t om = om_pack((uint32_t)pb.size() & (kGroupPatBytes - 1), P[i].m);
+    pb.insert(pb.end(), P[i].p, P[i].p + P[i].m);
+    pb.resize(align_up(pb.size(), 4), 0);
+    if (pb.size() > kGroupPatBytes) return false;  // split: records address 4 MiB of pattern bytes
+    if (j == i + 1) ones.push_back({P[i].at, rec_inline(P[i].pid, om), &P[i]});
+    for (size_t q = i; j > i + 1 && q < j; q += kSameMaxCount) {
+      const uint32_t c = (uint32_t)std::min<size_t>(kSameMaxCount, j - q);
+      ones.push_back({P[i].at, rec_ids((uint32_t)ids.size(), c, om), &P[i]});
+      for (size_t t = q; t < q + c; ++t) ids.push_back(P[t].pid);
     }
-    ents[i].off_m = om_pack(off, P[i].m);  // offset relative to the pattern block
-    max_m = std::max(max_m, P[i].m);
+    i = j;
   }
-  if (pb.size() > kGroupPatBytes) return false;  // split: entries address 4 MiB of pattern bytes
-  pb.resize(pb.size() + 16, 0);  // the kernel reads a pattern's first 16 bytes at once, whatever its length
-  if (table) {
-    // one record per cuckoo slot: the run of entries whose table key sits in
-    // that slot, a single entry held inline
-    const uint32_t S = (uint32_t)out.tab.size(), sh = D.fp_mask;
-    std::vector<uint64_t> rec(S, 0);
-    for (size_t i = 0; i < P.size();) {
-      size_t j = i;
-      while (j < P.size() && (uint32_t)P[j].key == (uint32_t)P[i].key) ++j;
-      const uint32_t h = (uint32_t)P[i].key;
-      uint32_t s = ck_slot1(h, sh);
-      if (out.tab[s] != h) s = ck_slot2(h, sh);
-      rec[s] = key_record(ents, i, j);
-      i = j;
+  pb.resize(pb.size() + 48, 0);  // the kernel reads 48 bytes from any pattern's start
+  // one record per lookup bit: its pattern's, or a run of records behind them
+  std::vector<One> tab;
+  std::vector<std::pair<size_t, size_t>> runs;  // of ones; the record that refers to run i comes at tab index -1
+  for (size_t i = 0; i < ones.size();) {
+    size_t j = i + 1;
+    while (j < ones.size() && ones[j].at == ones[i].at) ++j;
+    tab.push_back(ones[i]);
+    if (j > i + 1) {
+      tab.back().rec = 0;
+      runs.emplace_back(i, j);
     }
-    D.ht_mask = S - 1;
-    D.ht_off = put_bytes(out.glob, rec.data(), rec.size() * 8);
-  } else {
-    // key -> run record, open addressing
-    const uint32_t S = std::max<uint32_t>(2, next_pow2(2 * (uint32_t)dist.size()));
-    std::vector<uint64_t> keys(S, kEmptyKey), vals(S, 0);
-    for (size_t i = 0; i < P.size();) {
-      size_t j = i;
-      while (j < P.size() && P[j].key == P[i].key) ++j;
-      uint32_t s = ht_slot(P[i].key, S - 1);
-      while (keys[s] != kEmptyKey) s = (s + 1) & (S - 1);
-      keys[s] = P[i].key;
-      vals[s] = key_record(ents, i, j);
-      i = j;
-    }
-    std::vector<uint8_t> ht(S * 16);
-    memcpy(ht.data(), keys.data(), S * 8);
-    memcpy(ht.data() + S * 8, vals.data(), S * 8);
-    D.ht_mask = S - 1;
-    D.ht_off = put_bytes(out.glob, ht.data(), ht.size());
+    i = j;
   }
-  D.ent_off = put_bytes(out.glob, ents.data(), ents.size() * sizeof(Entry));
-  D.pat_off = put_bytes(out.glob, pb.data(), pb.size());
-  D.max_m = max_m;
+  const size_t nord = tab.size();
+  size_t run = 0;
+  for (size_t i = 0; i < nord; ++i) {
+    if (tab[i].rec) continue;
+    const size_t lo = runs[run].first, hi = runs[run].second;
+    ++run;
+    tab[i].rec = rec_run((uint32_t)tab.size(), (uint32_t)(hi - lo));
+    for (size_t q = lo; q < hi; ++q) tab.push_back(ones[q]);
+  }
+  D.ntab = (uint32_t)tab.size();
+  std::vector<uint8_t> tb(24 * tab.size(), 0);
+  for (size_t i = 0; i < tab.size(); ++i) {
+    const PatRef &r = *tab[i].p;
+    const uint32_t t = std::min(r.m, 16u);
+    memcpy(tb.data() + 16 * i + 16 - t, r.p + r.m - t, t);
+    memcpy(tb.data() + 16 * tab.size() + 8 * i, &tab[i].rec, 8);
+  }
+  out.ids_lds = tab_lds && 4 * ids.size() <= kIdsLds;
+  out.tab_lds = out.ids_lds && tb.size() <= kTabLds;
+  out.pat_lds = tab_lds && pb.size() <= kPatLds;
+  if (out.tab_lds) D.shift |= 1u << 16;
+  if (out.pat_lds) D.shift |= 1u << 17;
+  if (out.ids_lds) D.shift |= 1u << 18;
+  D.tab_off = put_bytes(out.tab_lds ? out.lds : out.glob, tb.data(), tb.size());
+  D.ids_off = put_bytes(out.ids_lds ? out.lds : out.glob, ids.data(), ids.size() * 4);
+  D.pat_off = put_bytes(out.pat_lds ? out.lds : out.glob, pb.data(), pb.size());
   return true;
 }
 
 // Emits G, splitting its pattern list in halves while it does not fit.
-static void expand_group(const GroupIn &G, std::vector<GroupBody> &bodies) {
+static void expand_group(const GroupIn &G, bool tab_lds, std::vector<GroupBody> &bodies) {
   GroupBody gb;
-  if (emit_group(G, gb) || G.pats.size() < 2) {
+  if (emit_group(G, tab_lds, gb) || G.pats.size() < 2) {
     bodies.push_back(std::move(gb));
     return;
   }
@@ -335,17 +302,24 @@ static void expand_group(const GroupIn &G, std::vector<GroupBody> &bodies) {
   const size_t h = G.pats.size() / 2;
   a.pats.assign(G.pats.begin(), G.pats.begin() + h);
   b.pats.assign(G.pats.begin() + h, G.pats.end());
-  expand_group(a, bodies);
-  expand_group(b, bodies);
+  expand_group(a, tab_lds, bodies);
+  expand_group(b, tab_lds, bodies);
 }
 
 // Packs groups greedily into virtual instances whose LDS part (header,
-// descriptors, cuckoo tables) fits kImgLimit.  Image layout:
+// descriptors, bitmaps, record tables) fits kImgLimit.  Image layout:
 //   [ImageHeader][BucketDesc x nb][LDS parts ...][device-memory parts ...]
 static rk_status build_images(rk_ctx *ctx, const std::vector<GroupIn> &groups, uint32_t src_inst,
                               std::vector<VInst> &vinsts, std::vector<uint8_t> &blob) {
   std::vector<GroupBody> bodies;
-  for (const GroupIn &G : groups) expand_group(G, bodies);
+  for (const GroupIn &G : groups) expand_group(G, true, bodies);
+  // records go to device memory rather than to another image (another scan)
+  uint64_t all = sizeof(ImageHeader);
+  for (const GroupBody &b : bodies) all += 64 + align_up(b.lds.size(), 16);
+  if (all > kImgLimit) {
+    bodies.clear();
+    for (const GroupIn &G : groups) expand_group(G, false, bodies);
+  }
   size_t i = 0;
   while (i < bodies.size()) {
     size_t j = i;
@@ -378,13 +352,16 @@ static rk_status build_images(rk_ctx *ctx, const std::vector<GroupIn> &groups, u
     bool only_one_list = true;
     for (size_t b = i; b < j; ++b) {
       BucketDesc d = bodies[b].D;
-      npat += d.npat;
-      if (d.kind == kTableScreen || d.kind == kTableExact) d.fp_off += lds_base[b - i];
-      d.ht_off += glob_base[b - i];
-      d.ent_off += glob_base[b - i];
-      d.pat_off += glob_base[b - i];
-      max_m = std::max(max_m, d.max_m);
-      if (d.kind != kListScreen || (d.shift >> 8) != 1u) only_one_list = false;
+      npat += bodies[b].npat;
+      if (d.kind == kTableScreen || d.kind == kTableExact) {
+        d.test_off += lds_base[b - i];
+        d.lk_off += lds_base[b - i];
+      }
+      d.tab_off += bodies[b].tab_lds ? lds_base[b - i] : glob_base[b - i];
+      d.ids_off += bodies[b].ids_lds ? lds_base[b - i] : glob_base[b - i];
+      d.pat_off += bodies[b].pat_lds ? lds_base[b - i] : glob_base[b - i];
+      max_m = std::max(max_m, bodies[b].max_m);
+      if (d.kind != kListScreen) only_one_list = false;
       memcpy(img.data() + sizeof(ImageHeader) + 64 * (b - i), &d, 64);
     }
     ImageHeader hd;
@@ -430,34 +407,37 @@ static std::vector<GroupIn> group_patterns(const uint8_t *bytes, const uint64_t 
   std::map<uint32_t, GroupIn> by;
   for (uint32_t j = 0; j < k; ++j) {
     const uint32_t m = (uint32_t)(offs[j + 1] - offs[j]);
-    const uint8_t *p = bytes + offs[j];
-    GroupIn &G = by[group_id(mode, m)];
     PatRef r;
     r.pid = pid_base + j;
-    r.p = p;
+    r.p = bytes + offs[j];
     r.m = m;
-    r.hx = host_hash(p, m);
-    // the window a group's stream hashes: the shortest length of the group,
-    // at most kStreamM bytes in exact mode
-    const uint32_t ms = mode == RK_MODE_EXACT ? std::min(m, kStreamM) : m;
-    if (G.pats.empty()) {
-      G.screen = mode != RK_MODE_EXACT;
-      G.shift = screen_shift(m);
-      G.mask = screen_mask(m);
-      G.m = ms;
-    }
-    G.m = std::min(G.m, ms);
-    r.key = G.screen ? (uint64_t)screen_hash(p, m) : 0;
-    G.pats.push_back(r);
+    r.at = r.lk = 0;
+    r.key = 0;
+    by[length_class(m)].pats.push_back(r);
   }
+  auto join = [&](uint32_t from, uint32_t to, size_t most) {
+    auto f = by.find(from), t = by.find(to);
+    if (f == by.end() || t == by.end() || f->second.pats.size() > most) return;
+    t->second.pats.insert(t->second.pats.end(), f->second.pats.begin(), f->second.pats.end());
+    by.erase(f);
+  };
+  join(6, 5, kJoinLong);
+  join(5, 4, kJoinShort);
   std::vector<GroupIn> out;
   for (auto &kv : by) {
     GroupIn &G = kv.second;
-    // exact keys: the exact hash of each pattern's last G.m bytes (the whole
-    // pattern when it is that long)
-    if (!G.screen)
-      for (PatRef &r : G.pats) r.key = r.m == G.m ? r.hx : host_hash(r.p + r.m - G.m, G.m);
-    out.push_back(G);
+    G.screen = mode != RK_MODE_EXACT;
+    G.m = G.pats[0].m;
+    for (const PatRef &r : G.pats) G.m = std::min(G.m, r.m);
+    G.shift = screen_shift(G.m);
+    G.mask = G.m < 4 ? (1u << (8 * G.m)) - 1u : 0xFFFFFFFFu;
+    if (!G.screen) G.m = std::min(G.m, kStreamM);
+    for (PatRef &r : G.pats) {
+      r.lk = screen_hash(r.p, r.m, G.shift, G.mask);
+      // exact keys: the exact hash of the last G.m bytes
+      r.key = G.screen ? (uint64_t)r.lk : host_hash(r.p + r.m - G.m, G.m);
+    }
+    out.push_back(std::move(G));
   }
   return out;
 }

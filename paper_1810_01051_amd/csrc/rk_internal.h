@@ -15,48 +15,58 @@ constexpr uint32_t kStreamM = 64;          // longest window hashed by a rolling
                                            // keyed by their last kStreamM bytes
 constexpr uint32_t kPosBits = 40;          // hit record = pid << 40 | start position
 constexpr uint64_t kPosMask = (1ull << kPosBits) - 1;
-constexpr uint32_t kCandCap = 1024;        // candidate slots in LDS per workgroup (window index in the tile, u16)
-constexpr uint32_t kMaxWaves = 16;
+constexpr uint32_t kWaveCand = 256;         // candidate slots in LDS per wave (window index in the sub-tile, u16)
+constexpr uint32_t kListBlock = 256;       // threads of a single-bucket scan's block (its waves are independent)
 constexpr uint32_t kNoLink = 0xFFFFFFFFu;
 constexpr uint64_t kEmptyKey = ~0ull;      // empty exact-table slot (no canonical hash is >= q)
 
 // Screen/test variants of one bucket (one pattern length inside one instance).
 enum BucketKind : uint32_t {
-  kListScreen = 0,   // screen mode: shift-add hash compared with up to 4 targets
-  kTableScreen = 1,  // screen mode: shift-add hash probed in the LDS cuckoo table
-  kListExact = 2,    // exact mode: lazy 61-bit state compared with up to 4 lazy targets
-  kTableExact = 3,   // exact mode: low word of the canonical 61-bit hash probed in the cuckoo table
+  kListScreen = 0,   // screen mode, one key: shift-add hash compared with it
+  kTableScreen = 1,  // screen mode: shift-add hash tested in the LDS bitmap
+  kListExact = 2,    // exact mode, one key: lazy 61-bit state compared with its lazy forms
+  kTableExact = 3,   // exact mode: low word of the lazy state tested in the LDS bitmap
   kDump = 4,         // exact rolling state written out for sampled windows (no patterns)
 };
 
 // Group descriptor as laid out in an instance image (64 bytes).  A group is a
 // set of patterns tested with one hash stream: one length class in exact mode
 // (keyed on its shortest length), one screen-hash span in screen mode.
+//
+// Bitmaps have 2^(32 - sh) 32-bit words; a 32-bit value v sits in word v >> sh,
+// bit v & 31.  The test bitmap holds what the stream tests (screen: the keys
+// times kMix; exact: the low word of every lazy form of every key), the lookup
+// bitmap the patterns' shift-add keys times kMix, whose bits in ascending
+// order number the records; it is followed by u16 counts of the set bits
+// before each word.  In screen groups the two are one.
 struct BucketDesc {
   uint32_t m;          // the group's shortest length: the window its exact stream hashes
   uint32_t kind;       // BucketKind
-  uint32_t shift;      // screen groups: shift s in bits 0-7, list target count (1 or 4) in bits 8-15
+  uint32_t shift;      // shift s of the screen or lookup hash in bits 0-7; one exact key: its lazy forms in
+                       // bits 8-15; in the LDS part: bit 16 tails and records, 17 pattern bytes, 18 ids
   uint32_t mask;       // screen-hash mask (all ones unless m < 4 with s = 8)
   uint32_t tgt[4];     // list kinds: targets (padded by repetition)
-  uint32_t fp_off;     // table kinds: image offset of the cuckoo table (u32 keys; LDS part)
-  uint32_t fp_mask;    // table kinds: 32 - log2(table slots), the slot shift of ck_slot1/2
-  uint32_t ht_off;     // list kinds: key table, u64 keys[ht_mask+1] then u64 records[ht_mask+1];
-                       // table kinds: u64 records[ht_mask+1], one per cuckoo slot
-  uint32_t ht_mask;    // key-table (list) or cuckoo-table (table) slots - 1
-  uint32_t ent_off;    // Entry[npat], sorted by (key, length, pattern id)
-  uint32_t max_m;      // longest pattern in the group
-  uint32_t pat_off;    // pattern bytes; Entry::off_m low 24 bits are relative to this
-  uint32_t npat;       // patterns in this group
+  uint32_t test_off;   // table kinds: image offset of the test bitmap (LDS part)
+  uint32_t test_sh;    // its sh
+  uint32_t lk_off;     // table kinds: image offset of the lookup bitmap and its counts (LDS part)
+  uint32_t lk_sh;      // the lookup bitmap's sh
+  uint32_t tab_off;    // per record its pattern's last 16 bytes (zeros before a shorter one), then u64 records
+  uint32_t ntab;       // records: one per lookup bit, then those of the bits' runs
+  uint32_t ids_off;    // u32 pattern ids of the patterns that have several
+  uint32_t pat_off;    // pattern bytes; om_pack offsets are relative to this
 };
 static_assert(sizeof(BucketDesc) == 64, "bucket descriptor is 64 bytes");
 
-// One pattern of a group (16 bytes).
-struct Entry {
-  uint64_t hx;     // exact hash of the pattern, canonical
-  uint32_t pid;    // global pattern id
-  uint32_t off_m;  // om_pack(byte offset of the pattern, length)
-};
-static_assert(sizeof(Entry) == 16, "entry is 16 bytes");
+// Shift-add keys are looked up times this odd constant, mod 2^32.  The product
+// rolls like the hash itself (p <- (p << s) + kMix c) at no cost: the
+// multiplication by kMix takes the entering byte out of its word, which the
+// hash needs an instruction for as well.  Its high bits spread like random
+// ones: on word text with 1,024 patterns 1.5% of the windows pass an 8 KiB
+// bitmap besides the matches, as many as bits are set; the high half of the
+// hash itself lets 5.4% pass (sums of letters).
+constexpr uint32_t kMix = 0x85EBCB;
+
+constexpr uint32_t kMinBitmap = 256, kMaxBitmap = 32 * 1024;  // bytes
 
 // Pattern reference of an entry: byte offset in its group's pattern block
 // (bits 0-21, so a group holds at most 4 MiB of pattern bytes) and length - 1
@@ -67,39 +77,28 @@ __host__ __device__ inline uint32_t om_pack(uint32_t off, uint32_t m) { return o
 __host__ __device__ inline uint32_t om_len(uint32_t om) { return (om >> kOmOffBits) + 1u; }
 __host__ __device__ inline uint32_t om_off(uint32_t om) { return om & (kGroupPatBytes - 1u); }
 
-// Record of a key (list kinds: in the key table; table kinds: per cuckoo
-// slot): the run of entries with that key, or the single entry inline.
-//   bit 63 set : one entry, pattern id in bits 32..55, off_m in bits 0..31
-//   bits 63-62 = 01: a run of identical patterns (one pattern under several
-//                ids): count - 1 in bits 54..61, first entry in bits 32..53,
-//                their shared off_m in bits 0..31
-//   bits 63-62 = 00: count in bits 32..61 (0: no entry), first entry in bits 0..31
-__host__ __device__ inline uint64_t slot_inline(uint32_t pid, uint32_t off_m) {
+// Record of a lookup bit (list kinds: of the one key): its pattern, or the run
+// of records of several different patterns.
+//   bit 63 set : one pattern with one id, in bits 32..55, off_m in bits 0..31
+//   bits 63-62 = 01: one pattern with several ids: count - 1 in bits 54..61,
+//                index of the first in the id list in bits 32..53, off_m in
+//                bits 0..31
+//   bits 63-62 = 00: records [first, first + count): count in bits 32..61 (0:
+//                no record), first in bits 0..31
+__host__ __device__ inline uint64_t rec_inline(uint32_t pid, uint32_t off_m) {
   return (1ull << 63) | ((uint64_t)pid << 32) | off_m;
 }
-__host__ __device__ inline uint64_t slot_run(uint32_t first, uint32_t count) {
+__host__ __device__ inline uint64_t rec_run(uint32_t first, uint32_t count) {
   return ((uint64_t)count << 32) | first;
 }
 constexpr uint32_t kSameMaxCount = 256, kSameMaxFirst = 1u << 22;
-__host__ __device__ inline uint64_t slot_same(uint32_t first, uint32_t count, uint32_t off_m) {
+__host__ __device__ inline uint64_t rec_ids(uint32_t first, uint32_t count, uint32_t off_m) {
   return (1ull << 62) | ((uint64_t)(count - 1u) << 54) | ((uint64_t)first << 32) | off_m;
 }
-__host__ __device__ inline bool rec_one_pattern(uint64_t rec) { return (rec >> 62) != 0; }  // inline or identical run
+__host__ __device__ inline bool rec_one_pattern(uint64_t rec) { return (rec >> 62) != 0; }
 __host__ __device__ inline bool rec_same(uint64_t rec) { return (rec >> 62) == 1u; }
 __host__ __device__ inline uint32_t same_count(uint64_t rec) { return (uint32_t)((rec >> 54) & 0xFFu) + 1u; }
 __host__ __device__ inline uint32_t same_first(uint64_t rec) { return (uint32_t)(rec >> 32) & (kSameMaxFirst - 1u); }
-
-// Slot of a key in a group's key table (the host builds it, the kernel probes it).
-__host__ __device__ inline uint32_t ht_slot(uint64_t key, uint32_t mask) {
-  return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 40) & mask;
-}
-
-// Two slots of a 32-bit key in a cuckoo table of 2^(32-sh) slots (built on
-// the host, probed by the kernel): multiplicative mixes of the key's low and
-// high 24 bits (each a 24 x 24-bit product, one full-rate multiply on gfx950).
-__host__ __device__ inline uint32_t ck_slot1(uint32_t h, uint32_t sh) { return ((h & 0xFFFFFFu) * 0x9E3779u) >> sh; }
-__host__ __device__ inline uint32_t ck_slot2(uint32_t h, uint32_t sh) { return ((h >> 8) * 0xC2B2AFu) >> sh; }
-constexpr uint32_t kMaxTableBits = 13;  // largest cuckoo table: 8192 slots, 32 KiB of LDS
 
 // Header at the start of an instance image (16 bytes), followed by nb
 // descriptors, the parts staged in LDS and the parts read from device memory.
@@ -107,7 +106,7 @@ struct ImageHeader {
   uint32_t nbuckets;
   uint32_t bytes;      // total image bytes (multiple of 16)
   uint32_t max_m;
-  uint32_t lds_bytes;  // leading bytes staged in LDS (header, descriptors, cuckoo tables)
+  uint32_t lds_bytes;  // leading bytes staged in LDS (header, descriptors, bitmaps, small record tables)
 };
 
 // One instance of a scan job (48 bytes).
@@ -122,10 +121,16 @@ struct InstDesc {
 };
 static_assert(sizeof(InstDesc) == 48, "instance descriptor is 48 bytes");
 
-// The count pass adds each tile's hits to its block of 2^kTileSumLog2 tiles
-// (the blocks of the collect's prefix sum of the tile counts, which then
-// starts from these sums).
-constexpr uint32_t kTileSumLog2 = 12;
+// The count pass adds up its hits in kTotals counters of a 128-byte line each
+// (a wave's hits once, at its end): additions to one address are served one
+// after the other, about 7 ns each, which a counter per pass, added to by
+// every tile, made the bound of dense scans (a 1 GiB text's 61,681 tiles,
+// twice each: 0.8 ms).
+constexpr uint32_t kTotals = 16, kTotalStride = 128;
+
+// A run of consecutive tiles of one instance in a work list.
+constexpr uint32_t kItemShift = 48;
+constexpr uint64_t kItemTile = (1ull << kItemShift) - 1;
 
 // Kernel parameters of the scan (passed by value).
 struct ScanParams {
@@ -133,25 +138,28 @@ struct ScanParams {
   uint32_t ninst;
   uint32_t img_cap;           // LDS bytes reserved for an instance image
   const uint8_t *blob;        // instance images
-  const uint64_t *items;      // item -> global tile id (nullptr: identity)
-  uint64_t nitems;
+  uint32_t sub;               // sub-tiles of 64 C bytes per tile
+  const uint64_t *items;      // runs: first global tile id | tiles << kItemShift; wave_items: tile ids
+  uint64_t nitems;            // runs (wave_items: listed tiles)
   const uint32_t *nitems_dev; // optional device-side bound on nitems (rescan list length)
+  uint64_t inst_tiles;        // without items: tiles of each instance,
+  uint64_t inst_runs;         // runs of each,
+  uint32_t run;               // and tiles per run (the last one of an instance may have fewer)
+  uint32_t wave_items;        // 1: items lists tiles, one for each wave in turn (one instance, or one-wave blocks)
   uint32_t *tile_counts;      // hits per global tile
   uint64_t *out;              // count mode: slabs [tile][slab_cap]; direct mode: compact array
   const uint64_t *tile_offsets; // direct mode: first output slot of each tile
   uint32_t slab_cap;
   uint32_t direct;            // 1: rescan writing every hit at tile_offsets[tile]
-  unsigned long long *total;  // count mode: hits over all tiles
+  unsigned long long *totals; // count mode: hits over all tiles, in kTotals counters
   uint32_t *ovf_count;        // count mode: number of tiles with more hits than slab_cap
   uint64_t *ovf_list;         // count mode: those tiles' global ids
   uint32_t *queue;            // atomic work-queue cursor (nullptr: static striding)
-  uint32_t grab;              // items taken per queue pop
   uint64_t *dump_out;         // kDump buckets: destination of sampled hashes
   uint64_t dump_stride;
   uint64_t dump_cap;
   unsigned long long *pid_counts; // count mode, optional: hits per global pattern id
   uint64_t tile0;             // count mode: global id of the first tile of out's slabs
-  unsigned long long *blk_sums; // count mode, optional: hits per 2^kTileSumLog2 global tiles
 };
 
 // Kernel parameters of the single-bucket scan (one text, one bucket whose set
@@ -164,20 +172,22 @@ struct ListParams {
   BucketDesc D;               // the bucket (offsets relative to gimg)
   uint32_t rot;               // 8 m mod 61
   uint32_t slab_cap;
-  uint64_t rec1;              // record of the bucket's key if it has exactly one (else 0: look it up)
+  uint32_t sub;               // sub-tiles of 64 C bytes per tile
+  uint32_t tail[4];           // the record's tail
+  uint64_t rec1;              // record of the bucket's one key
   uint32_t *tile_counts;
   uint64_t *out;              // slabs [tile][slab_cap]
-  unsigned long long *total;
+  unsigned long long *totals; // hits, in kTotals counters
   uint32_t *ovf_count;
   uint64_t *ovf_list;
   uint64_t *dump_out;         // kDump bucket: destination of sampled hashes (no counts then)
   uint64_t dump_stride;
   uint64_t dump_cap;
   unsigned long long *pid_counts; // optional: hits per pattern id
-  unsigned long long *blk_sums; // optional: hits per 2^kTileSumLog2 tiles
 };
 
-// Host-side geometry table (workgroup size, windows per thread).
+// Host-side geometry table (windows per lane c; a tile is wg * c bytes, wg / 64
+// sub-tiles, in all but small texts).
 struct TileCfg {
   uint32_t wg;
   uint32_t c;
@@ -185,11 +195,15 @@ struct TileCfg {
 constexpr int kNumTileCfg = 4;
 constexpr TileCfg kTileCfgs[kNumTileCfg] = {{256, 68}, {256, 132}, {512, 68}, {256, 36}};
 
+// Largest block of the general kernel: 1,024 threads leave 128 VGPRs a lane,
+// which the exact family's words of a 132-window lane do not fit.
+constexpr uint32_t scan_block_max(int c, int fam) { return c > 68 && fam == 2 ? 512u : 1024u; }
+
 // Kernel families: each scan kernel is compiled for the bucket kinds one plan
 // can hold, so that a single-pattern search does not pay the register budget
 // of the multi-pattern and exact variants.
 enum Family : int {
-  kFamScreen1 = 0,  // list screen with one target per bucket
+  kFamScreen1 = 0,  // list screen buckets only
   kFamScreen = 1,   // every screen kind
   kFamExact = 2,    // every exact kind and the hash dump
 };

@@ -23,8 +23,11 @@
 namespace rk {
 
 constexpr uint64_t kStaticScratchBytes = RK_STATIC_SCRATCH_BYTES;
+// Beside the limit that callers see: the per-tile arrays of a short text's
+// smaller tiles (Layout::extra, at most 123 KB an image).
+constexpr uint64_t kStaticExtra = 2u << 20;
 
-static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
+static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes + kStaticExtra];
 
 // Device address of this device's copy of scratch, taken once per device.
 static std::mutex g_scratch_mu;
@@ -56,9 +59,14 @@ extern "C" rk_status rk_search_static(rk_ctx *ctx, const rk_plan *plan, const ui
   uint8_t *base = (uint8_t *)ctx->static_scratch;
   hipStream_t st = (hipStream_t)s;
   Layout L;
+  struct Lean {  // slabs as small as the array's limit is stated for
+    rk_ctx *c;
+    explicit Lean(rk_ctx *c) : c(c) { c->lean_slabs = true; }
+    ~Lean() { c->lean_slabs = false; }
+  } lean(ctx);
   rk_status r = make_layout(ctx, plan, n, L);
   if (r != RK_OK) return r;
-  if (L.total > kStaticScratchBytes)
+  if (L.total - L.extra > kStaticScratchBytes || L.extra > kStaticExtra)
     return set_err(ctx, RK_ENOSPACE, "search needs %llu bytes of scratch, the static array holds %llu",
                    (unsigned long long)L.total, (unsigned long long)kStaticScratchBytes);
   r = count_enqueue(ctx, plan, text_dev, n, base, L.total, nullptr, st);
@@ -69,7 +77,7 @@ extern "C" rk_status rk_search_static(rk_ctx *ctx, const rk_plan *plan, const ui
   *total_host = total;
   const uint64_t work_off = (L.total + 255) / 256 * 256;
   const uint64_t work = work_bytes_for(plan, total);
-  if (work_off + work > kStaticScratchBytes)
+  if (work_off - L.extra + work > kStaticScratchBytes)
     return set_err(ctx, RK_ENOSPACE, "collect of %llu hits needs %llu bytes of scratch, the static array holds %llu",
                    (unsigned long long)total, (unsigned long long)(work_off + work),
                    (unsigned long long)kStaticScratchBytes);

@@ -12,6 +12,7 @@
 namespace rk {
 
 constexpr uint32_t kImgLimit = 64 * 1024;  // largest instance image staged in LDS
+constexpr uint32_t kLdsPerCU = 160 * 1024;
 
 struct ProfEvent {
   hipEvent_t a, b;
@@ -57,6 +58,8 @@ struct Part {
   uint32_t inst0 = 0, ninst = 0;   // its instance descriptors (batch: in inst_dev)
   uint64_t item0 = 0, nitems = 0;  // its work-queue entries in items_dev (batch)
   uint64_t tile0 = 0, ntiles = 0;  // its tiles in the plan's tile numbering (batch)
+  uint32_t sub = 1;                // sub-tiles per tile (batch)
+  uint32_t block = 64;             // threads per block of its scan
 };
 
 struct RealInst {
@@ -74,6 +77,7 @@ struct rk_ctx {
   std::string arch;
   std::string err;
   uint32_t slab_cap = 0;
+  bool lean_slabs = false;     // rk_search_static: no more slab records than one per 16 (64) text bytes
   int tile_cfg = -1;
   uint32_t grid = 0;
   bool profile = false;
@@ -101,9 +105,10 @@ struct rk_plan {
   int fam = rk::kFamScreen1;
   uint32_t k_total = 0;
   uint32_t img_cap = 0;       // LDS bytes reserved for images (max image size)
-  bool list1 = false;         // one text, one bucket with register targets: single-bucket kernel
+  bool list1 = false;         // one text, one bucket with one key: single-bucket kernel
   rk::BucketDesc list_desc;   // that bucket
-  uint64_t list_rec1 = 0;     // its key's record when it has a single key
+  uint64_t list_rec1 = 0;     // its key's record
+  uint32_t list_tail[4] = {}; // and tail
   uint64_t text_bytes = 0;
   uint32_t max_m = 0;         // longest pattern
   std::vector<rk::RealInst> insts;
@@ -123,23 +128,32 @@ namespace rk {
 struct PartRun {
   uint64_t tile0 = 0, ntiles = 0;  // tiles of the part in the pass's numbering
   uint32_t W = 0;                  // tile bytes
+  uint32_t sub = 1;                // sub-tiles per tile
   uint32_t S = 0;                  // slab slots per tile
   uint64_t slabs = 0;              // scratch offset of the part's slabs [tile][S]
 };
 
-// Scratch of a pass: counters (total at 0, per-part overflow counts at 8 + 4p,
-// per-part queue cursors at 48 + 4p), instance descriptors (single plans),
+// Scratch of a pass: counters (per-part overflow counts at 8 + 4p, per-part
+// queue cursors at 48 + 4p, then the kTotals hit counters), instance descriptors (single plans),
 // per-tile counts, offsets and overflow lists, scan partials, slabs.
 struct Layout {
   uint64_t T = 0;      // tiles over all parts
   uint64_t T1 = 0;     // tiles per virtual instance (single plans)
   std::vector<PartRun> parts;
   uint64_t ctr = 0, inst = 0, counts = 0, offsets = 0, ovf = 0, total = 0;
-  uint64_t bsum = 0, nbsum = 0;  // the tiles' block sums (u64, nbsum entries) right after the 64 counter words
+  uint64_t extra = 0;  // bytes of total beyond what tiles of wg * c bytes would take
+  uint64_t bsum = 0;   // work of the tile counts' prefix sum
 };
-constexpr uint32_t kCtrOvf = 8, kCtrQueue = 48;
-// Tiles that overflowed their slabs, summed over parts, from the first 64
-// counter bytes.
+constexpr uint32_t kCtrOvf = 8, kCtrQueue = 48, kCtrTotals = 128;
+constexpr uint32_t kCtrBytes = kCtrTotals + kTotals * kTotalStride;  // read back after a count
+static_assert(kCtrBytes <= 4096, "the context's pinned buffer holds the counters");
+// Hits of a pass, from the counters.
+inline uint64_t hit_total(const uint64_t *ctr) {
+  uint64_t t = 0;
+  for (uint32_t i = 0; i < kTotals; ++i) t += ctr[(kCtrTotals + i * kTotalStride) / 8];
+  return t;
+}
+// Tiles that overflowed their slabs, summed over parts, from the counters.
 inline uint32_t ovf_total(const uint64_t *ctr) {
   const uint32_t *w = (const uint32_t *)ctr;
   uint32_t t = 0;
@@ -153,8 +167,6 @@ inline rk_status hip_err_or_ok(rk_ctx *ctx, hipError_t e) {
   return e == hipSuccess ? RK_OK : hip_err(ctx, e, "profiling event");
 }
 uint64_t host_hash(const uint8_t *p, uint64_t m);
-uint32_t screen_shift(uint32_t m);
-uint32_t screen_hash(const uint8_t *p, uint32_t m);
 
 rk_status plan_build(rk_ctx *ctx, const rk_instance *inst, uint32_t count, int mode, bool batch, rk_plan **out);
 rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L);
@@ -182,6 +194,13 @@ hipError_t prof_begin(rk_ctx *ctx, hipStream_t s, int kind, int *slot);
 hipError_t prof_end(rk_ctx *ctx, hipStream_t s, int slot);
 hipError_t launch_stream_read(const void *data, uint64_t n, uint32_t *out, uint32_t grid, hipStream_t s);
 
+// What a scan kernel's blocks take and how many are resident.
+struct ScanFit {
+  uint32_t wave_lds = 0;   // LDS bytes per wave beside the image
+  uint32_t max_block = 0;  // largest block (threads)
+  int blocks = 0;          // resident per CU
+};
+
 // Launchers of the scan kernels of one family (kFamScreen1 / kFamScreen /
 // kFamExact) and one geometry CFG of kTileCfgs.  The kernels are defined in
 // rk_scan.h and instantiated in the rk_scan_*.hip translation units (split by
@@ -189,9 +208,9 @@ hipError_t launch_stream_read(const void *data, uint64_t n, uint32_t *out, uint3
 // unit sees these declarations only.
 template <int FAM, int CFG>
 struct ScanGeom {
-  // the general scan kernel
-  static hipError_t launch(const ScanParams &p, uint32_t grid, uint32_t lds_bytes, hipStream_t s);
-  static hipError_t occupancy(uint32_t lds_bytes, int *blocks);
+  // the general scan kernel, in blocks of any multiple of 64 threads
+  static hipError_t launch(const ScanParams &p, uint32_t grid, uint32_t block, hipStream_t s);
+  static hipError_t fit(uint32_t img_cap, uint32_t block, ScanFit *f);
   static hipError_t prepare();
   // the single-bucket kernel
   static hipError_t list(const ListParams *p, uint32_t grid, hipStream_t s, int *blocks);
@@ -199,16 +218,12 @@ struct ScanGeom {
 };
 
 // device translation unit
-uint32_t scan_lds_bytes(int cfg, uint32_t img_cap);
-hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uint32_t lds_bytes, hipStream_t s);
-hipError_t scan_occupancy(int cfg, int fam, uint32_t lds_bytes, int *blocks_per_cu);
+hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uint32_t block, hipStream_t s);
+hipError_t scan_fit(int cfg, int fam, uint32_t img_cap, uint32_t block, ScanFit *f);
 hipError_t list_scan(int cfg, int fam, const ListParams *p, uint32_t grid, hipStream_t s, int *blocks_per_cu);
 uint64_t scan_tmp_words(uint64_t n);
 hipError_t launch_exclusive_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, uint64_t *total_dev,
                                  hipStream_t s);
-// the same scan when bsum already holds the sums of the counts' blocks of
-// 2^kTileSumLog2 (bsum: ceil(n / 2^kTileSumLog2) + 1 entries, overwritten)
-hipError_t launch_exclusive_scan_summed(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *bsum, hipStream_t s);
 // sparse: fewer hits than tiles (a lane per tile); offsets1: a single
 // pattern's offsets, written {0, total}, or null
 hipError_t launch_compact(const uint32_t *counts, const uint64_t *offs, uint64_t ntiles, const uint64_t *slabs,

@@ -9,7 +9,8 @@
 // in registers, so every text byte is read from HBM once.
 //
 // Window identity: a window is named by its END byte e (bytes e-m+1 .. e).
-// Thread t of a tile owns the windows ending at tile bytes [t*C, t*C + C).
+// A wave scans sub-tiles of 64 C bytes on its own: lane l owns the windows
+// ending at sub-tile bytes [l*C, l*C + C).
 //
 // Two ways to test a window (same results):
 //   exact  : the d=256, q=2^61-1 hash is rolled for every window
@@ -18,14 +19,16 @@
 //   screen : the paper's shift-and-add hash h' = (h << s) + in mod 2^32 is
 //            rolled for every window (s*m >= 32, so bytes older than the window
 //            shift out and no out-term is needed) and compared with the set.
-// A candidate window (its hash passed the set test) is hashed again from
-// scratch (exact: Horner, canonical value; screen: shift-and-add), looked up
-// in the open-addressing table of its bucket and confirmed byte by byte
-// against every pattern chained under that hash.
+// One key is compared in a register; a set of keys is a bitmap in LDS, indexed
+// by bits of the hash: one LDS read and a bit test per window.  A candidate
+// window (its hash passed the set test) finds its pattern by the rank of its
+// bit in a bitmap of the patterns' shift-add hashes, and is confirmed byte by
+// byte against every pattern of that bit.
 //
-// Hits are compacted with a block-wide prefix sum in ascending window order per
-// bucket into a per-tile staging slab; later kernels scan the tile counts,
-// compact the slabs and sort stably by pattern id.
+// Hits are appended in ascending window order per bucket to the staging slab
+// of their tile (a run of sub-tiles that one wave scans in order); later
+// kernels scan the tile counts, compact the slabs and sort stably by pattern
+// id.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -46,31 +49,37 @@ struct Bits {
   uint32_t b[(C + 31) / 32];
 };
 
-// Bit layout of Bits: window i lives in word i/32; inside a word the earliest
-// window takes the highest used bit (the flags are shifted in one by one).
+// Bit layout of Bits: window i is bit i%32 of word i/32.  The flags are
+// shifted in from the top, one instruction each: the low bit of f.
 template <int C>
 __device__ __forceinline__ constexpr int word_windows(int j) {
   return (C - 32 * j) < 32 ? (C - 32 * j) : 32;
 }
 template <int C>
-__device__ __forceinline__ uint32_t bit_of(int i) {
-  return 1u << (word_windows<C>(i >> 5) - 1 - (i & 31));
+__device__ __forceinline__ void put_bit(Bits<C> &bits, uint32_t &acc, int i, uint32_t f) {
+  acc = __builtin_amdgcn_alignbit(f, acc, 1);
+  if ((i & 31) == 31 || i == C - 1) bits.b[i >> 5] = acc >> (32 - word_windows<C>(i >> 5));
 }
-
-// Shifts the flag of window i into the mask.  The empty asm keeps the chain
-// sequential; otherwise the OR tree is reassociated and every flag of the
-// unrolled loop stays live at once.
+// The same with the flags of a wave's lanes in a mask: shifted in from the
+// bottom as an add with carry, then reversed.
 template <int C>
-__device__ __forceinline__ void put_bit(Bits<C> &bits, uint32_t &acc, int i, bool c) {
-  acc = acc + acc + (uint32_t)c;
-  __asm__ volatile("" : "+v"(acc));
+__device__ __forceinline__ void put_mask(Bits<C> &bits, uint32_t &acc, int i, uint64_t f) {
+  uint64_t carry;
+  __asm__("v_addc_co_u32 %0, %1, %0, %0, %2" : "+v"(acc), "=s"(carry) : "s"(f));
   if ((i & 31) == 31 || i == C - 1) {
-    bits.b[i >> 5] = acc;
+    bits.b[i >> 5] = __builtin_bitreverse32(acc) >> (32 - word_windows<C>(i >> 5));
     acc = 0;
   }
 }
 
 typedef __attribute__((address_space(3))) const uint32_t lds_word;
+typedef __attribute__((address_space(3))) uint16_t lds_half;
+typedef uint32_t rk_u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const rk_u32x4 lds_quad;
+// LDS reads by byte address (no generic pointers: a read that the compiler
+// merged with one from device memory would wait for the loads in flight).
+__device__ __forceinline__ uint32_t lds32(uint32_t a) { return *(lds_word *)(uintptr_t)a; }
+__device__ __forceinline__ uint32_t lds16(uint32_t a) { return *(lds_half *)(uintptr_t)a; }
 
 // ---------------------------------------------------- LDS reads out of sight
 // The tile pipeline issues the next tiles' loads-to-LDS before testing the
@@ -296,27 +305,17 @@ __device__ __forceinline__ void lds_read_words(uint32_t *w, uint32_t a) {
 
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lds_word *)p; }
 
-// The thread's bytes, loaded from the LDS tile by each pass itself (so that
+// The lane's bytes, loaded from the LDS sub-tile by each pass itself (so that
 // the loads, and the byte extractions that follow them, are not shared between
 // the test variants of a bucket and hoisted above the variant switch, which
-// would keep every extracted byte of every variant live at once; no register
-// copy of the words stays live across buckets either).
-template <int NW>
-__device__ __forceinline__ void load_words(uint32_t *w, const uint32_t *tw) {
-  lds_read_words<NW>(w, lds_addr(tw));
-}
+// would keep every extracted byte of every variant live at once).  Passes take
+// the LDS address of the lane's first window end (mine).
+// Words before a lane's first window end that the screen passes read: the 16
+// bytes their hash can reach back over.
+constexpr int kWarm = 4;
 
-// The thread's words of a tile already in registers (the 64 bytes before its
-// first window end and its C bytes; for exact passes also the out-stream
-// dwords), or none (nullptr): then each pass reads them from the LDS tile.
-template <int C>
-struct PreWords {
-  uint32_t w[16 + C / 4];
-  uint32_t d[C / 4 + 1];
-};
-
-// Shift-add hash state after the 64 bytes held in w[0..16), i.e. before the
-// thread's first window end: h = sum_j b[63-j] << (S*j) mod 2^32 (bytes older
+// Shift-add hash state after the 16 bytes held in w[0..4), i.e. before the
+// lane's first window end: h = sum_j b[15-j] << (S*j) mod 2^32 (bytes older
 // than 32/S positions have shifted out).  For S = 2 four bytes at a time with
 // one dot product each: the weights 4^3..4^0 of a word's bytes fit in bytes.
 template <int S>
@@ -324,13 +323,13 @@ __device__ __forceinline__ uint32_t screen_init(const uint32_t *w) {
   if constexpr (S == 2) {
     uint32_t h = 0;
 #pragma unroll
-    for (int q = 12; q < 16; ++q) h = __builtin_amdgcn_udot4(w[q], 0x01041040u, h << 8, false);
+    for (int q = 0; q < kWarm; ++q) h = __builtin_amdgcn_udot4(w[q], 0x01041040u, h << 8, false);
     return h;
   } else {
-    constexpr int WU = 32 / S - 1;  // bytes before the first window end that are still in the hash
+    constexpr int WU = (32 + S - 1) / S - 1;  // bytes before the first window end that are still in the hash
     uint32_t h = 0;
 #pragma unroll
-    for (int j = 64 - WU; j < 64; ++j) h = (h << S) + byte_at(w, j);
+    for (int j = 4 * kWarm - WU; j < 4 * kWarm; ++j) h = (h << S) + byte_at(w, j);
     return h;
   }
 }
@@ -342,93 +341,57 @@ __device__ __forceinline__ void any_or(uint64_t &any, uint64_t b) {
   __asm__ volatile("" : "+s"(any));
 }
 
-template <int C, int S, int NT, bool ANY>
-__device__ __forceinline__ void pass_list_screen_w(const uint32_t *w, uint32_t msk, const uint32_t *tg, uint64_t &any,
-                                                   Bits<C> &bits) {
+// One key: the hash of every window compared with it.
+template <int C, int S, bool ANY>
+__device__ __forceinline__ void pass_list_screen(uint32_t mine, uint32_t msk, uint32_t tgt, uint64_t &any,
+                                                 Bits<C> &bits) {
+  uint32_t w[kWarm + C / 4];
+  lds_read_words<kWarm + C / 4>(w, mine - 4 * kWarm);
   uint32_t h = screen_init<S>(w), acc = 0;
 #pragma unroll
   for (int i = 0; i < C; ++i) {
-    h = (h << S) + byte_at(w, 64 + i);
-    const uint32_t v = (S == 8) ? (h & msk) : h;
-    if (ANY) {
-      uint64_t b = ballot(v == tg[0]);
-      if (NT > 1) b |= ballot(v == tg[1]);
-      if (NT > 2) b |= ballot(v == tg[2]);
-      if (NT > 3) b |= ballot(v == tg[3]);
-      any_or(any, b);
-    } else {
-      bool c = v == tg[0];
-      if (NT > 1) c = c || v == tg[1];
-      if (NT > 2) c = c || v == tg[2];
-      if (NT > 3) c = c || v == tg[3];
-      put_bit<C>(bits, acc, i, c);
-    }
+    h = (h << S) + byte_at(w, 4 * kWarm + i);
+    const uint64_t f = ballot(((S == 8) ? (h & msk) : h) == tgt);
+    if (ANY) any_or(any, f);
+    else put_mask<C>(bits, acc, i, f);
   }
 }
 
-// The words come from registers (pre) or from the LDS tile; each branch
-// passes its own register array, so that no pointer selects between them.
-template <int C, int S, int NT, bool ANY, bool PRE>
-__device__ __forceinline__ void pass_list_screen(const uint32_t *tw, uint32_t msk, const uint32_t *tg, uint64_t &any,
-                                                 Bits<C> &bits, const PreWords<C> *pre) {
-  if constexpr (PRE) {
-    pass_list_screen_w<C, S, NT, ANY>(pre->w, msk, tg, any, bits);
-  } else {
-    uint32_t w[16 + C / 4];
-    load_words<16 + C / 4>(w, tw);
-    pass_list_screen_w<C, S, NT, ANY>(w, msk, tg, any, bits);
-  }
+// Word of a bitmap (LDS address base) for value v and, as the lowest bit, v's
+// bit in it.
+__device__ __forceinline__ uint32_t filter_word(uint32_t base, uint32_t sh, uint32_t v) {
+  return lds32(base + ((v >> sh) << 2));
 }
+__device__ __forceinline__ uint32_t filter_bit(uint32_t word, uint32_t v) { return word >> (v & 31u); }
 
-// Set test against a cuckoo table in LDS: the key is in one of its two slots.
-__device__ __forceinline__ bool in_cuckoo(const uint32_t *tab, uint32_t sh, uint32_t h) {
-  return (tab[ck_slot1(h, sh)] == h) | (tab[ck_slot2(h, sh)] == h);
-}
-
-// Windows per block of the table tests: the LDS probes of a block's windows
-// are all issued before the first of them is compared, so that their
-// latencies overlap (C is a multiple of 4 in every geometry).
+// Windows per block of the bitmap tests: the LDS reads of a block's windows
+// are all issued before the first of them is tested, so that their latencies
+// overlap (C is a multiple of 4 in every geometry).
 constexpr int kProbeBlock = 4;
 
-template <int C, int S, bool ANY>
-__device__ __forceinline__ void pass_table_screen_w(const uint32_t *w, uint32_t msk, const uint32_t *tab, uint32_t sh,
-                                                    uint64_t &any, Bits<C> &bits) {
+// A set of keys: kMix times the hash of every window tested in the bucket's
+// bitmap.  MASKED: windows shorter than the hash's span (one to three bytes),
+// whose hash is masked before the product (below 2^24, as kMix is).
+template <int C, int S, bool MASKED>
+__device__ __forceinline__ void pass_filter_screen(uint32_t mine, uint32_t msk, uint32_t base, uint32_t sh,
+                                                   Bits<C> &bits) {
   static_assert(C % kProbeBlock == 0, "whole probe blocks");
+  uint32_t w[kWarm + C / 4];
+  lds_read_words<kWarm + C / 4>(w, mine - 4 * kWarm);
   uint32_t h = screen_init<S>(w), acc = 0;
+  if (!MASKED) h *= kMix;
 #pragma unroll
   for (int i0 = 0; i0 < C; i0 += kProbeBlock) {
-    uint32_t v[kProbeBlock], t1[kProbeBlock], t2[kProbeBlock];
+    uint32_t v[kProbeBlock], t[kProbeBlock];
 #pragma unroll
     for (int j = 0; j < kProbeBlock; ++j) {
-      h = (h << S) + byte_at(w, 64 + i0 + j);
-      v[j] = (S == 8) ? (h & msk) : h;
+      const uint32_t c = byte_at(w, 4 * kWarm + i0 + j);
+      h = (h << S) + (MASKED ? c : __umul24(c, kMix));
+      v[j] = MASKED ? __umul24(h & msk, kMix) : h;
+      t[j] = filter_word(base, sh, v[j]);
     }
 #pragma unroll
-    for (int j = 0; j < kProbeBlock; ++j) {
-      t1[j] = tab[ck_slot1(v[j], sh)];
-      t2[j] = tab[ck_slot2(v[j], sh)];
-    }
-    if (ANY) {
-      uint64_t b = 0;
-#pragma unroll
-      for (int j = 0; j < kProbeBlock; ++j) b |= ballot(t1[j] == v[j]) | ballot(t2[j] == v[j]);
-      any_or(any, b);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i0 + j, (t1[j] == v[j]) | (t2[j] == v[j]));
-    }
-  }
-}
-
-template <int C, int S, bool ANY, bool PRE>
-__device__ __forceinline__ void pass_table_screen(const uint32_t *tw, uint32_t msk, const uint32_t *tab, uint32_t sh,
-                                                  uint64_t &any, Bits<C> &bits, const PreWords<C> *pre) {
-  if constexpr (PRE) {
-    pass_table_screen_w<C, S, ANY>(pre->w, msk, tab, sh, any, bits);
-  } else {
-    uint32_t w[16 + C / 4];
-    load_words<16 + C / 4>(w, tw);
-    pass_table_screen_w<C, S, ANY>(w, msk, tab, sh, any, bits);
+    for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i0 + j, filter_bit(t[j], v[j]));
   }
 }
 
@@ -499,16 +462,13 @@ __device__ __forceinline__ int out_kind(uint32_t r) { return r <= 24 ? 0 : ((r >
 // o = 4*ceil(m/4) bytes before the thread's first window end and realigned by
 // sh = o - m bytes with alignbyte, four windows per dword.
 struct OutStream {
-  const uint32_t *d;  // LDS, 4-byte aligned
+  uint32_t d;  // LDS address, 4-byte aligned
   uint32_t sh;
 };
 
-__device__ __forceinline__ OutStream out_stream(const uint8_t *mine, uint32_t m) {
+__device__ __forceinline__ OutStream out_stream(uint32_t mine, uint32_t m) {
   const uint32_t o = (m + 3u) & ~3u;
-  OutStream os;
-  os.d = (const uint32_t *)(mine - o);
-  os.sh = o - m;
-  return os;
+  return OutStream{mine - o, o - m};
 }
 
 // The exact rolling hash over the thread's C windows, the one loop every
@@ -534,54 +494,45 @@ __device__ __forceinline__ void roll_exact(const uint32_t *w, const uint32_t *d,
   }
 }
 
-template <int C, bool ANY, bool TABLE, int NT, int OUTK>
-__device__ __forceinline__ void pass_exact_w(const uint32_t *w, const uint32_t *d, OutStream os, uint32_t m, uint32_t r,
-                                             const uint32_t *tg, const uint32_t *fp, uint32_t sh, uint64_t &any,
-                                             Bits<C> &bits) {
-  uint32_t acc = 0;
+// FILTER: the low word of the lazy state in the bucket's bitmap, which holds
+// every lazy form of every key; else compared with the one key's lazy forms.
+template <int C, bool ANY, bool FILTER, int NT, int OUTK>
+__device__ __forceinline__ void pass_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
+                                           uint32_t base, uint32_t fsh, uint64_t &any, Bits<C> &bits) {
+  static_assert(!(ANY && FILTER), "bitmap tests fill the mask");
+  uint32_t w[16 + C / 4], d[C / 4 + 1], acc = 0;
+  lds_read_words<16 + C / 4>(w, mine - 64);
+  lds_read_words<C / 4 + 1>(d, os.d);
+  uint32_t v[kProbeBlock], t[kProbeBlock];
   roll_exact<C, OUTK>(w, d, os, m, r, [&](int i, uint64_t s) __attribute__((always_inline)) {
-    if (TABLE) {
-      const bool c = in_cuckoo(fp, sh, (uint32_t)canon(s));
-      if (ANY) any_or(any, ballot(c));
-      else put_bit<C>(bits, acc, i, c);
-    } else {
-      // lazy state s = H + j*q for j in {0,1,2}; the host lists the low words
-      const uint32_t lo = (uint32_t)s;
-      if (ANY) {
-        uint64_t b = ballot(lo == tg[0]) | ballot(lo == tg[1]);
-        if (NT > 2) b |= ballot(lo == tg[2]) | ballot(lo == tg[3]);
-        any_or(any, b);
-      } else {
-        bool c = lo == tg[0] || lo == tg[1];
-        if (NT > 2) c = c || lo == tg[2] || lo == tg[3];
-        put_bit<C>(bits, acc, i, c);
+    // lazy state s = H + j*q for j in {0,1,2}; the host lists the low words
+    const uint32_t lo = (uint32_t)s;
+    if constexpr (FILTER) {
+      v[i % kProbeBlock] = lo;
+      t[i % kProbeBlock] = filter_word(base, fsh, lo);
+      if (i % kProbeBlock == kProbeBlock - 1) {
+#pragma unroll
+        for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i + 1 - kProbeBlock + j, filter_bit(t[j], v[j]));
       }
+    } else if (ANY) {
+      uint64_t b = ballot(lo == tg[0]) | ballot(lo == tg[1]);
+      if (NT > 2) b |= ballot(lo == tg[2]);
+      any_or(any, b);
+    } else {
+      uint64_t f = ballot(lo == tg[0]) | ballot(lo == tg[1]);
+      if (NT > 2) f |= ballot(lo == tg[2]);
+      put_mask<C>(bits, acc, i, f);
     }
   });
 }
 
-template <int C, bool ANY, bool TABLE, int NT, int OUTK, bool PRE>
-__device__ __forceinline__ void pass_exact(const uint32_t *tw, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
-                                           const uint32_t *fp, uint32_t sh, uint64_t &any, Bits<C> &bits,
-                                           const PreWords<C> *pre) {
-  if constexpr (PRE) {
-    pass_exact_w<C, ANY, TABLE, NT, OUTK>(pre->w, pre->d, os, m, r, tg, fp, sh, any, bits);
-  } else {
-    uint32_t w[16 + C / 4], d[C / 4 + 1];
-    load_words<16 + C / 4>(w, tw);
-    load_words<C / 4 + 1>(d, os.d);
-    pass_exact_w<C, ANY, TABLE, NT, OUTK>(w, d, os, m, r, tg, fp, sh, any, bits);
-  }
-}
-
-template <int C, bool ANY, bool TABLE, int NT, bool PRE>
-__device__ __forceinline__ void pass_exact_r(const uint32_t *tw, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
-                                             const uint32_t *fp, uint32_t sh, uint64_t &any, Bits<C> &bits,
-                                             const PreWords<C> *pre) {
+template <int C, bool ANY, bool FILTER, int NT>
+__device__ __forceinline__ void pass_exact_r(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
+                                             uint32_t base, uint32_t fsh, uint64_t &any, Bits<C> &bits) {
   const int k = out_kind(r);
-  if (k == 0) pass_exact<C, ANY, TABLE, NT, 0, PRE>(tw, os, m, r, tg, fp, sh, any, bits, pre);
-  else if (k == 1) pass_exact<C, ANY, TABLE, NT, 1, PRE>(tw, os, m, r, tg, fp, sh, any, bits, pre);
-  else pass_exact<C, ANY, TABLE, NT, 2, PRE>(tw, os, m, r, tg, fp, sh, any, bits, pre);
+  if (k == 0) pass_exact<C, ANY, FILTER, NT, 0>(mine, os, m, r, tg, base, fsh, any, bits);
+  else if (k == 1) pass_exact<C, ANY, FILTER, NT, 1>(mine, os, m, r, tg, base, fsh, any, bits);
+  else pass_exact<C, ANY, FILTER, NT, 2>(mine, os, m, r, tg, base, fsh, any, bits);
 }
 
 // Destination of a hash dump: the canonical hash of every window whose start
@@ -615,220 +566,103 @@ __device__ __forceinline__ void pass_dump_w(const uint32_t *w, const uint32_t *d
   });
 }
 
-// The dump of one tile for the thread: words from registers (pre) or the LDS tile.
-template <int C, bool PRE>
-__device__ __forceinline__ void pass_dump(const uint32_t *tw, OutStream os, uint32_t m, uint32_t r, int64_t e0, uint64_t n,
-                                          const DumpDst &dst, const PreWords<C> *pre) {
-  uint32_t wl[PRE ? 1 : 16 + C / 4], dl[PRE ? 1 : C / 4 + 1];
-  const uint32_t *w = wl, *d = dl;
-  if constexpr (PRE) {
-    w = pre->w;
-    d = pre->d;
-  } else {
-    load_words<16 + C / 4>(wl, tw);
-    load_words<C / 4 + 1>(dl, os.d);
-  }
+template <int C>
+__device__ __forceinline__ void pass_dump(uint32_t mine, OutStream os, uint32_t m, uint32_t r, int64_t e0, uint64_t n,
+                                          const DumpDst &dst) {
+  uint32_t w[16 + C / 4], d[C / 4 + 1];
+  lds_read_words<16 + C / 4>(w, mine - 64);
+  lds_read_words<C / 4 + 1>(d, os.d);
   const int k = out_kind(r);
   if (k == 0) pass_dump_w<C, 0>(w, d, os, m, r, e0, n, dst);
   else if (k == 1) pass_dump_w<C, 1>(w, d, os, m, r, e0, n, dst);
   else pass_dump_w<C, 2>(w, d, os, m, r, e0, n, dst);
 }
 
-// Runs the test pass of bucket D over the thread's windows: ANY=true ORs the
-// wave ballots into any, ANY=false fills the per-thread candidate mask.
-// D.shift holds the screen shift in bits 0-7 and the number of list targets
-// (1, or up to 4 padded by repetition) in bits 8-15.  PRE: the thread's words
-// are already in registers (*pre); else each pass reads them from the tile.
-template <int C, bool ANY, int FAM, bool PRE = false>
-__device__ __forceinline__ void run_pass(const BucketDesc &D, const uint32_t *tw, OutStream os, uint32_t r,
-                                         const uint32_t *fp, uint64_t &any, Bits<C> &bits,
-                                         const PreWords<C> *pre = nullptr) {
+// Runs the test pass of bucket D over the lane's windows: ANY=true ORs the
+// wave ballots into any (one-key buckets), ANY=false fills the lane's
+// candidate mask.  D.shift holds the screen shift in bits 0-7 and, for one
+// exact key, the number of its lazy forms in bits 8-15; base: LDS address of
+// the bucket's bitmap.
+template <int C, bool ANY, int FAM>
+__device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r,
+                                         uint32_t base, uint64_t &any, Bits<C> &bits) {
   const uint32_t sh = D.shift & 0xFFu;
-  if constexpr (FAM == kFamScreen1) {
-    if (sh == 2) pass_list_screen<C, 2, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-    else if (sh == 4) pass_list_screen<C, 4, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-    else pass_list_screen<C, 8, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-  } else if constexpr (FAM == kFamScreen) {
-    if (D.kind == kListScreen) {
-      if ((D.shift >> 8) == 1u) {
-        if (sh == 2) pass_list_screen<C, 2, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-        else if (sh == 4) pass_list_screen<C, 4, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-        else pass_list_screen<C, 8, 1, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-      } else {
-        if (sh == 2) pass_list_screen<C, 2, 4, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-        else if (sh == 4) pass_list_screen<C, 4, 4, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-        else pass_list_screen<C, 8, 4, ANY, PRE>(tw, D.mask, D.tgt, any, bits, pre);
-      }
+  if constexpr (FAM == kFamExact) {
+    if (ANY || D.kind == kListExact) {
+      if (((D.shift >> 8) & 0xFFu) <= 2u)
+        pass_exact_r<C, ANY, false, 2>(mine, os, D.m, r, D.tgt, 0, 0, any, bits);
+      else
+        pass_exact_r<C, ANY, false, 3>(mine, os, D.m, r, D.tgt, 0, 0, any, bits);
     } else {
-      if (sh == 2) pass_table_screen<C, 2, ANY, PRE>(tw, D.mask, fp, D.fp_mask, any, bits, pre);
-      else if (sh == 4) pass_table_screen<C, 4, ANY, PRE>(tw, D.mask, fp, D.fp_mask, any, bits, pre);
-      else pass_table_screen<C, 8, ANY, PRE>(tw, D.mask, fp, D.fp_mask, any, bits, pre);
+      pass_exact_r<C, false, true, 2>(mine, os, D.m, r, D.tgt, base, D.test_sh, any, bits);
     }
   } else {
-    // the single-bucket kernel (PRE) runs list buckets only
-    if (PRE || D.kind == kListExact) {
-      if ((D.shift >> 8) <= 2u) pass_exact_r<C, ANY, false, 2, PRE>(tw, os, D.m, r, D.tgt, fp, D.fp_mask, any, bits, pre);
-      else pass_exact_r<C, ANY, false, 4, PRE>(tw, os, D.m, r, D.tgt, fp, D.fp_mask, any, bits, pre);
+    if (ANY || FAM == kFamScreen1 || D.kind == kListScreen) {
+      if (sh == 2) pass_list_screen<C, 2, ANY>(mine, D.mask, D.tgt[0], any, bits);
+      else if (sh == 3) pass_list_screen<C, 3, ANY>(mine, D.mask, D.tgt[0], any, bits);
+      else if (sh == 4) pass_list_screen<C, 4, ANY>(mine, D.mask, D.tgt[0], any, bits);
+      else pass_list_screen<C, 8, ANY>(mine, D.mask, D.tgt[0], any, bits);
     } else {
-      pass_exact_r<C, ANY, true, 2, PRE>(tw, os, D.m, r, D.tgt, fp, D.fp_mask, any, bits, pre);
+      if (sh == 2) pass_filter_screen<C, 2, false>(mine, 0, base, D.test_sh, bits);
+      else if (sh == 3) pass_filter_screen<C, 3, false>(mine, 0, base, D.test_sh, bits);
+      else if (sh == 4) pass_filter_screen<C, 4, false>(mine, 0, base, D.test_sh, bits);
+      else if (D.mask == 0xFFFFFFFFu) pass_filter_screen<C, 8, false>(mine, 0, base, D.test_sh, bits);
+      else pass_filter_screen<C, 8, true>(mine, D.mask, base, D.test_sh, bits);
     }
   }
 }
 
-// ------------------------------------------------------- block-level helpers
-template <int WG>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *wsum, uint32_t &total) {
-  constexpr int NW = WG / 64;
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    if (lane >= (uint32_t)d) x += y;
-  }
-  wg_barrier();
-  if (lane == 63) wsum[wave] = x;
-  wg_barrier();
-  uint32_t before = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const uint32_t s = wsum[i];
-    before += (uint32_t)i < wave ? s : 0u;
-    tot += s;
-  }
-  total = tot;
-  return before + x - v;
+// -------------------------------------------------------- wave-level helpers
+// Inclusive prefix sum over the wave's lanes (DPP: shifts by 1, 2, 4, 8 within
+// rows of 16, then each row's last lane added to the rows after it).
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return (uint32_t)x;
 }
 
-// The four bytes ending at *last (LDS, any alignment) in memory order (the
-// oldest in the low byte), from the two aligned dwords that hold them.
-__device__ __forceinline__ uint32_t raw_word_ending_at(const uint8_t *last) {
-  const uint8_t *a = last - 3;
-  const uint32_t mis = (uint32_t)(uintptr_t)a & 3u;
-  const uint32_t *aw = (const uint32_t *)(a - mis);
-  return __builtin_amdgcn_alignbyte(aw[1], aw[0], mis);
+// Number of set bits of b below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t b) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
-// The same four bytes as a big-endian word: (last[-3] << 24) | ... | last[0].
-__device__ __forceinline__ uint32_t word_ending_at(const uint8_t *last) {
-  return __builtin_bswap32(raw_word_ending_at(last));
-}
-
-// Exact hash (canonical) of the m <= kStreamM bytes ending at *end (LDS):
-// Horner over big-endian words, 2^32 per word (four bytes at a time), the
-// oldest word masked to the window's bytes.  The candidate key of exact
-// buckets; equal to the value the rolling pass held for that window.
-__device__ __forceinline__ uint64_t exact_key(const uint8_t *end, uint32_t m) {
-  const uint32_t nw = (m + 3u) >> 2, lead = 4u * nw - m;  // lead: bytes of the oldest word before the window
-  uint64_t s = 0;
-  for (uint32_t j = nw; j-- > 0;) {
-    uint32_t w = word_ending_at(end - 4 * j);
-    if (j == nw - 1u && lead) w &= 0xFFFFFFFFu >> (8u * lead);
-    s = mul2p32_lazy(s) + w;
-  }
-  return canon(s);
+// Orders this wave's LDS writes before its later reads of them (LDS accesses
+// of one wave take effect in issue order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Shift-add value of four window bytes rw (memory order: the oldest in the
 // low byte) with the oldest weighted 2^(3s), ..., the newest 1: one byte dot
-// product for s = 2, two for s = 4, the big-endian word for s = 8.
+// product for s = 2, two for s = 3 and 4, the big-endian word for s = 8.
 __device__ __forceinline__ uint32_t screen_word(uint32_t rw, uint32_t shift) {
   if (shift == 2) return __builtin_amdgcn_udot4(rw, 0x01041040u, 0u, false);
+  if (shift == 3)
+    return (__builtin_amdgcn_udot4(rw, 0x00000840u, 0u, false) << 3) + __builtin_amdgcn_udot4(rw, 0x01080000u, 0u, false);
   if (shift == 4)
     return (__builtin_amdgcn_udot4(rw, 0x00000110u, 0u, false) << 8) + __builtin_amdgcn_udot4(rw, 0x01100000u, 0u, false);
   return __builtin_bswap32(rw);
 }
 
-// Shift-add hash of the span = 32/s bytes ending at *end (the value the scan's
-// screen pass held for that window end), masked as the group's hash is.
-// Four bytes at a time: word j back from the end weighs 2^(4 s j).
-__device__ __forceinline__ uint32_t screen_key(const uint8_t *end, uint32_t shift, uint32_t mask) {
-  const uint32_t span = 32u / shift, nw = span >> 2;
-  uint32_t h = 0;
-  for (uint32_t j = nw; j-- > 0;) {
-    const uint32_t v = screen_word(raw_word_ending_at(end - 4 * j), shift);
-    h = j == nw - 1u ? v : (h << (4 * shift)) + v;  // (one word when shift = 8: no 32-bit shift)
-  }
-  return h & mask;
-}
-
-// Record (slot_inline / slot_run) stored under key in a list bucket's key
-// table, read from the instance image in device memory (gimg); 0 if absent.
-__device__ __forceinline__ uint64_t key_lookup(const uint8_t *gimg, const BucketDesc &D, uint64_t key) {
-  const uint64_t *keys = (const uint64_t *)(gimg + D.ht_off);
-  const uint64_t *recs = keys + (D.ht_mask + 1u);
-  uint32_t slot = ht_slot(key, D.ht_mask);
-  for (uint32_t probe = 0; probe <= D.ht_mask; ++probe) {
-    const uint64_t k = keys[slot];
-    if (k == key) return recs[slot];
-    if (k == kEmptyKey) return 0;
-    slot = (slot + 1u) & D.ht_mask;
-  }
-  return 0;
-}
-
-// Record of the 32-bit key h of a table bucket: the cuckoo slot holding h
-// (LDS) indexes the per-slot records in device memory.  The load is issued
-// without waiting for it: found tells whether h is a key at all (the record
-// is then to be dropped), so that the lookups of several candidates overlap.
-__device__ __forceinline__ uint64_t table_record(const uint8_t *img, const uint8_t *gimg, const BucketDesc &D,
-                                                 uint32_t h, bool &found) {
-  const uint32_t *tab = (const uint32_t *)(img + D.fp_off);
-  const uint32_t s1 = ck_slot1(h, D.fp_mask), s2 = ck_slot2(h, D.fp_mask);
-  const bool in1 = tab[s1] == h, in2 = tab[s2] == h;
-  found = in1 || in2;
-  return ((const uint64_t *)(gimg + D.ht_off))[in1 ? s1 : s2];
-}
-
-// Compares the m bytes ending at *end (LDS tile, any alignment) with the
-// pattern at pat (device memory, 4-byte aligned), four bytes per step: the tile
-// dwords are realigned with alignbyte and the tail of the last one is masked.
-__device__ __forceinline__ bool window_equals(const uint8_t *end, const uint8_t *pat, uint32_t m) {
-  const uint8_t *a = end - (m - 1);
-  const uint32_t mis = (uint32_t)(uintptr_t)a & 3u;
-  const uint32_t *aw = (const uint32_t *)(a - mis);
-  const uint32_t *pw = (const uint32_t *)pat;
-  uint32_t lo = aw[0];
-  for (uint32_t q = 0; 4 * q < m; ++q) {
-    const uint32_t hi = aw[q + 1];
-    const uint32_t rem = m - 4 * q;
-    const uint32_t keep = rem >= 4 ? 0xFFFFFFFFu : ((1u << (8 * rem)) - 1u);
-    if ((__builtin_amdgcn_alignbyte(hi, lo, mis) ^ pw[q]) & keep) return false;
-    lo = hi;
-  }
-  return true;
-}
-
-// Compares the m <= kFront bytes ending at *end (LDS tile) with a pattern
-// whose first 16 bytes are hd (already in registers) and whose bytes are at
-// pat (device memory, 4-byte aligned): the first min(m, 16) bytes against hd,
-// the rest, if they agree, four bytes per step against pat.
-__device__ __forceinline__ bool window_equals_head(const uint8_t *end, const uint32_t (&hd)[4], const uint8_t *pat,
-                                                   uint32_t m) {
-  const uint8_t *a = end - (m - 1);
-  const uint32_t mis = (uint32_t)(uintptr_t)a & 3u;
-  const uint32_t *aw = (const uint32_t *)(a - mis);
-  uint32_t lo = aw[0], diff = 0;
+// Shift-add hash of the window whose last 16 bytes are raw (memory order),
+// as the screen pass holds it for that window end (its last ceil(32/s) bytes,
+// masked as the group's hash is).
+__device__ __forceinline__ uint32_t screen_key(const uint32_t (&raw)[4], uint32_t shift, uint32_t mask) {
+  if (shift == 2) {
+    uint32_t h = screen_word(raw[0], 2);
 #pragma unroll
-  for (uint32_t q = 0; q < 4; ++q) {
-    if (4 * q < m) {
-      const uint32_t hi = aw[q + 1];
-      const uint32_t rem = m - 4 * q;
-      const uint32_t keep = rem >= 4 ? 0xFFFFFFFFu : ((1u << (8 * rem)) - 1u);
-      diff |= (__builtin_amdgcn_alignbyte(hi, lo, mis) ^ hd[q]) & keep;
-      lo = hi;
-    }
+    for (int j = 1; j < 4; ++j) h = (h << 8) + screen_word(raw[j], 2);
+    return h;
   }
-  if (diff) return false;
-  const uint32_t *pw = (const uint32_t *)pat;
-  for (uint32_t q = 4; 4 * q < m; ++q) {
-    const uint32_t hi = aw[q + 1];
-    const uint32_t rem = m - 4 * q;
-    const uint32_t keep = rem >= 4 ? 0xFFFFFFFFu : ((1u << (8 * rem)) - 1u);
-    if ((__builtin_amdgcn_alignbyte(hi, lo, mis) ^ pw[q]) & keep) return false;
-    lo = hi;
-  }
-  return true;
+  if (shift == 3) return (((screen_word(raw[1], 3) << 12) + screen_word(raw[2], 3)) << 12) + screen_word(raw[3], 3);
+  if (shift == 4) return (screen_word(raw[2], 4) << 16) + screen_word(raw[3], 4);
+  return screen_word(raw[3], 8) & mask;
 }
 
 // Compares the m bytes at a (device memory: the text, any alignment) with the
@@ -851,93 +685,25 @@ __device__ __forceinline__ bool window_equals_global(const uint8_t *a, const uin
   return true;
 }
 
-// Whether the pattern referenced by om (om_pack) occurs as the window ending
-// at *end (LDS tile; global end index e): the window must start inside the
-// text and its bytes must equal the pattern's (the byte comparison of Sec. 3.1
-// that follows every hash hit).  Windows that reach beyond the tile's front
-// halo (patterns longer than kFront) are compared in the text itself (gtext).
-__device__ __forceinline__ bool entry_matches(const uint8_t *gimg, const BucketDesc &D, uint32_t om,
-                                              const uint8_t *end, int64_t e, const uint8_t *gtext) {
-  const uint32_t m = om_len(om);
-  const int64_t x = e - (int64_t)m + 1;
-  if (x < 0) return false;
-  const uint8_t *pat = gimg + D.pat_off + om_off(om);
-  if (m <= kFront) return window_equals(end, pat, m);
-  return window_equals_global(gtext + x, pat, m);
-}
-
-// Verifies the entries of a plain run record (slot_run) for the candidate
-// window ending at *end (global end index e).  Consecutive entries with the
-// same pattern bytes (identical patterns under several ids) share one
-// comparison.  Returns the number of matching entries; bit i of mask is set
-// for a matching entry i < 32 of the run.
-__device__ __forceinline__ uint32_t verify_run(const uint8_t *gimg, const BucketDesc &D, uint64_t rec, const uint8_t *end,
-                                               int64_t e, const uint8_t *gtext, uint32_t &mask) {
-  mask = 0;
-  const Entry *ent = (const Entry *)(gimg + D.ent_off);
-  const uint32_t first = (uint32_t)rec, cnt = (uint32_t)(rec >> 32);
-  uint32_t nh = 0, prev = kNoLink;
-  bool prev_ok = false;
-  for (uint32_t i = 0; i < cnt; ++i) {
-    const uint32_t om = ent[first + i].off_m;
-    if (om != prev) {
-      prev_ok = entry_matches(gimg, D, om, end, e, gtext);
-      prev = om;
-    }
-    if (prev_ok) {
-      ++nh;
-      if (i < 32) mask |= 1u << i;
-    }
+// Whether r bytes (r <= 16 counts, more: all 16; r <= 0: none) at LDS address
+// a equal the first of p.
+__device__ __forceinline__ bool quad_equals(uint32_t a, const rk_u32x4 p, int r) {
+  const uint32_t mis = a & 3u, aw = a & ~3u;
+  uint32_t diff = 0, lo = lds32(aw);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t hi = lds32(aw + 4 * (j + 1));
+    const int left = r - 4 * j;
+    const uint32_t keep = left <= 0 ? 0u : (left >= 4 ? 0xFFFFFFFFu : (1u << (8 * left)) - 1u);
+    diff |= (__builtin_amdgcn_alignbyte(hi, lo, mis) ^ p[j]) & keep;
+    lo = hi;
   }
-  return nh;
-}
-
-// Writes the matching entries of a verified record as hit records
-// (pid << 40 | start) at slab[o..], up to cap; o advances over all of them.
-// pid_counts (optional): per-pattern hit counters, one increment per hit.
-__device__ __forceinline__ void write_hits(const uint8_t *gimg, const BucketDesc &D, uint64_t rec, uint32_t mask,
-                                           const uint8_t *end, int64_t e, const uint8_t *gtext, uint64_t *slab,
-                                           uint32_t cap, uint32_t &o, unsigned long long *pid_counts) {
-  if (rec >> 63) {
-    if (mask) {
-      const uint32_t om = (uint32_t)rec, pid = (uint32_t)(rec >> 32) & 0xFFFFFFu;
-      const uint64_t x = (uint64_t)(e - (int64_t)om_len(om) + 1);
-      if (o < cap) slab[o] = ((uint64_t)pid << kPosBits) | x;
-      if (pid_counts) atomicAdd(pid_counts + pid, 1ull);
-      ++o;
-    }
-    return;
-  }
-  const Entry *ent = (const Entry *)(gimg + D.ent_off);
-  if (rec_same(rec)) {
-    // one pattern under several ids: a hit for each
-    if (mask) {
-      const uint32_t first = same_first(rec), cnt = same_count(rec);
-      const uint64_t x = (uint64_t)(e - (int64_t)om_len((uint32_t)rec) + 1);
-      for (uint32_t i = 0; i < cnt; ++i) {
-        const uint32_t pid = ent[first + i].pid;
-        if (o < cap) slab[o] = ((uint64_t)pid << kPosBits) | x;
-        if (pid_counts) atomicAdd(pid_counts + pid, 1ull);
-        ++o;
-      }
-    }
-    return;
-  }
-  const uint32_t first = (uint32_t)rec, cnt = (uint32_t)(rec >> 32);
-  for (uint32_t i = 0; i < cnt; ++i) {
-    const Entry en = ent[first + i];
-    const bool hit = i < 32 ? ((mask >> i) & 1u) != 0 : entry_matches(gimg, D, en.off_m, end, e, gtext);
-    if (!hit) continue;
-    const uint64_t x = (uint64_t)(e - (int64_t)om_len(en.off_m) + 1);
-    if (o < cap) slab[o] = ((uint64_t)en.pid << kPosBits) | x;
-    if (pid_counts) atomicAdd(pid_counts + en.pid, 1ull);
-    ++o;
-  }
+  return diff == 0;
 }
 
 // ------------------------------------------------------- tile staging (LDS DMA)
 // One 16-byte chunk per active lane from device memory straight into LDS:
-// lane i's chunk at g lands at dst + 16 i (dst wave-uniform).  Issued in asm
+// lane i's chunk at g lands at dst + 16 i (LDS address dst, wave-uniform).  Issued in asm
 // so that the compiler does not see an LDS write in flight: it would make
 // every later LDS read wait for all such loads (vmcnt(0)), the reads of the
 // tile being tested included, so that the next tile's loads would no longer
@@ -947,71 +713,222 @@ __device__ __forceinline__ void write_hits(const uint8_t *gimg, const BucketDesc
 // wait state required between a write of M0 and the load that uses it.)  The
 // loads are non-temporal (nt): the text is read once, and streaming it past
 // the caches reads 4 GiB at 6.6 TB/s against 6.1 without the hint.
-__device__ __forceinline__ void lds_dma16(const void *g, const uint8_t *dst) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr(dst));
+__device__ __forceinline__ void lds_dma16(const void *g, uint32_t dst) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane(dst);
   __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(m0) : "memory");
 }
 
-// Issues the loads of one tile into an LDS slot: text bytes [tstart - kFront,
-// tstart + W) as 16-byte chunks that the load unit writes straight into LDS
-// (no register staging, so the next tile's loads cost no VGPRs while they are
-// in flight).  The body is W/1024 whole-wave loads of 1 KiB (lane i: bytes
-// 16i..16i+15) dealt round-robin to the waves; the last wave also loads the
-// 64-byte front halo with four lanes.  Chunks outside the text read the
-// text's first chunk instead: those LDS bytes only feed windows that start
-// before the text or end after it, which the edge masks drop.
-template <int WG, int C>
-__device__ __forceinline__ void dma_tile(uint8_t *slot, const uint8_t *text, uint64_t n, int64_t tstart) {
-  constexpr uint32_t W = WG * C, J = W / 1024, NW = WG / 64;
-  static_assert(W % 1024 == 0, "a tile is a whole number of 1 KiB wave loads");
-  const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
-  if (tstart >= (int64_t)kFront && (uint64_t)tstart + W <= n) {
-    // interior tile: every chunk is text
-    const uint8_t *base = text + tstart + 16u * lane;
-    for (uint32_t j = wave; j < J; j += NW)
-      lds_dma16(base + 1024u * j, slot + kFront + 1024u * j);
-    if (wave == NW - 1 && lane < 4)
-      lds_dma16(base - kFront, slot);
+// LDS of one wave: sub-tile slots (front halo, 64 C bytes, 16 bytes that the
+// realigning reads may touch) and the candidate list.
+template <int C>
+constexpr uint32_t sub_slot_bytes() {
+  return kFront + 64 * C + 16;
+}
+template <int C>
+constexpr uint32_t wave_lds_bytes(uint32_t slots) {
+  return slots * sub_slot_bytes<C>() + kWaveCand * 2;
+}
+
+// Issues the loads of one sub-tile into an LDS slot of the calling wave: text
+// bytes [start - kFront, start + 64 C) as 16-byte chunks that the load unit
+// writes straight into LDS (no register staging), whole-wave loads of 1 KiB
+// and a partial one.  Chunks outside the text read the text's first chunk
+// instead: those LDS bytes only feed windows that start before the text or end
+// after it, which the edge masks drop.
+template <int C>
+__device__ __forceinline__ void dma_sub(uint32_t slot, const uint8_t *text, uint64_t n, uint64_t start) {
+  constexpr uint32_t NCH = 4 + 4 * C, J = NCH / 64, REM = NCH % 64;
+  const uint32_t lane = threadIdx.x & 63;
+  if (start >= kFront && start + 64 * C <= n) {
+    // interior: every chunk is text
+    const uint8_t *base = text + (start - kFront) + 16u * lane;
+#pragma unroll
+    for (uint32_t j = 0; j < J; ++j) lds_dma16(base + 1024u * j, slot + 1024u * j);
+    if (lane < REM) lds_dma16(base + 1024u * J, slot + 1024u * J);
     return;
   }
-  for (uint32_t j = wave; j < J; j += NW) {
-    const uint64_t g = (uint64_t)tstart + 1024u * j + 16u * lane;
-    const uint8_t *src = g < n ? text + g : text;
-    lds_dma16(src, slot + kFront + 1024u * j);
-  }
-  if (wave == NW - 1 && lane < 4) {
-    const int64_t g = tstart - (int64_t)kFront + 16 * (int64_t)lane;
-    const uint8_t *src = g >= 0 ? text + g : text;
-    lds_dma16(src, slot);
+#pragma unroll 1
+  for (uint32_t j = 0; j <= J; ++j) {
+    const uint64_t g = start + 1024u * j + 16u * lane;  // chunk start + kFront
+    const uint8_t *src = g >= kFront && g - kFront < n ? text + (g - kFront) : text;
+    if (j < J || lane < REM) lds_dma16(src, slot + 1024u * j);
   }
 }
 
-// Candidate phase of one bucket on one tile.  bits holds the thread's
-// candidate mask (window i of the thread at bit word_windows-1-(i%32) of word
-// i/32).  Windows that start before the text or end after it are dropped, the
-// candidates are compacted block-wide into the LDS list in window order, and
-// each is checked by one thread: key recomputed, its record (table buckets:
-// the cuckoo slot in the LDS image img; list buckets: the key table in the
-// device image gimg), byte comparison with every pattern of the record.  Hits
-// go to the tile's slab (up to cap records) in window order; tile_hits counts
-// them all.  ncand returns the number of candidates (block-uniform).
-template <int WG, int C, int Q>
-__device__ __forceinline__ void candidate_phase(Bits<C> &bits, const BucketDesc &D, const uint8_t *tile, int64_t tstart,
-                                                uint64_t n, int64_t e0, const uint8_t *img, const uint8_t *gimg,
-                                                uint16_t *cand,
-                                                uint32_t *misc, uint64_t *slab, uint32_t cap, uint32_t &tile_hits,
-                                                uint32_t &ncand, const uint8_t *gtext,
-                                                unsigned long long *pid_counts, uint64_t rec1 = 0) {
-  static_assert(WG * C <= 65536, "window indices of a tile fit the u16 candidate list");
-  constexpr uint32_t W = WG * C;
+// This wave's loads-to-LDS have landed.
+__device__ __forceinline__ void wait_loads() { __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+// This wave's LDS reads are done.
+__device__ __forceinline__ void wait_lds() { __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// A record and the last 16 bytes of its pattern, zeros in front of a shorter
+// one.
+struct Looked {
+  uint64_t rec;
+  rk_u32x4 tail;
+};
+
+// Where a bucket's records are: in the LDS image, in device memory, or only
+// one, held in registers.  The candidate phase is compiled for each, so that
+// the LDS one holds no load from memory that could be under way: a wait for
+// one would be a wait for every hit stored before it.
+enum RecordPlace { kRecLds, kRecGlobal, kRecOne };
+
+struct Records {
+  uint32_t img;         // LDS address of the image
+  const uint8_t *gimg;  // device image
+  Looked one;
+};
+
+// Record i of a bucket's table.
+template <RecordPlace AT>
+__device__ __forceinline__ Looked table_record(const BucketDesc &D, const Records &R, uint32_t i) {
+  Looked L;
+  if constexpr (AT == kRecLds) {
+    const uint32_t r = R.img + D.tab_off + 16u * D.ntab + 8u * i;
+    L.tail = *(lds_quad *)(uintptr_t)(R.img + D.tab_off + 16u * i);
+    L.rec = (uint64_t)lds32(r + 4) << 32 | lds32(r);
+  } else if constexpr (AT == kRecGlobal) {
+    L.tail = *(const rk_u32x4 *)(R.gimg + D.tab_off + 16u * i);
+    L.rec = *(const uint64_t *)(R.gimg + D.tab_off + 16u * D.ntab + 8u * i);
+  } else {
+    L = R.one;
+  }
+  return L;
+}
+
+// The record of a bucket for the window whose last 16 bytes are raw: the rank
+// of the window key's bit in the lookup bitmap (rec 0: the bit is not set).
+// One-key buckets hold one record.
+template <RecordPlace AT>
+__device__ __forceinline__ Looked bucket_lookup(const BucketDesc &D, const Records &R, const uint32_t (&raw)[4]) {
+  if constexpr (AT == kRecOne) return R.one;
+  uint32_t ord = 0;
+  bool in = true;
+  if (D.kind == kTableScreen || D.kind == kTableExact) {
+    const uint32_t v = screen_key(raw, D.shift & 0xFFu, D.mask) * kMix;
+    const uint32_t i = v >> D.lk_sh;
+    const uint32_t w = lds32(R.img + D.lk_off + 4u * i);
+    const uint32_t below = lds16(R.img + D.lk_off + (4u << (32u - D.lk_sh)) + 2u * i);
+    in = filter_bit(w, v) & 1u;
+    ord = in ? below + __builtin_popcount(w & ((1u << (v & 31u)) - 1u)) : 0u;
+  }
+  Looked L = table_record<AT>(D, R, ord);
+  if (!in) L.rec = 0;
+  return L;
+}
+
+// The 16 bytes ending at LDS address end (memory order), from the five aligned
+// dwords that hold them.
+__device__ __forceinline__ void last_bytes(uint32_t end, uint32_t (&raw)[4]) {
+  const uint32_t mis = (end + 1u) & 3u, aw = end - 15u - mis;
+  const uint32_t d0 = lds32(aw), d1 = lds32(aw + 4), d2 = lds32(aw + 8), d3 = lds32(aw + 12), d4 = lds32(aw + 16);
+  raw[0] = __builtin_amdgcn_alignbyte(d1, d0, mis);
+  raw[1] = __builtin_amdgcn_alignbyte(d2, d1, mis);
+  raw[2] = __builtin_amdgcn_alignbyte(d3, d2, mis);
+  raw[3] = __builtin_amdgcn_alignbyte(d4, d3, mis);
+}
+
+// Whether the windows ending at sub-tile bytes er[q] (last 16 bytes raw[q])
+// are occurrences of the patterns of L[q] (one pattern each; rec 0: none):
+// they start inside the text and all their bytes are equal (Sec. 3.1).  The
+// last 16 bytes are compared with the record's tail, the others of a longer
+// pattern with the plan's bytes, which are loaded for all Q windows, as many
+// as any lane needs, before the first is used.
+template <RecordPlace AT, int Q>
+__device__ __forceinline__ void verify(const BucketDesc &D, const Records &R, const Looked (&L)[Q],
+                                       const uint32_t (&raw)[Q][4], const uint32_t (&er)[Q], uint32_t sub,
+                                       uint64_t start, const uint8_t *gtext, bool (&ok)[Q]) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  bool m16 = false;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t mj = om_len((uint32_t)L[q].rec);
+    uint32_t diff = 0;
+    if ((D.shift & 0xFFu) == 2) {  // no pattern below 16 bytes
+      diff = (raw[q][0] ^ L[q].tail.x) | (raw[q][1] ^ L[q].tail.y) | (raw[q][2] ^ L[q].tail.z) | (raw[q][3] ^ L[q].tail.w);
+    } else {
+      // shorter than 16 bytes: the newest mj of them
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int nb = (int)mj - 4 * (3 - j);
+        const uint32_t keep = nb <= 0 ? 0u : (nb >= 4 ? 0xFFFFFFFFu : 0xFFFFFFFFu << (8 * (4 - nb)));
+        diff |= (raw[q][j] ^ L[q].tail[j]) & keep;
+      }
+    }
+    ok[q] = L[q].rec != 0 && diff == 0 && start + er[q] + 1u >= mj;
+    m16 = m16 || (ok[q] && mj > 16);
+  }
+  if (ballot(m16) == 0) return;
+  bool m32 = false, m48 = false, m64 = false;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t mj = om_len((uint32_t)L[q].rec);
+    m32 = m32 || (ok[q] && mj > 32);
+    m48 = m48 || (ok[q] && mj > 48);
+    m64 = m64 || (ok[q] && mj > kFront);
+  }
+  m32 = ballot(m32) != 0;
+  m48 = ballot(m48) != 0;
+  rk_u32x4 h[Q][3];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t pat = D.pat_off + om_off((uint32_t)L[q].rec);
+    if (ok[q] && om_len((uint32_t)L[q].rec) > 16) {
+      if (AT == kRecLds && (D.shift & (1u << 17))) {
+        const uint32_t p = R.img + pat;
+        h[q][0] = rk_u32x4{lds32(p), lds32(p + 4), lds32(p + 8), lds32(p + 12)};
+        if (m32) h[q][1] = rk_u32x4{lds32(p + 16), lds32(p + 20), lds32(p + 24), lds32(p + 28)};
+        if (m48) h[q][2] = rk_u32x4{lds32(p + 32), lds32(p + 36), lds32(p + 40), lds32(p + 44)};
+      } else {
+        h[q][0] = *(const u32x4 *)(R.gimg + pat);
+        if (m32) h[q][1] = *(const u32x4 *)(R.gimg + pat + 16);
+        if (m48) h[q][2] = *(const u32x4 *)(R.gimg + pat + 32);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t mj = om_len((uint32_t)L[q].rec), a = sub + kFront + er[q] + 1u - mj;
+    if (ok[q] && mj > 16 && mj <= kFront) {
+      ok[q] = quad_equals(a, h[q][0], (int)mj - 16);
+      if (m32) ok[q] = ok[q] && quad_equals(a + 16, h[q][1], (int)mj - 32);
+      if (m48) ok[q] = ok[q] && quad_equals(a + 32, h[q][2], (int)mj - 48);
+    }
+    // beyond the sub-tile's front halo: compared in the text itself (the LDS
+    // part leads the device image, so offsets hold in both)
+    if (ballot(m64) && ok[q] && mj > kFront)
+      ok[q] = window_equals_global(gtext + (start + er[q] + 1u - mj), R.gimg + D.pat_off + om_off((uint32_t)L[q].rec), mj);
+  }
+}
+
+// Candidate phase of one bucket on one sub-tile, by one wave.  bits holds the
+// lane's candidate mask (window i: bit i%32 of word i/32).
+// Windows that start before the text or end after it are dropped, the
+// candidates are compacted into the wave's LDS list in window order, and each
+// is checked by one lane: its key's record, then its bytes.  A bit that
+// several patterns share is put off: its candidates go back to the front of
+// the list and are checked after the others, one pattern after the other (a
+// pattern's hits come all from the one or all from the other, so each keeps
+// the window order).  Hits go to the tile's slab (up to cap records);
+// tile_hits counts them all.  Returns the number of candidates (uniform).
+//
+// A wave works alone (no block barrier anywhere in the scan), so its LDS and
+// memory latencies are covered by the other waves of the CU, whatever they
+// are doing; records and pattern bytes in memory are loaded for 128 candidates
+// at a time.
+template <int C, RecordPlace AT>
+__device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketDesc &D, uint32_t sub, uint64_t start,
+                                                    uint64_t n, const Records &R, uint32_t cand,
+                                                    uint64_t *slab, uint32_t cap, uint32_t &tile_hits,
+                                                    const uint8_t *gtext, unsigned long long *pid_counts) {
+  constexpr uint32_t SUB = 64 * C;
   constexpr int NB = (C + 31) / 32;
-  const uint32_t tid = threadIdx.x;
-  const uint32_t m = D.m;
+  const uint32_t lane = threadIdx.x & 63;
   // only windows with m-1 <= e <= n-1 exist
-  const bool edge = tstart < (int64_t)m - 1 || (uint64_t)(tstart + W) > n;
-  if (edge) {
+  if (start < (uint64_t)D.m - 1 || start + SUB > n) {
     // my windows i are valid for ilo <= i < ihi
-    const int64_t lo64 = (int64_t)m - 1 - e0, hi64 = (int64_t)n - e0;
+    const int64_t e0 = (int64_t)start + lane * C;
+    const int64_t lo64 = (int64_t)D.m - 1 - e0, hi64 = (int64_t)n - e0;
     const int ilo = (int)(lo64 < 0 ? 0 : (lo64 > C ? C : lo64));
     const int ihi = (int)(hi64 < 0 ? 0 : (hi64 > C ? C : hi64));
 #pragma unroll
@@ -1020,456 +937,421 @@ __device__ __forceinline__ void candidate_phase(Bits<C> &bits, const BucketDesc 
       int a = ilo - 32 * j, b2 = ihi - 32 * j;
       a = a < 0 ? 0 : (a > nw ? nw : a);
       b2 = b2 < 0 ? 0 : (b2 > nw ? nw : b2);
-      // local window k sits at bit nw-1-k: keep bits [nw-b2, nw-a)
-      const uint32_t below_hi = (nw - a) >= 32 ? 0xFFFFFFFFu : ((1u << (nw - a)) - 1u);
-      const uint32_t below_lo = (nw - b2) >= 32 ? 0xFFFFFFFFu : ((1u << (nw - b2)) - 1u);
-      bits.b[j] &= (b2 > a) ? (below_hi & ~below_lo) : 0u;
+      // keep bits [a, b2)
+      const uint32_t below_b = b2 >= 32 ? 0xFFFFFFFFu : ((1u << b2) - 1u);
+      const uint32_t below_a = a >= 32 ? 0xFFFFFFFFu : ((1u << a) - 1u);
+      bits.b[j] &= below_b & ~below_a;
     }
   }
   uint32_t cnt = 0;
 #pragma unroll
   for (int j = 0; j < NB; ++j) cnt += __builtin_popcount(bits.b[j]);
-  const uint32_t cbase = block_excl_scan<WG>(cnt, misc, ncand);
+  if (ballot(cnt != 0) == 0) return 0;
+  const uint32_t incl = wave_incl_scan(cnt);
+  const uint32_t ncand = __builtin_amdgcn_readlane(incl, 63);
 
-  for (uint32_t r0 = 0; r0 < ncand; r0 += kCandCap) {
-    wg_barrier();  // cand list free
-    if (cnt) {
-      uint32_t idx = cbase;
+  for (uint32_t r0 = 0; r0 < ncand; r0 += kWaveCand) {
+    wave_lds_fence();  // the list's readers of the last round are done
+    uint32_t idx = incl - cnt - r0;  // (wraps for entries of earlier rounds: not below kWaveCand)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        uint32_t bb = bits.b[j];
+    for (int j = 0; j < NB; ++j) {
+      uint32_t bb = bits.b[j];
+      const uint32_t first = lane * C + 32u * j;
+      if (ncand <= kWaveCand) {
         while (bb) {
-          const uint32_t hb = 31u - __builtin_clz(bb);  // highest bit = earliest window
-          const uint32_t i = 32u * j + (uint32_t)word_windows<C>(j) - 1u - hb;
-          bb &= ~(1u << hb);
-          if (idx >= r0 && idx < r0 + kCandCap) cand[idx - r0] = (uint16_t)(tid * C + i);
-          ++idx;
+          *(lds_half *)(uintptr_t)(cand + 2u * idx++) = (uint16_t)(first + __builtin_ctz(bb));
+          bb &= bb - 1u;
         }
+      } else {
+        for (; bb; bb &= bb - 1u, ++idx)
+          if (idx < kWaveCand) *(lds_half *)(uintptr_t)(cand + 2u * idx) = (uint16_t)(first + __builtin_ctz(bb));
       }
     }
-    wg_barrier();
-    const uint32_t nc = min(kCandCap, ncand - r0);
-    const bool screen = D.kind == kListScreen || D.kind == kTableScreen;
-    const bool table = D.kind == kTableScreen || D.kind == kTableExact;
-    // The record stored under a candidate's key; the load is left in flight
-    // (found: whether the key is in the bucket at all).
-    auto record_of = [&](uint32_t ci, const uint8_t *&end, int64_t &e, bool &found)
-        __attribute__((always_inline)) -> uint64_t {
-      const uint32_t e_rel = cand[ci];
-      end = tile + kFront + e_rel;
-      e = tstart + (int64_t)e_rel;
-      found = true;
-      if (rec1) return rec1;  // the bucket has one key: every candidate's record
-      const uint64_t key = screen ? (uint64_t)screen_key(end, D.shift & 0xFFu, D.mask) : exact_key(end, m);
-      return table ? table_record(img, gimg, D, (uint32_t)key, found) : key_lookup(gimg, D, key);
+    wave_lds_fence();
+    const uint32_t nc = min(kWaveCand, ncand - r0);
+    auto window = [&](uint32_t i, uint32_t count, uint32_t &e_rel, uint32_t(&raw)[4])
+        __attribute__((always_inline)) -> Looked {
+      e_rel = lds16(cand + 2u * min(i + lane, count - 1));
+      last_bytes(sub + kFront + e_rel, raw);
+      Looked L = bucket_lookup<AT>(D, R, raw);
+      if (i + lane >= count) L.rec = 0;
+      return L;
     };
-    // Up to Q candidates per thread, q = ceil(left / WG) of them, contiguous
-    // (thread order is candidate order, so the block scan of hit counts keeps
-    // the window order).  Three steps, each issuing its loads for all of the
-    // thread's candidates before any is waited for: the records; the first 16
-    // bytes of the pattern of each record that holds one pattern; the byte
-    // comparisons (longer patterns and runs of patterns read the rest then).
-    // Waves holding no candidate skip the lookups.  Q is 1 in the exact
-    // family (fewer registers: it keeps its occupancy).
-    for (uint32_t i0 = 0; i0 < nc; i0 += Q * WG) {
-      const uint32_t left = nc - i0;
-      const uint32_t q = left >= Q * WG ? Q : (left + WG - 1) / WG;  // uniform, 1..Q
-      const uint32_t c0 = i0 + tid * q;
-      const bool wave_has = i0 + (tid & ~63u) * q < nc;               // uniform per wave
-      uint64_t rec[Q];
-      const uint8_t *end[Q];
-      int64_t e[Q];
-      uint32_t nh[Q], hm[Q];
-      bool fnd[Q];
-#pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        rec[j] = 0;
-        end[j] = tile;
-        e[j] = 0;
-        nh[j] = 0;
-        hm[j] = 0;
-        fnd[j] = false;
+    // a hit for each of the pattern's ids
+    auto emit = [&](bool ok, uint64_t rec, uint32_t e_rel) __attribute__((always_inline)) {
+      uint64_t hit = ballot(ok);
+      if (hit == 0) return;
+      const uint64_t x = start + e_rel + 1u - om_len((uint32_t)rec);
+      const uint32_t nid = ok ? (rec_same(rec) ? same_count(rec) : 1u) : 0u;
+      uint32_t pid = (uint32_t)(rec >> 32) & 0xFFFFFFu;
+      const bool ids = ballot(ok && rec_same(rec)) != 0;
+      for (uint32_t j = 0;;) {
+        if (ids && nid > j && rec_same(rec)) {
+          const uint32_t q = D.ids_off + 4u * (same_first(rec) + j);
+          if (AT == kRecLds || (AT == kRecGlobal && (D.shift & (1u << 18)))) pid = lds32(R.img + q);
+          else pid = *(const uint32_t *)(R.gimg + q);
+        }
+        if (nid > j) {
+          const uint32_t o = tile_hits + lanes_below(hit);
+          if (o < cap) slab[o] = ((uint64_t)pid << kPosBits) | x;
+          if (pid_counts) atomicAdd(pid_counts + pid, 1ull);
+        }
+        tile_hits += (uint32_t)__builtin_popcountll(hit);
+        if (!ids) break;
+        ++j;
+        hit = ballot(nid > j);
+        if (!hit) break;
       }
-      if (wave_has) {
+    };
+    constexpr int Q = AT == kRecOne ? 1 : 2;
+    uint32_t nd = 0;  // put off (never past what has been read of the list)
+    for (uint32_t i0 = 0; i0 < nc; i0 += 64 * Q) {
+      Looked L[Q];
+      uint32_t er[Q], raw[Q][4];
+      bool ok[Q];
 #pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          if ((uint32_t)j < q) {
-            // out-of-range lanes look up the last candidate and drop the result
-            const bool v = c0 + j < nc;
-            rec[j] = record_of(v ? c0 + j : nc - 1, end[j], e[j], fnd[j]);
-            fnd[j] = fnd[j] && v;
-          }
+      for (int q = 0; q < Q; ++q) {
+        if (q == 0 || i0 + 64 * q < nc) {
+          L[q] = window(i0 + 64 * q, nc, er[q], raw[q]);
+        } else {
+          L[q] = Looked{};
+          er[q] = raw[q][0] = raw[q][1] = raw[q][2] = raw[q][3] = 0;
         }
-        uint32_t hd[Q][4];
+      }
+      if constexpr (AT != kRecOne) {
 #pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          if (!fnd[j]) rec[j] = 0;
-          hd[j][0] = hd[j][1] = hd[j][2] = hd[j][3] = 0;
-          if ((uint32_t)j < q && rec_one_pattern(rec[j])) {
-            const uint32_t *pw = (const uint32_t *)(gimg + D.pat_off + om_off((uint32_t)rec[j]));
-            hd[j][0] = pw[0];
-            hd[j][1] = pw[1];
-            hd[j][2] = pw[2];
-            hd[j][3] = pw[3];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          if ((uint32_t)j >= q || !rec[j]) continue;
-          if (rec_one_pattern(rec[j])) {
-            // one pattern (under one id, or under several: a hit per id):
-            // starts inside the text, bytes equal (Sec. 3.1)
-            const uint32_t om = (uint32_t)rec[j], mj = om_len(om);
-            const int64_t x = e[j] - (int64_t)mj + 1;
-            const uint8_t *pat = gimg + D.pat_off + om_off(om);
-            const bool ok = x >= 0 && (mj <= kFront ? window_equals_head(end[j], hd[j], pat, mj)
-                                                     : window_equals_global(gtext + x, pat, mj));
-            hm[j] = ok ? 0xFFFFFFFFu : 0u;
-            nh[j] = ok ? (rec_same(rec[j]) ? same_count(rec[j]) : 1u) : 0u;
-          } else {
-            nh[j] = verify_run(gimg, D, rec[j], end[j], e[j], gtext, hm[j]);
+        for (int q = 0; q < Q; ++q) {
+          const bool run = L[q].rec && !rec_one_pattern(L[q].rec);
+          const uint64_t b = ballot(run);
+          if (b) {
+            if (run) {
+              *(lds_half *)(uintptr_t)(cand + 2u * (nd + lanes_below(b))) = (uint16_t)er[q];
+              L[q].rec = 0;
+            }
+            nd += (uint32_t)__builtin_popcountll(b);
           }
         }
       }
-      uint32_t mine = 0;
+      verify<AT, Q>(D, R, L, raw, er, sub, start, gtext, ok);
 #pragma unroll
-      for (int j = 0; j < Q; ++j) mine += nh[j];
-      uint32_t nht;
-      const uint32_t hb = block_excl_scan<WG>(mine, misc, nht);
-      if (mine) {
-        uint32_t o = tile_hits + hb;
-#pragma unroll
-        for (int j = 0; j < Q; ++j)
-          if (nh[j]) write_hits(gimg, D, rec[j], hm[j], end[j], e[j], gtext, slab, cap, o, pid_counts);
+      for (int q = 0; q < Q; ++q) emit(ok[q], L[q].rec, er[q]);
+    }
+    if constexpr (AT != kRecOne) {
+      if (nd) wave_lds_fence();
+      for (uint32_t i0 = 0; i0 < nd; i0 += 64) {
+        Looked L[1];
+        uint32_t er[1], raw[1][4];
+        bool ok[1];
+        const uint64_t run = window(i0, nd, er[0], raw[0]).rec;
+        const uint32_t first = (uint32_t)run, count = (uint32_t)(run >> 32);
+        for (uint32_t i = 0; ballot(i < count); ++i) {
+          L[0] = table_record<AT>(D, R, i < count ? first + i : 0);
+          if (i >= count) L[0].rec = 0;
+          verify<AT, 1>(D, R, L, raw, er, sub, start, gtext, ok);
+          emit(ok[0], L[0].rec, er[0]);
+        }
       }
-      tile_hits += nht;
     }
   }
-  // nothing of this phase left in flight (a load whose value some path did
-  // not use would otherwise make the compiler wait for it, with a count that
-  // also covers the next tile's loads, at the next LDS read)
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  return ncand;
 }
 
-// A tile with at least this many candidates in a bucket makes the next tile
-// of the workgroup skip that bucket's test pass (hits are dense: the mask pass
-// runs directly).  Sparse hits (a planted occurrence now and then) keep the
-// cheaper test pass.
-constexpr uint32_t kDenseCand = 32;
-
-// Bucket descriptor b of the LDS image, as wave-uniform values.
-__device__ __forceinline__ BucketDesc read_desc(const uint8_t *img, uint32_t b) {
-  const BucketDesc *dp = (const BucketDesc *)(img + sizeof(ImageHeader) + 64u * b);
+// Bucket descriptor b of the image at gimg (device memory, wave-uniform), by
+// scalar loads.
+typedef const __attribute__((address_space(4))) uint32_t const_word;
+__device__ __forceinline__ BucketDesc read_desc(const uint8_t *gimg, uint32_t b) {
+  const_word *q = (const_word *)(uintptr_t)(gimg + sizeof(ImageHeader) + 64u * b);
   BucketDesc D;
-  D.m = uni(dp->m);
-  D.kind = uni(dp->kind);
-  D.shift = uni(dp->shift);
-  D.mask = uni(dp->mask);
+  uint32_t *d = (uint32_t *)&D;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) D.tgt[j] = uni(dp->tgt[j]);
-  D.fp_off = uni(dp->fp_off);
-  D.fp_mask = uni(dp->fp_mask);
-  D.ht_off = uni(dp->ht_off);
-  D.ht_mask = uni(dp->ht_mask);
-  D.ent_off = uni(dp->ent_off);
-  D.max_m = 0;
-  D.pat_off = uni(dp->pat_off);
-  D.npat = 0;
+  for (int j = 0; j < 16; ++j) d[j] = q[j];
   return D;
+}
+
+// Adds a wave's hits to its counter.
+__device__ __forceinline__ void add_total(unsigned long long *totals, uint32_t wave_id, uint64_t hits) {
+  atomicAdd(totals + (wave_id % kTotals) * (kTotalStride / 8), (unsigned long long)hits);
+}
+
+// A uniform u64 held in lanes, as a scalar.
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+  return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v);
 }
 
 // ------------------------------------------------------------ the scan kernel
 //
-// LDS: [slot 0][slot 1][cand: kCandCap u16][misc: 64 u32][image: img_cap]
+// Work comes in runs of consecutive tiles of one instance; the waves of a
+// block take a run's tiles in turn, each wave scanning its tile's sub-tiles in
+// order.  The block shares the instance image in LDS, so its waves meet
+// (barriers) when the image changes and, with a queue and several waves, when
+// a run is popped; a block of one wave never waits for another.  A wave has
+// one sub-tile slot: the next sub-tile's loads are issued when the last read
+// of the current one is done, and the other waves' work covers them (a second
+// slot would cost the waves that do so).
+//
+// LDS: [image: img_cap][queue word: 16][per wave: slot, candidates]
 template <int WG, int C, int FAM>
-__global__ __launch_bounds__(WG) void scan_kernel(ScanParams p) {
-  constexpr uint32_t W = WG * C;
-  constexpr uint32_t TILE_LDS = (kFront + W + 16 + 15) & ~15u;  // one slot
+__global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams p) {
+  constexpr uint32_t SUB = 64 * C;
   constexpr int NB = (C + 31) / 32;
+  static_assert(WG % 64 == 0, "a tile is at most WG / 64 sub-tiles");
   extern __shared__ __align__(16) uint8_t lds[];
-  uint16_t *cand = (uint16_t *)(lds + 2 * TILE_LDS);
-  uint32_t *misc = (uint32_t *)(cand + kCandCap);  // [0,16) scan sums, [16,48) any flags, [48] queue
-  uint8_t *img = (uint8_t *)(misc + 64);
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), nw = blockDim.x >> 6;
+  const uint32_t img = lds_addr(lds);
+  uint32_t *popw = (uint32_t *)(lds + p.img_cap);
+  const uint32_t sub = img + p.img_cap + 16 + wave * wave_lds_bytes<C>(1);
+  const uint32_t cand = sub + sub_slot_bytes<C>(), mine = sub + kFront + lane * C;
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t cur_inst = kNoLink;
-  uint64_t static_item = blockIdx.x;
-  uint32_t flag_parity = 0;
-  uint32_t dense_mask = 0;  // buckets whose last tile had candidates
-  const uint64_t nitems = p.nitems_dev ? min(p.nitems, (uint64_t)*p.nitems_dev) : p.nitems;
-
-  // Next work item (uniform across the workgroup).  With a queue, thread 0
-  // pops and the value is read back after the barrier that follows.
-  auto pop = [&]() -> uint64_t {
-    if (p.queue) {
-      wg_barrier();
-      if (tid == 0) misc[48] = atomicAdd(p.queue, 1u);
-      wg_barrier();
-      return misc[48];
-    }
-    const uint64_t it = static_item;
-    static_item += gridDim.x;
-    return it;
-  };
   struct Item {
-    uint64_t gt;
-    uint32_t inst;
+    uint64_t gt;         // tile
+    uint64_t n, tstart;  // its text's length, its first byte
     const uint8_t *text;
-    uint64_t n;
-    int64_t tstart;
+    uint32_t inst;
   };
-  auto locate = [&](uint64_t item) -> Item {
-    Item it;
-    it.gt = p.items ? p.items[item] : item;
-    uint32_t lo = 0, hi = p.ninst;  // instance owning global tile gt
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (p.inst[mid].tile_base <= it.gt) lo = mid;
-      else hi = mid;
+  // the run this wave is in: its remaining tiles are tnext, tnext + nw, ...
+  uint64_t next_run = blockIdx.x, tnext = 0, tbase = 0, rn = 0;
+  const uint8_t *rtext = nullptr;
+  uint32_t tleft = 0, rinst = 0;
+  const uint64_t nlist = p.nitems_dev ? min(p.nitems, (uint64_t)uni(*p.nitems_dev)) : p.nitems;
+  const uint64_t nruns = p.wave_items ? (nlist + nw - 1) / nw : p.nitems;
+
+  // The wave's next tile: 1 (in it), 2 (none in this run, but its image is to
+  // be switched to), 0 (no run left).
+  auto next_item = [&](Item &it) __attribute__((always_inline)) -> uint32_t {
+    if (tleft == 0) {
+      uint64_t r;
+      if (p.queue) {
+        uint32_t v = 0;
+        if (nw == 1) {
+          if (lane == 0) v = atomicAdd(p.queue, 1u);
+          r = uni(v);
+        } else {
+          wg_barrier();
+          if (tid == 0) popw[0] = atomicAdd(p.queue, 1u);
+          wg_barrier();
+          r = uni(popw[0]);
+        }
+      } else {
+        r = next_run;
+        next_run += gridDim.x;
+      }
+      if (r >= nruns) return 0;
+      uint64_t first;
+      if (p.wave_items) {
+        const uint64_t q = r * nw + wave;
+        tleft = q < nlist ? 1u : 0u;
+        first = tnext = uni64(p.items[q < nlist ? q : nlist - 1]);
+      } else {
+        uint32_t cnt;
+        if (p.items) {
+          const uint64_t v = uni64(p.items[r]);
+          first = v & kItemTile;
+          cnt = (uint32_t)(v >> kItemShift);
+        } else {
+          const uint64_t i = p.ninst > 1 ? r / p.inst_runs : 0, q = (r - i * p.inst_runs) * p.run;
+          first = i * p.inst_tiles + q;
+          cnt = (uint32_t)min((uint64_t)p.run, p.inst_tiles - q);
+        }
+        tleft = cnt > wave ? (cnt - wave + nw - 1u) / nw : 0u;
+        tnext = first + wave;
+      }
+      uint32_t lo = 0, hi = p.ninst;  // instance owning the tile
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (uni64(p.inst[mid].tile_base) <= first) lo = mid;
+        else hi = mid;
+      }
+      rinst = lo;
+      rtext = (const uint8_t *)uni64((uint64_t)(uintptr_t)p.inst[lo].text);
+      rn = uni64(p.inst[lo].n);
+      tbase = uni64(p.inst[lo].tile_base);
     }
-    it.inst = lo;
-    it.text = p.inst[lo].text;
-    it.n = p.inst[lo].n;
-    it.tstart = (int64_t)((it.gt - p.inst[lo].tile_base) * W);
-    return it;
+    it.inst = rinst;
+    if (tleft == 0) return 2;
+    it.gt = tnext;
+    it.text = rtext;
+    it.n = rn;
+    it.tstart = (tnext - tbase) * ((uint64_t)SUB * p.sub);
+    tnext += nw;
+    --tleft;
+    return 1;
   };
-  // Two LDS slots: tile k is processed in one while the loads of tile k+1
-  // land in the other.
-  uint32_t slot = 0;
+
+  uint32_t cur_inst = kNoLink, nb = 0;
+  uint64_t hits = 0;  // of this wave
   const uint8_t *gimg = nullptr;  // current instance image in device memory
-  uint64_t item = pop();
   Item cur;
-  if (item < nitems) {
-    cur = locate(item);
-    dma_tile<WG, C>(lds, cur.text, cur.n, cur.tstart);
-  }
-  while (item < nitems) {
-    const uint64_t next = pop();
-    const bool have_next = next < nitems;
-    Item nx;
-    if (have_next) nx = locate(next);
-    // this tile has landed, and every wave is done with the other slot
-    wg_barrier_loads();
-    uint8_t *tile = lds + slot * TILE_LDS;
+  uint32_t st = next_item(cur);
+  if (st == 1) dma_sub<C>(sub, cur.text, cur.n, cur.tstart);
+  while (st) {
     if (cur.inst != cur_inst) {
       // the image's leading part goes to LDS; the rest is read in place
-      gimg = p.blob + p.inst[cur.inst].img_off;
+      if (nw > 1) wg_barrier();
+      gimg = p.blob + uni(p.inst[cur.inst].img_off);
       const uint4 *src = (const uint4 *)gimg;
-      uint4 *dst = (uint4 *)img;
-      const uint32_t nq = p.inst[cur.inst].lds_bytes / 16u;
-      for (uint32_t q = tid; q < nq; q += WG) dst[q] = src[q];
+      uint4 *dst = (uint4 *)lds;
+      const uint32_t nq = uni(p.inst[cur.inst].lds_bytes) / 16u;
+      for (uint32_t q = tid; q < nq; q += blockDim.x) dst[q] = src[q];
       cur_inst = cur.inst;
       wg_barrier();
+      nb = *(const_word *)(uintptr_t)gimg;  // ImageHeader::nbuckets
     }
-    const uint64_t gt = cur.gt;
-    const uint64_t n = cur.n;
-    const int64_t tstart = cur.tstart;
+    if (st == 2) {
+      st = next_item(cur);
+      if (st == 1) dma_sub<C>(sub, cur.text, cur.n, cur.tstart);
+      continue;
+    }
     uint64_t *slab = nullptr;
-    if (p.out) slab = p.direct ? (p.out + p.tile_offsets[gt]) : (p.out + (gt - p.tile0) * (uint64_t)p.slab_cap);
+    if (p.out)
+      slab = p.direct ? p.out + uni64(p.tile_offsets[cur.gt]) : p.out + (cur.gt - p.tile0) * (uint64_t)p.slab_cap;
     const uint32_t cap = p.direct ? 0xFFFFFFFFu : p.slab_cap;
-    // Everything this tile reads from memory into registers is there before
-    // the next tile's loads are issued (the compiler would otherwise wait for
-    // a late load with a count that also covers those loads).
-    __asm__ volatile("" ::"v"(slab), "v"(n), "v"(tstart), "v"(gt), "v"(gimg) : "memory");
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    if (have_next) dma_tile<WG, C>(lds + (slot ^ 1u) * TILE_LDS, nx.text, nx.n, nx.tstart);
-
-    // this thread's bytes: 64 before its first window end, then C
-    const uint32_t *tw = (const uint32_t *)(tile + kFront + tid * C - 64);
-    const uint8_t *mine = tile + kFront + tid * C;  // LDS byte of my first window end
-    const int64_t e0 = tstart + (int64_t)(tid * C); // global end index of my first window
-
-    const ImageHeader *H = (const ImageHeader *)img;
-    const uint32_t nb = uni(H->nbuckets);
+    const uint32_t ns = (uint32_t)min((uint64_t)p.sub, (cur.n - cur.tstart + SUB - 1) / SUB);
     uint32_t tile_hits = 0;
-
-    // Buckets go in chunks of 32: the test pass of every bucket of the chunk
-    // first (one flag bit per bucket and wave), one barrier, then the mask
-    // pass and candidate phase of the buckets whose tile had a candidate.
-    for (uint32_t b0 = 0; b0 < nb; b0 += 32) {
-      const uint32_t nbc = min(32u, nb - b0);
-      uint32_t wave_bits = 0, need = 0;
-      for (uint32_t bi = 0; bi < nbc; ++bi) {
-        const uint32_t b = b0 + bi;
-        const BucketDesc D = read_desc(img, b);
-        const uint32_t m = D.m;
-        const uint32_t r = (8u * m) % 61u;
-        const OutStream os = out_stream(mine, m);
+    Item nx;
+    for (uint32_t s = 0; s < ns; ++s) {
+      const uint64_t start = cur.tstart + (uint64_t)s * SUB;
+      if (s + 1 == ns) st = next_item(nx);  // (its reads are under way with the sub-tile's)
+      wait_loads();                         // this sub-tile has landed
+      for (uint32_t b = 0; b < nb; ++b) {
+        const BucketDesc D = read_desc(gimg, b);
+        const uint32_t r = (8u * D.m) % 61u;
+        const OutStream os = out_stream(mine, D.m);
         if constexpr (FAM == kFamExact) {
           if (D.kind == kDump) {
-            pass_dump<C, false>(tw, os, m, r, e0, n, DumpDst{p.dump_out, p.dump_stride, p.dump_cap}, nullptr);
+            pass_dump<C>(mine, os, D.m, r, (int64_t)(start + lane * C), cur.n,
+                         DumpDst{p.dump_out, p.dump_stride, p.dump_cap});
             continue;
           }
         }
-        // skipped while the bucket's previous tile had candidates (dense
-        // hits): the mask pass and its block scan decide then
-        if (b < 32 && ((dense_mask >> b) & 1u)) {
-          need |= 1u << bi;
-          continue;
-        }
-        uint64_t any = 0;
-        Bits<C> nob;
-        run_pass<C, true, FAM>(D, tw, os, r, (const uint32_t *)(img + D.fp_off), any, nob);
-        if (any) wave_bits |= 1u << bi;
-      }
-      uint32_t *flags = misc + 16 + 16 * flag_parity;
-      flag_parity ^= 1u;
-      if (lane == 0) flags[wave] = wave_bits;
-      wg_barrier();
-#pragma unroll
-      for (int i = 0; i < WG / 64; ++i) need |= flags[i];
-      need = uni(need);
-      while (need) {
-        const uint32_t bi = __builtin_ctz(need);
-        need &= need - 1u;
-        const uint32_t b = b0 + bi;
-        const BucketDesc D = read_desc(img, b);
-        const uint32_t m = D.m;
-        const uint32_t r = (8u * m) % 61u;
-        const OutStream os = out_stream(mine, m);
         Bits<C> bits;
 #pragma unroll
         for (int j = 0; j < NB; ++j) bits.b[j] = 0;
         uint64_t dummy = 0;
-        run_pass<C, false, FAM>(D, tw, os, r, (const uint32_t *)(img + D.fp_off), dummy, bits);
-        uint32_t ncand;
-        candidate_phase<WG, C, FAM == kFamExact ? 1 : kCandCap / WG>(bits, D, tile, tstart, n, e0, img, gimg, cand,
-                                                                     misc, slab, cap,
-                                                     tile_hits, ncand,
-                               cur.text, p.direct ? nullptr : p.pid_counts);
-        if (b < 32) dense_mask = ncand >= kDenseCand ? (dense_mask | (1u << b)) : (dense_mask & ~(1u << b));
+        run_pass<C, false, FAM>(D, mine, os, r, img + D.test_off, dummy, bits);
+        const Records R{img, gimg, Looked{}};
+        unsigned long long *const pc = p.direct ? nullptr : p.pid_counts;
+        if (D.shift & (1u << 16))
+          wave_candidates<C, kRecLds>(bits, D, sub, start, cur.n, R, cand, slab, cap, tile_hits, cur.text, pc);
+        else
+          wave_candidates<C, kRecGlobal>(bits, D, sub, start, cur.n, R, cand, slab, cap, tile_hits, cur.text, pc);
       }
+      wait_lds();  // every read of the slot is done
+      if (s + 1 < ns) dma_sub<C>(sub, cur.text, cur.n, start + SUB);
+      else if (st == 1) dma_sub<C>(sub, nx.text, nx.n, nx.tstart);
     }
-
-    if (tid == 0 && !p.direct) {
-      p.tile_counts[gt] = tile_hits;
-      if (tile_hits) {
-        atomicAdd(p.total, (unsigned long long)tile_hits);
-        if (p.blk_sums) atomicAdd(p.blk_sums + (gt >> kTileSumLog2), (unsigned long long)tile_hits);
-      }
+    if (lane == 0 && !p.direct) {
+      p.tile_counts[cur.gt] = tile_hits;
       if (tile_hits > p.slab_cap) {
         const uint32_t o = atomicAdd(p.ovf_count, 1u);
-        p.ovf_list[o] = gt;
+        p.ovf_list[o] = cur.gt;
       }
     }
-    item = next;
+    hits += tile_hits;
     cur = nx;
-    slot ^= 1u;
   }
+  if (lane == 0 && hits && !p.direct) add_total(p.totals, blockIdx.x * nw + wave, hits);
 }
 
 // ------------------------------------------------- single-bucket scan kernel
-// The same scan for the most common plan shape: one text and one bucket whose
-// set fits in registers (up to 4 targets: one pattern, or a few patterns of
-// similar length).  The bucket descriptor and the text come as kernel
-// arguments, tiles are strided statically over the persistent grid, and there
-// is no image staging, work list or instance lookup, so a tile costs little
-// beyond its hash pass.  Count mode only (hits into per-tile slabs); a tile
-// whose slab overflows is rescanned by the general kernel.
+// The same scan for the most common plan shape: one text and one bucket with
+// one key (one pattern, or one pattern under several ids).  The bucket
+// descriptor, the text and the key's record come as kernel arguments, tiles
+// are strided statically over the waves of the grid, and there is no image
+// staging, work list or instance lookup, so a sub-tile costs little beyond its
+// hash pass.  Count mode only (hits into per-tile slabs); a tile whose slab
+// overflows is rescanned by the general kernel.
 //
-// Tile t+1 loads into the other slot while tile t is tested: the thread's
-// words of tile t are read into registers first (out of the compiler's sight,
-// so that it does not wait for the new loads), then tile t+1's loads are
-// issued, then the test runs on registers only.
+// A sub-tile without a candidate is decided by the test pass alone (a compare
+// and a scalar OR per window); after one with candidates the wave runs the
+// mask pass straight away, until a sub-tile has none.  Two slots: the next
+// sub-tile loads while this one is tested.
 //
-// LDS: [slot 0][slot 1][cand: kCandCap u16][misc: 64 u32]
+// LDS: per wave [slot 0][slot 1][candidates]
 template <int WG, int C, int FAM>
-__global__ __launch_bounds__(WG) void scan_list_kernel(ListParams p) {
-  constexpr uint32_t W = WG * C;
-  constexpr uint32_t TILE_LDS = (kFront + W + 16 + 15) & ~15u;
+__global__ __launch_bounds__(kListBlock) void scan_list_kernel(ListParams p) {
+  constexpr uint32_t SUB = 64 * C, SLOT = sub_slot_bytes<C>();
   constexpr int NB = (C + 31) / 32;
   extern __shared__ __align__(16) uint8_t lds[];
-  uint16_t *cand = (uint16_t *)(lds + 2 * TILE_LDS);
-  uint32_t *misc = (uint32_t *)(cand + kCandCap);
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+  const uint32_t slots = lds_addr(lds) + wave * wave_lds_bytes<C>(2);
+  const uint32_t cand = slots + 2 * SLOT;
   const BucketDesc D = p.D;
-  const uint32_t m = D.m;
   const uint32_t r = p.rot;
-  uint32_t slot = 0, flag_parity = 0;
+  const uint64_t W = (uint64_t)SUB * p.sub, stride = (uint64_t)gridDim.x * (kListBlock / 64);
+  uint32_t slot = 0;
   bool dense = false;
-  uint64_t t = blockIdx.x;
-  if (t < p.ntiles) dma_tile<WG, C>(lds, p.text, p.n, (int64_t)(t * W));
-  while (t < p.ntiles) {
-    const uint64_t nt = t + gridDim.x;
-    wg_barrier_loads();  // tile t has landed; every wave is done with the other slot
-    const uint8_t *tile = lds + slot * TILE_LDS;
-    const int64_t tstart = (int64_t)(t * W);
-    const uint32_t *tw = (const uint32_t *)(tile + kFront + tid * C - 64);
-    const OutStream os = out_stream(tile + kFront + tid * C, m);
-    PreWords<C> pre;
-    load_words<16 + C / 4>(pre.w, tw);
-    if constexpr (FAM == kFamExact) load_words<C / 4 + 1>(pre.d, os.d);
-    if (nt < p.ntiles) dma_tile<WG, C>(lds + (slot ^ 1u) * TILE_LDS, p.text, p.n, (int64_t)(nt * W));
-    const int64_t e0 = tstart + (int64_t)(tid * C);
-    if constexpr (FAM == kFamExact) {
-      if (D.kind == kDump) {
-        // hash dump: this kernel's own rolling loop over the words read above
-        pass_dump<C, true>(tw, os, m, r, e0, p.n, DumpDst{p.dump_out, p.dump_stride, p.dump_cap}, &pre);
-        t = nt;
-        slot ^= 1u;
-        continue;
-      }
-    }
+  uint64_t hits = 0;  // of this wave
+  uint64_t t = (uint64_t)blockIdx.x * (kListBlock / 64) + wave;
+  if (t < p.ntiles) dma_sub<C>(slots, p.text, p.n, t * W);
+  for (; t < p.ntiles; t += stride) {
+    const uint64_t tstart = t * W;
+    const uint32_t ns = (uint32_t)min((uint64_t)p.sub, (p.n - tstart + SUB - 1) / SUB);
     uint32_t tile_hits = 0;
-    bool run2 = dense;
-    if (!dense) {
-      uint64_t any = 0;
-      Bits<C> nob;
-      run_pass<C, true, FAM, true>(D, tw, os, r, nullptr, any, nob, &pre);
-      uint32_t *flags = misc + 16 + 16 * flag_parity;
-      flag_parity ^= 1u;
-      if (lane == 0) flags[wave] = any != 0;
-      wg_barrier();
-      uint32_t blk_any = 0;
-#pragma unroll
-      for (int i = 0; i < WG / 64; ++i) blk_any |= flags[i];
-      run2 = blk_any != 0;
-    }
-    if (run2) {
+    for (uint32_t s = 0; s < ns; ++s) {
+      const uint32_t sub = slots + slot * SLOT, mine = sub + kFront + lane * C;
+      const uint64_t start = tstart + (uint64_t)s * SUB;
+      wait_loads();
+      const uint64_t nstart = s + 1 < ns ? start + SUB : (t + stride < p.ntiles ? (t + stride) * W : p.n);
+      if (nstart < p.n) dma_sub<C>(slots + (slot ^ 1u) * SLOT, p.text, p.n, nstart);
+      slot ^= 1u;
+      const OutStream os = out_stream(mine, D.m);
       Bits<C> bits;
+      if constexpr (FAM == kFamExact) {
+        if (D.kind == kDump) {
+          pass_dump<C>(mine, os, D.m, r, (int64_t)(start + lane * C), p.n,
+                       DumpDst{p.dump_out, p.dump_stride, p.dump_cap});
+          continue;
+        }
+      }
+      uint64_t any = 0;
+      if (!dense) {
+        run_pass<C, true, FAM>(D, mine, os, r, 0, any, bits);
+        if (any == 0) continue;
+      }
 #pragma unroll
       for (int j = 0; j < NB; ++j) bits.b[j] = 0;
-      uint64_t dummy = 0;
-      run_pass<C, false, FAM, true>(D, tw, os, r, nullptr, dummy, bits, &pre);
-      uint32_t ncand;
-      candidate_phase<WG, C, FAM == kFamExact ? 1 : 2>(bits, D, tile, tstart, p.n, e0, nullptr, p.gimg, cand, misc,
-                             p.out + t * (uint64_t)p.slab_cap, p.slab_cap, tile_hits, ncand, p.text, p.pid_counts,
-                             p.rec1);
-      dense = ncand >= kDenseCand;
+      run_pass<C, false, FAM>(D, mine, os, r, 0, any, bits);
+      const Records R{0, p.gimg, Looked{p.rec1, {p.tail[0], p.tail[1], p.tail[2], p.tail[3]}}};
+      uint64_t *const slab = p.out + t * (uint64_t)p.slab_cap;
+      uint32_t nc;
+      if (rec_one_pattern(p.rec1))
+        nc = wave_candidates<C, kRecOne>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
+                                         p.pid_counts);
+      else
+        nc = wave_candidates<C, kRecGlobal>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
+                                            p.pid_counts);
+      dense = nc != 0;
     }
-    if (tid == 0) {
+    if (lane == 0 && D.kind != kDump) {
       p.tile_counts[t] = tile_hits;
-      if (tile_hits) {
-        atomicAdd(p.total, (unsigned long long)tile_hits);
-        if (p.blk_sums) atomicAdd(p.blk_sums + (t >> kTileSumLog2), (unsigned long long)tile_hits);
-      }
       if (tile_hits > p.slab_cap) {
         const uint32_t o = atomicAdd(p.ovf_count, 1u);
         p.ovf_list[o] = t;
       }
     }
-    t = nt;
-    slot ^= 1u;
+    hits += tile_hits;
   }
+  if (lane == 0 && hits) add_total(p.totals, blockIdx.x * (kListBlock / 64) + wave, hits);
 }
 
 // ------------------------------------------------------------------ launchers
-template <int WG, int C>
+template <int C>
 constexpr uint32_t list_lds_bytes_t() {
-  return 2 * ((kFront + WG * C + 16 + 15) & ~15u) + kCandCap * 2 + 64 * 4;
+  return kListBlock / 64 * wave_lds_bytes<C>(2);
 }
 
 template <int WG, int C, int FAM>
-static hipError_t launch_scan_t(const ScanParams &p, uint32_t grid, uint32_t lds_bytes, hipStream_t s) {
+static hipError_t launch_scan_t(const ScanParams &p, uint32_t grid, uint32_t block, hipStream_t s) {
   // the dynamic LDS limit was raised by prepare_scan_kernels() at context creation
-  hipLaunchKernelGGL((scan_kernel<WG, C, FAM>), dim3(grid), dim3(WG), lds_bytes, s, p);
+  const uint32_t lds = p.img_cap + 16 + block / 64 * wave_lds_bytes<C>(1);
+  hipLaunchKernelGGL((scan_kernel<WG, C, FAM>), dim3(grid), dim3(block), lds, s, p);
   return hipGetLastError();
 }
 
 template <int WG, int C, int FAM>
 static hipError_t launch_list_t(const ListParams &p, uint32_t grid, hipStream_t s) {
-  constexpr uint32_t lds = list_lds_bytes_t<WG, C>();
-  hipLaunchKernelGGL((scan_list_kernel<WG, C, FAM>), dim3(grid), dim3(WG), lds, s, p);
+  constexpr uint32_t lds = list_lds_bytes_t<C>();
+  hipLaunchKernelGGL((scan_list_kernel<WG, C, FAM>), dim3(grid), dim3(kListBlock), lds, s, p);
   return hipGetLastError();
 }
 
@@ -1480,22 +1362,25 @@ struct Geom {
 };
 
 template <int FAM, int CFG>
-hipError_t ScanGeom<FAM, CFG>::launch(const ScanParams &p, uint32_t grid, uint32_t lds_bytes, hipStream_t s) {
-  return launch_scan_t<Geom<CFG>::WG, Geom<CFG>::C, FAM>(p, grid, lds_bytes, s);
+hipError_t ScanGeom<FAM, CFG>::launch(const ScanParams &p, uint32_t grid, uint32_t block, hipStream_t s) {
+  return launch_scan_t<Geom<CFG>::WG, Geom<CFG>::C, FAM>(p, grid, block, s);
 }
 
 template <int FAM, int CFG>
-hipError_t ScanGeom<FAM, CFG>::occupancy(uint32_t lds_bytes, int *blocks) {
+hipError_t ScanGeom<FAM, CFG>::fit(uint32_t img_cap, uint32_t block, ScanFit *f) {
   constexpr int WG = Geom<CFG>::WG, C = Geom<CFG>::C;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void *)scan_kernel<WG, C, FAM>, WG, lds_bytes);
+  f->wave_lds = wave_lds_bytes<C>(1);
+  f->max_block = scan_block_max(C, FAM);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&f->blocks, (const void *)scan_kernel<WG, C, FAM>, block,
+                                                      img_cap + 16 + block / 64 * f->wave_lds);
 }
 
 template <int FAM, int CFG>
 hipError_t ScanGeom<FAM, CFG>::list(const ListParams *p, uint32_t grid, hipStream_t s, int *blocks) {
   constexpr int WG = Geom<CFG>::WG, C = Geom<CFG>::C;
   if (p) return launch_list_t<WG, C, FAM>(*p, grid, s);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void *)scan_list_kernel<WG, C, FAM>, WG,
-                                                      list_lds_bytes_t<WG, C>());
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, (const void *)scan_list_kernel<WG, C, FAM>, kListBlock,
+                                                      list_lds_bytes_t<C>());
 }
 
 template <int FAM, int CFG>
@@ -1514,7 +1399,7 @@ hipError_t ScanGeom<FAM, CFG>::list_prepare() {
 // the single-bucket kernel's (X = list) for family FAM and geometry CFG.
 #define RK_INSTANTIATE_SCAN(FAM, CFG)                                                                     \
   template hipError_t ScanGeom<FAM, CFG>::launch(const ScanParams &, uint32_t, uint32_t, hipStream_t); \
-  template hipError_t ScanGeom<FAM, CFG>::occupancy(uint32_t, int *);                                   \
+  template hipError_t ScanGeom<FAM, CFG>::fit(uint32_t, uint32_t, ScanFit *);                           \
   template hipError_t ScanGeom<FAM, CFG>::prepare();
 #define RK_INSTANTIATE_LIST(FAM, CFG)                                                                    \
   template hipError_t ScanGeom<FAM, CFG>::list(const ListParams *, uint32_t, hipStream_t, int *);      \

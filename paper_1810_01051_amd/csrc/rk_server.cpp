@@ -126,7 +126,7 @@ struct Slot {
   uint64_t hstage_cap = 0;
   uint64_t *hres = nullptr;   // pinned: merged per-pattern offsets of the step
   uint64_t hres_cap = 0;      // bytes
-  uint64_t *hctr = nullptr;   // pinned: total, overflow count
+  uint64_t *hctr = nullptr;   // pinned: the pass's counters (hits, overflowed tiles)
   hipGraphExec_t gcount = nullptr, gcollect = nullptr;
   std::vector<Request *> reqs;
   uint64_t step_id = 0, n_total = 0, total = 0, plan_bytes = 0;
@@ -367,16 +367,17 @@ static rk_status start_step(rk_server *S, Slot &sl, std::unique_lock<std::mutex>
   // Staging records per tile, from the expected hits per tile (a tile with
   // more is rescanned by the collect pass, a whole extra scan for the dense
   // outputs of merged steps): four times the expected count, between the
-  // default (tile bytes / 16) and half the tile, with the slabs of a step
-  // kept under 2 GiB.
+  // default (a sixteenth of the geometry's tile) and half the tile, with the
+  // slabs of a step kept under 2 GiB.
   sl.slab_cap = 0;
   if (st == RK_OK && S->hits_per_pattern > 0 && nbytes > 0) {
-    const uint64_t W = (uint64_t)kTileCfgs[sl.plan.cfg].wg * kTileCfgs[sl.plan.cfg].c;
+    const TileCfg g = kTileCfgs[sl.plan.cfg];
+    const uint64_t W = sl.plan.parts.empty() ? 1 : 64ull * g.c * sl.plan.parts[0].sub;
     // tiles of the step: every image (m-bucket of the merged patterns) scans
     // the corpus once
     const uint64_t tiles = std::max<uint64_t>(1, sl.plan.total_tiles);
     const double per_tile = S->hits_per_pattern * (double)kt / (double)tiles;
-    const uint64_t lo = W / 16, hi = std::min<uint64_t>(W / 2, (2ull << 30) / (8 * tiles));
+    const uint64_t lo = g.wg * g.c / 16, hi = std::min<uint64_t>(W / 2, (2ull << 30) / (8 * tiles));
     const uint64_t want = aup((uint64_t)(4.0 * per_tile) + 1, 64);
     if (want > lo && hi > lo) sl.slab_cap = (uint32_t)std::min(want, hi);
   }
@@ -405,7 +406,7 @@ static rk_status start_step(rk_server *S, Slot &sl, std::unique_lock<std::mutex>
       if (e != hipSuccess) return hip_err(S->ctx, e, "plan upload");
       rk_status s2 = count_enqueue(S->ctx, &sl.plan, nullptr, 0, sl.scratch, sl.scratch_cap, nullptr, sl.stream);
       if (s2 != RK_OK) return s2;
-      e = hipMemcpyAsync(sl.hctr, sl.scratch, 64, hipMemcpyDeviceToHost, sl.stream);
+      e = hipMemcpyAsync(sl.hctr, sl.scratch, kCtrBytes, hipMemcpyDeviceToHost, sl.stream);
       return e == hipSuccess ? RK_OK : hip_err(S->ctx, e, "count readback");
     });
   }
@@ -573,7 +574,7 @@ static void scheduler(rk_server *S) {
       if (sl.state == kCounting) {
         const hipError_t q = hipEventQuery(sl.ev_count);
         if (q == hipSuccess) {
-          sl.total = sl.hctr[0];
+          sl.total = hit_total(sl.hctr);
           sl.ovf = ovf_total(sl.hctr);
           sl.state = kCounted;
           progress = true;
@@ -712,7 +713,7 @@ rk_status rk_server_create(rk_ctx *ctx, const rk_server_cfg *cfg_in, rk_server *
     e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.ev_count, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.ev_collect, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&sl.hctr, 64, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&sl.hctr, kCtrBytes, hipHostMallocDefault);
     if (e != hipSuccess) break;
   }
   if (e != hipSuccess) {

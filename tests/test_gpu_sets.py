@@ -1,0 +1,102 @@
+"""Pattern sets at the edges of the scan's tables, against the oracle: bitmaps
+and record tables that fit the LDS image and that do not, patterns sharing a
+bitmap bit, one pattern under many ids, every length class, and texts from one
+sub-tile to several tiles per wave."""
+import numpy as np
+import pytest
+
+import oracle
+import rkgen
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rk():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1810_01051_amd as rk
+    return rk
+
+
+@pytest.fixture(scope="module")
+def ctx(rk):
+    c = rk.Context(0)
+    yield c
+    c.close()
+
+
+def search(ctx, rk, text, pats, mode):
+    plan = rk.Plan(ctx, pats, mode)
+    off, pos = plan.search(torch.from_numpy(text).to("cuda:0"))
+    torch.cuda.synchronize()
+    plan.close()
+    return off.cpu().numpy().astype(np.uint64), pos.cpu().numpy().astype(np.uint64)
+
+
+def draw(g, text, table, k, lo, hi):
+    out = []
+    for j in range(k):
+        m = int(g.integers(lo, hi + 1))
+        if j % 2 == 0:
+            o = int(g.integers(0, len(text) - m + 1))
+            out.append(text[o:o + m].tobytes())
+        else:
+            out.append(table[g.integers(0, len(table), size=m)].tobytes())
+    return out
+
+
+@pytest.mark.parametrize("mode", ["screen", "exact"])
+@pytest.mark.parametrize("lo,hi", [(1, 3), (4, 7), (8, 15), (16, 16), (16, 64), (17, 33), (1, 100)])
+@pytest.mark.parametrize("k", [2, 40, 1030, 4200])
+def test_set_sizes_and_lengths(ctx, rk, mode, lo, hi, k):
+    g = rkgen.rng(81, 1000 * lo + 10 * hi + k % 7)
+    for n, table in ((2300, rkgen.ACGT), (300007, rkgen.LOWER)):
+        if lo < 4 and k > 1000 and n > 10000:
+            n = 40009  # thousands of one-byte patterns hit everywhere
+        text = rkgen.iid_text(g, n, table[:6])
+        pats = draw(g, text, table, k, lo, min(hi, n))
+        ref = oracle.search(text, pats, threads=4)
+        got = search(ctx, rk, text, pats, mode)
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), (n, k)
+
+
+@pytest.mark.parametrize("mode", ["screen", "exact"])
+@pytest.mark.parametrize("ids", [1, 2, 255, 256, 257, 600])
+def test_one_pattern_under_many_ids(ctx, rk, mode, ids):
+    """Alone (the single-bucket scan) and beside other patterns, some of which
+    end in the same 16 bytes (one key) or hold the same bytes in other
+    lengths."""
+    g = rkgen.rng(82, ids)
+    text = rkgen.iid_text(g, 70001, rkgen.ACGT)
+    p = text[333:333 + 24].tobytes()
+    for o in (1000, 1024, 5000, 69000, 69977):
+        text[o:o + 24] = np.frombuffer(p, np.uint8)
+    for others in ([], [p[8:], p[1:], b"A" + p[1:], p[8:20], b"ACGTACGT", p + b"T"]):
+        pats = [p] * ids + others + [p]
+        ref = oracle.search(text, pats)
+        got = search(ctx, rk, text, pats, mode)
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), (ids, len(others))
+
+
+@pytest.mark.parametrize("mode", ["screen", "exact"])
+def test_batch_of_large_and_small_sets(ctx, rk, mode):
+    """Instances whose images differ in size by far, in one batch: blocks of
+    several waves that switch images together."""
+    g = rkgen.rng(83, 0)
+    texts, sets = [], []
+    for k, n in ((900, 50000), (1, 4096), (3, 200001), (1500, 9000), (30, 17), (700, 120000)):
+        text = rkgen.iid_text(g, n, rkgen.LOWER[:8])
+        texts.append(text)
+        sets.append(draw(g, text, rkgen.LOWER, k, 4, min(40, n)))
+    bp = rk.BatchPlan(ctx, [torch.from_numpy(t).to("cuda:0") for t in texts], sets, mode)
+    for _ in range(2):
+        off, pos = bp.search()
+        torch.cuda.synchronize()
+        per = bp.split(off, pos)
+        for i, (t, s) in enumerate(zip(texts, sets)):
+            ref = oracle.split(*oracle.search(t, s, threads=4))
+            for j in range(len(s)):
+                assert np.array_equal(np.asarray(per[i][j]).astype(np.uint64), ref[j]), (i, j)
+    bp.close()
