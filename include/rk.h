@@ -67,17 +67,19 @@ typedef enum {
  *                   against the pattern-hash set; equal hashes are byte-checked.
  *                   A set whose lengths all agree (one pattern, say) hashes
  *                   whole windows.  Several lengths share one stream per
- *                   length class (1, 2, 3, 4..7, 8..15, 16..31, 32 and more):
+ *                   length class (1, 2, 3, 4..7, 8..15, 16 and more; a class of
+ *                   few patterns joins the next shorter one):
  *                   it hashes the last l bytes of every window, l the shortest
  *                   length of the class (at most RK_STREAM_M), and each
  *                   pattern is keyed by the hash of its last l bytes.
  *   RK_MODE_SCREEN: every window gets a shift-and-add hash in the paper's form
  *                   h <- (h << s) + c taken mod 2^32 (the polynomial hash
- *                   with d = 2^s, q = 2^32) with s = 8 for patterns shorter
- *                   than 8 bytes (masked to the window below 4), 4 for 8..15
- *                   and 2 from 16 (so the hash covers the last 32/s bytes of
- *                   a window: every pattern of 16 bytes or more shares one
- *                   stream), tested against the set of the patterns' shift-add
+ *                   with d = 2^s, q = 2^32), one stream per length class as
+ *                   above, with s = 8 where its shortest pattern has fewer than
+ *                   8 bytes (masked to the window below 4), 4 for 8..10, 3 for
+ *                   11..15 and 2 from 16 (so the hash covers the last 32/s
+ *                   bytes of a window: every pattern of 16 bytes or more shares
+ *                   one stream), tested against the set of the patterns' shift-add
  *                   hashes; windows in the set are byte-checked against the
  *                   patterns with that hash (the byte check stands in for the
  *                   exact hash, which can only pass what the bytes pass).  A

@@ -32,8 +32,11 @@ static int pick_cfg(const rk_ctx *ctx, int mode, uint32_t m) {
 // Scan geometry of a batch instance: the one with the least tuned time per
 // MiB summed over the instance's m-buckets (each bucket timed alone by the
 // autotuner; the instance's buckets share one scan of its text), else the
-// tuned choice of its largest bucket, else the per-length choice.
-static int instance_cfg(const rk_ctx *ctx, int mode, const uint32_t npat[kNumMClass], uint32_t max_m) {
+// tuned choice of its largest bucket, else the per-length choice.  per_mib
+// receives the sums (all zero where a bucket was not timed).
+static int instance_cfg(const rk_ctx *ctx, int mode, const uint32_t npat[kNumMClass], uint32_t max_m,
+                        double per_mib[kNumTileCfg]) {
+  for (int g = 0; g < kNumTileCfg; ++g) per_mib[g] = 0;
   if (ctx->tile_cfg >= 0) return ctx->tile_cfg;
   const int md = mode == RK_MODE_EXACT ? 1 : 2;
   int best = -1;
@@ -47,6 +50,7 @@ static int instance_cfg(const rk_ctx *ctx, int mode, const uint32_t npat[kNumMCl
       known = t >= 0;
       sum += t;
     }
+    if (known) per_mib[g] = sum;
     if (known && (best < 0 || sum < best_ms)) {
       best = g;
       best_ms = sum;
@@ -59,6 +63,14 @@ static int instance_cfg(const rk_ctx *ctx, int mode, const uint32_t npat[kNumMCl
   if (npat[cmax] && ctx->tune_b[md][cmax][k_class(npat[cmax])] >= 0) return ctx->tune_b[md][cmax][k_class(npat[cmax])];
   return pick_cfg(ctx, mode, std::min(std::max(max_m, 1u), kStreamM));
 }
+
+// A batch scans with one geometry unless its instances' own choices are
+// together faster than the best single one by more than this share of the
+// tuned times: each launch ends with only its last waves at work and the next
+// one starts after it (1,024 instances of up to 16 MiB: 912 us in the two
+// launches of their own choices, 1% faster by the tuned times, and 875 us in
+// the one launch of the single choice).
+constexpr double kOneCfg = 1.05;
 
 static int part_family(int mode, const std::vector<VInst> &vs, const std::vector<uint32_t> &members) {
   if (mode == RK_MODE_EXACT) return kFamExact;
@@ -123,6 +135,7 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
   uint64_t ktot = 0;
   // weight of each length (bytes x patterns) to pick one scan geometry
   std::map<uint32_t, double> mweight;
+  double own_ms = 0, one_ms[kNumTileCfg] = {};  // a batch's tuned times: own choices, one geometry
   for (uint32_t i = 0; i < count; ++i) {
     const rk_instance &I = inst[i];
     if (batch) {
@@ -151,7 +164,11 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     if (batch) {
       uint32_t npat[kNumMClass];
       instance_buckets(I.bytes_host, I.offsets_host, I.k, mode, npat);
-      const int g = instance_cfg(ctx, mode, npat, inst_max_m);
+      double per_mib[kNumTileCfg];
+      const int g = instance_cfg(ctx, mode, npat, inst_max_m, per_mib);
+      const double mib = (double)I.n / (double)(1u << 20);
+      own_ms += per_mib[g] * mib;
+      for (int q = 0; q < kNumTileCfg; ++q) one_ms[q] += per_mib[q] * mib;
       for (size_t vi = v0; vi < P->vinsts.size(); ++vi) P->vinsts[vi].cfg = g;
     }
     ktot += I.k;
@@ -202,11 +219,16 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     return RK_OK;
   }
   // Batch: every instance image holds all its m-buckets (one scan of its
-  // text) and takes the geometry its buckets' tuned timings favour; the
-  // images of one geometry form a part, scanned by one persistent launch over
-  // a work queue of (instance, tile) items, heavier images (more buckets,
-  // longer patterns) first, so that a workgroup keeps one image across
-  // consecutive pops.
+  // text) and takes the geometry its buckets' tuned timings favour, or all
+  // take the one that is best for the batch (kOneCfg); the images of one
+  // geometry form a part, scanned by one persistent launch over a work queue
+  // of (instance, tile) items, heavier images (more buckets, longer patterns)
+  // first, so that a workgroup keeps one image across consecutive pops.
+  if (own_ms > 0 && ctx->tile_cfg < 0) {
+    const int one = (int)(std::min_element(one_ms, one_ms + kNumTileCfg) - one_ms);
+    if (one_ms[one] < kOneCfg * own_ms)
+      for (VInst &v : P->vinsts) v.cfg = one;
+  }
   std::vector<uint32_t> members[kMaxParts];
   for (uint32_t vi = 0; vi < P->vinsts.size(); ++vi) members[P->vinsts[vi].cfg].push_back(vi);
   uint64_t base = 0;

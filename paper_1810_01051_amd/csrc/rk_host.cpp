@@ -172,18 +172,16 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
   for (const PatRef &r : P) dist.push_back(r.key);
   std::sort(dist.begin(), dist.end());
   dist.erase(std::unique(dist.begin(), dist.end()), dist.end());
-  std::vector<uint32_t> tkeys;
-  if (G.screen) {
-    for (uint64_t h : dist) tkeys.push_back((uint32_t)h);
-  } else {
-    // low words of every lazy form the rolling state can take
-    for (uint64_t H : dist) {
-      tkeys.push_back((uint32_t)H);
-      tkeys.push_back((uint32_t)(H + kQ));
-      if (H + 2 * kQ < (1ull << 62) + (1ull << 11)) tkeys.push_back((uint32_t)(H + 2 * kQ));
-    }
-  }
   const bool table = dist.size() > 1;
+  std::vector<uint32_t> tkeys;
+  for (uint64_t H : dist) {
+    if (G.screen) {
+      tkeys.push_back(table ? (uint32_t)H * kMix : (uint32_t)H);
+      continue;
+    }
+    // every lazy form the rolling state can take
+    for (uint64_t s = H; s < (1ull << 62) + (1ull << 11); s += kQ) tkeys.push_back(table ? exact_mix(s) : (uint32_t)s);
+  }
   if (!table) {
     D.kind = G.screen ? kListScreen : kListExact;
     for (size_t j = 0; j < 4; ++j) D.tgt[j] = tkeys[j < tkeys.size() ? j : 0];
@@ -195,10 +193,7 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
     std::vector<uint32_t> test(tb / 4, 0), look(lb / 4, 0);
     D.test_sh = 32 - (uint32_t)__builtin_ctz(tb / 4);
     D.lk_sh = 32 - (uint32_t)__builtin_ctz(lb / 4);
-    for (uint32_t v : tkeys) {
-      if (G.screen) v *= kMix;
-      test[v >> D.test_sh] |= 1u << (v & 31u);
-    }
+    for (uint32_t v : tkeys) test[v >> D.test_sh] |= 1u << (v & 31u);
     for (PatRef &r : P) {
       const uint32_t v = r.lk * kMix;
       r.at = (v >> D.lk_sh) * 32 + (v & 31u);

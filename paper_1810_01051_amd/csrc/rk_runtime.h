@@ -133,8 +133,9 @@ struct PartRun {
   uint64_t slabs = 0;              // scratch offset of the part's slabs [tile][S]
 };
 
-// Scratch of a pass: counters (per-part overflow counts at 8 + 4p, per-part
-// queue cursors at 48 + 4p, then the kTotals hit counters), instance descriptors (single plans),
+// Scratch of a pass: counters (per-part overflow counts at 8 + 4p,
+// then kTotals lines of a hit counter at 0 and per-part queue cursors at
+// 64 + 4p), instance descriptors (single plans),
 // per-tile counts, offsets and overflow lists, scan partials, slabs.
 struct Layout {
   uint64_t T = 0;      // tiles over all parts
@@ -144,7 +145,7 @@ struct Layout {
   uint64_t extra = 0;  // bytes of total beyond what tiles of wg * c bytes would take
   uint64_t bsum = 0;   // work of the tile counts' prefix sum
 };
-constexpr uint32_t kCtrOvf = 8, kCtrQueue = 48, kCtrTotals = 128;
+constexpr uint32_t kCtrOvf = 8, kCtrTotals = 128, kCtrQueue = kCtrTotals + 64;
 constexpr uint32_t kCtrBytes = kCtrTotals + kTotals * kTotalStride;  // read back after a count
 static_assert(kCtrBytes <= 4096, "the context's pinned buffer holds the counters");
 // Hits of a pass, from the counters.

@@ -494,8 +494,15 @@ __device__ __forceinline__ void roll_exact(const uint32_t *w, const uint32_t *d,
   }
 }
 
-// FILTER: the low word of the lazy state in the bucket's bitmap, which holds
-// every lazy form of every key; else compared with the one key's lazy forms.
+// exact_mix in one instruction.
+__device__ __forceinline__ uint32_t exact_mix2(uint64_t s) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  const u16x2 k = {(unsigned short)kExactMixLo, (unsigned short)kExactMixHi};
+  return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, (uint32_t)s), k, (uint32_t)(s >> 32), false);
+}
+
+// FILTER: the lazy state in the bucket's bitmap, which holds every lazy form
+// of every key; else its low word compared with the one key's lazy forms.
 template <int C, bool ANY, bool FILTER, int NT, int OUTK>
 __device__ __forceinline__ void pass_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
                                            uint32_t base, uint32_t fsh, uint64_t &any, Bits<C> &bits) {
@@ -508,8 +515,8 @@ __device__ __forceinline__ void pass_exact(uint32_t mine, OutStream os, uint32_t
     // lazy state s = H + j*q for j in {0,1,2}; the host lists the low words
     const uint32_t lo = (uint32_t)s;
     if constexpr (FILTER) {
-      v[i % kProbeBlock] = lo;
-      t[i % kProbeBlock] = filter_word(base, fsh, lo);
+      v[i % kProbeBlock] = exact_mix2(s);
+      t[i % kProbeBlock] = filter_word(base, fsh, v[i % kProbeBlock]);
       if (i % kProbeBlock == kProbeBlock - 1) {
 #pragma unroll
         for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i + 1 - kProbeBlock + j, filter_bit(t[j], v[j]));
@@ -1056,9 +1063,14 @@ __device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketD
   return ncand;
 }
 
-// Bucket descriptor b of the image at gimg (device memory, wave-uniform), by
-// scalar loads.
+// Scalar loads of what the kernel does not write (p wave-uniform).
 typedef const __attribute__((address_space(4))) uint32_t const_word;
+__device__ __forceinline__ uint32_t const32(const void *p) { return *(const_word *)(uintptr_t)p; }
+__device__ __forceinline__ uint64_t const64(const void *p) {
+  return *(const __attribute__((address_space(4))) uint64_t *)(uintptr_t)p;
+}
+
+// Bucket descriptor b of the image at gimg (device memory).
 __device__ __forceinline__ BucketDesc read_desc(const uint8_t *gimg, uint32_t b) {
   const_word *q = (const_word *)(uintptr_t)(gimg + sizeof(ImageHeader) + 64u * b);
   BucketDesc D;
@@ -1071,11 +1083,6 @@ __device__ __forceinline__ BucketDesc read_desc(const uint8_t *gimg, uint32_t b)
 // Adds a wave's hits to its counter.
 __device__ __forceinline__ void add_total(unsigned long long *totals, uint32_t wave_id, uint64_t hits) {
   atomicAdd(totals + (wave_id % kTotals) * (kTotalStride / 8), (unsigned long long)hits);
-}
-
-// A uniform u64 held in lanes, as a scalar.
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-  return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v);
 }
 
 // ------------------------------------------------------------ the scan kernel
@@ -1111,40 +1118,44 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
   // the run this wave is in: its remaining tiles are tnext, tnext + nw, ...
   uint64_t next_run = blockIdx.x, tnext = 0, tbase = 0, rn = 0;
   const uint8_t *rtext = nullptr;
-  uint32_t tleft = 0, rinst = 0;
-  const uint64_t nlist = p.nitems_dev ? min(p.nitems, (uint64_t)uni(*p.nitems_dev)) : p.nitems;
+  uint32_t tleft = 0, rinst = kNoLink;
+  const uint64_t nlist = p.nitems_dev ? min(p.nitems, (uint64_t)const32(p.nitems_dev)) : p.nitems;
   const uint64_t nruns = p.wave_items ? (nlist + nw - 1) / nw : p.nitems;
 
   // The wave's next tile: 1 (in it), 2 (none in this run, but its image is to
   // be switched to), 0 (no run left).
   auto next_item = [&](Item &it) __attribute__((always_inline)) -> uint32_t {
     if (tleft == 0) {
-      uint64_t r;
-      if (p.queue) {
+      uint64_t r = next_run;
+      if (!p.queue) {
+        next_run += gridDim.x;
+      } else if (next_run == blockIdx.x) {
+        next_run = ~0ull;  // the first run needs no pop
+      } else {
+        // the block's cursor hands out every ncur-th of the other runs
+        const uint32_t ncur = min(gridDim.x, kTotals), c = blockIdx.x % ncur;
+        uint32_t *q = p.queue + c * (kTotalStride / 4);
         uint32_t v = 0;
         if (nw == 1) {
-          if (lane == 0) v = atomicAdd(p.queue, 1u);
-          r = uni(v);
+          if (lane == 0) v = atomicAdd(q, 1u);
         } else {
           wg_barrier();
-          if (tid == 0) popw[0] = atomicAdd(p.queue, 1u);
+          if (tid == 0) popw[0] = atomicAdd(q, 1u);
           wg_barrier();
-          r = uni(popw[0]);
+          v = popw[0];
         }
-      } else {
-        r = next_run;
-        next_run += gridDim.x;
+        r = gridDim.x + (uint64_t)uni(v) * ncur + c;
       }
       if (r >= nruns) return 0;
       uint64_t first;
       if (p.wave_items) {
         const uint64_t q = r * nw + wave;
         tleft = q < nlist ? 1u : 0u;
-        first = tnext = uni64(p.items[q < nlist ? q : nlist - 1]);
+        first = tnext = const64(p.items + (q < nlist ? q : nlist - 1));
       } else {
         uint32_t cnt;
         if (p.items) {
-          const uint64_t v = uni64(p.items[r]);
+          const uint64_t v = const64(p.items + r);
           first = v & kItemTile;
           cnt = (uint32_t)(v >> kItemShift);
         } else {
@@ -1158,13 +1169,15 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
       uint32_t lo = 0, hi = p.ninst;  // instance owning the tile
       while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (uni64(p.inst[mid].tile_base) <= first) lo = mid;
+        if (const64(&p.inst[mid].tile_base) <= first) lo = mid;
         else hi = mid;
       }
-      rinst = lo;
-      rtext = (const uint8_t *)uni64((uint64_t)(uintptr_t)p.inst[lo].text);
-      rn = uni64(p.inst[lo].n);
-      tbase = uni64(p.inst[lo].tile_base);
+      if (lo != rinst) {
+        rinst = lo;
+        rtext = (const uint8_t *)const64(&p.inst[lo].text);
+        rn = const64(&p.inst[lo].n);
+        tbase = const64(&p.inst[lo].tile_base);
+      }
     }
     it.inst = rinst;
     if (tleft == 0) return 2;
@@ -1187,14 +1200,14 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
     if (cur.inst != cur_inst) {
       // the image's leading part goes to LDS; the rest is read in place
       if (nw > 1) wg_barrier();
-      gimg = p.blob + uni(p.inst[cur.inst].img_off);
+      gimg = p.blob + const32(&p.inst[cur.inst].img_off);
       const uint4 *src = (const uint4 *)gimg;
       uint4 *dst = (uint4 *)lds;
-      const uint32_t nq = uni(p.inst[cur.inst].lds_bytes) / 16u;
+      const uint32_t nq = const32(&p.inst[cur.inst].lds_bytes) / 16u;
       for (uint32_t q = tid; q < nq; q += blockDim.x) dst[q] = src[q];
       cur_inst = cur.inst;
       wg_barrier();
-      nb = *(const_word *)(uintptr_t)gimg;  // ImageHeader::nbuckets
+      nb = const32(gimg);  // ImageHeader::nbuckets
     }
     if (st == 2) {
       st = next_item(cur);
@@ -1203,7 +1216,7 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
     }
     uint64_t *slab = nullptr;
     if (p.out)
-      slab = p.direct ? p.out + uni64(p.tile_offsets[cur.gt]) : p.out + (cur.gt - p.tile0) * (uint64_t)p.slab_cap;
+      slab = p.direct ? p.out + const64(p.tile_offsets + cur.gt) : p.out + (cur.gt - p.tile0) * (uint64_t)p.slab_cap;
     const uint32_t cap = p.direct ? 0xFFFFFFFFu : p.slab_cap;
     const uint32_t ns = (uint32_t)min((uint64_t)p.sub, (cur.n - cur.tstart + SUB - 1) / SUB);
     uint32_t tile_hits = 0;
