@@ -309,10 +309,52 @@ __global__ __launch_bounds__(64) void radix_scatter(const uint64_t *in, uint64_t
 // tiles.  Tile t's counts[t] records are its slab (slabs + (t - tile0) * S)
 // when they fit, else those of the collect's rescan, written at tile_off[t]
 // of the direct buffer.
-__device__ __forceinline__ const uint64_t *tile_records(const TileSrc &src, uint64_t t, uint32_t &c) {
-  c = __builtin_amdgcn_readfirstlane(src.counts[t]);
-  return c <= src.S ? src.slabs + (t - src.tile0) * src.S : src.direct + src.tile_off[t];
-}
+//
+// A wave walks its tiles as chunks of up to 64 records of one tile, the counts
+// of 64 tiles loaded at once (a lane each): a round of chunks spans as many
+// tiles as it takes, so that tiles of some hundred records keep as many loads
+// in flight as large ones (a round of one tile's records: 113 us for the
+// scatter of 130 K records in tiles of 100 to 270; see radix_scatter_tiles).
+struct TileChunks {
+  const TileSrc &src;
+  uint64_t t, t1;         // next tile, end
+  uint32_t step, i;       // tiles between this wave's, index of t in batch
+  uint32_t batch;         // the lane's tile's count
+  uint32_t c = 0, j = 0;  // current tile: records, records handed out
+  const uint64_t *in;
+
+  __device__ __forceinline__ TileChunks(const TileSrc &s, uint64_t first, uint64_t end, uint32_t st)
+      : src(s), t(first), t1(end), step(st), in(s.slabs) {
+    load_batch();
+  }
+  __device__ __forceinline__ void load_batch() {
+    const uint64_t q = t + (uint64_t)(threadIdx.x & 63) * step;
+    batch = q < t1 ? src.counts[q] : 0u;
+    i = 0;
+  }
+  // The next N chunks: records r[u] (clamped loads, all unconditional) of the
+  // lanes below lim[u]; false when there are none left.
+  template <int N>
+  __device__ __forceinline__ bool load(uint64_t (&r)[N], uint32_t (&lim)[N]) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      while (j >= c && t < t1) {
+        if (i == 64) load_batch();
+        c = __builtin_amdgcn_readlane(batch, i);
+        in = c <= src.S ? src.slabs + (t - src.tile0) * src.S : src.direct + src.tile_off[t];
+        j = 0;
+        t += step;
+        ++i;
+      }
+      lim[u] = min(c - j, 64u);
+      // (no chunk left: a record that is there, not used)
+      const uint64_t *p = lim[u] ? in + j : src.slabs;
+      r[u] = p[min(threadIdx.x & 63u, max(lim[u], 1u) - 1u)];
+      j += lim[u];
+    }
+    return lim[0] != 0;
+  }
+};
 
 // Four waves per block, wave w taking the block's tiles w, w + 4, ...
 template <int DB>
@@ -321,39 +363,26 @@ __global__ __launch_bounds__(256) void radix_hist_tiles(TileSrc src, uint32_t *g
   __shared__ uint32_t h[ND];
   for (uint32_t i = threadIdx.x; i < ND; i += 256) h[i] = 0;
   __syncthreads();
-  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
   const uint64_t t1 = min(t0 + src.G, src.tile0 + src.ntiles);
-  for (uint64_t t = t0 + w; t < t1; t += 4) {
-    uint32_t c;
-    const uint64_t *in = tile_records(src, t, c);
-    for (uint32_t j = 0; j < c; j += 64 * kRadixR) {
-      uint64_t rec[kRadixR];
+  TileChunks q(src, t0 + w, t1, 4);
+  uint64_t rec[kRadixR];
+  uint32_t lim[kRadixR];
+  while (q.load(rec, lim)) {
 #pragma unroll
-      for (int u = 0; u < kRadixR; ++u) {
-        const uint32_t i = j + u * 64 + lane;
-        rec[u] = i < c ? in[i] : ~0ull;
-      }
-#pragma unroll
-      for (int u = 0; u < kRadixR; ++u)
-        if (rec[u] != ~0ull) atomicAdd(&h[(rec[u] >> kPosBits) & (ND - 1u)], 1u);
-    }
+    for (int u = 0; u < kRadixR; ++u)
+      if (lane < lim[u]) atomicAdd(&h[(rec[u] >> kPosBits) & (ND - 1u)], 1u);
   }
   __syncthreads();
   for (uint32_t d = threadIdx.x; d < ND; d += 256) ghist[(src.blk0 + blockIdx.x) * ND + d] = h[d];
 }
 
 // Positions of the records to their final place (the last and only pass),
-// ranked as in radix_scatter.  The block's tiles are one stream of rounds of
-// 64 * kRadixR records.  A round's loads are unconditional (indices clamped
-// to the tile's last record; the lanes past it are skipped when ranking), so
-// that the compiler can count them, and the next round's loads are issued
-// before the current round is ranked: a wave then waits for its loads once
-// per two rounds' latency instead of draining before every round.
-__device__ __forceinline__ void tiles_load_round(const uint64_t *in, uint32_t j, uint32_t c, uint64_t (&r)[kRadixR]) {
-#pragma unroll
-  for (int u = 0; u < kRadixR; ++u) r[u] = in[min(j + (uint32_t)u * 64u + threadIdx.x, c - 1u)];
-}
+// ranked as in radix_scatter.  The next round's loads are issued before the
+// current round is ranked: a wave then waits for its loads once per two
+// rounds' latency instead of draining before every round.
+constexpr int kTileRound = 8;  // chunks per round
 
 template <int DB>
 __global__ __launch_bounds__(64) void radix_scatter_tiles(TileSrc src, const uint64_t *goff, uint64_t nblk,
@@ -362,6 +391,8 @@ __global__ __launch_bounds__(64) void radix_scatter_tiles(TileSrc src, const uin
   __shared__ uint64_t run[ND];
   __shared__ unsigned long long grp[ND];
   const uint64_t b = src.blk0 + blockIdx.x;
+  const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
+  TileChunks q(src, t0, min(t0 + src.G, src.tile0 + src.ntiles), 1);
   for (uint32_t d = threadIdx.x; d < ND; d += 64) {
     run[d] = goff[b * ND + d];
     grp[d] = 0;
@@ -369,38 +400,14 @@ __global__ __launch_bounds__(64) void radix_scatter_tiles(TileSrc src, const uin
   __syncthreads();
   const uint32_t lane = threadIdx.x;
   const uint64_t me = 1ull << lane, lt_mask = me - 1ull;
-  const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
-  const uint64_t t1 = min(t0 + src.G, src.tile0 + src.ntiles);
-  // the first tile holding records (the round is (t, j): records j.. of tile t)
-  uint64_t t = t0;
-  uint32_t c = 0, j = 0;
-  const uint64_t *in = nullptr;
-  for (; t < t1; ++t) {
-    in = tile_records(src, t, c);
-    if (c) break;
-  }
-  if (t >= t1) return;
-  uint64_t cur[kRadixR];
-  tiles_load_round(in, j, c, cur);
-  for (;;) {
-    // the next round: further in this tile, else the next tile with records
-    uint64_t nt = t;
-    uint32_t nj = j + 64u * kRadixR, nc = c;
-    const uint64_t *nin = in;
-    if (nj >= c) {
-      nj = 0;
-      for (++nt; nt < t1; ++nt) {
-        nin = tile_records(src, nt, nc);
-        if (nc) break;
-      }
-    }
-    const bool more = nt < t1;
-    uint64_t nxt[kRadixR];
-    // after the last round this reloads the current one (not used)
-    tiles_load_round(more ? nin : in, more ? nj : j, more ? nc : c, nxt);
+  uint64_t cur[kTileRound], nxt[kTileRound];
+  uint32_t clim[kTileRound], nlim[kTileRound];
+  bool more = q.load(cur, clim);
+  while (more) {
+    more = q.load(nxt, nlim);
 #pragma unroll
-    for (int u = 0; u < kRadixR; ++u) {
-      if (j + (uint32_t)u * 64u + lane >= c) continue;
+    for (int u = 0; u < kTileRound; ++u) {
+      if (lane >= clim[u]) continue;
       const uint64_t rec = cur[u];
       const uint32_t dg = (uint32_t)(rec >> kPosBits) & (ND - 1u);
       atomicOr(&grp[dg], (unsigned long long)me);
@@ -412,13 +419,11 @@ __global__ __launch_bounds__(64) void radix_scatter_tiles(TileSrc src, const uin
         grp[dg] = 0;
       }
     }
-    if (!more) break;
 #pragma unroll
-    for (int u = 0; u < kRadixR; ++u) cur[u] = nxt[u];
-    t = nt;
-    j = nj;
-    c = nc;
-    in = nin;
+    for (int u = 0; u < kTileRound; ++u) {
+      cur[u] = nxt[u];
+      clim[u] = nlim[u];
+    }
   }
 }
 
@@ -524,6 +529,58 @@ __global__ __launch_bounds__(256) void digit_block_starts(const uint32_t *__rest
   }
 }
 
+// All of it in one block, for up to kDigitOne blocks (one chunk): two launches
+// less, for histograms that a block reads in a few microseconds.
+constexpr uint32_t kDigitOne = 32;
+
+__global__ __launch_bounds__(256) void digit_starts_one(const uint32_t *__restrict__ h, uint32_t nblk, uint32_t nd,
+                                                        uint64_t *__restrict__ goff, uint32_t k, uint64_t n,
+                                                        uint64_t *__restrict__ offsets) {
+  constexpr uint32_t kPer = 8;  // digits per thread of the totals' scan (256 * 8 = 2048)
+  __shared__ uint64_t start[256 * kPer];
+  __shared__ uint64_t wsum[4];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t d = threadIdx.x; d < 256 * kPer; d += 256) {
+    uint64_t t = 0;
+    if (d < nd) {
+#pragma unroll 8
+      for (uint32_t b = 0; b < nblk; ++b) t += h[b * nd + d];
+    }
+    start[d] = t;
+  }
+  __syncthreads();
+  uint64_t v[kPer], x = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    v[i] = start[threadIdx.x * kPer + i];
+    x += v[i];
+  }
+  const uint64_t mine = x;
+  for (int sh = 1; sh < 64; sh <<= 1) {
+    const uint64_t y = __shfl_up(x, sh, 64);
+    if (lane >= (uint32_t)sh) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  uint64_t before = x - mine;
+  for (uint32_t i = 0; i < wave; ++i) before += wsum[i];
+#pragma unroll
+  for (uint32_t i = 0; i < kPer; ++i) {
+    start[threadIdx.x * kPer + i] = before;
+    before += v[i];
+  }
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j <= k; j += 256) offsets[j] = j < k ? start[j] : n;
+  for (uint32_t d = threadIdx.x; d < nd; d += 256) {
+    uint64_t run = start[d];
+#pragma unroll 8
+    for (uint32_t b = 0; b < nblk; ++b) {
+      goff[b * nd + d] = run;
+      run += h[b * nd + d];
+    }
+  }
+}
+
 __global__ void pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets) {
   const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j > k) return;
@@ -617,6 +674,10 @@ uint64_t radix_blocks(uint64_t n) { return (n + kRadixBlock - 1) / kRadixBlock; 
 static hipError_t digit_offsets(const uint32_t *h, uint64_t nblk, uint32_t nd, uint64_t *goff, uint8_t *cs,
                                 uint32_t k, uint64_t n, uint64_t *offsets, hipStream_t s) {
   if (nd > 2048 || k > nd) return hipErrorInvalidValue;
+  if (nblk <= kDigitOne) {
+    hipLaunchKernelGGL(digit_starts_one, dim3(1), dim3(256), 0, s, h, (uint32_t)nblk, nd, goff, k, n, offsets);
+    return hipGetLastError();
+  }
   const uint64_t nchunk = (nblk + kDigitChunk - 1) / kDigitChunk;
   uint32_t *csum = (uint32_t *)cs;
   uint64_t *crel = (uint64_t *)(cs + ((nchunk * nd * 4 + 255) & ~255ull));

@@ -93,24 +93,24 @@ static uint32_t pick_sub(int cfg, uint64_t units) {
 // Threads per block of the general kernel: the waves of a block share the
 // image in LDS, so larger images want larger blocks for as many resident
 // waves; smaller blocks cost no meeting of their waves (meet: several
-// instances), and take the tie.
-static uint32_t pick_block(int cfg, int fam, uint32_t img_cap, bool meet, uint32_t *waves_per_cu = nullptr) {
-  if (waves_per_cu) *waves_per_cu = 0;
+// instances), and take the tie.  Also the waves then resident per CU, and
+// those of one-wave blocks (a rescan of several instances runs those).
+static void pick_block(int cfg, int fam, uint32_t img_cap, bool meet, Part *pt) {
+  pt->block = 64;
+  pt->waves = pt->waves1 = 4;
   ScanFit f;
-  if (scan_fit(cfg, fam, 0, 64, &f) != hipSuccess || f.blocks < 1) return 256;
+  if (scan_fit(cfg, fam, 0, 64, &f) != hipSuccess || f.blocks < 1) return;
   const uint32_t wmax = (uint32_t)f.blocks;
-  uint32_t best = 64, best_waves = 0;
+  uint32_t best_waves = 0;
   for (uint32_t nw = 1; nw * 64 <= f.max_block; nw *= 2) {
     const uint32_t lds = img_cap + 16 + nw * f.wave_lds;
-    const uint32_t blocks = std::min(kLdsPerCU / ((lds + 1279) / 1280 * 1280), wmax / nw);
-    const uint32_t waves = blocks * nw;
+    const uint32_t waves = nw * std::min(kLdsPerCU / ((lds + 1279) / 1280 * 1280), wmax / nw);
+    if (nw == 1) pt->waves1 = std::max(waves, 1u);
     if (meet ? waves * 4 > best_waves * 5 : waves > best_waves) {
-      best = nw * 64;
-      best_waves = waves;
+      pt->block = nw * 64;
+      pt->waves = best_waves = waves;
     }
   }
-  if (waves_per_cu) *waves_per_cu = best_waves;
-  return best;
 }
 
 // A pattern set whose image leaves fewer than kFullWaves waves per CU resident
@@ -206,13 +206,14 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     pt.fam = P->fam;
     pt.img_cap = P->img_cap;
     pt.ninst = (uint32_t)P->vinsts.size();
-    uint32_t waves = 0, waves3 = 0;
-    pt.block = pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1, &waves);
-    if (ctx->tile_cfg < 0 && !P->list1 && waves < kFullWaves) {
-      const uint32_t b3 = pick_block(kNarrowCfg, pt.fam, pt.img_cap, pt.ninst > 1, &waves3);
-      if (waves3 > waves) {
-        P->cfg = pt.cfg = kNarrowCfg;
-        pt.block = b3;
+    pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1, &pt);
+    if (ctx->tile_cfg < 0 && !P->list1 && pt.waves < kFullWaves) {
+      Part narrow = pt;
+      narrow.cfg = kNarrowCfg;
+      pick_block(kNarrowCfg, pt.fam, pt.img_cap, pt.ninst > 1, &narrow);
+      if (narrow.waves > pt.waves) {
+        pt = narrow;
+        P->cfg = kNarrowCfg;
       }
     }
     P->parts.assign(1, pt);
@@ -246,7 +247,7 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
     uint64_t units = 0;
     for (uint32_t vi : members[c]) units += (P->insts[P->vinsts[vi].src].n + SUB - 1) / SUB;
     pt.sub = pick_sub(c, units);
-    pt.block = pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1);
+    pick_block(pt.cfg, pt.fam, pt.img_cap, pt.ninst > 1, &pt);
     const uint32_t W = pt.sub * SUB;
     std::vector<uint64_t> first(members[c].size());
     for (size_t q = 0; q < members[c].size(); ++q) {
@@ -481,11 +482,9 @@ hipError_t prof_end(rk_ctx *ctx, hipStream_t s, int slot) {
   return hipEventRecord(ctx->prof_events[slot].b, s);
 }
 
-static uint32_t scan_grid(rk_ctx *ctx, int cfg, int fam, uint32_t img_cap, uint32_t block, uint64_t nruns) {
-  if (ctx->grid) return (uint32_t)std::min<uint64_t>(ctx->grid, std::max<uint64_t>(nruns, 1));
-  ScanFit f;
-  if (scan_fit(cfg, fam, img_cap, block, &f) != hipSuccess || f.blocks < 1) f.blocks = 1;
-  const uint64_t g = (uint64_t)ctx->num_cu * (uint64_t)f.blocks;
+// Blocks of a general-kernel launch: those of `waves` waves per CU.
+static uint32_t scan_grid(const rk_ctx *ctx, uint32_t waves, uint32_t block, uint64_t nruns) {
+  const uint64_t g = ctx->grid ? ctx->grid : (uint64_t)ctx->num_cu * std::max(waves * 64 / block, 1u);
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, nruns));
 }
 
@@ -617,7 +616,7 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
       p.out = (uint64_t *)(sc + r.slabs);
       p.pid_counts = (unsigned long long *)counts;
       if (use_queue) p.queue = (uint32_t *)(sc + L.ctr + kCtrQueue) + pi;
-      const uint32_t grid = scan_grid(ctx, pt.cfg, pt.fam, pt.img_cap, pt.block, p.nitems);
+      const uint32_t grid = scan_grid(ctx, pt.waves, pt.block, p.nitems);
       e = prof_begin(ctx, s, 0, &slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
       e = launch_scan(pt.cfg, pt.fam, p, grid, pt.block, s);
@@ -729,7 +728,7 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
   WorkLayout WL = work_layout(total, k);
   uint64_t *target = k == 1 ? positions : (uint64_t *)((uint8_t *)work + WL.a);
   // Dense hits (at least 64 per tile on average) up to 2,048 patterns: the
-  // sort reads the records from the slabs, G tiles per radix block (8,192 to
+  // sort reads the records from the slabs, G tiles per radix block (2,048 to
   // 32,768 records), and the compaction is skipped; the rescan below still
   // writes the overflowed tiles' records to the work buffer.
   TileSrc tsrc[kMaxParts];
@@ -741,8 +740,10 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
     while ((1u << bits) < k) ++bits;
     // records per block: 32,768 once there are 1,024 such blocks (longer runs
     // per digit and block make the scatter's writes fuller lines), down to
-    // 8,192 for fewer hits (blocks enough to fill the chip)
-    const uint64_t rb = std::min<uint64_t>(32768, std::max<uint64_t>(8192, total / 1024));
+    // 2,048 to 8,192 for fewer hits (more blocks at work; a block's histogram
+    // and its scan then cost about as much as its records)
+    const uint64_t least = std::min<uint64_t>(8192, 8ull << bits);
+    const uint64_t rb = std::min<uint64_t>(32768, std::max<uint64_t>(least, total / 1024));
     const uint32_t G = (uint32_t)std::max<uint64_t>(1, (rb * L.T + total - 1) / total);
     for (const PartRun &r : L.parts) {
       TileSrc &t = tsrc[ntsrc++];
@@ -796,7 +797,7 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
       p.direct = 1;
       // the waves of a block take tiles of their own: one instance, or one wave
       const uint32_t block = pt.ninst > 1 ? 64 : pt.block;
-      const uint32_t grid = scan_grid(ctx, pt.cfg, pt.fam, pt.img_cap, block, (r.ntiles * 64 + block - 1) / block);
+      const uint32_t grid = scan_grid(ctx, block == 64 ? pt.waves1 : pt.waves, block, (r.ntiles * 64 + block - 1) / block);
       e = prof_begin(ctx, s, 1, &slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
       e = launch_scan(pt.cfg, pt.fam, p, grid, block, s);
@@ -911,7 +912,7 @@ extern "C" rk_status rk_scan_dump(rk_ctx *ctx, const uint8_t *text, uint64_t n, 
   p.dump_out = out;
   p.dump_stride = stride;
   p.dump_cap = cap;
-  const uint32_t grid = scan_grid(ctx, cfg, kFamExact, p.img_cap, 64, I.ntiles);
+  const uint32_t grid = scan_grid(ctx, 4, 64, I.ntiles);
   e = launch_scan(cfg, kFamExact, p, grid, 64, st);
   if (e != hipSuccess) return hip_err(ctx, e, "dump launch");
   e = hipStreamSynchronize(st);

@@ -60,6 +60,7 @@ struct Part {
   uint64_t tile0 = 0, ntiles = 0;  // its tiles in the plan's tile numbering (batch)
   uint32_t sub = 1;                // sub-tiles per tile (batch)
   uint32_t block = 64;             // threads per block of its scan
+  uint32_t waves = 4, waves1 = 4;  // waves resident per CU, and those of one-wave blocks
 };
 
 struct RealInst {

@@ -690,8 +690,6 @@ rk_status rk_server_create(rk_ctx *ctx, const rk_server_cfg *cfg_in, rk_server *
     delete S;
     return set_err(ctx, st, "server context");
   }
-  // fixed persistent grid: no occupancy query while a stream is being captured
-  S->ctx->grid = (uint32_t)S->ctx->num_cu * 4;
   // staging records per tile: the plan default (one per 16 text bytes for
   // pattern sets), since served requests are hit-dense and a tile whose
   // records overflow is scanned a second time

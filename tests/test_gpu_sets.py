@@ -100,3 +100,26 @@ def test_batch_of_large_and_small_sets(ctx, rk, mode):
             for j in range(len(s)):
                 assert np.array_equal(np.asarray(per[i][j]).astype(np.uint64), ref[j]), (i, j)
     bp.close()
+
+
+@pytest.mark.parametrize("k", [2, 200, 257, 700, 2048])
+@pytest.mark.parametrize("n", [700, 69632, 600011, 5 << 20])
+def test_dense_hits_sorted_from_small_tiles(ctx, rk, k, n):
+    """Hundreds of hits per tile, so the sort reads the tiles' slabs: rounds of
+    chunks over tiles of different fill, tiles without hits, tiles that
+    overflowed their slab, fewer and more than 64 tiles and 32 sort blocks,
+    every digit width."""
+    g = rkgen.rng(82, k)
+    text = rkgen.iid_text(g, n, rkgen.ACGT)
+    for o in range(0, n - 9000, 50021):
+        text[o:o + 9000] = ord("C")  # a hit at every offset
+        text[max(0, o - 6000):o] = ord("x")  # no hit at all
+    pats = [b"CCCC"]
+    while len(pats) < k:
+        m = int(g.integers(4, 7)) if len(pats) < 120 else 12
+        pats.append(rkgen.ACGT[g.integers(0, 4, size=m)].tobytes())
+    ref = oracle.search(text, pats, threads=4)
+    assert n < 50000 or int(ref[0][-1]) > n // 32
+    off, pos = search(ctx, rk, text, pats, "screen")
+    assert off.tolist() == ref[0].tolist()
+    assert (pos == ref[1]).all()
