@@ -492,7 +492,8 @@ static uint32_t scan_grid(const rk_ctx *ctx, uint32_t waves, uint32_t block, uin
 constexpr uint32_t kListGridMul = 32;
 
 // Fills ScanParams common to the count pass and the rescan of part pi.
-static void base_params(const rk_plan *plan, const Layout &L, uint32_t pi, uint8_t *sc, ScanParams &p) {
+static void base_params(const rk_plan *plan, const Layout &L, uint32_t pi, uint8_t *sc, const uint8_t *text, uint64_t n,
+                        ScanParams &p) {
   memset(&p, 0, sizeof p);
   const Part &pt = plan->parts[pi];
   const PartRun &r = L.parts[pi];
@@ -507,17 +508,22 @@ static void base_params(const rk_plan *plan, const Layout &L, uint32_t pi, uint8
   p.inst_tiles = L.T1;
   p.inst_runs = (L.T1 + p.run - 1) / p.run;
   p.tile0 = r.tile0;
-  p.totals = (unsigned long long *)(sc + L.ctr + kCtrTotals);
-  p.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf) + pi;
-  p.ovf_list = (uint64_t *)(sc + L.ovf) + r.tile0;  // the part's own overflow list
+  if (!plan->batch && pt.ninst == 1) {
+    p.inst = nullptr;
+    p.one.text = text;
+    p.one.n = n;
+    p.one.ntiles = L.T1;
+    p.one.img_off = plan->vinsts[0].img_off;
+    p.one.lds_bytes = plan->vinsts[0].lds_bytes;
+  }
 }
 
-// Instance descriptors of a single-text plan's text (one per virtual
-// instance) into the scratch; nothing for batch plans, whose descriptors
-// live in the plan.
+// Instance descriptors of a single-text plan of several virtual instances into
+// the scratch; nothing for one instance, whose descriptor goes with the
+// launch, and for batch plans, whose descriptors live in the plan.
 static hipError_t upload_insts(const rk_plan *plan, const Layout &L, uint8_t *sc, const uint8_t *text, uint64_t n,
                                hipStream_t s) {
-  if (plan->batch || plan->vinsts.empty()) return hipSuccess;
+  if (plan->batch || plan->vinsts.size() < 2) return hipSuccess;
   std::vector<InstDesc> d(plan->vinsts.size());
   for (size_t i = 0; i < d.size(); ++i) {
     memset(&d[i], 0, sizeof(InstDesc));
@@ -533,7 +539,7 @@ static hipError_t upload_insts(const rk_plan *plan, const Layout &L, uint8_t *sc
 }
 
 rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, uint64_t n, void *scratch,
-                        uint64_t scratch_bytes, uint64_t *counts, hipStream_t s) {
+                        uint64_t scratch_bytes, uint64_t *counts, uint64_t *host, hipStream_t s) {
   if (plan->device != ctx->device) return set_err(ctx, RK_EINVAL, "plan belongs to another device");
   if (plan->batch) {
     if (text) return set_err(ctx, RK_EINVAL, "batch plans take text_dev = NULL");
@@ -552,22 +558,25 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
   hipError_t e;
   const bool use_queue = ctx->queue == 1 || (ctx->queue == -1 && plan->batch);
   // one text, one bucket with register targets: the single-bucket kernel,
-  // which takes the text itself (the general kernel reads it through the
-  // instance descriptors, uploaded here for it and by a rescan)
+  // which takes the text itself (the general kernel reads that of several
+  // instances through their descriptors, uploaded here for it and by a rescan)
   const bool list = plan->list1 && !use_queue;
   if (!list) {
     e = upload_insts(plan, L, sc, text, n, s);
     if (e != hipSuccess) return hip_err(ctx, e, "instance upload");
   }
-  e = launch_fill_u32((uint32_t *)(sc + L.ctr), kCtrBytes / 4, 0u, s);
-  if (e != hipSuccess) return hip_err(ctx, e, "counter reset");
+  if (use_queue) {  // (without one the scan resets the overflow count itself)
+    e = launch_fill_u32((uint32_t *)(sc + L.ctr), kCtrBytes / 4, 0u, s);
+    if (e != hipSuccess) return hip_err(ctx, e, "counter reset");
+  }
   if (counts) {
     e = launch_fill_u32((uint32_t *)counts, 2ull * plan->k_total, 0u, s);
     if (e != hipSuccess) return hip_err(ctx, e, "per-pattern count reset");
   }
-  if (L.T == 0) return RK_OK;
   int slot;
-  if (list) {
+  if (L.T == 0) {
+    // no tile: the total below is zero
+  } else if (list) {
     const PartRun &r = L.parts[0];
     ListParams lp;
     memset(&lp, 0, sizeof lp);
@@ -583,9 +592,8 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     lp.rec1 = plan->list_rec1;
     lp.tile_counts = (uint32_t *)(sc + L.counts);
     lp.out = (uint64_t *)(sc + r.slabs);
-    lp.totals = (unsigned long long *)(sc + L.ctr + kCtrTotals);
     lp.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf);
-    lp.ovf_list = (uint64_t *)(sc + L.ovf);
+    lp.done = (uint32_t *)(sc + L.ctr + kCtrDone);
     lp.pid_counts = (unsigned long long *)counts;
     // The grid is kListGridMul times what is resident at once: blocks of a
     // few tiles each, dispatched as others finish, scan faster than one
@@ -610,11 +618,13 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
       const PartRun &r = L.parts[pi];
       if (r.ntiles == 0) continue;
       ScanParams p;
-      base_params(plan, L, pi, sc, p);
+      base_params(plan, L, pi, sc, text, n, p);
       p.items = plan->batch ? plan->items_dev + pt.item0 : nullptr;
       p.nitems = plan->batch ? pt.nitems : p.inst_runs * pt.ninst;
       p.out = (uint64_t *)(sc + r.slabs);
       p.pid_counts = (unsigned long long *)counts;
+      p.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf) + pi;
+      p.done = (uint32_t *)(sc + L.ctr + kCtrDone);
       if (use_queue) p.queue = (uint32_t *)(sc + L.ctr + kCtrQueue) + pi;
       const uint32_t grid = scan_grid(ctx, pt.waves, pt.block, p.nitems);
       e = prof_begin(ctx, s, 0, &slot);
@@ -625,6 +635,27 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
     }
   }
+  // the collect's tile offsets, with the total and the overflowed tiles
+  TileTotals tt;
+  memset(&tt, 0, sizeof tt);
+  tt.nparts = (uint32_t)L.parts.size();
+  for (uint32_t pi = 0; pi < tt.nparts; ++pi) {
+    tt.S[pi] = L.parts[pi].S;
+    tt.tile0[pi] = L.parts[pi].tile0;
+  }
+  tt.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf);
+  tt.ovf_list = (uint64_t *)(sc + L.ovf);
+  tt.ctr = (uint64_t *)(sc + L.ctr);
+  tt.host = host;
+  tt.done = (uint32_t *)(sc + L.ctr + kCtrDone);
+  host[kHostTotal] = kNoTotal;
+  e = prof_begin(ctx, s, 2, &slot);
+  if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
+  e = launch_tile_scan((const uint32_t *)(sc + L.counts), L.T, (uint64_t *)(sc + L.offsets), (uint64_t *)(sc + L.bsum),
+                       tt, s);
+  if (e != hipSuccess) return hip_err(ctx, e, "tile scan");
+  e = prof_end(ctx, s, slot);
+  if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
   CountMemo &mm = ctx->memo[ctx->memo_next++ % 16];
   mm.scratch = scratch;
   mm.plan = plan;
@@ -634,25 +665,27 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
   return RK_OK;
 }
 
-rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total) {
-  hipError_t e = hipMemcpyAsync(ctx->pinned, scratch, kCtrBytes, hipMemcpyDeviceToHost, s);
-  if (e != hipSuccess) return hip_err(ctx, e, "total readback");
-  // A count pass of a few GiB takes about a millisecond, less than a blocking
-  // wait adds in wake-up latency: the stream is polled for up to kSpinUs,
-  // then waited for.
+// The total is read as soon as it is there, which costs less than asking for
+// the stream (the count of a 1 MiB text: 18 against 32 us).  Beyond kSpinUs, far
+// more than a count pass of a few GiB takes and no less than a blocking wait
+// adds in wake-up latency, the stream is waited for.
+hipError_t wait_total(rk_ctx *ctx, hipStream_t s) {
   constexpr int64_t kSpinUs = 4000;
   const auto t0 = std::chrono::steady_clock::now();
-  for (;;) {
-    e = hipStreamQuery(s);
-    if (e != hipErrorNotReady) break;
+  while (__atomic_load_n(&ctx->pinned[kHostTotal], __ATOMIC_ACQUIRE) == kNoTotal)
     if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) {
-      e = hipStreamSynchronize(s);
-      break;
+      const hipError_t e = hipStreamSynchronize(s);
+      if (e != hipSuccess) return e;
+      return ctx->pinned[kHostTotal] == kNoTotal ? hipErrorUnknown : hipSuccess;
     }
-  }
+  return hipSuccess;
+}
+
+rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total) {
+  const hipError_t e = wait_total(ctx, s);
   if (e != hipSuccess) return hip_err(ctx, e, "scan");
-  *total = hit_total(ctx->pinned);
-  const uint32_t ovf = ovf_total(ctx->pinned);
+  *total = ctx->pinned[kHostTotal];
+  const uint32_t ovf = (uint32_t)ctx->pinned[kHostOvf];
   for (auto &mm : ctx->memo)
     if (mm.scratch == scratch && mm.plan == plan) {
       mm.total = *total;
@@ -680,10 +713,10 @@ rk_status collect_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text,
       overflow = mm.overflow;
     }
   if (total == ~0ull) {
-    hipError_t e = hipMemcpyAsync(ctx->pinned, sc + L.ctr, kCtrBytes, hipMemcpyDeviceToHost, s);
+    hipError_t e = hipMemcpyAsync(ctx->pinned, sc + L.ctr, kCtrHead, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_err(ctx, e, "total readback");
-    total = hit_total(ctx->pinned);
+    total = ctx->pinned[0];
   }
   return collect_enqueue_known(ctx, plan, text, n, scratch, scratch_bytes, work, work_bytes, offsets, positions, capacity,
                                total, overflow, s);
@@ -722,9 +755,7 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
     if (e != hipSuccess) return hip_err(ctx, e, "offsets");
     return hip_err_or_ok(ctx, prof_end(ctx, s, slot));
   }
-  uint64_t *tile_off = (uint64_t *)(sc + L.offsets);
-  e = launch_exclusive_scan((const uint32_t *)(sc + L.counts), L.T, tile_off, (uint64_t *)(sc + L.bsum), nullptr, s);
-  if (e != hipSuccess) return hip_err(ctx, e, "tile scan");
+  const uint64_t *tile_off = (const uint64_t *)(sc + L.offsets);  // from the count pass
   WorkLayout WL = work_layout(total, k);
   uint64_t *target = k == 1 ? positions : (uint64_t *)((uint8_t *)work + WL.a);
   // Dense hits (at least 64 per tile on average) up to 2,048 patterns: the
@@ -775,8 +806,8 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
   // rescan of tiles whose hits did not fit their slab, part by part (each
   // part's count read on the device; skipped when the count pass reported none)
   if (overflow != 0) {
-    // the rescan runs the general kernel, which reads the text through the
-    // instance descriptors (a single-bucket count did not upload them)
+    // the rescan runs the general kernel (the single-bucket count of several
+    // instances uploaded no descriptors)
     if (!plan->batch && !plan->vinsts.empty()) {
       if (!text) return set_err(ctx, RK_EINVAL, "the rescan of overflowed tiles needs text_dev");
       e = upload_insts(plan, L, sc, text, n, s);
@@ -787,11 +818,11 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
       const PartRun &r = L.parts[pi];
       if (r.ntiles == 0) continue;
       ScanParams p;
-      base_params(plan, L, pi, sc, p);
-      p.items = p.ovf_list;
+      base_params(plan, L, pi, sc, text, n, p);
+      p.items = (const uint64_t *)(sc + L.ovf) + r.tile0;
       p.wave_items = 1;
       p.nitems = r.ntiles;
-      p.nitems_dev = p.ovf_count;
+      p.nitems_dev = (const uint32_t *)(sc + L.ctr + kCtrOvf) + pi;
       p.out = target;
       p.tile_offsets = tile_off;
       p.direct = 1;

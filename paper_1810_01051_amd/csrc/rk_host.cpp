@@ -493,7 +493,7 @@ rk_status rk_ctx_create(int device, uint64_t d, uint64_t q, rk_ctx **out) {
   }
   c->num_cu = prop.multiProcessorCount;
   c->arch = prop.gcnArchName;
-  if (hipHostMalloc((void **)&c->pinned, 4096, hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void **)&c->pinned, 4096, hipHostMallocCoherent) != hipSuccess) {
     delete c;
     return RK_ENOMEM;
   }
@@ -627,7 +627,7 @@ rk_status rk_count(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, uint64
   if (!ctx || !plan || !total_host) return RK_EINVAL;
   hipStream_t st = (hipStream_t)s;
   uint64_t total = 0;
-  rk_status r = count_enqueue(ctx, plan, text, n, scratch, scratch_bytes, counts_dev, st);
+  rk_status r = count_enqueue(ctx, plan, text, n, scratch, scratch_bytes, counts_dev, ctx->pinned, st);
   if (r != RK_OK) return r;
   r = count_finish(ctx, plan, scratch, st, &total);
   if (r != RK_OK) return r;

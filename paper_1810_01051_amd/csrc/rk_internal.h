@@ -132,14 +132,14 @@ struct InstDesc {
 };
 static_assert(sizeof(InstDesc) == 48, "instance descriptor is 48 bytes");
 
-// The count pass adds up its hits in kTotals counters of a 128-byte line each
-// (a wave's hits once, at its end): additions to one address are served one
-// after the other, about 7 ns each, which a counter per pass, added to by
-// every tile, made the bound of dense scans (a 1 GiB text's 61,681 tiles,
-// twice each: 0.8 ms).
-// The work queue of a batch has as many cursors for the same reason (15 ns a
-// pop: with one cursor 1,024 instances of 2 GB spent 0.5 of 1.0 ms on pops).
-constexpr uint32_t kTotals = 16, kTotalStride = 128;
+// The work queue of a batch has kCursors cursors on a 128-byte line each:
+// additions to one address are served one after the other, 15 ns a pop (with
+// one cursor 1,024 instances of 2 GB spent 0.5 of 1.0 ms on pops).  For the
+// same reason the scan adds its hits to no counter: the prefix sum over the
+// tiles' counts, which the collect needs anyway, yields the total (every tile
+// adding to one counter was the bound of dense scans, 0.8 ms for the 61,681
+// tiles of a 1 GiB text).
+constexpr uint32_t kCursors = 16, kCursorStride = 128;
 
 // A run of consecutive tiles of one instance in a work list.
 constexpr uint32_t kItemShift = 48;
@@ -147,7 +147,7 @@ constexpr uint64_t kItemTile = (1ull << kItemShift) - 1;
 
 // Kernel parameters of the scan (passed by value).
 struct ScanParams {
-  const InstDesc *inst;
+  const InstDesc *inst;       // nullptr: one instance, in `one`
   uint32_t ninst;
   uint32_t img_cap;           // LDS bytes reserved for an instance image
   const uint8_t *blob;        // instance images
@@ -164,15 +164,14 @@ struct ScanParams {
   const uint64_t *tile_offsets; // direct mode: first output slot of each tile
   uint32_t slab_cap;
   uint32_t direct;            // 1: rescan writing every hit at tile_offsets[tile]
-  unsigned long long *totals; // count mode: hits over all tiles, in kTotals counters
-  uint32_t *ovf_count;        // count mode: number of tiles with more hits than slab_cap
-  uint64_t *ovf_list;         // count mode: those tiles' global ids
-  uint32_t *queue;            // first of kTotals work-queue cursors, kTotalStride apart (nullptr: static striding)
+  uint32_t *ovf_count, *done; // count mode without queue: set to zero (the tile scan's counters)
+  uint32_t *queue;            // first of kCursors work-queue cursors, kCursorStride apart (nullptr: static striding)
   uint64_t *dump_out;         // kDump buckets: destination of sampled hashes
   uint64_t dump_stride;
   uint64_t dump_cap;
   unsigned long long *pid_counts; // count mode, optional: hits per global pattern id
   uint64_t tile0;             // count mode: global id of the first tile of out's slabs
+  InstDesc one;               // inst == nullptr: the only instance
 };
 
 // Kernel parameters of the single-bucket scan (one text, one bucket whose set
@@ -190,9 +189,7 @@ struct ListParams {
   uint64_t rec1;              // record of the bucket's one key
   uint32_t *tile_counts;
   uint64_t *out;              // slabs [tile][slab_cap]
-  unsigned long long *totals; // hits, in kTotals counters
-  uint32_t *ovf_count;
-  uint64_t *ovf_list;
+  uint32_t *ovf_count, *done; // set to zero
   uint64_t *dump_out;         // kDump bucket: destination of sampled hashes (no counts then)
   uint64_t dump_stride;
   uint64_t dump_cap;

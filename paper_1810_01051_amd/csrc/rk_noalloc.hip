@@ -69,7 +69,7 @@ extern "C" rk_status rk_search_static(rk_ctx *ctx, const rk_plan *plan, const ui
   if (L.total - L.extra > kStaticScratchBytes || L.extra > kStaticExtra)
     return set_err(ctx, RK_ENOSPACE, "search needs %llu bytes of scratch, the static array holds %llu",
                    (unsigned long long)L.total, (unsigned long long)kStaticScratchBytes);
-  r = count_enqueue(ctx, plan, text_dev, n, base, L.total, nullptr, st);
+  r = count_enqueue(ctx, plan, text_dev, n, base, L.total, nullptr, ctx->pinned, st);
   if (r != RK_OK) return r;
   uint64_t total = 0;
   r = count_finish(ctx, plan, base, st, &total);

@@ -181,7 +181,9 @@ __device__ __forceinline__ uint32_t flag_mask(const uint8_t *flags, uint64_t i, 
 // Count of set flags per block of kFlagBlock.  Bound by the read of the
 // flags: 16 bytes per lane, a wave's loads contiguous (320 MB: 0.07 ms,
 // 0.29 ms with one byte per lane and load).
-__global__ __launch_bounds__(kFlagWG) void flag_counts(const uint8_t *flags, uint64_t nf, uint32_t *counts) {
+__global__ __launch_bounds__(kFlagWG) void flag_counts(const uint8_t *flags, uint64_t nf, uint32_t *counts,
+                                                       uint32_t *done) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;  // of the scan that follows
   const uint64_t base = (uint64_t)blockIdx.x * kFlagBlock + 16u * threadIdx.x;
   uint32_t c = 0;
 #pragma unroll
@@ -302,14 +304,14 @@ extern "C" rk_status rk_paper_positions(rk_ctx *ctx, const uint8_t *flags_dev, u
   uint32_t *counts = (uint32_t *)sc;
   uint64_t *offs = (uint64_t *)(sc + (nb * 4 + 255) / 256 * 256);
   uint64_t *tmp = (uint64_t *)((uint8_t *)offs + (nb * 8 + 255) / 256 * 256);
-  uint64_t *total_dev = (uint64_t *)((uint8_t *)tmp + scan_tmp_words(nb) * 8);
-  hipLaunchKernelGGL(flag_counts, dim3((uint32_t)nb), dim3(kFlagWG), 0, hs, flags_dev, nflags, counts);
+  uint32_t *done = (uint32_t *)((uint8_t *)tmp + scan_tmp_words(nb) * 8);
+  ctx->pinned[kHostTotal] = kNoTotal;
+  hipLaunchKernelGGL(flag_counts, dim3((uint32_t)nb), dim3(kFlagWG), 0, hs, flags_dev, nflags, counts, done);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = launch_exclusive_scan(counts, nb, offs, tmp, total_dev, hs);
-  if (e == hipSuccess) e = hipMemcpyAsync(ctx->pinned, total_dev, 8, hipMemcpyDeviceToHost, hs);
-  if (e == hipSuccess) e = hipStreamSynchronize(hs);
+  if (e == hipSuccess) e = launch_exclusive_scan(counts, nb, offs, tmp, ctx->pinned, done, hs);
+  if (e == hipSuccess) e = wait_total(ctx, hs);
   if (e != hipSuccess) return hip_err(ctx, e, "paper positions count");
-  const uint64_t total = ctx->pinned[0];
+  const uint64_t total = ctx->pinned[kHostTotal];
   *total_host = total;
   if (total > capacity) return set_err(ctx, RK_ENOSPACE, "positions capacity %llu < %llu matches",
                                        (unsigned long long)capacity, (unsigned long long)total);

@@ -134,10 +134,10 @@ struct PartRun {
   uint64_t slabs = 0;              // scratch offset of the part's slabs [tile][S]
 };
 
-// Scratch of a pass: counters (per-part overflow counts at 8 + 4p,
-// then kTotals lines of a hit counter at 0 and per-part queue cursors at
-// 64 + 4p), instance descriptors (single plans),
-// per-tile counts, offsets and overflow lists, scan partials, slabs.
+// Scratch of a pass: counters (the total at 0, per-part overflow counts at
+// 8 + 4p, the tile scan's finished blocks at kCtrDone, then kCursors lines of per-part queue cursors, part p's at 4p),
+// instance descriptors (single plans), per-tile counts, offsets and overflow
+// lists, scan partials, slabs.
 struct Layout {
   uint64_t T = 0;      // tiles over all parts
   uint64_t T1 = 0;     // tiles per virtual instance (single plans)
@@ -146,15 +146,13 @@ struct Layout {
   uint64_t extra = 0;  // bytes of total beyond what tiles of wg * c bytes would take
   uint64_t bsum = 0;   // work of the tile counts' prefix sum
 };
-constexpr uint32_t kCtrOvf = 8, kCtrTotals = 128, kCtrQueue = kCtrTotals + 64;
-constexpr uint32_t kCtrBytes = kCtrTotals + kTotals * kTotalStride;  // read back after a count
-static_assert(kCtrBytes <= 4096, "the context's pinned buffer holds the counters");
-// Hits of a pass, from the counters.
-inline uint64_t hit_total(const uint64_t *ctr) {
-  uint64_t t = 0;
-  for (uint32_t i = 0; i < kTotals; ++i) t += ctr[(kCtrTotals + i * kTotalStride) / 8];
-  return t;
-}
+constexpr uint32_t kCtrOvf = 8, kCtrQueue = 128;
+constexpr uint32_t kCtrHead = kCtrOvf + 4 * kMaxParts;  // total and overflow counts
+constexpr uint32_t kCtrDone = kCtrHead;
+constexpr uint32_t kCtrBytes = kCtrQueue + kCursors * kCursorStride;
+// What a count pass leaves in pinned host memory: the total and whether any
+// tile overflowed its slab.
+constexpr uint32_t kHostTotal = 0, kHostOvf = 1;
 // Tiles that overflowed their slabs, summed over parts, from the counters.
 inline uint32_t ovf_total(const uint64_t *ctr) {
   const uint32_t *w = (const uint32_t *)ctr;
@@ -173,8 +171,13 @@ uint64_t host_hash(const uint8_t *p, uint64_t m);
 rk_status plan_build(rk_ctx *ctx, const rk_instance *inst, uint32_t count, int mode, bool batch, rk_plan **out);
 rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L);
 uint64_t work_bytes_for(const rk_plan *plan, uint64_t total);
+// host: pinned, receives kHostTotal and kHostOvf
 rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, uint64_t n, void *scratch,
-                        uint64_t scratch_bytes, uint64_t *counts, hipStream_t s);
+                        uint64_t scratch_bytes, uint64_t *counts, uint64_t *host, hipStream_t s);
+// A total that a kernel writes to the context's pinned memory as the last
+// thing of its pass: reset before the pass is enqueued, waited for after.
+constexpr uint64_t kNoTotal = ~0ull;  // (no count reaches it)
+hipError_t wait_total(rk_ctx *ctx, hipStream_t s);
 rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total);
 rk_status collect_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, uint64_t n, void *scratch,
                           uint64_t scratch_bytes, void *work, uint64_t work_bytes, uint64_t *offsets,
@@ -224,8 +227,23 @@ hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uin
 hipError_t scan_fit(int cfg, int fam, uint32_t img_cap, uint32_t block, ScanFit *f);
 hipError_t list_scan(int cfg, int fam, const ListParams *p, uint32_t grid, hipStream_t s, int *blocks_per_cu);
 uint64_t scan_tmp_words(uint64_t n);
-hipError_t launch_exclusive_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, uint64_t *total_dev,
-                                 hipStream_t s);
+hipError_t launch_exclusive_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, uint64_t *total,
+                                 uint32_t *done, hipStream_t s);
+// What the prefix sum over a count pass's tile counts yields besides: the
+// total (ctr[0], host[kHostTotal], written last), the tiles whose counts are above their
+// part's S (appended to the part's list, ovf_list + tile0) and whether there
+// are any (host[kHostOvf]).  Parts by ascending tile0.
+struct TileTotals {
+  uint32_t nparts;
+  uint32_t S[kMaxParts];
+  uint64_t tile0[kMaxParts];
+  uint32_t *ovf_count;  // per part, zero
+  uint64_t *ovf_list;
+  uint64_t *ctr, *host;
+  uint32_t *done;       // blocks that are done, zero
+};
+hipError_t launch_tile_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, const TileTotals &tt,
+                            hipStream_t s);
 // sparse: fewer hits than tiles (a lane per tile); offsets1: a single
 // pattern's offsets, written {0, total}, or null
 hipError_t launch_compact(const uint32_t *counts, const uint64_t *offs, uint64_t ntiles, const uint64_t *slabs,

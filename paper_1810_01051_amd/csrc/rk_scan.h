@@ -1080,11 +1080,6 @@ __device__ __forceinline__ BucketDesc read_desc(const uint8_t *gimg, uint32_t b)
   return D;
 }
 
-// Adds a wave's hits to its counter.
-__device__ __forceinline__ void add_total(unsigned long long *totals, uint32_t wave_id, uint64_t hits) {
-  atomicAdd(totals + (wave_id % kTotals) * (kTotalStride / 8), (unsigned long long)hits);
-}
-
 // ------------------------------------------------------------ the scan kernel
 //
 // Work comes in runs of consecutive tiles of one instance; the waves of a
@@ -1115,6 +1110,11 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
     const uint8_t *text;
     uint32_t inst;
   };
+  // (the instance of a launch of one comes with the kernel's arguments)
+  const InstDesc *const insts =
+      p.inst ? p.inst
+             : (const InstDesc *)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(ScanParams, one));
+  if (!p.queue && p.ovf_count && blockIdx.x == 0 && tid == 0) *p.ovf_count = *p.done = 0;
   // the run this wave is in: its remaining tiles are tnext, tnext + nw, ...
   uint64_t next_run = blockIdx.x, tnext = 0, tbase = 0, rn = 0;
   const uint8_t *rtext = nullptr;
@@ -1133,8 +1133,8 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
         next_run = ~0ull;  // the first run needs no pop
       } else {
         // the block's cursor hands out every ncur-th of the other runs
-        const uint32_t ncur = min(gridDim.x, kTotals), c = blockIdx.x % ncur;
-        uint32_t *q = p.queue + c * (kTotalStride / 4);
+        const uint32_t ncur = min(gridDim.x, kCursors), c = blockIdx.x % ncur;
+        uint32_t *q = p.queue + c * (kCursorStride / 4);
         uint32_t v = 0;
         if (nw == 1) {
           if (lane == 0) v = atomicAdd(q, 1u);
@@ -1169,14 +1169,14 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
       uint32_t lo = 0, hi = p.ninst;  // instance owning the tile
       while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (const64(&p.inst[mid].tile_base) <= first) lo = mid;
+        if (const64(&insts[mid].tile_base) <= first) lo = mid;
         else hi = mid;
       }
       if (lo != rinst) {
         rinst = lo;
-        rtext = (const uint8_t *)const64(&p.inst[lo].text);
-        rn = const64(&p.inst[lo].n);
-        tbase = const64(&p.inst[lo].tile_base);
+        rtext = (const uint8_t *)const64(&insts[lo].text);
+        rn = const64(&insts[lo].n);
+        tbase = const64(&insts[lo].tile_base);
       }
     }
     it.inst = rinst;
@@ -1191,7 +1191,6 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
   };
 
   uint32_t cur_inst = kNoLink, nb = 0;
-  uint64_t hits = 0;  // of this wave
   const uint8_t *gimg = nullptr;  // current instance image in device memory
   Item cur;
   uint32_t st = next_item(cur);
@@ -1200,10 +1199,10 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
     if (cur.inst != cur_inst) {
       // the image's leading part goes to LDS; the rest is read in place
       if (nw > 1) wg_barrier();
-      gimg = p.blob + const32(&p.inst[cur.inst].img_off);
+      gimg = p.blob + const32(&insts[cur.inst].img_off);
       const uint4 *src = (const uint4 *)gimg;
       uint4 *dst = (uint4 *)lds;
-      const uint32_t nq = const32(&p.inst[cur.inst].lds_bytes) / 16u;
+      const uint32_t nq = const32(&insts[cur.inst].lds_bytes) / 16u;
       for (uint32_t q = tid; q < nq; q += blockDim.x) dst[q] = src[q];
       cur_inst = cur.inst;
       wg_barrier();
@@ -1252,17 +1251,9 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
       if (s + 1 < ns) dma_sub<C>(sub, cur.text, cur.n, start + SUB);
       else if (st == 1) dma_sub<C>(sub, nx.text, nx.n, nx.tstart);
     }
-    if (lane == 0 && !p.direct) {
-      p.tile_counts[cur.gt] = tile_hits;
-      if (tile_hits > p.slab_cap) {
-        const uint32_t o = atomicAdd(p.ovf_count, 1u);
-        p.ovf_list[o] = cur.gt;
-      }
-    }
-    hits += tile_hits;
+    if (lane == 0 && !p.direct) p.tile_counts[cur.gt] = tile_hits;
     cur = nx;
   }
-  if (lane == 0 && hits && !p.direct) add_total(p.totals, blockIdx.x * nw + wave, hits);
 }
 
 // ------------------------------------------------- single-bucket scan kernel
@@ -1293,7 +1284,7 @@ __global__ __launch_bounds__(kListBlock) void scan_list_kernel(ListParams p) {
   const uint64_t W = (uint64_t)SUB * p.sub, stride = (uint64_t)gridDim.x * (kListBlock / 64);
   uint32_t slot = 0;
   bool dense = false;
-  uint64_t hits = 0;  // of this wave
+  if (p.ovf_count && blockIdx.x == 0 && threadIdx.x == 0) *p.ovf_count = *p.done = 0;
   uint64_t t = (uint64_t)blockIdx.x * (kListBlock / 64) + wave;
   if (t < p.ntiles) dma_sub<C>(slots, p.text, p.n, t * W);
   for (; t < p.ntiles; t += stride) {
@@ -1335,16 +1326,8 @@ __global__ __launch_bounds__(kListBlock) void scan_list_kernel(ListParams p) {
                                             p.pid_counts);
       dense = nc != 0;
     }
-    if (lane == 0 && D.kind != kDump) {
-      p.tile_counts[t] = tile_hits;
-      if (tile_hits > p.slab_cap) {
-        const uint32_t o = atomicAdd(p.ovf_count, 1u);
-        p.ovf_list[o] = t;
-      }
-    }
-    hits += tile_hits;
+    if (lane == 0 && D.kind != kDump) p.tile_counts[t] = tile_hits;
   }
-  if (lane == 0 && hits) add_total(p.totals, blockIdx.x * (kListBlock / 64) + wave, hits);
 }
 
 // ------------------------------------------------------------------ launchers

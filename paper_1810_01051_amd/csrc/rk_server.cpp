@@ -126,7 +126,7 @@ struct Slot {
   uint64_t hstage_cap = 0;
   uint64_t *hres = nullptr;   // pinned: merged per-pattern offsets of the step
   uint64_t hres_cap = 0;      // bytes
-  uint64_t *hctr = nullptr;   // pinned: the pass's counters (hits, overflowed tiles)
+  uint64_t *hctr = nullptr;   // pinned: the pass's total and overflow
   hipGraphExec_t gcount = nullptr, gcollect = nullptr;
   std::vector<Request *> reqs;
   uint64_t step_id = 0, n_total = 0, total = 0, plan_bytes = 0;
@@ -404,10 +404,7 @@ static rk_status start_step(rk_server *S, Slot &sl, std::unique_lock<std::mutex>
     st = run_maybe_graph(S, sl, &sl.gcount, [&]() -> rk_status {
       hipError_t e = hipMemcpyAsync(sl.dplan, sl.hstage, sl.plan_bytes, hipMemcpyHostToDevice, sl.stream);
       if (e != hipSuccess) return hip_err(S->ctx, e, "plan upload");
-      rk_status s2 = count_enqueue(S->ctx, &sl.plan, nullptr, 0, sl.scratch, sl.scratch_cap, nullptr, sl.stream);
-      if (s2 != RK_OK) return s2;
-      e = hipMemcpyAsync(sl.hctr, sl.scratch, kCtrBytes, hipMemcpyDeviceToHost, sl.stream);
-      return e == hipSuccess ? RK_OK : hip_err(S->ctx, e, "count readback");
+      return count_enqueue(S->ctx, &sl.plan, nullptr, 0, sl.scratch, sl.scratch_cap, nullptr, sl.hctr, sl.stream);
     });
   }
   if (st == RK_OK) {
@@ -574,8 +571,8 @@ static void scheduler(rk_server *S) {
       if (sl.state == kCounting) {
         const hipError_t q = hipEventQuery(sl.ev_count);
         if (q == hipSuccess) {
-          sl.total = hit_total(sl.hctr);
-          sl.ovf = ovf_total(sl.hctr);
+          sl.total = sl.hctr[kHostTotal];
+          sl.ovf = (uint32_t)sl.hctr[kHostOvf];
           sl.state = kCounted;
           progress = true;
         } else if (q != hipErrorNotReady) {
@@ -711,7 +708,7 @@ rk_status rk_server_create(rk_ctx *ctx, const rk_server_cfg *cfg_in, rk_server *
     e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.ev_count, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.ev_collect, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&sl.hctr, kCtrBytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&sl.hctr, 64, hipHostMallocCoherent);
     if (e != hipSuccess) break;
   }
   if (e != hipSuccess) {
