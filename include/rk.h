@@ -265,10 +265,12 @@ typedef struct {
  * device (Sec. 3.1); here the text moves piece by piece: piece i owns the
  * windows starting in [i L, (i+1) L), L = piece_bytes - (m_max - 1), and holds
  * the m_max - 1 bytes after them, so each window is searched in exactly one
- * piece.  Staging of the next piece (host threads), its host-to-device copy
- * and the search of the current one overlap.  plan: a single-text plan (not a
- * batch).  *out receives the result (free with rk_host_result_free).
- * Allocates device memory for the pieces, scratch and each piece's hits. */
+ * piece.  Staging of the text (host threads), its host-to-device copy and the
+ * search of the piece before overlap.  plan: a single-text plan (not a batch).
+ * *out receives the result (free with rk_host_result_free).  Allocates device
+ * memory for the pieces, scratch and each piece's hits; the context keeps a
+ * pinned staging ring of 32 MiB from the first such search until it is
+ * destroyed. */
 rk_status rk_search_host(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text_host, uint64_t n,
                          uint64_t piece_bytes, rk_host_result **out);
 /* The same for the bytes of the file at path (read with pread, piece by piece). */

@@ -529,6 +529,8 @@ void rk_ctx_destroy(rk_ctx *ctx) {
     hipEventDestroy(ev.b);
   }
   if (ctx->pinned) hipHostFree(ctx->pinned);
+  if (ctx->stage) hipHostFree(ctx->stage);
+  if (ctx->copy) hipStreamDestroy(ctx->copy);
   if (ctx->aux) hipStreamDestroy(ctx->aux);
   delete ctx;
 }

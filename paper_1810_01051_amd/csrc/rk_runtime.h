@@ -84,7 +84,9 @@ struct rk_ctx {
   bool profile = false;
   int queue = -1;
   uint64_t *pinned = nullptr;  // 4 KiB of pinned host memory for small transfers
-  hipStream_t aux = nullptr;   // the context's own non-blocking stream (plan uploads)
+  hipStream_t aux = nullptr;   // the context's own non-blocking stream (plan uploads, streamed searches)
+  uint8_t *stage = nullptr;    // pinned ring of the streamed searches, from the first one on
+  hipStream_t copy = nullptr;  // and their copy stream
   std::vector<uint8_t> upload; // staging for instance descriptors
   std::vector<rk::ProfEvent> prof_events, free_events;
   int tune[3][RK_MAX_M + 1];

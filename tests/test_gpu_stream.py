@@ -85,3 +85,52 @@ def test_stream_edges(ctx, rk):
         plan.search_host(np.zeros(10, np.uint8), 1000)
     assert e.value.status == rk._lib.RK_EINVAL
     plan.close()
+
+
+@pytest.mark.parametrize("n,piece", [((2 << 20) - 1, 256 << 20), (2 << 20, 256 << 20), ((2 << 20) + 1, 1 << 30),
+                                     ((70 << 20) + 11, 3 << 20), ((70 << 20) + 11, 128 << 20),
+                                     (2 * (3 << 20) - 30, 3 << 20), (5 << 20, 1 << 16)])
+def test_staging_ring_chunk_edges(ctx, rk, n, piece):
+    """Texts of one chunk of the staging ring, of just more, of more chunks
+    than the ring has slots, pieces of a broken number of chunks, and a last
+    piece that lies in its predecessor's overlap but for some bytes; twice,
+    as the ring outlives a call."""
+    pats = [b"ACGTTGCAACGGTACC", b"TTTTTTTTTTTT", rkgen.ACGT[rkgen.rng(93, 0).integers(0, 4, size=64)].tobytes()]
+    if piece < n:
+        text = planted_text(n % 97, n, pats, piece)
+    else:
+        text = rkgen.iid_text(rkgen.rng(93, 1), n, rkgen.ACGT)
+        for x in (0, (2 << 20) - 20, n - 64):
+            text[x:x + len(pats[x % 2])] = np.frombuffer(pats[x % 2], np.uint8)[:n - x]
+    ro, rp = oracle.search(text, pats, threads=8)
+    plan = rk.Plan(ctx, pats, "screen")
+    for _ in range(2):
+        off, pos = plan.search_host(text, piece)
+        assert off.tolist() == ro.tolist() and pos.tolist() == rp.tolist()
+    plan.close()
+
+
+def test_streamed_searches_of_two_threads(rk):
+    """A context, and so a ring, per thread."""
+    import threading
+    pats = [b"ACGTACGTAC", b"GGGGGGGG"]
+    texts = [rkgen.iid_text(rkgen.rng(94, i), (9 << 20) + i, rkgen.ACGT) for i in range(2)]
+    want = [oracle.search(t, pats, threads=4) for t in texts]
+    bad = []
+
+    def work(i):
+        c = rk.Context(0)
+        plan = rk.Plan(c, pats, "screen")
+        for _ in range(4):
+            off, pos = plan.search_host(texts[i], 4 << 20)
+            if off.tolist() != want[i][0].tolist() or pos.tolist() != want[i][1].tolist():
+                bad.append(i)
+        plan.close()
+        c.close()
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not bad
