@@ -184,8 +184,13 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
   }
   if (!table) {
     D.kind = G.screen ? kListScreen : kListExact;
-    for (size_t j = 0; j < 4; ++j) D.tgt[j] = tkeys[j < tkeys.size() ? j : 0];
-    if (!G.screen) D.shift |= (uint32_t)tkeys.size() << 8;  // compare count the kernel unrolls
+    for (int j = 0; j < 4; ++j) {
+      // exact: the lowest of three consecutive low words of the key times
+      // 2^(24-8j), by the window's place in its four
+      const uint32_t rot = 24 - 8 * j;
+      const uint64_t t = ((dist[0] << rot) & kQ) | dist[0] >> (61 - rot);
+      D.tgt[j] = G.screen ? tkeys[0] : (uint32_t)t - 2u;
+    }
     for (PatRef &r : P) r.at = 0;
   } else {
     D.kind = G.screen ? kTableScreen : kTableExact;

@@ -24,7 +24,7 @@ constexpr uint64_t kEmptyKey = ~0ull;      // empty exact-table slot (no canonic
 enum BucketKind : uint32_t {
   kListScreen = 0,   // screen mode, one key: shift-add hash compared with it
   kTableScreen = 1,  // screen mode: shift-add hash tested in the LDS bitmap
-  kListExact = 2,    // exact mode, one key: lazy 61-bit state compared with its lazy forms
+  kListExact = 2,    // exact mode, one key: lazy 61-bit hash compared with its lazy forms
   kTableExact = 3,   // exact mode: lazy state tested in the LDS bitmap
   kDump = 4,         // exact rolling state written out for sampled windows (no patterns)
 };
@@ -42,10 +42,10 @@ enum BucketKind : uint32_t {
 struct BucketDesc {
   uint32_t m;          // the group's shortest length: the window its exact stream hashes
   uint32_t kind;       // BucketKind
-  uint32_t shift;      // shift s of the screen or lookup hash in bits 0-7; one exact key: its lazy forms in
-                       // bits 8-15; in the LDS part: bit 16 tails and records, 17 pattern bytes, 18 ids
+  uint32_t shift;      // shift s of the screen or lookup hash in bits 0-7; in the LDS part: bit 16 tails and
+                       // records, 17 pattern bytes, 18 ids
   uint32_t mask;       // screen-hash mask (all ones unless m < 4 with s = 8)
-  uint32_t tgt[4];     // list kinds: targets (padded by repetition)
+  uint32_t tgt[4];     // one screen key (four times); one exact key by the window's place in a step of four
   uint32_t test_off;   // table kinds: image offset of the test bitmap (LDS part)
   uint32_t test_sh;    // its sh
   uint32_t lk_off;     // table kinds: image offset of the lookup bitmap and its counts (LDS part)

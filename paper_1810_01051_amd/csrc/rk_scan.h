@@ -501,45 +501,78 @@ __device__ __forceinline__ uint32_t exact_mix2(uint64_t s) {
   return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, (uint32_t)s), k, (uint32_t)(s >> 32), false);
 }
 
-// FILTER: the lazy state in the bucket's bitmap, which holds every lazy form
-// of every key; else its low word compared with the one key's lazy forms.
-template <int C, bool ANY, bool FILTER, int NT, int OUTK>
-__device__ __forceinline__ void pass_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
-                                           uint32_t base, uint32_t fsh, uint64_t &any, Bits<C> &bits) {
-  static_assert(!(ANY && FILTER), "bitmap tests fill the mask");
+// A set of keys: the lazy state of every window in the bucket's bitmap, which
+// holds every lazy form of every key.
+template <int C, int OUTK>
+__device__ __forceinline__ void pass_filter_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, uint32_t base,
+                                                  uint32_t fsh, Bits<C> &bits) {
   uint32_t w[16 + C / 4], d[C / 4 + 1], acc = 0;
   lds_read_words<16 + C / 4>(w, mine - 64);
   lds_read_words<C / 4 + 1>(d, os.d);
   uint32_t v[kProbeBlock], t[kProbeBlock];
   roll_exact<C, OUTK>(w, d, os, m, r, [&](int i, uint64_t s) __attribute__((always_inline)) {
-    // lazy state s = H + j*q for j in {0,1,2}; the host lists the low words
-    const uint32_t lo = (uint32_t)s;
-    if constexpr (FILTER) {
-      v[i % kProbeBlock] = exact_mix2(s);
-      t[i % kProbeBlock] = filter_word(base, fsh, v[i % kProbeBlock]);
-      if (i % kProbeBlock == kProbeBlock - 1) {
+    // lazy state s = H + j*q for j in {0,1,2}
+    v[i % kProbeBlock] = exact_mix2(s);
+    t[i % kProbeBlock] = filter_word(base, fsh, v[i % kProbeBlock]);
+    if (i % kProbeBlock == kProbeBlock - 1) {
 #pragma unroll
-        for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i + 1 - kProbeBlock + j, filter_bit(t[j], v[j]));
-      }
-    } else if (ANY) {
-      uint64_t b = ballot(lo == tg[0]) | ballot(lo == tg[1]);
-      if (NT > 2) b |= ballot(lo == tg[2]);
-      any_or(any, b);
-    } else {
-      uint64_t f = ballot(lo == tg[0]) | ballot(lo == tg[1]);
-      if (NT > 2) f |= ballot(lo == tg[2]);
-      put_mask<C>(bits, acc, i, f);
+      for (int j = 0; j < kProbeBlock; ++j) put_bit<C>(bits, acc, i + 1 - kProbeBlock + j, filter_bit(t[j], v[j]));
     }
   });
 }
 
-template <int C, bool ANY, bool FILTER, int NT>
-__device__ __forceinline__ void pass_exact_r(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
-                                             uint32_t base, uint32_t fsh, uint64_t &any, Bits<C> &bits) {
-  const int k = out_kind(r);
-  if (k == 0) pass_exact<C, ANY, FILTER, NT, 0>(mine, os, m, r, tg, base, fsh, any, bits);
-  else if (k == 1) pass_exact<C, ANY, FILTER, NT, 1>(mine, os, m, r, tg, base, fsh, any, bits);
-  else pass_exact<C, ANY, FILTER, NT, 2>(mine, os, m, r, tg, base, fsh, any, bits);
+// out * 2^r mod q for a 32-bit word, r uniform; K: r <= 29 (0: nothing leaves
+// the 61 bits), r >= 32 (1: the low word is only what wraps), else (2).
+__device__ __forceinline__ int rot_kind(uint32_t r) { return r <= 29 ? 0 : r >= 32 ? 1 : 2; }
+template <int K>
+__device__ __forceinline__ uint64_t rot61_word(uint32_t v, uint32_t r) {
+  if (K == 0) return (uint64_t)v << r;
+  if (K == 1) return (uint64_t)((v << (r - 32u)) & 0x1FFFFFFFu) << 32 | v >> (61u - r);
+  return rot61(v, r);
+}
+
+// One key: the hash of every window compared with it, four windows a step.
+// With Y = 2^32 H for the hash H before the four, I and O the four entering and
+// leaving bytes (the first one on top) and R(x) = x * 256^m mod q, the hash
+// after j + 1 of them is, times 2^(24-8j),
+//   X_j = Y + (I & top j + 1 bytes) - R(O & top j + 1 bytes)  (mod q)
+// and R of the masked bytes is R(O) masked by R of the mask (a rotation).  So
+// the rolling state moves once per four windows, and a window costs the low
+// word of X_j: one mask each for I and R(O), one three-way sum.  It is compared
+// with the low word of the key times 2^(24-8j): X_j + q is that plus 0, q or 2q
+// (Y < 2^61 + 2^35), whose low words are consecutive from tg[j] on (q is -1 in
+// 32 bits).  s < 2^62 + 2^35 after each step.
+// Bound by these operations: 8 a window where one 64-bit step per window
+// took 12 (1 GiB, m = 32: 316 us against 434).
+template <int C, bool ANY, int K>
+__device__ __forceinline__ void pass_list_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
+                                                uint64_t &any, Bits<C> &bits) {
+  uint32_t w[16 + C / 4], d[C / 4 + 1], acc = 0, low = ~0u;
+  lds_read_words<16 + C / 4>(w, mine - 64);
+  lds_read_words<C / 4 + 1>(d, os.d);
+  uint64_t s = exact_init(w, m);
+  const uint32_t osel = 0x00010203u + 0x01010101u * os.sh;  // bytes sh..sh + 3 of a pair of dwords, reversed
+  uint32_t keep[3];  // what R leaves of R(O) outside the mask's image
+#pragma unroll
+  for (int j = 0; j < 3; ++j) keep[j] = ~(uint32_t)rot61_word<K>(0xFFFFFFFFu << (24 - 8 * j), r);
+#pragma unroll
+  for (int i = 0; i < C; i += 4) {
+    const uint32_t in = __builtin_bswap32(w[16 + i / 4]);
+    const uint64_t neg = kQ ^ rot61_word<K>(__builtin_amdgcn_perm(d[i / 4 + 1], d[i / 4], osel), r);
+    const uint64_t y = mul2p32_lazy(s);
+    uint32_t x[4];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      x[j] = (uint32_t)y + (in & (0xFFFFFFFFu << (24 - 8 * j))) + ((uint32_t)neg | keep[j]) - tg[j];
+    s = y + in + neg;
+    x[3] = (uint32_t)s - tg[3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (ANY) low = min(low, x[j]);
+      else put_mask<C>(bits, acc, i + j, ballot(x[j] <= 2u));
+    }
+  }
+  if (ANY) any |= ballot(low <= 2u);
 }
 
 // Destination of a hash dump: the canonical hash of every window whose start
@@ -587,21 +620,23 @@ __device__ __forceinline__ void pass_dump(uint32_t mine, OutStream os, uint32_t 
 
 // Runs the test pass of bucket D over the lane's windows: ANY=true ORs the
 // wave ballots into any (one-key buckets), ANY=false fills the lane's
-// candidate mask.  D.shift holds the screen shift in bits 0-7 and, for one
-// exact key, the number of its lazy forms in bits 8-15; base: LDS address of
-// the bucket's bitmap.
+// candidate mask.  D.shift holds the screen shift in bits 0-7; base: LDS
+// address of the bucket's bitmap.
 template <int C, bool ANY, int FAM>
 __device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r,
                                          uint32_t base, uint64_t &any, Bits<C> &bits) {
   const uint32_t sh = D.shift & 0xFFu;
   if constexpr (FAM == kFamExact) {
     if (ANY || D.kind == kListExact) {
-      if (((D.shift >> 8) & 0xFFu) <= 2u)
-        pass_exact_r<C, ANY, false, 2>(mine, os, D.m, r, D.tgt, 0, 0, any, bits);
-      else
-        pass_exact_r<C, ANY, false, 3>(mine, os, D.m, r, D.tgt, 0, 0, any, bits);
+      const int k = rot_kind(r);
+      if (k == 0) pass_list_exact<C, ANY, 0>(mine, os, D.m, r, D.tgt, any, bits);
+      else if (k == 1) pass_list_exact<C, ANY, 1>(mine, os, D.m, r, D.tgt, any, bits);
+      else pass_list_exact<C, ANY, 2>(mine, os, D.m, r, D.tgt, any, bits);
     } else {
-      pass_exact_r<C, false, true, 2>(mine, os, D.m, r, D.tgt, base, D.test_sh, any, bits);
+      const int k = out_kind(r);
+      if (k == 0) pass_filter_exact<C, 0>(mine, os, D.m, r, base, D.test_sh, bits);
+      else if (k == 1) pass_filter_exact<C, 1>(mine, os, D.m, r, base, D.test_sh, bits);
+      else pass_filter_exact<C, 2>(mine, os, D.m, r, base, D.test_sh, bits);
     }
   } else {
     if (ANY || FAM == kFamScreen1 || D.kind == kListScreen) {

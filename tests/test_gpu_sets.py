@@ -123,3 +123,26 @@ def test_dense_hits_sorted_from_small_tiles(ctx, rk, k, n):
     off, pos = search(ctx, rk, text, pats, "screen")
     assert off.tolist() == ref[0].tolist()
     assert (pos == ref[1]).all()
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 7, 8, 15, 19, 29, 30, 42, 45, 61, 63, 64, 65, 80, 200])
+def test_one_exact_pattern_of_every_rotation(ctx, rk, m):
+    """The four-window step of one exact key: the outgoing rotation 8 m mod 61
+    below 30, from 32 and between; texts with the key at every place of a step,
+    of one byte value (the lazy sums at their ends), across lanes and tiles."""
+    g = rkgen.rng(84, m)
+    for n, fill in ((m, None), (m + 7, None), (9000, 0), (9000, 255), (70001, None), (70001, 255)):
+        text = rkgen.iid_text(g, n, np.array([0, 255, 1, 128], np.uint8))
+        if fill is not None:
+            text[100:8000] = fill
+        pats = [text[n - m:].tobytes(), text[:m].tobytes()]
+        if n > 8000:
+            pats += [text[o:o + m].tobytes() for o in (4351, 2304, 333)]
+            for j, x in enumerate(range(8200, n - 2 * m - 300, 271)):
+                text[x:x + m] = np.frombuffer(pats[j % 5], np.uint8)
+        for p in pats:
+            ref = oracle.search(text, [p])
+            off, pos = search(ctx, rk, text, [p], "exact")
+            assert pos.tolist() == ref[1].tolist(), (n, fill)
+            off, pos = search(ctx, rk, text, [p, p], "exact")
+            assert pos.tolist() == ref[1].tolist() * 2
