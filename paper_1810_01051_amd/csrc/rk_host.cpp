@@ -119,8 +119,18 @@ static uint32_t length_class(uint32_t m) { return m < 4 ? m : m < 8 ? 4 : m < 16
 // eight bytes occur every 3,000 bytes, its last four every 300, and a
 // candidate costs about 130 instructions: the pass is the dearer of the two up
 // to some 100 long and 15 short patterns; half of each keeps clear of texts
-// that repeat more.
-constexpr size_t kJoinLong = 64, kJoinShort = 8;
+// that repeat more.  Long patterns that join a class of no pattern below 11
+// bytes keep keys of 11 bytes and more, which recur a fourth as often, and the
+// exact pass is the dearer one, so those limits are higher (200 MiB of word
+// text, lengths from 12 to 64: 80 patterns 303 -> 216 us exact and 156 -> 133
+// screened, 300 patterns 346 -> 266 us exact; from 8 to 64: 80 patterns
+// 336 -> 303 us exact, but 300 patterns 374 -> 555 us, which stay apart).
+constexpr uint32_t kJoinKey = 11;
+constexpr size_t kJoinShort = 8;
+static size_t join_long(bool exact, uint32_t shortest) {
+  if (shortest >= kJoinKey) return exact ? 512 : 256;
+  return exact ? 96 : 64;
+}
 
 // Bytes of a bitmap for nbits set bits: at least 8 bytes a bit (a random
 // window passes at most one time in 64) up to 1,024 bits, 4 bytes beyond,
@@ -421,7 +431,11 @@ static std::vector<GroupIn> group_patterns(const uint8_t *bytes, const uint64_t 
     t->second.pats.insert(t->second.pats.end(), f->second.pats.begin(), f->second.pats.end());
     by.erase(f);
   };
-  join(6, 5, kJoinLong);
+  if (by.count(5)) {
+    uint32_t shortest = ~0u;
+    for (const PatRef &r : by[5].pats) shortest = std::min(shortest, r.m);
+    join(6, 5, join_long(mode == RK_MODE_EXACT, shortest));
+  }
   join(5, 4, kJoinShort);
   std::vector<GroupIn> out;
   for (auto &kv : by) {

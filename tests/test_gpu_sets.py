@@ -125,6 +125,24 @@ def test_dense_hits_sorted_from_small_tiles(ctx, rk, k, n):
     assert (pos == ref[1]).all()
 
 
+@pytest.mark.parametrize("mode,lo,k", [("screen", 11, 256), ("screen", 11, 330), ("screen", 10, 70), ("screen", 10, 90),
+                                       ("exact", 11, 500), ("exact", 11, 640), ("exact", 10, 96), ("exact", 10, 130)])
+def test_long_patterns_joined_and_apart(ctx, rk, mode, lo, k):
+    """Sets of lengths lo..64 with as many patterns of 16 bytes and more as
+    join the 8..15 class, and with more, in a text that repeats itself."""
+    g = rkgen.rng(83, k)
+    words = [rkgen.LOWER[g.integers(0, 26, size=int(g.integers(2, 12)))] for _ in range(150)]
+    text = np.concatenate([words[i] for i in g.integers(0, 150, size=30000)])
+    pats = [text[o:o + lo].tobytes() for o in (5, 700)]
+    for m in g.integers(lo, 65, size=k - 2):
+        o = int(g.integers(0, len(text) - m))
+        pats.append(text[o:o + int(m)].tobytes())
+    ref = oracle.search(text, pats, threads=4)
+    off, pos = search(ctx, rk, text, pats, mode)
+    assert off.tolist() == ref[0].tolist()
+    assert (pos == ref[1]).all()
+
+
 @pytest.mark.parametrize("m", [1, 2, 3, 4, 7, 8, 15, 19, 29, 30, 42, 45, 61, 63, 64, 65, 80, 200])
 def test_one_exact_pattern_of_every_rotation(ctx, rk, m):
     """The four-window step of one exact key: the outgoing rotation 8 m mod 61
