@@ -345,7 +345,7 @@ uint64_t rk_plan_text_bytes(const rk_plan *plan);
  *   - for each batch bucket (m-class 0..4: lengths 1-3, 4-7, 8-15, 16-31,
  *     32-64; k-class 0..3: 1, 4, 32, 256 patterns), both modes, the general
  *     kernel over a one-instance batch plan of the text's first n_b bytes
- *     (n_b = min(n, 1 MiB) for m-class 0, min(n, 32 MiB) otherwise), pattern j
+ *     (n_b = min(n, 1 MiB) for m-class 0, 64 MiB for 1, 512 MiB otherwise), pattern j
  *     of length lo + j mod (hi - lo + 1) copied from the text at
  *     (n_b/3 + 7919 j) mod (n_b - m + 1), reversed when j is odd,
  * stores the fastest geometry of each and every bucket timing in the context

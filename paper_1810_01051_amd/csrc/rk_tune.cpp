@@ -152,8 +152,13 @@ static const uint32_t kClassHi[kNumMClass] = {3, 7, 15, 31, 64};
 static const uint32_t kClassK[kNumKClass] = {1, 4, 32, 256};
 
 // Text bytes a bucket shape is timed on: the first 1 MiB for m-class 0 (one-
-// to three-byte patterns hit every few bytes), else the first 32 MiB.
-static uint64_t bucket_text(uint64_t n, int mc) { return std::min<uint64_t>(n, mc == 0 ? (1u << 20) : (32u << 20)); }
+// to three-byte patterns hit every few bytes), the first 64 MiB for m-class 1,
+// else the first 512 MiB: many tiles for each wave, as a large batch has (of
+// 32 MiB the resident waves of the largest tiles take 1.1 each, and the second
+// round makes their geometry look a fourth slower than it is).
+static uint64_t bucket_text(uint64_t n, int mc) {
+  return std::min<uint64_t>(n, mc == 0 ? 1u << 20 : mc == 1 ? 64u << 20 : 512u << 20);
+}
 
 // Pattern set of a bucket shape over text[0..n): k patterns, pattern j of
 // length lo + j mod (hi - lo + 1), copied from the text at (n/3 + 7919 j) mod
