@@ -56,14 +56,17 @@ __device__ __forceinline__ uint64_t add_flagged(uint64_t a, uint64_t b) {
 // thread (mine) brings.  Called by all threads.
 template <bool TILES>
 __device__ __forceinline__ void put_total(const TileTotals &tt, uint64_t nb, bool mine, uint64_t sum) {
-  __shared__ uint32_t last;
   if (mine) __hip_atomic_store(tt.ctr, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __threadfence();
+  // every wave's stores are in the L2; one thread writes it back (each fence
+  // does, and the four waves' own took a microsecond or two of seven)
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   __syncthreads();
-  if (threadIdx.x == 0)
-    last = nb == 1 || __hip_atomic_fetch_add(tt.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
-  __syncthreads();
-  if (!last || threadIdx.x) return;
+  if (threadIdx.x) return;
+  if (nb > 1) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (__hip_atomic_fetch_add(tt.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != nb - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
   const uint64_t t = __hip_atomic_load(tt.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (TILES) {
     __hip_atomic_store(tt.ctr, t & ~kOvfBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
