@@ -33,7 +33,7 @@ namespace rk {
 constexpr int kScanWG = 256;
 constexpr int kScanPer = 16;
 constexpr int kScanBlock = kScanWG * kScanPer;  // items per block
-constexpr uint64_t kScanSelf = 16;              // most blocks that add up the counts before them
+constexpr uint64_t kScanSelf = 4;              // most blocks that add up the counts before them
 constexpr uint64_t kOvfBit = 1ull << 63;
 
 // most records of tile t's slab
@@ -316,111 +316,29 @@ __global__ __launch_bounds__(256) void compact_sparse(const uint32_t *counts, co
 
 // -------------------------------------------------- stable radix by pattern id
 // Records are pid << 40 | x.  One DB-bit digit of the pid per pass (8 bits,
-// or 9..11 when a single pass covers every pid); a block is one wave walking
-// its BLK records in order, so ranks are stable.  Each lane loads kRadixR
-// records before it handles any, so that a wave keeps kRadixR * 64 loads in
-// flight instead of one round trip per 64 records.
-constexpr int kRadixBlock = 1024;        // records per block, 8-bit digits
-constexpr int kRadixBlock11 = 8192;      // records per block, 9..11-bit digits (at most 2048 digits per block)
-constexpr int kRadixR = 16;              // records per lane in flight
-
-// BM: the histogram is block-major (block b's ND counts contiguous, the
-// one-pass sorts); else digit-major (the 8-bit passes, scanned as one array).
-template <int DB, int BLK, bool BM>
-__global__ __launch_bounds__(64) void radix_hist(const uint64_t *in, uint64_t n, uint32_t shift, uint32_t *ghist,
-                                                 uint64_t nblk) {
-  constexpr uint32_t ND = 1u << DB;
-  static_assert(BLK % (64 * kRadixR) == 0, "block is whole rounds");
-  __shared__ uint32_t h[ND];
-  for (uint32_t i = threadIdx.x; i < ND; i += 64) h[i] = 0;
-  __syncthreads();
-  const uint64_t base = (uint64_t)blockIdx.x * BLK;
-  for (int j = 0; j < BLK; j += 64 * kRadixR) {
-    uint64_t rec[kRadixR];
-#pragma unroll
-    for (int u = 0; u < kRadixR; ++u) {
-      const uint64_t i = base + j + u * 64 + threadIdx.x;
-      rec[u] = i < n ? in[i] : ~0ull;
-    }
-#pragma unroll
-    for (int u = 0; u < kRadixR; ++u)
-      if (rec[u] != ~0ull) atomicAdd(&h[(rec[u] >> shift) & (ND - 1u)], 1u);
-  }
-  __syncthreads();
-  for (uint32_t d = threadIdx.x; d < ND; d += 64)
-    ghist[BM ? (uint64_t)blockIdx.x * ND + d : (uint64_t)d * nblk + blockIdx.x] = h[d];
-}
-
-// STRIP: the pass is the last one, and writes each record's position only
-// (the final positions array) instead of the record.  Ranks within 64
-// records: every lane ORs its bit into the LDS mask of its digit, reads the
-// mask back (the lanes holding that digit) and counts the lower ones; the
-// highest lane of each digit advances the digit's cursor and clears the
-// mask.  The block is one wave, whose LDS operations take effect in issue
-// order, so no barrier is needed between those steps.
-template <int DB, int BLK, bool STRIP, bool BM>
-__global__ __launch_bounds__(64) void radix_scatter(const uint64_t *in, uint64_t n, uint32_t shift,
-                                                    const uint64_t *goff, uint64_t nblk, uint64_t *out) {
-  constexpr uint32_t ND = 1u << DB;
-  __shared__ uint64_t run[ND];
-  __shared__ unsigned long long grp[ND];
-  for (uint32_t d = threadIdx.x; d < ND; d += 64) {
-    run[d] = goff[BM ? (uint64_t)blockIdx.x * ND + d : (uint64_t)d * nblk + blockIdx.x];
-    grp[d] = 0;
-  }
-  __syncthreads();
-  const uint32_t lane = threadIdx.x;
-  const uint64_t me = 1ull << lane, lt_mask = me - 1ull;
-  // rounds of 64 * kRadixR records; the next round's loads are issued before
-  // the current one is ranked, all unconditional (indices clamped to the
-  // block's last record, the lanes past it skipped when ranking)
-  const uint64_t base = (uint64_t)blockIdx.x * BLK, end = min(base + BLK, n);
-  auto load_round = [&](uint64_t j, uint64_t (&r)[kRadixR]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kRadixR; ++u) r[u] = in[min(j + (uint64_t)u * 64u + lane, end - 1)];
-  };
-  uint64_t cur[kRadixR];
-  load_round(base, cur);
-  for (uint64_t j = base;; j += 64u * kRadixR) {
-    // (a block of one round has no next one: 8-bit passes)
-    const bool more = BLK > 64 * kRadixR && j + 64u * kRadixR < end;
-    uint64_t nxt[kRadixR];
-    if constexpr (BLK > 64 * kRadixR) load_round(more ? j + 64u * kRadixR : j, nxt);
-#pragma unroll
-    for (int u = 0; u < kRadixR; ++u) {
-      if (j + (uint64_t)u * 64u + lane >= end) continue;
-      const uint64_t rec = cur[u];
-      const uint32_t dg = (uint32_t)(rec >> shift) & (ND - 1u);
-      atomicOr(&grp[dg], (unsigned long long)me);
-      const uint64_t peers = grp[dg];
-      const uint64_t at = run[dg];
-      out[at + __builtin_popcountll(peers & lt_mask)] = STRIP ? (rec & kPosMask) : rec;
-      if ((peers >> lane) == 1ull) {
-        run[dg] = at + __builtin_popcountll(peers);
-        grp[dg] = 0;
-      }
-    }
-    if (!more) break;
-    if constexpr (BLK > 64 * kRadixR) {
-#pragma unroll
-      for (int u = 0; u < kRadixR; ++u) cur[u] = nxt[u];
-    }
-  }
-}
-
-// ------------------------------- one radix pass reading the staging slabs
-// For dense hits the compaction is skipped: the records of a part's tiles
-// are read where the count pass left them, tile by tile in tile order (the
-// order the compaction would have produced), a block taking G consecutive
-// tiles.  Tile t's counts[t] records are its slab (slabs + (t - tile0) * S)
-// when they fit, else those of the collect's rescan, written at tile_off[t]
-// of the direct buffer.
+// or 9..11 when a single pass covers every pid): a histogram per block of the
+// input, the starts of every (digit, block), and the scatter.
 //
+// The input is an array of n records, rb to a block, or (TILES) the count
+// pass's staging slabs: for dense hits the compaction is skipped and the
+// records of a part's tiles are read where they are, in tile order (the order
+// the compaction would have produced), a block taking G consecutive tiles.
+// Tile t's counts[t] records are its slab (slabs + (t - tile0) * S) when they
+// fit, else those of the collect's rescan, written at tile_off[t] of the direct
+// buffer.
+struct RecordSrc {
+  TileSrc tiles;       // TILES
+  const uint64_t *in;  // else
+  uint64_t n;
+  uint32_t rb;
+};
+constexpr int kRadixR = 16;  // records per lane in flight
+
 // A wave walks its tiles as chunks of up to 64 records of one tile, the counts
 // of 64 tiles loaded at once (a lane each): a round of chunks spans as many
 // tiles as it takes, so that tiles of some hundred records keep as many loads
-// in flight as large ones (a round of one tile's records: 113 us for the
-// scatter of 130 K records in tiles of 100 to 270; see radix_scatter_tiles).
+// in flight as large ones (a histogram of 130 K records in tiles of 100 to 270:
+// 28 us in rounds of one tile's records, 4 us so).
 struct TileChunks {
   const TileSrc &src;
   uint64_t t, t1;         // next tile, end
@@ -462,78 +380,207 @@ struct TileChunks {
   }
 };
 
-// Four waves per block, wave w taking the block's tiles w, w + 4, ...
-template <int DB>
-__global__ __launch_bounds__(256) void radix_hist_tiles(TileSrc src, uint32_t *ghist, uint64_t nblk) {
+// Histogram of a block, block-major (block b's ND counts contiguous).  Four
+// waves, wave w taking the block's tiles w, w + 4, ..., or every fourth round
+// of the array's records.
+template <int DB, bool TILES>
+__global__ __launch_bounds__(256) void radix_hist(RecordSrc src, uint32_t shift, uint32_t *ghist) {
   constexpr uint32_t ND = 1u << DB;
   __shared__ uint32_t h[ND];
   for (uint32_t i = threadIdx.x; i < ND; i += 256) h[i] = 0;
   __syncthreads();
   const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
-  const uint64_t t1 = min(t0 + src.G, src.tile0 + src.ntiles);
-  TileChunks q(src, t0 + w, t1, 4);
   uint64_t rec[kRadixR];
-  uint32_t lim[kRadixR];
-  while (q.load(rec, lim)) {
+  if constexpr (TILES) {
+    const uint64_t t0 = src.tiles.tile0 + (uint64_t)blockIdx.x * src.tiles.G;
+    TileChunks q(src.tiles, t0 + w, min(t0 + src.tiles.G, src.tiles.tile0 + src.tiles.ntiles), 4);
+    uint32_t lim[kRadixR];
+    while (q.load(rec, lim)) {
 #pragma unroll
-    for (int u = 0; u < kRadixR; ++u)
-      if (lane < lim[u]) atomicAdd(&h[(rec[u] >> kPosBits) & (ND - 1u)], 1u);
+      for (int u = 0; u < kRadixR; ++u)
+        if (lane < lim[u]) atomicAdd(&h[(rec[u] >> shift) & (ND - 1u)], 1u);
+    }
+  } else {
+    const uint64_t base = (uint64_t)blockIdx.x * src.rb, end = min(base + src.rb, src.n);
+    for (uint64_t j = base + w * 64u * kRadixR; j < end; j += 4 * 64u * kRadixR) {
+#pragma unroll
+      for (int u = 0; u < kRadixR; ++u) rec[u] = src.in[min(j + u * 64u + lane, end - 1)];
+#pragma unroll
+      for (int u = 0; u < kRadixR; ++u)
+        if (j + u * 64u + lane < end) atomicAdd(&h[(rec[u] >> shift) & (ND - 1u)], 1u);
+    }
   }
   __syncthreads();
-  for (uint32_t d = threadIdx.x; d < ND; d += 256) ghist[(src.blk0 + blockIdx.x) * ND + d] = h[d];
+  const uint64_t b = (TILES ? src.tiles.blk0 : 0) + blockIdx.x;
+  for (uint32_t d = threadIdx.x; d < ND; d += 256) ghist[b * ND + d] = h[d];
 }
 
-// Positions of the records to their final place (the last and only pass),
-// ranked as in radix_scatter.  The next round's loads are issued before the
-// current round is ranked: a wave then waits for its loads once per two
-// rounds' latency instead of draining before every round.
-constexpr int kTileRound = 8;  // chunks per round
+// The records to their place in the output (STRIP: the last pass, which writes
+// their positions only), by blocks of four waves in rounds of kSortRound
+// records that are sorted in LDS first: a wave takes kSortPer chunks of the round, each lane a record of each;
+// the waves count their digits, the counts of all four give every (wave, digit)
+// its place in the round and every digit its place in the output, and the
+// waves rank their chunks in order (the lanes of one digit found by a ballot
+// per bit).  Then consecutive lanes write consecutive records of a digit.
+// Bound by the writes: a wave that writes 64 records as it finds them makes 64
+// requests, most to lines of their own, which each leave the L2 before the
+// next record of the digit comes (35 M records of 1,024 digits: 253 us, 167 us
+// sorted; with rounds of 4,096 records, which leave room for two blocks a CU
+// instead of three, 200 us).
+constexpr uint32_t kSortPer = 12, kSortRound = 4 * 64 * kSortPer;
 
+// Lanes (of the active ones) whose low DB bits of d are this lane's: four
+// instructions a bit, the bit spread over a word, its ballot, and both halves
+// of the mask without the lanes where the ballot differs.
 template <int DB>
-__global__ __launch_bounds__(64) void radix_scatter_tiles(TileSrc src, const uint64_t *goff, uint64_t nblk,
-                                                          uint64_t *out) {
-  constexpr uint32_t ND = 1u << DB;
-  __shared__ uint64_t run[ND];
-  __shared__ unsigned long long grp[ND];
-  const uint64_t b = src.blk0 + blockIdx.x;
-  const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
-  TileChunks q(src, t0, min(t0 + src.G, src.tile0 + src.ntiles), 1);
-  for (uint32_t d = threadIdx.x; d < ND; d += 64) {
-    run[d] = goff[b * ND + d];
-    grp[d] = 0;
-  }
-  __syncthreads();
-  const uint32_t lane = threadIdx.x;
-  const uint64_t me = 1ull << lane, lt_mask = me - 1ull;
-  uint64_t cur[kTileRound], nxt[kTileRound];
-  uint32_t clim[kTileRound], nlim[kTileRound];
-  bool more = q.load(cur, clim);
-  while (more) {
-    more = q.load(nxt, nlim);
+__device__ __forceinline__ uint64_t same_digit(uint32_t d) {
+  const uint64_t all = __ballot(1);
+  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
 #pragma unroll
-    for (int u = 0; u < kTileRound; ++u) {
-      if (lane >= clim[u]) continue;
-      const uint64_t rec = cur[u];
-      const uint32_t dg = (uint32_t)(rec >> kPosBits) & (ND - 1u);
-      atomicOr(&grp[dg], (unsigned long long)me);
-      const uint64_t peers = grp[dg];
-      const uint64_t at = run[dg];
-      out[at + __builtin_popcountll(peers & lt_mask)] = rec & kPosMask;
-      if ((peers >> lane) == 1ull) {
-        run[dg] = at + __builtin_popcountll(peers);
-        grp[dg] = 0;
+  for (int b = 0; b < DB; ++b) {
+    const uint32_t mine = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);
+    const uint64_t m = __ballot(mine != 0);
+    lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, mine, 0x90);          // lo & ~(m ^ mine)
+    hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), mine, 0x90);
+  }
+  return (uint64_t)hi << 32 | lo;
+}
+
+template <int DB, bool TILES, bool STRIP>
+__global__ __launch_bounds__(256) void radix_scatter(RecordSrc rsrc, uint32_t shift, const uint64_t *goff,
+                                                     uint64_t *out) {
+  constexpr uint32_t ND = 1u << DB, PER = ND / 256;
+  __shared__ uint64_t sorted[kSortRound];
+  __shared__ uint64_t delta[ND];           // a digit's place in the output less its place in the round
+  __shared__ uint32_t cnt[4][ND];          // counts, then next places in the round
+  __shared__ uint32_t first[TILES ? kSortTiles : 1];  // chunks of the block's tiles before each
+  __shared__ uint32_t count[TILES ? kSortTiles : 1];  // records of each
+  __shared__ uint32_t wsum[4];
+  const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const TileSrc &src = rsrc.tiles;
+  const uint64_t base0 = (uint64_t)blockIdx.x * rsrc.rb;  // the array's first record
+  const uint32_t nrec = TILES ? 0 : (uint32_t)min((uint64_t)rsrc.rb, rsrc.n - base0);
+  const uint64_t t0 = src.tile0 + (uint64_t)blockIdx.x * src.G;
+  const uint32_t ng = TILES ? (uint32_t)min((uint64_t)src.G, src.tile0 + src.ntiles - t0) : 0;
+  // exclusive prefix sum over the block of each thread's v; *all: the sum
+  auto block_scan = [&](uint32_t v, uint32_t *all) __attribute__((always_inline)) -> uint32_t {
+    uint32_t x = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(x, d, 64);
+      if (lane >= (uint32_t)d) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    uint32_t before = 0, sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      before += i < w ? wsum[i] : 0;
+      sum += wsum[i];
+    }
+    *all = sum;
+    return before + x - v;
+  };
+  uint32_t nch = (nrec + 63) / 64;
+  if constexpr (TILES) {
+    constexpr uint32_t Q = (kSortTiles + 255) / 256;
+    uint32_t c[Q], v = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) {
+      const uint32_t i = threadIdx.x * Q + q;
+      c[q] = i < ng ? src.counts[t0 + i] : 0u;
+      if (i < kSortTiles) count[i] = c[q];
+      v += (c[q] + 63) / 64;
+    }
+    uint32_t at = block_scan(v, &nch);
+#pragma unroll
+    for (uint32_t q = 0; q < Q; ++q) {
+      if (threadIdx.x * Q + q < kSortTiles) first[threadIdx.x * Q + q] = at;
+      at += (c[q] + 63) / 64;
+    }
+  }
+  uint64_t place[PER];  // next place in the output of digits threadIdx.x * PER ..
+#pragma unroll
+  for (uint32_t q = 0; q < PER; ++q) place[q] = goff[((TILES ? src.blk0 : 0) + blockIdx.x) * ND + threadIdx.x * PER + q];
+  __syncthreads();
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  for (uint32_t q0 = 0; q0 < nch; q0 += 4 * kSortPer) {
+    // the wave's chunks, one looked up by each of its first lanes
+    const uint64_t *p = TILES ? src.slabs : rsrc.in;  // (no chunk: a record that is there, not used)
+    uint32_t len = 0;
+    const uint32_t q = q0 + w * kSortPer + min(lane, kSortPer - 1);
+    if (q < nch) {
+      if constexpr (TILES) {
+        uint32_t lo = 0, hi = ng;
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (first[mid] <= q) lo = mid;
+          else hi = mid;
+        }
+        const uint32_t c = count[lo], off = (q - first[lo]) * 64;
+        const uint64_t t = t0 + lo;
+        p = (c <= src.S ? src.slabs + (t - src.tile0) * src.S : src.direct + src.tile_off[t]) + off;
+        len = min(c - off, 64u);
+      } else {
+        p = rsrc.in + base0 + 64ull * q;
+        len = min(nrec - 64 * q, 64u);
       }
     }
+    uint64_t rec[kSortPer];
+    uint32_t lim[kSortPer];
 #pragma unroll
-    for (int u = 0; u < kTileRound; ++u) {
-      cur[u] = nxt[u];
-      clim[u] = nlim[u];
+    for (uint32_t u = 0; u < kSortPer; ++u) {
+      lim[u] = __builtin_amdgcn_readlane(len, u);
+      const uint64_t at = (uint64_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)p >> 32), u) << 32 |
+                          (uint32_t)__builtin_amdgcn_readlane((uint32_t)(uint64_t)p, u);
+      // (known to be global memory: a flat load would wait on LDS too)
+      rec[u] = ((const __attribute__((address_space(1))) uint64_t *)at)[min(lane, max(lim[u], 1u) - 1u)];
+    }
+    for (uint32_t d = lane; d < ND; d += 64) cnt[w][d] = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kSortPer; ++u)
+      if (lane < lim[u]) atomicAdd(&cnt[w][(uint32_t)(rec[u] >> shift) & (ND - 1u)], 1u);
+    __syncthreads();
+    uint32_t tot[PER], v = 0, n;
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) {
+      const uint32_t d = threadIdx.x * PER + i;
+      tot[i] = cnt[0][d] + cnt[1][d] + cnt[2][d] + cnt[3][d];
+      v += tot[i];
+    }
+    uint32_t at = block_scan(v, &n);
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) {
+      const uint32_t d = threadIdx.x * PER + i;
+      delta[d] = place[i] - at;
+      place[i] += tot[i];
+#pragma unroll
+      for (uint32_t x = 0; x < 4; ++x) {
+        const uint32_t c = cnt[x][d];
+        cnt[x][d] = at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < kSortPer; ++u) {
+      if (lane >= lim[u]) continue;
+      const uint32_t d = (uint32_t)(rec[u] >> shift) & (ND - 1u);
+      const uint64_t peers = same_digit<DB>(d);
+      const uint32_t base = cnt[w][d];
+      sorted[base + __builtin_popcountll(peers & lt_mask)] = rec[u];
+      if ((peers >> lane) == 1ull) cnt[w][d] = base + __builtin_popcountll(peers);
+    }
+    __syncthreads();
+    // (the next round writes delta and sorted only after its barriers)
+    for (uint32_t i = threadIdx.x; i < n; i += 256) {
+      const uint64_t r = sorted[i];
+      out[delta[(uint32_t)(r >> shift) & (ND - 1u)] + i] = STRIP ? r & kPosMask : r;
     }
   }
 }
 
-// Start of every (digit, block) of a one-pass sort from its block-major
+// Start of every (digit, block) of a pass from its block-major
 // histogram h[b][d] (nblk blocks, nd digits).  The blocks go in chunks of
 // kDigitChunk: digit_chunk_sums sums each chunk's rows (csum[c][d]);
 // digit_chunk_starts scans every digit's column over the chunks (crel[c][d]:
@@ -586,8 +633,9 @@ __global__ __launch_bounds__(64 * kDigitWaves) void digit_chunk_starts(const uin
 }
 
 // Chunk x's blocks, digits 256y..256y+255.  Every block scans the digit
-// totals itself (nd is at most 2048); block (0, 0) also writes offsets (the digit is the whole pid of a
-// one-pass sort): offsets[j] = start of pid j, offsets[k] = n.
+// totals itself (nd is at most 2048); block (0, 0) also writes offsets, if
+// asked for (the digit is the whole pid of a one-pass sort): offsets[j] = start
+// of pid j, offsets[k] = n.
 __global__ __launch_bounds__(256) void digit_block_starts(const uint32_t *__restrict__ h, uint64_t nblk, uint32_t nd,
                                                           const uint64_t *__restrict__ crel,
                                                           const uint64_t *__restrict__ dtot,
@@ -619,7 +667,7 @@ __global__ __launch_bounds__(256) void digit_block_starts(const uint32_t *__rest
     before += v[i];
   }
   __syncthreads();
-  if (blockIdx.x == 0 && blockIdx.y == 0)
+  if (offsets && blockIdx.x == 0 && blockIdx.y == 0)
     for (uint32_t j = threadIdx.x; j <= k; j += 256) offsets[j] = j < k ? start[j] : n;
   const uint64_t b0 = (uint64_t)blockIdx.x * kDigitChunk, b1 = min(b0 + kDigitChunk, nblk);
   const uint32_t d = blockIdx.y * 256 + threadIdx.x;
@@ -676,7 +724,8 @@ __global__ __launch_bounds__(256) void digit_starts_one(const uint32_t *__restri
     before += v[i];
   }
   __syncthreads();
-  for (uint32_t j = threadIdx.x; j <= k; j += 256) offsets[j] = j < k ? start[j] : n;
+  if (offsets)
+    for (uint32_t j = threadIdx.x; j <= k; j += 256) offsets[j] = j < k ? start[j] : n;
   for (uint32_t d = threadIdx.x; d < nd; d += 256) {
     uint64_t run = start[d];
 #pragma unroll 8
@@ -787,14 +836,12 @@ hipError_t launch_compact(const uint32_t *counts, const uint64_t *offs, uint64_t
   return hipGetLastError();
 }
 
-uint64_t radix_blocks(uint64_t n) { return (n + kRadixBlock - 1) / kRadixBlock; }
-
-// Starts of every (digit, block) of a one-pass sort into goff (block-major,
-// like h) and of every digit into offsets (k + 1 entries); cs: work of
+// Starts of every (digit, block) of a pass into goff (block-major, like h) and,
+// of a one-pass sort, of every digit into offsets (k + 1 entries; else null); cs: work of
 // digit_cs_bytes(nblk * nd, nd) bytes.
 static hipError_t digit_offsets(const uint32_t *h, uint64_t nblk, uint32_t nd, uint64_t *goff, uint8_t *cs,
                                 uint32_t k, uint64_t n, uint64_t *offsets, hipStream_t s) {
-  if (nd > 2048 || k > nd) return hipErrorInvalidValue;
+  if (nd > 2048 || (offsets && k > nd)) return hipErrorInvalidValue;
   if (nblk <= kDigitOne) {
     hipLaunchKernelGGL(digit_starts_one, dim3(1), dim3(256), 0, s, h, (uint32_t)nblk, nd, goff, k, n, offsets);
     return hipGetLastError();
@@ -816,17 +863,45 @@ uint64_t digit_cs_bytes(uint64_t nh, uint32_t nd) {
   return ((cells * 4 + 255) & ~255ull) + cells * 8 + nd * 8;
 }
 
-template <int DB>
-static hipError_t radix_one_pass(const uint64_t *src, uint64_t n, uint32_t k, uint32_t *ghist, uint64_t *goff,
-                                 uint8_t *cs, uint64_t *offsets, uint64_t *positions, hipStream_t s) {
-  constexpr int BLK = DB == 8 ? kRadixBlock : kRadixBlock11;
-  const uint64_t nblk = (n + BLK - 1) / BLK;
-  hipLaunchKernelGGL((radix_hist<DB, BLK, true>), dim3((uint32_t)nblk), dim3(64), 0, s, src, n, kPosBits, ghist,
-                     nblk);
+// Records per block of a pass of `bits` bits: 16,384 once there are 1,024 such
+// blocks (longer runs per digit and block make the scatter's writes fuller
+// lines; 32,768 leave too few blocks for the chip: 188 us against 167 for 35 M
+// records of 1,024 digits), down to 2,048 to 8,192 for fewer (more blocks at
+// work; a block's histogram and its scan then cost about as much as its
+// records).
+uint32_t radix_block_records(uint64_t n, uint32_t bits) {
+  const uint64_t least = std::min<uint64_t>(8192, 8ull << bits);
+  return (uint32_t)std::min<uint64_t>(16384, std::max<uint64_t>(least, n / 1024));
+}
+
+// One pass over the parts' tiles (nparts > 0, nblk blocks in all) or over `in`.
+template <int DB, bool STRIP>
+static hipError_t radix_pass(const TileSrc *parts, uint32_t nparts, uint64_t nblk, const uint64_t *in, uint64_t n,
+                             uint32_t shift, uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint32_t k,
+                             uint64_t *offsets, uint64_t *out, hipStream_t s) {
+  RecordSrc r = {};
+  r.in = in;
+  r.n = n;
+  r.rb = radix_block_records(n, DB);
+  if (!nparts) {
+    nblk = (n + r.rb - 1) / r.rb;
+    hipLaunchKernelGGL((radix_hist<DB, false>), dim3((uint32_t)nblk), dim3(256), 0, s, r, shift, ghist);
+  }
+  auto blocks = [](const TileSrc &t) { return dim3((uint32_t)((t.ntiles + t.G - 1) / t.G)); };
+  for (uint32_t i = 0; i < nparts; ++i) {
+    r.tiles = parts[i];
+    if (r.tiles.ntiles)
+      hipLaunchKernelGGL((radix_hist<DB, true>), blocks(r.tiles), dim3(256), 0, s, r, shift, ghist);
+  }
   hipError_t e = digit_offsets(ghist, nblk, 1u << DB, goff, cs, k, n, offsets, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((radix_scatter<DB, BLK, true, true>), dim3((uint32_t)nblk), dim3(64), 0, s, src, n, kPosBits,
-                     goff, nblk, positions);
+  if (!nparts)
+    hipLaunchKernelGGL((radix_scatter<DB, false, STRIP>), dim3((uint32_t)nblk), dim3(256), 0, s, r, shift, goff, out);
+  for (uint32_t i = 0; i < nparts; ++i) {
+    r.tiles = parts[i];
+    if (r.tiles.ntiles)
+      hipLaunchKernelGGL((radix_scatter<DB, true, STRIP>), blocks(r.tiles), dim3(256), 0, s, r, shift, goff, out);
+  }
   return hipGetLastError();
 }
 
@@ -834,30 +909,27 @@ static hipError_t radix_one_pass(const uint64_t *src, uint64_t n, uint32_t k, ui
 // written out as per-pid offsets (k+1) and positions (n).  Up to 2,048 pids:
 // one pass whose digit is the whole pid, scattering positions straight to
 // their final place, with the offsets read from the scanned histogram.
-// Beyond: 8-bit passes ping-ponging between a and b, then a binary search
-// for the offsets and a strip of the records.  ghist / goff / tmp are sized
-// for 256 * radix_blocks(n) entries, which also covers the one-pass digits
-// (at most 2048 per 8192-record block).
-hipError_t launch_radix(uint64_t *a, uint64_t *b, uint64_t n, uint32_t k, uint32_t *ghist, uint64_t *goff,
-                        uint64_t *tmp, uint8_t *cs, uint64_t *offsets, uint64_t *positions, hipStream_t s) {
-  uint32_t pid_bits = 0;
-  while (pid_bits < 32 && (1ull << pid_bits) < k) ++pid_bits;
+// Beyond: 8-bit passes ping-ponging between b and a, then a binary search
+// for the offsets and a strip of the records.  The first pass reads the parts'
+// tiles (nparts > 0; parts[i].G and blk0 set by the caller, nblk blocks in all)
+// or a.  ghist and goff hold 2^DB entries per block of each pass.
+hipError_t launch_radix(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t *a, uint64_t *b, uint64_t n,
+                        uint32_t k, uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets,
+                        uint64_t *positions, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (pid_bits <= 8) return radix_one_pass<8>(a, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 9) return radix_one_pass<9>(a, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 10) return radix_one_pass<10>(a, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 11) return radix_one_pass<11>(a, n, k, ghist, goff, cs, offsets, positions, s);
+  const uint32_t bits = pid_bits(k);
+#define RK_ONE_PASS(DB) \
+  radix_pass<DB, true>(parts, nparts, nblk, a, n, kPosBits, ghist, goff, cs, k, offsets, positions, s)
+  if (bits <= 8) return RK_ONE_PASS(8);
+  if (bits == 9) return RK_ONE_PASS(9);
+  if (bits == 10) return RK_ONE_PASS(10);
+  if (bits == 11) return RK_ONE_PASS(11);
+#undef RK_ONE_PASS
   uint64_t *src = a, *dst = b;
-  const uint64_t nblk = radix_blocks(n);
-  const uint32_t npass = (pid_bits + 7) / 8;
-  for (uint32_t ps = 0; ps < npass; ++ps) {
-    const uint32_t shift = kPosBits + 8 * ps;
-    hipLaunchKernelGGL((radix_hist<8, kRadixBlock, false>), dim3((uint32_t)nblk), dim3(64), 0, s, src, n, shift, ghist,
-                       nblk);
-    hipError_t e = launch_exclusive_scan(ghist, 256 * nblk, goff, tmp, nullptr, nullptr, s);
+  for (uint32_t done = 0; done < bits; done += 8) {
+    hipError_t e = radix_pass<8, false>(parts, done ? 0 : nparts, nblk, src, n, kPosBits + done, ghist, goff, cs, k,
+                                        nullptr, dst, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((radix_scatter<8, kRadixBlock, false, false>), dim3((uint32_t)nblk), dim3(64), 0, s, src, n, shift,
-                       goff, nblk, dst);
     uint64_t *t = src;
     src = dst;
     dst = t;
@@ -865,41 +937,6 @@ hipError_t launch_radix(uint64_t *a, uint64_t *b, uint64_t n, uint32_t k, uint32
   hipError_t e = launch_pid_offsets(src, n, k, offsets, s);
   if (e != hipSuccess) return e;
   return launch_strip(src, n, positions, s);
-}
-
-template <int DB>
-static hipError_t radix_tiles_pass(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t n, uint32_t k,
-                                   uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets,
-                                   uint64_t *positions, hipStream_t s) {
-  for (uint32_t i = 0; i < nparts; ++i) {
-    const uint64_t nb = (parts[i].ntiles + parts[i].G - 1) / parts[i].G;
-    if (nb) hipLaunchKernelGGL((radix_hist_tiles<DB>), dim3((uint32_t)nb), dim3(256), 0, s, parts[i], ghist, nblk);
-  }
-  hipError_t e = digit_offsets(ghist, nblk, 1u << DB, goff, cs, k, n, offsets, s);
-  if (e != hipSuccess) return e;
-  for (uint32_t i = 0; i < nparts; ++i) {
-    const uint64_t nb = (parts[i].ntiles + parts[i].G - 1) / parts[i].G;
-    if (nb)
-      hipLaunchKernelGGL((radix_scatter_tiles<DB>), dim3((uint32_t)nb), dim3(64), 0, s, parts[i], goff, nblk,
-                         positions);
-  }
-  return hipGetLastError();
-}
-
-// The one-pass sort (up to 2,048 pids) over records read from the staging
-// slabs (see TileSrc); parts[i].G and blk0 set by the caller, nblk the total
-// block count (the histograms hold 2^pid_bits * nblk entries).
-hipError_t launch_radix_tiles(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t n, uint32_t k,
-                              uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets, uint64_t *positions,
-                              hipStream_t s) {
-  uint32_t pid_bits = 0;
-  while (pid_bits < 32 && (1ull << pid_bits) < k) ++pid_bits;
-  if (n == 0) return hipSuccess;
-  if (pid_bits <= 8) return radix_tiles_pass<8>(parts, nparts, nblk, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 9) return radix_tiles_pass<9>(parts, nparts, nblk, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 10) return radix_tiles_pass<10>(parts, nparts, nblk, n, k, ghist, goff, cs, offsets, positions, s);
-  if (pid_bits == 11) return radix_tiles_pass<11>(parts, nparts, nblk, n, k, ghist, goff, cs, offsets, positions, s);
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets, hipStream_t s) {

@@ -423,7 +423,7 @@ rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
 }
 
 struct WorkLayout {
-  uint64_t nblk = 0, a = 0, b = 0, ghist = 0, goff = 0, tmp = 0, cs = 0, total = 0;
+  uint64_t a = 0, b = 0, ghist = 0, goff = 0, cs = 0, total = 0;
   uint64_t nh = 0;  // histogram entries the work holds
 };
 
@@ -432,21 +432,20 @@ struct WorkLayout {
 // histograms and their scan
 static WorkLayout work_layout(uint64_t total, uint32_t k) {
   WorkLayout w;
-  w.nblk = radix_blocks(total);
   uint64_t o = 0;
   auto take = [&o](uint64_t bytes) {
     const uint64_t r = o;
     o = align_up(o + bytes, 256);
     return r;
   };
-  // digit histograms: 256 per 1024-record block (8-bit passes) or up to 2048
-  // per 8192-record block (one pass of 9..11 bits), whichever is larger
-  const uint64_t nh = std::max<uint64_t>(256 * w.nblk, 2048 * ((total + 8191) / 8192));
+  // digit histograms: 2^bits entries per block of at least 2,048 (8-bit passes)
+  // to 8,192 records, a part's last block being smaller, or as many blocks as
+  // 1,024 records each would make, whichever is larger
+  const uint64_t nh = std::max<uint64_t>(256 * ((total + 1023) / 1024), 2048 * ((total + 8191) / 8192));
   w.a = take(total * 8);
   w.b = k > 2048 ? take(total * 8) : w.a;
   w.ghist = take(nh * 4);
   w.goff = take(nh * 8);
-  w.tmp = take(scan_tmp_words(nh) * 8);
   w.cs = take(digit_cs_bytes(nh, 2048));
   w.total = o;
   w.nh = nh;
@@ -758,23 +757,16 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
   const uint64_t *tile_off = (const uint64_t *)(sc + L.offsets);  // from the count pass
   WorkLayout WL = work_layout(total, k);
   uint64_t *target = k == 1 ? positions : (uint64_t *)((uint8_t *)work + WL.a);
-  // Dense hits (at least 64 per tile on average) up to 2,048 patterns: the
-  // sort reads the records from the slabs, G tiles per radix block (2,048 to
-  // 32,768 records), and the compaction is skipped; the rescan below still
-  // writes the overflowed tiles' records to the work buffer.
+  // Dense hits (at least 64 per tile on average): the sort reads the records
+  // from the slabs, G tiles per radix block, and the compaction is skipped; the
+  // rescan below still writes the overflowed tiles' records to the work buffer.
   TileSrc tsrc[kMaxParts];
   uint32_t ntsrc = 0;
   uint64_t tblk = 0;
   bool from_slabs = false;
-  if (k > 1 && k <= 2048 && total >= 64 * L.T && L.parts.size() <= (size_t)kMaxParts) {
-    uint32_t bits = 8;
-    while ((1u << bits) < k) ++bits;
-    // records per block: 32,768 once there are 1,024 such blocks (longer runs
-    // per digit and block make the scatter's writes fuller lines), down to
-    // 2,048 to 8,192 for fewer hits (more blocks at work; a block's histogram
-    // and its scan then cost about as much as its records)
-    const uint64_t least = std::min<uint64_t>(8192, 8ull << bits);
-    const uint64_t rb = std::min<uint64_t>(32768, std::max<uint64_t>(least, total / 1024));
+  if (k > 1 && total >= 64 * L.T && L.parts.size() <= (size_t)kMaxParts) {
+    const uint32_t bits = k > 2048 ? 8 : std::max(8u, pid_bits(k));
+    const uint64_t rb = radix_block_records(total, bits);
     const uint32_t G = (uint32_t)std::max<uint64_t>(1, (rb * L.T + total - 1) / total);
     for (const PartRun &r : L.parts) {
       TileSrc &t = tsrc[ntsrc++];
@@ -789,7 +781,7 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
       t.G = G;
       tblk += (r.ntiles + G - 1) / G;
     }
-    from_slabs = tblk > 0 && (1ull << bits) * tblk <= WL.nh;
+    from_slabs = tblk > 0 && tsrc[0].G <= kSortTiles && (1ull << bits) * tblk <= WL.nh;
   }
   // a single pattern's offsets ({0, total}) come from the first compaction
   uint64_t *offsets1 = k == 1 ? offsets : nullptr;
@@ -842,12 +834,8 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
   if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
   {
     uint8_t *wk = (uint8_t *)work;
-    if (from_slabs)
-      e = launch_radix_tiles(tsrc, ntsrc, tblk, total, k, (uint32_t *)(wk + WL.ghist), (uint64_t *)(wk + WL.goff),
-                             wk + WL.cs, offsets, positions, s);
-    else
-      e = launch_radix((uint64_t *)(wk + WL.a), (uint64_t *)(wk + WL.b), total, k, (uint32_t *)(wk + WL.ghist),
-                       (uint64_t *)(wk + WL.goff), (uint64_t *)(wk + WL.tmp), wk + WL.cs, offsets, positions, s);
+    e = launch_radix(tsrc, from_slabs ? ntsrc : 0, tblk, (uint64_t *)(wk + WL.a), (uint64_t *)(wk + WL.b), total, k,
+                     (uint32_t *)(wk + WL.ghist), (uint64_t *)(wk + WL.goff), wk + WL.cs, offsets, positions, s);
     if (e != hipSuccess) return hip_err(ctx, e, "radix sort");
   }
   e = prof_end(ctx, s, slot);

@@ -251,10 +251,7 @@ hipError_t launch_tile_scan(const uint32_t *in, uint64_t n, uint64_t *out, uint6
 hipError_t launch_compact(const uint32_t *counts, const uint64_t *offs, uint64_t ntiles, const uint64_t *slabs,
                           uint32_t slab_cap, uint64_t *out, bool sparse, uint64_t *offsets1, uint64_t total,
                           hipStream_t s);
-uint64_t radix_blocks(uint64_t n);
-hipError_t launch_radix(uint64_t *a, uint64_t *b, uint64_t n, uint32_t k, uint32_t *ghist, uint64_t *goff,
-                        uint64_t *tmp, uint8_t *cs, uint64_t *offsets, uint64_t *positions, hipStream_t s);
-// work bytes of the one-pass sorts' digit offsets for up to nh histogram
+// work bytes of a pass's digit offsets for up to nh histogram
 // entries of nd digits
 uint64_t digit_cs_bytes(uint64_t nh, uint32_t nd);
 // Records of one part's tiles as the count pass left them (dense hits: the
@@ -272,9 +269,16 @@ struct TileSrc {
   uint32_t S, G;
 };
 
-hipError_t launch_radix_tiles(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t n, uint32_t k,
-                              uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets, uint64_t *positions,
-                              hipStream_t s);
+constexpr uint32_t kSortTiles = 520;  // most tiles of a block (G)
+inline uint32_t pid_bits(uint32_t k) {
+  uint32_t b = 0;
+  while (b < 32 && (1ull << b) < k) ++b;
+  return b;
+}
+uint32_t radix_block_records(uint64_t n, uint32_t bits);
+hipError_t launch_radix(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t *a, uint64_t *b, uint64_t n,
+                        uint32_t k, uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets,
+                        uint64_t *positions, hipStream_t s);
 hipError_t launch_pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets, hipStream_t s);
 hipError_t launch_strip(const uint64_t *rec, uint64_t n, uint64_t *pos, hipStream_t s);
 hipError_t launch_window_hashes(const uint8_t *text, uint64_t n, uint32_t m, const uint64_t *xs, uint64_t cnt,
