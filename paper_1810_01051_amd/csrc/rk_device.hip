@@ -736,8 +736,17 @@ __global__ __launch_bounds__(256) void digit_starts_one(const uint32_t *__restri
   }
 }
 
-__global__ void pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets) {
-  const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The records sorted by pid to offsets (a binary search per pid, the first
+// blocks) and positions (the others, two records per thread).
+__global__ __launch_bounds__(256) void sorted_results(const uint64_t *sorted, uint64_t n, uint32_t k, uint32_t oblocks,
+                                                      uint64_t *offsets, uint64_t *pos) {
+  if (blockIdx.x >= oblocks) {
+    const uint64_t i = ((uint64_t)(blockIdx.x - oblocks) * 256 + threadIdx.x) * 2;
+    if (i < n) pos[i] = sorted[i] & kPosMask;
+    if (i + 1 < n) pos[i + 1] = sorted[i + 1] & kPosMask;
+    return;
+  }
+  const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (j > k) return;
   if (j == k) {
     offsets[k] = n;
@@ -750,11 +759,6 @@ __global__ void pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint
     else hi = mid;
   }
   offsets[j] = lo;
-}
-
-__global__ void strip_positions(const uint64_t *rec, uint64_t n, uint64_t *pos) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) pos[i] = rec[i] & kPosMask;
 }
 
 // ------------------------------------------------------------- window hashes
@@ -909,8 +913,8 @@ static hipError_t radix_pass(const TileSrc *parts, uint32_t nparts, uint64_t nbl
 // written out as per-pid offsets (k+1) and positions (n).  Up to 2,048 pids:
 // one pass whose digit is the whole pid, scattering positions straight to
 // their final place, with the offsets read from the scanned histogram.
-// Beyond: 8-bit passes ping-ponging between b and a, then a binary search
-// for the offsets and a strip of the records.  The first pass reads the parts'
+// Beyond: 8-bit passes ping-ponging between b and a, then the offsets and
+// positions from the sorted records.  The first pass reads the parts'
 // tiles (nparts > 0; parts[i].G and blk0 set by the caller, nblk blocks in all)
 // or a.  ghist and goff hold 2^DB entries per block of each pass.
 hipError_t launch_radix(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t *a, uint64_t *b, uint64_t n,
@@ -934,23 +938,11 @@ hipError_t launch_radix(const TileSrc *parts, uint32_t nparts, uint64_t nblk, ui
     src = dst;
     dst = t;
   }
-  hipError_t e = launch_pid_offsets(src, n, k, offsets, s);
-  if (e != hipSuccess) return e;
-  return launch_strip(src, n, positions, s);
-}
-
-hipError_t launch_pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets, hipStream_t s) {
-  const uint64_t th = (uint64_t)k + 1;
-  hipLaunchKernelGGL(pid_offsets, dim3((uint32_t)((th + 255) / 256)), dim3(256), 0, s, sorted, n, k, offsets);
+  const uint32_t oblocks = (k + 256) / 256;  // k + 1 offsets
+  hipLaunchKernelGGL(sorted_results, dim3(oblocks + (uint32_t)((n + 511) / 512)), dim3(256), 0, s, src, n, k, oblocks,
+                     offsets, positions);
   return hipGetLastError();
 }
-
-hipError_t launch_strip(const uint64_t *rec, uint64_t n, uint64_t *pos, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(strip_positions, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, rec, n, pos);
-  return hipGetLastError();
-}
-
 
 hipError_t launch_window_hashes(const uint8_t *text, uint64_t n, uint32_t m, const uint64_t *xs, uint64_t cnt,
                                 uint64_t *out, hipStream_t s) {

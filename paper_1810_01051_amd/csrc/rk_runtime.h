@@ -279,8 +279,6 @@ uint32_t radix_block_records(uint64_t n, uint32_t bits);
 hipError_t launch_radix(const TileSrc *parts, uint32_t nparts, uint64_t nblk, uint64_t *a, uint64_t *b, uint64_t n,
                         uint32_t k, uint32_t *ghist, uint64_t *goff, uint8_t *cs, uint64_t *offsets,
                         uint64_t *positions, hipStream_t s);
-hipError_t launch_pid_offsets(const uint64_t *sorted, uint64_t n, uint32_t k, uint64_t *offsets, hipStream_t s);
-hipError_t launch_strip(const uint64_t *rec, uint64_t n, uint64_t *pos, hipStream_t s);
 hipError_t launch_window_hashes(const uint8_t *text, uint64_t n, uint32_t m, const uint64_t *xs, uint64_t cnt,
                                 uint64_t *out, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint64_t words, uint32_t v, hipStream_t s);
