@@ -3,8 +3,8 @@
 // Hot path (Shah & Oza, Sec. 3.1, GPU procedure): every text window gets a
 // polynomial hash, the hash is tested against the pattern-hash set and a hit
 // is confirmed by comparing bytes.  The paper gives one thread per window and
-// recomputes each window's hash from global memory; here a workgroup stages a
-// tile of the text (plus a 64-byte halo in front of it) in LDS with coalesced
+// recomputes each window's hash from global memory; here a wave stages a
+// sub-tile of the text (plus a 64-byte halo in front of it) in LDS with coalesced
 // 16-byte loads, and each thread rolls the hash over C consecutive windows held
 // in registers, so every text byte is read from HBM once.
 //
@@ -15,7 +15,8 @@
 // Two ways to test a window (same results):
 //   exact  : the d=256, q=2^61-1 hash is rolled for every window
 //            (H' = 256 H + in - out*256^m mod q, with a lazily reduced 64-bit
-//            state) and compared with the set;
+//            state; for one key of six bytes or more, four windows a step)
+//            and compared with the set;
 //   screen : the paper's shift-and-add hash h' = (h << s) + in mod 2^32 is
 //            rolled for every window (s*m >= 32, so bytes older than the window
 //            shift out and no out-term is needed) and compared with the set.
