@@ -283,8 +283,9 @@ void rk_host_result_free(rk_host_result *r);
 /* The paper's GPU procedure as printed (Sec. 3.1), for rerunning its
  * experiments (Tables 1-3: threads per block, pattern length) next to the
  * tiled scans: threads over the offsets x in [0, n - m] (blocks of
- * threads_per_block threads, 1..1024, a thread taking 16 consecutive offsets),
- * each offset's m bytes at text_dev + x hashed by h <- (h << 1) + c in a
+ * threads_per_block threads, 1..1024, a thread taking 16 consecutive offsets,
+ * whose hashes follow from the first one's), each offset's m bytes at
+ * text_dev + x hashed by h <- (h << 1) + c in a
  * 32-bit word (d = 2, q = 2^32) read straight from device memory, comparing
  * with the pattern's hash (computed here on the host from pattern_host) and,
  * on equality, comparing the m bytes with pattern_dev.  result_dev[x] = 1 for

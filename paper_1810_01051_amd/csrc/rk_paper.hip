@@ -6,10 +6,11 @@
 //     dimensions as the paper does; a thread takes 16 consecutive offsets (the
 //     paper's takes one);
 //   - for each, it hashes the m bytes at T + x with the paper's shift-and-add
-//     hash h <- (h << 1) + c, read straight from device memory (no tile, no
-//     rolling), in a 32-bit word (the paper leaves the word width open; the
-//     hash is the polynomial hash with d = 2, q = 2^32, in which all but the
-//     window's last 32 bytes have weight 0);
+//     hash h <- (h << 1) + c, read straight from device memory (no tile), in a
+//     32-bit word (the paper leaves the word width open; the hash is the
+//     polynomial hash with d = 2, q = 2^32, in which all but the window's last
+//     32 bytes have weight 0); the hash of a thread's first offset comes from
+//     the window's bytes, the others' from it;
 //   - if the hash equals the pattern's (computed once on the host) the m bytes
 //     are compared, and the result array gets 1 at x for a match.
 // Deviations: the result byte is written for every x (0 or 1), so the array
@@ -33,44 +34,42 @@ constexpr uint32_t kPaperPer = 16;
 constexpr uint32_t kPaperDwords = 13;  // hold the 31 + 16 bytes hashed, from any byte of the first
 
 // Hashes of 16 consecutive windows whose last 32 bytes are bytes i..i+31 of e
-// (i < 16), each from its own words K0..7: word K0's bytes with the weights of
-// w0 (0 before the window), the others with 8, 4, 2, 1.  A phase's windows
-// share the sums of one, two and four words.
-template <int K0>
-__device__ __forceinline__ void window_hashes16(const uint32_t *e, uint32_t w0, uint32_t *h) {
+// (i < 16): the first from its words K0..7 (word K0's bytes with the weights of
+// w0, 0 before the window, the others with 8, 4, 2, 1), the others from the one
+// before: 2 h + c, less the byte that leaves (SHORT: windows of fewer than 32
+// bytes; the byte's weight is 0 in a longer one), which is byte out of word K0
+// for the second window.
+template <int K0, bool SHORT>
+__device__ __forceinline__ void window_hashes16(const uint32_t *e, uint32_t w0, uint32_t out, uint32_t m,
+                                                uint32_t *h) {
+  uint32_t x = __builtin_amdgcn_udot4(e[K0], w0, 0u, false);
 #pragma unroll
-  for (uint32_t ph = 0; ph < 4; ++ph) {  // windows ph + 4 i
-    uint32_t w[11], v1[11], v2[10], v4[8];
+  for (int j = K0 + 1; j < 8; ++j) x = __builtin_amdgcn_udot4(e[j], 0x01020408u, x << 4, false);
+  h[0] = x;
+  uint32_t o[4] = {};
+  if (SHORT) {
 #pragma unroll
-    for (uint32_t j = 0; j < 11; ++j) {
-      w[j] = ph ? __builtin_amdgcn_alignbyte(e[j + 1], e[j], ph) : e[j];
-      v1[j] = __builtin_amdgcn_udot4(w[j], 0x01020408u, 0u, false);
-    }
+    for (int j = 0; j < 4; ++j) o[j] = __builtin_amdgcn_alignbyte(e[K0 + j + 1], e[K0 + j], out);
+  }
 #pragma unroll
-    for (uint32_t j = 0; j < 10; ++j) v2[j] = (v1[j] << 4) + v1[j + 1];
-#pragma unroll
-    for (uint32_t j = 0; j < 8; ++j) v4[j] = (v2[j] << 8) + v2[j + 2];
-#pragma unroll
-    for (uint32_t i = 0; i < 4; ++i) {
-      constexpr int F = 7 - K0;  // whole words
-      uint32_t x = __builtin_amdgcn_udot4(w[i + K0], w0, 0u, false);
-      if constexpr (F >= 4) x = (x << 16) + v4[i + K0 + 1];
-      if constexpr (F & 2) x = (x << 8) + v2[i + K0 + 1 + (F & 4)];
-      if constexpr (F & 1) x = (x << 4) + v1[i + 7];
-      h[4 * i + ph] = x;
-    }
+  for (int i = 1; i < 16; ++i) {
+    x = (x << 1) + byte_at(e, 31 + i);
+    if (SHORT) x -= byte_at(o, i - 1) << m;
+    h[i] = x;
   }
 }
 
-// Every offset's hash from its own bytes.  h <- (h << 1) + c in a 32-bit word
-// gives byte i of the window the weight 2^(m-1-i), which is 0 for all but the
-// last 32 bytes: those are hashed, four bytes at a time (the weights 8, 4, 2,
-// 1 of a word's bytes are one byte dot product, word k back from the end
-// weighs 16^k), and their flags leave in one store.  Bound by the read of the text and the
+// Every offset's hash from the text in device memory.  h <- (h << 1) + c in a
+// 32-bit word gives byte i of the window the weight 2^(m-1-i), which is 0 for
+// all but the last 32 bytes: those of a thread's first window are hashed four
+// bytes at a time (the weights 8, 4, 2, 1 of a word's bytes are one byte dot
+// product, word k back from the end weighs 16^k), the other windows follow from
+// it, and their flags leave in one store.  Bound by the read of the text and the
 // write of the flags: 320 MB with m = 25 at 1,024 threads per block take
-// 0.19 ms (3.4 TB/s; nothing but the two would take 0.11 ms); one offset per
-// thread took 1.30 ms with the same dwords and products (the blocks' start and
-// load latency), 1.87 ms with a byte load per hashed byte (m = 800: 29 ms).
+// 0.145 ms (nothing but the two would take 0.11 ms); 0.19 ms with every window
+// hashed from its words, one offset per thread took 1.30 ms with the same
+// dwords and products (the blocks' start and load latency), 1.87 ms with a byte
+// load per hashed byte (m = 800: 29 ms).
 __global__ void paper_kernel(const uint8_t *T, uint64_t n, uint64_t nwin, const uint8_t *P, uint32_t m, uint32_t hx,
                              uint8_t *result, uint32_t *hash_out) {
   const uint64_t block = blockIdx.x + (uint64_t)blockIdx.y * gridDim.x + (uint64_t)gridDim.x * gridDim.y * blockIdx.z;
@@ -108,15 +107,20 @@ __global__ void paper_kernel(const uint8_t *T, uint64_t n, uint64_t nwin, const 
   const uint32_t w0 = 0x01020408u & (0xFFFFFFFFu << (8u * (lead & 3u)));
   uint32_t h[kPaperPer];
   // (m is uniform: one case per wave)
-  switch (k0) {
-    case 0: window_hashes16<0>(e, w0, h); break;
-    case 1: window_hashes16<1>(e, w0, h); break;
-    case 2: window_hashes16<2>(e, w0, h); break;
-    case 3: window_hashes16<3>(e, w0, h); break;
-    case 4: window_hashes16<4>(e, w0, h); break;
-    case 5: window_hashes16<5>(e, w0, h); break;
-    case 6: window_hashes16<6>(e, w0, h); break;
-    default: window_hashes16<7>(e, w0, h); break;
+  const uint32_t out = lead & 3u;
+  if (m >= 32) {
+    window_hashes16<0, false>(e, w0, out, m, h);
+  } else {
+    switch (k0) {
+      case 0: window_hashes16<0, true>(e, w0, out, m, h); break;
+      case 1: window_hashes16<1, true>(e, w0, out, m, h); break;
+      case 2: window_hashes16<2, true>(e, w0, out, m, h); break;
+      case 3: window_hashes16<3, true>(e, w0, out, m, h); break;
+      case 4: window_hashes16<4, true>(e, w0, out, m, h); break;
+      case 5: window_hashes16<5, true>(e, w0, out, m, h); break;
+      case 6: window_hashes16<6, true>(e, w0, out, m, h); break;
+      default: window_hashes16<7, true>(e, w0, out, m, h); break;
+    }
   }
   uint32_t cand = 0, hit = 0;
 #pragma unroll
@@ -179,12 +183,14 @@ __device__ __forceinline__ uint32_t flag_mask(const uint8_t *flags, uint64_t i, 
 }
 
 // Count of set flags per block of kFlagBlock.  Bound by the read of the
-// flags: 16 bytes per lane, a wave's loads contiguous (320 MB: 0.07 ms,
-// 0.29 ms with one byte per lane and load).
+// flags: 16 bytes per lane, a wave's loads contiguous, the last flags first, as
+// those written last are still in the cache behind the L2 (320 MB: 51 us, 75 us
+// with the first flags first, 0.29 ms with one byte per lane and load).
 __global__ __launch_bounds__(kFlagWG) void flag_counts(const uint8_t *flags, uint64_t nf, uint32_t *counts,
                                                        uint32_t *done) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;  // of the scan that follows
-  const uint64_t base = (uint64_t)blockIdx.x * kFlagBlock + 16u * threadIdx.x;
+  const uint32_t blk = gridDim.x - 1 - blockIdx.x;
+  const uint64_t base = (uint64_t)blk * kFlagBlock + 16u * threadIdx.x;
   uint32_t c = 0;
 #pragma unroll
   for (uint32_t j = 0; j < kFlagRounds; ++j) c += __builtin_popcount(flag_mask(flags, base + j * kFlagRound, nf));
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(kFlagWG) void flag_counts(const uint8_t *flags, uin
   if (threadIdx.x == 0) {
     uint32_t t = 0;
     for (uint32_t w = 0; w < kFlagWG / 64; ++w) t += red[w];
-    counts[blockIdx.x] = t;
+    counts[blk] = t;
   }
 }
 
