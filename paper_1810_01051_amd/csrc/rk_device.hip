@@ -210,14 +210,32 @@ __global__ __launch_bounds__(kScanWG) void scan_local(const uint32_t *in, uint64
   }
   bool any = false;  // a tile of this thread overflowed
   if (TILES) {
+    uint32_t over = 0;
 #pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-      if (v[j] <= slab_of(tt, i0 + j)) continue;
-      any = true;
-      uint32_t part = 0;
-      for (uint32_t q = 1; q < tt.nparts; ++q)
-        if (i0 + j >= tt.tile0[q]) part = q;
-      tt.ovf_list[tt.tile0[part] + atomicAdd(tt.ovf_count + part, 1u)] = i0 + j;
+    for (int j = 0; j < kScanPer; ++j) over |= v[j] > slab_of(tt, i0 + j) ? 1u << j : 0u;
+    any = over != 0;
+    if (tt.nparts == 1) {
+      // places for a wave's tiles at once (additions to one address are served
+      // one after the other)
+      const uint32_t c = __builtin_popcount(over);
+      uint32_t at = c;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(at, d, 64);
+        if (lane >= (uint32_t)d) at += y;
+      }
+      uint32_t first = 0;
+      if (lane == 63 && at) first = atomicAdd(tt.ovf_count, at);
+      at += __shfl(first, 63, 64) - c;
+      for (; over; over &= over - 1) tt.ovf_list[at++] = i0 + __builtin_ctz(over);
+    } else {
+      for (; over; over &= over - 1) {
+        const uint64_t t = i0 + __builtin_ctz(over);
+        uint32_t part = 0;
+        for (uint32_t q = 1; q < tt.nparts; ++q)
+          if (t >= tt.tile0[q]) part = q;
+        tt.ovf_list[tt.tile0[part] + atomicAdd(tt.ovf_count + part, 1u)] = t;
+      }
     }
   }
   if (lane == 63) wsum[wave] = x;

@@ -487,6 +487,9 @@ static uint32_t scan_grid(const rk_ctx *ctx, uint32_t waves, uint32_t block, uin
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(g, nruns));
 }
 
+// Most images of one text whose overflowed tiles are rescanned image by image.
+constexpr uint32_t kSplitRescan = 16;
+
 // Blocks per resident slot of the single-bucket scan's grid.
 constexpr uint32_t kListGridMul = 32;
 
@@ -816,16 +819,32 @@ rk_status collect_enqueue_known(rk_ctx *ctx, const rk_plan *plan, const uint8_t 
       p.wave_items = 1;
       p.nitems = r.ntiles;
       p.nitems_dev = (const uint32_t *)(sc + L.ctr + kCtrOvf) + pi;
+      p.item_hi = ~0ull;
       p.out = target;
       p.tile_offsets = tile_off;
       p.direct = 1;
-      // the waves of a block take tiles of their own: one instance, or one wave
-      const uint32_t block = pt.ninst > 1 ? 64 : pt.block;
+      // The waves of a block take tiles of their own: those of one instance, or
+      // one wave.  One text's images are large (two or more for one text), and
+      // one-wave blocks leave two waves a CU: its rescan is a launch per
+      // image over the whole list, which passes over the tiles of the others
+      // (10.9 M hits of 6,000 patterns in 64 MiB, the dense tiles
+      // rescanned: 165 us, 605 in one launch of one-wave blocks).
+      const bool split = !plan->batch && pt.ninst > 1 && pt.ninst <= kSplitRescan;
+      const uint32_t block = pt.ninst > 1 && !split ? 64 : pt.block;
       const uint32_t grid = scan_grid(ctx, block == 64 ? pt.waves1 : pt.waves, block, (r.ntiles * 64 + block - 1) / block);
       e = prof_begin(ctx, s, 1, &slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
-      e = launch_scan(pt.cfg, pt.fam, p, grid, block, s);
-      if (e != hipSuccess) return hip_err(ctx, e, "rescan launch");
+      for (uint32_t v = 0; v < (split ? pt.ninst : 1); ++v) {
+        ScanParams pv = p;
+        if (split) {
+          pv.inst = p.inst + v;
+          pv.ninst = 1;
+          pv.item_lo = L.T1 * v;
+          pv.item_hi = L.T1 * (v + 1);
+        }
+        e = launch_scan(pt.cfg, pt.fam, pv, grid, block, s);
+        if (e != hipSuccess) return hip_err(ctx, e, "rescan launch");
+      }
       e = prof_end(ctx, s, slot);
       if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
     }

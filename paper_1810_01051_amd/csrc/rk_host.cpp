@@ -206,7 +206,10 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
     for (PatRef &r : P) r.at = 0;
   } else {
     D.kind = G.screen ? kTableScreen : kTableExact;
-    const uint32_t tb = bitmap_bytes(tkeys.size()), lb = G.screen ? tb : bitmap_bytes((P.size() + 3) / 4);
+    // (exact: the lookup bitmap and its counts beside a test bitmap of any size
+    // in one image; with fewer bits the records of a bit are more)
+    const uint32_t tb = bitmap_bytes(tkeys.size());
+    const uint32_t lb = G.screen ? tb : std::min(kMaxBitmap / 2, bitmap_bytes((P.size() + 3) / 4));
     std::vector<uint32_t> test(tb / 4, 0), look(lb / 4, 0);
     D.test_sh = 32 - (uint32_t)__builtin_ctz(tb / 4);
     D.lk_sh = 32 - (uint32_t)__builtin_ctz(lb / 4);
@@ -306,7 +309,8 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
 // Emits G, splitting its pattern list in halves while it does not fit.
 static void expand_group(const GroupIn &G, bool tab_lds, std::vector<GroupBody> &bodies) {
   GroupBody gb;
-  if (emit_group(G, tab_lds, gb) || G.pats.size() < 2) {
+  if ((emit_group(G, tab_lds, gb) && sizeof(ImageHeader) + 64 + align_up(gb.lds.size(), 16) <= kImgLimit) ||
+      G.pats.size() < 2) {
     bodies.push_back(std::move(gb));
     return;
   }

@@ -158,7 +158,8 @@ struct ScanParams {
   uint64_t inst_tiles;        // without items: tiles of each instance,
   uint64_t inst_runs;         // runs of each,
   uint32_t run;               // and tiles per run (the last one of an instance may have fewer)
-  uint32_t wave_items;        // 1: items lists tiles, one for each wave in turn (one instance, or one-wave blocks)
+  uint32_t wave_items;        // 1: items lists tiles, one for each wave in turn (one instance, or one-wave blocks);
+  uint64_t item_lo, item_hi;  // those outside [item_lo, item_hi) are passed over
   uint32_t *tile_counts;      // hits per global tile
   uint64_t *out;              // count mode: slabs [tile][slab_cap]; direct mode: compact array
   const uint64_t *tile_offsets; // direct mode: first output slot of each tile

@@ -979,9 +979,13 @@ __device__ __forceinline__ void verify(const BucketDesc &D, const Records &R, co
 // candidates are compacted into the wave's LDS list in window order, and each
 // is checked by one lane: its key's record, then its bytes.  A bit that
 // several patterns share is put off: its candidates go back to the front of
-// the list and are checked after the others, one pattern after the other (a
-// pattern's hits come all from the one or all from the other, so each keeps
-// the window order).  Hits go to the tile's slab (up to cap records);
+// the list and are checked after the others (a pattern's hits come all from
+// the one or all from the other, so each keeps the window order).  Where the
+// records fill device memory, runs are many and long: their pairs of a
+// candidate and a pattern are taken a lane each (6,000 patterns of word text,
+// runs of up to 8, 64 MiB: 371 us, 397 with as many rounds as the longest run
+// of 64 candidates, a lane walking its own); the fewer ones of a table in LDS
+// are walked (1,024 patterns, 1 GiB: 583 us in pairs, 565 walked).  Hits go to the tile's slab (up to cap records);
 // tile_hits counts them all.  Returns the number of candidates (uniform).
 //
 // A wave works alone (no block barrier anywhere in the scan), so its LDS and
@@ -1110,17 +1114,54 @@ __device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketD
     }
     if constexpr (AT != kRecOne) {
       if (nd) wave_lds_fence();
-      for (uint32_t i0 = 0; i0 < nd; i0 += 64) {
-        Looked L[1];
-        uint32_t er[1], raw[1][4];
-        bool ok[1];
-        const uint64_t run = window(i0, nd, er[0], raw[0]).rec;
-        const uint32_t first = (uint32_t)run, count = (uint32_t)(run >> 32);
-        for (uint32_t i = 0; ballot(i < count); ++i) {
-          L[0] = table_record<AT>(D, R, i < count ? first + i : 0);
-          if (i >= count) L[0].rec = 0;
-          verify<AT, 1>(D, R, L, raw, er, sub, start, gtext, ok);
-          emit(ok[0], L[0].rec, er[0]);
+      if constexpr (AT == kRecGlobal) {
+        for (uint32_t i0 = 0; i0 < nd; i0 += 64) {
+          // pairs of a candidate and a pattern of its run, 64 Q at a time, in
+          // the candidates' order
+          uint32_t e, last[4];
+          const uint64_t run = window(i0, nd, e, last).rec;
+          const uint32_t count = (uint32_t)(run >> 32), incl = wave_incl_scan(count);
+          const uint32_t rel = (uint32_t)run - (incl - count);  // record of pair p: rel + p
+          const uint32_t pairs = __builtin_amdgcn_readlane(incl, 63);
+          for (uint32_t p0 = 0; p0 < pairs; p0 += 64 * Q) {
+            Looked L[Q];
+            uint32_t er[Q], raw[Q][4];
+            bool ok[Q];
+  #pragma unroll
+            for (int q = 0; q < Q; ++q) {
+              L[q] = Looked{};
+              er[q] = raw[q][0] = raw[q][1] = raw[q][2] = raw[q][3] = 0;
+              if (q > 0 && p0 + 64 * q >= pairs) continue;
+              const uint32_t p = p0 + 64 * q + lane;
+              // its candidate's lane: the first one whose incl is above p
+              uint32_t o = 0;
+  #pragma unroll
+              for (uint32_t step = 32; step; step >>= 1)
+                o += (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (o + step - 1), (int)incl) <= p ? step : 0;
+              er[q] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * o, (int)e);
+              const uint32_t r = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * o, (int)rel) + p;
+              last_bytes(sub + kFront + er[q], raw[q]);
+              L[q] = table_record<AT>(D, R, p < pairs ? r : 0);
+              if (p >= pairs) L[q].rec = 0;
+            }
+            verify<AT, Q>(D, R, L, raw, er, sub, start, gtext, ok);
+  #pragma unroll
+            for (int q = 0; q < Q; ++q) emit(ok[q], L[q].rec, er[q]);
+          }
+        }
+      } else {
+        for (uint32_t i0 = 0; i0 < nd; i0 += 64) {
+          Looked L[1];
+          uint32_t er[1], raw[1][4];
+          bool ok[1];
+          const uint64_t run = window(i0, nd, er[0], raw[0]).rec;
+          const uint32_t first = (uint32_t)run, count = (uint32_t)(run >> 32);
+          for (uint32_t i = 0; ballot(i < count); ++i) {
+            L[0] = table_record<AT>(D, R, i < count ? first + i : 0);
+            if (i >= count) L[0].rec = 0;
+            verify<AT, 1>(D, R, L, raw, er, sub, start, gtext, ok);
+            emit(ok[0], L[0].rec, er[0]);
+          }
         }
       }
     }
@@ -1215,8 +1256,8 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
       uint64_t first;
       if (p.wave_items) {
         const uint64_t q = r * nw + wave;
-        tleft = q < nlist ? 1u : 0u;
         first = tnext = const64(p.items + (q < nlist ? q : nlist - 1));
+        tleft = q < nlist && first >= p.item_lo && first < p.item_hi ? 1u : 0u;
       } else {
         uint32_t cnt;
         if (p.items) {

@@ -164,3 +164,37 @@ def test_one_exact_pattern_of_every_rotation(ctx, rk, m):
             assert pos.tolist() == ref[1].tolist(), (n, fill)
             off, pos = search(ctx, rk, text, [p, p], "exact")
             assert pos.tolist() == ref[1].tolist() * 2
+
+
+@pytest.mark.parametrize("mode", ["screen", "exact"])
+@pytest.mark.parametrize("runs", [2, 3, 63, 64, 65, 130, 700])
+def test_long_runs_of_records_in_memory(ctx, rk, mode, runs):
+    """Thousands of patterns (records in device memory), among them `runs`
+    that share their last 16 bytes and differ before them, and such runs of
+    two: candidates with few and with many patterns next to each other, more
+    than 64 of them in one sub-tile, overlapping windows, the text's ends."""
+    g = rkgen.rng(85, runs)
+    tail = b"the quick brown "
+    tail2 = b"fox jumped over."
+    heads = [rkgen.LOWER[g.integers(0, 26, size=int(g.integers(1, 30)))].tobytes() for _ in range(runs)]
+    pats = [h + tail for h in dict.fromkeys(heads)]
+    pats += [b"a" + tail2, b"ba" + tail2, b"cba" + tail2]
+    while len(pats) < 3000 + runs:
+        pats.append(rkgen.LOWER[g.integers(0, 26, size=int(g.integers(16, 40)))].tobytes())
+    parts = [pats[0]]
+    for _ in range(900):
+        q = int(g.integers(0, 4))
+        if q == 0:
+            parts.append(pats[int(g.integers(0, len(heads)))])
+        elif q == 1:
+            parts.append(b"cba"[int(g.integers(0, 3)):] + tail2)
+        elif q == 2:
+            parts.append(tail)
+        else:
+            parts.append(rkgen.LOWER[g.integers(0, 26, size=int(g.integers(0, 60)))].tobytes())
+    text = np.frombuffer(b"".join(parts) + pats[1], np.uint8).copy()
+    ref = oracle.search(text, pats, threads=4)
+    assert int(ref[0][-1]) > 300
+    off, pos = search(ctx, rk, text, pats, mode)
+    assert off.tolist() == ref[0].tolist()
+    assert (pos == ref[1]).all()

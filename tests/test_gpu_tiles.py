@@ -110,3 +110,31 @@ def test_batch_of_two_geometries(rk, tmp_path, cap, queue):
             p += 1
     plan.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["screen", "exact"])
+@pytest.mark.parametrize("k", [6000, 150000])
+@pytest.mark.parametrize("cap", [1, 40])
+def test_rescan_of_a_dictionary_of_several_images(rk, mode, k, cap):
+    """Dictionaries whose patterns take several images (some few, and more
+    than are rescanned image by image), with tiles of every image overflowing
+    their slabs and tiles that do not."""
+    g = rkgen.rng(93, k % 97)
+    text = rkgen.iid_text(g, 60011, rkgen.LOWER)
+    text[20000:20200] = ord("q")
+    pats = [b"q" * m for m in (1, 5, 9, 14, 17, 33)]
+    lens = g.integers(1, 41, size=k)
+    at = g.integers(0, len(text) - 41, size=k)
+    for j in range(k - len(pats)):
+        m = max(4, int(lens[j]))
+        pats.append(text[at[j]:at[j] + m].tobytes() if j % 3 else rkgen.LOWER[g.integers(0, 26, size=m)].tobytes())
+    ref = oracle.search(text, pats, threads=8)
+    ctx = rk.Context(0)
+    ctx.set_option(rk._lib.RK_OPT_SLAB_CAP, cap)
+    plan = rk.Plan(ctx, pats, mode)
+    off, pos = plan.search(torch.from_numpy(text).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert off.cpu().numpy().astype(np.uint64).tolist() == ref[0].tolist()
+    assert (pos.cpu().numpy().astype(np.uint64) == ref[1]).all()
+    plan.close()
+    ctx.close()
