@@ -345,7 +345,8 @@ rk_status plan_build(rk_ctx *ctx, const rk_instance *inst, uint32_t count, int m
   return RK_OK;
 }
 
-rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
+// whole: no tiles of a short text's smaller sizes.
+static rk_status layout_of(rk_ctx *ctx, const rk_plan *plan, uint64_t n, bool whole, Layout &L) {
   L = Layout();
   // Staging records per tile: one per 64 text bytes for a single pattern
   // (hits are rare), one per 16 for pattern sets (sampled patterns hit often),
@@ -355,14 +356,18 @@ rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
   // which doubled its time).  A tile with more hits is rescanned by the
   // collect pass.
   const uint32_t per = plan->k_total > 1 ? 16 : 64;
+  // A caller's records per tile are those of the geometry's tile; a lean layout
+  // gives its smaller tiles their share of them.
   auto slots = [&](int cfg, uint32_t W) -> uint32_t {
-    if (ctx->slab_cap) return ctx->slab_cap;
-    return (ctx->lean_slabs ? W : kTileCfgs[cfg].wg * kTileCfgs[cfg].c) / per;
+    const uint32_t whole_tile = kTileCfgs[cfg].wg * kTileCfgs[cfg].c;
+    if (ctx->slab_cap)
+      return ctx->lean_slabs ? std::max(1u, (uint32_t)((uint64_t)ctx->slab_cap * W / whole_tile)) : ctx->slab_cap;
+    return (ctx->lean_slabs ? W : whole_tile) / per;
   };
   // Sizes of one text's tiles: T1 now, but every text up to n fits in the
   // scratch of n (its tiles are smaller when it is short), so room for Tcap
   // tiles and their slabs.
-  uint64_t Tcap = 0, Told = 0, slab_recs = 0;
+  uint64_t Tcap = 0, Told = 0, slab_recs = 0, old_recs = 0;
   if (plan->batch) {
     for (const Part &pt : plan->parts) {
       PartRun r;
@@ -373,21 +378,32 @@ rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
       r.S = slots(pt.cfg, r.W);
       L.parts.push_back(r);
     }
-    Tcap = L.T = plan->total_tiles;
-    Told = Tcap;
+    Tcap = Told = L.T = plan->total_tiles;
+    for (const PartRun &r : L.parts) old_recs += r.ntiles * (uint64_t)r.S;
+    if (ctx->lean_slabs) {
+      Told = old_recs = 0;
+      for (const VInst &v : plan->vinsts) {
+        const uint64_t tile = (uint64_t)kTileCfgs[v.cfg].wg * kTileCfgs[v.cfg].c;
+        const uint64_t tiles = (plan->insts[v.src].n + tile - 1) / tile;
+        Told += tiles;
+        old_recs += tiles * (ctx->slab_cap ? ctx->slab_cap : tile / per);
+      }
+    }
   } else {
     if (n > RK_MAX_N) return set_err(ctx, RK_EUNSUPPORTED, "text longer than 2^40-1 bytes");
     const TileCfg g = kTileCfgs[plan->cfg];
     const uint64_t SUB = 64ull * g.c, most = g.wg / 64, units = (n + SUB - 1) / SUB;
     PartRun r;
-    r.sub = pick_sub(plan->cfg, units);
+    r.sub = whole ? (uint32_t)most : pick_sub(plan->cfg, units);
     r.W = (uint32_t)SUB * r.sub;
     L.T1 = (units + r.sub - 1) / r.sub;
     r.ntiles = L.T = L.T1 * plan->vinsts.size();
     r.S = slots(plan->cfg, r.W);
-    Tcap = std::max(L.T1, std::min(units, 2 * kTilesWanted)) * plan->vinsts.size();
+    // (a lean layout is of this text alone)
+    Tcap = ctx->lean_slabs ? L.T : std::max(L.T1, std::min(units, 2 * kTilesWanted)) * plan->vinsts.size();
     Told = (units + most - 1) / most * plan->vinsts.size();
-    slab_recs = !ctx->slab_cap && ctx->lean_slabs ? Told * (most * SUB / per) : Tcap * r.S;
+    old_recs = Told * (ctx->slab_cap ? ctx->slab_cap : most * SUB / per);
+    slab_recs = Tcap * r.S;
     L.parts.push_back(r);
   }
   uint64_t o = 0;
@@ -412,14 +428,16 @@ rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
   take(Told * 4);
   take(Told * 8);
   take(Told * 8);
-  if (plan->batch) {
-    for (const PartRun &r : L.parts) take(r.ntiles * (uint64_t)r.S * 8);
-  } else {
-    const TileCfg g = kTileCfgs[plan->cfg];
-    take(Told * (ctx->slab_cap ? ctx->slab_cap : (uint64_t)g.wg * g.c / per) * 8);
-  }
+  take(old_recs * 8);
   L.extra = L.total > o ? L.total - o : 0;
   return RK_OK;
+}
+
+rk_status make_layout(rk_ctx *ctx, const rk_plan *plan, uint64_t n, Layout &L) {
+  const rk_status st = layout_of(ctx, plan, n, false, L);
+  // the per-tile arrays of very many images are kept to whole tiles
+  if (st == RK_OK && ctx->lean_slabs && L.extra > kStaticExtra) return layout_of(ctx, plan, n, true, L);
+  return st;
 }
 
 struct WorkLayout {

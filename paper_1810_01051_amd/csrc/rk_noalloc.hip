@@ -23,9 +23,6 @@
 namespace rk {
 
 constexpr uint64_t kStaticScratchBytes = RK_STATIC_SCRATCH_BYTES;
-// Beside the limit that callers see: the per-tile arrays of a short text's
-// smaller tiles (Layout::extra, at most 123 KB an image).
-constexpr uint64_t kStaticExtra = 2u << 20;
 
 static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes + kStaticExtra];
 
@@ -68,7 +65,7 @@ extern "C" rk_status rk_search_static(rk_ctx *ctx, const rk_plan *plan, const ui
   if (r != RK_OK) return r;
   if (L.total - L.extra > kStaticScratchBytes || L.extra > kStaticExtra)
     return set_err(ctx, RK_ENOSPACE, "search needs %llu bytes of scratch, the static array holds %llu",
-                   (unsigned long long)L.total, (unsigned long long)kStaticScratchBytes);
+                   (unsigned long long)(L.total - L.extra), (unsigned long long)kStaticScratchBytes);
   r = count_enqueue(ctx, plan, text_dev, n, base, L.total, nullptr, ctx->pinned, st);
   if (r != RK_OK) return r;
   uint64_t total = 0;
@@ -79,7 +76,7 @@ extern "C" rk_status rk_search_static(rk_ctx *ctx, const rk_plan *plan, const ui
   const uint64_t work = work_bytes_for(plan, total);
   if (work_off - L.extra + work > kStaticScratchBytes)
     return set_err(ctx, RK_ENOSPACE, "collect of %llu hits needs %llu bytes of scratch, the static array holds %llu",
-                   (unsigned long long)total, (unsigned long long)(work_off + work),
+                   (unsigned long long)total, (unsigned long long)(work_off - L.extra + work),
                    (unsigned long long)kStaticScratchBytes);
   return collect_enqueue(ctx, plan, text_dev, n, base, L.total, work ? base + work_off : nullptr, work, offsets_dev,
                          positions_dev, capacity, st);

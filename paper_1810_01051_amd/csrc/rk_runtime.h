@@ -163,6 +163,11 @@ inline uint32_t ovf_total(const uint64_t *ctr) {
   return t;
 }
 
+// What the static scratch array holds beside the limit that callers see: the
+// per-tile arrays of a short text's smaller tiles (Layout::extra: 20 bytes for each
+// tile more, of which an image has at most 8,191).
+constexpr uint64_t kStaticExtra = 2u << 20;
+
 rk_status set_err(rk_ctx *ctx, rk_status st, const char *fmt, ...);
 rk_status hip_err(rk_ctx *ctx, hipError_t e, const char *what);
 inline rk_status hip_err_or_ok(rk_ctx *ctx, hipError_t e) {
