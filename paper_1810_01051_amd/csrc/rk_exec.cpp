@@ -190,13 +190,15 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
   P->img_cap = (uint32_t)align_up(P->img_cap, 16);
   if (!batch && P->vinsts.size() == 1 && P->vinsts[0].nbuckets == 1) {
     memcpy(&P->list_desc, blob.data() + P->vinsts[0].img_off + sizeof(ImageHeader), sizeof(BucketDesc));
-    P->list1 = P->list_desc.kind == kListScreen || P->list_desc.kind == kListExact;
+    P->list_keys = P->vinsts[0].few;
+    P->list1 = P->list_keys.nkeys != 0;
     if (P->list1) {
-      // its one record and tail go to the kernel directly
-      const uint8_t *tab = blob.data() + P->vinsts[0].img_off + P->list_desc.tab_off;
-      memcpy(P->list_tail, tab, 16);
-      memcpy(&P->list_rec1, tab + 16 * P->list_desc.ntab, 8);
+      // its keys go to the kernel directly
+      const bool exact = mode == RK_MODE_EXACT;
+      P->list_desc.kind = exact ? kListExact : kListScreen;
+      memcpy(P->list_desc.tgt, P->list_keys.tgt, sizeof P->list_desc.tgt);
       P->list_desc.shift &= 0xFFFFu;  // (no image in LDS there)
+      P->list_fam = P->list_keys.nkeys == 1 ? P->fam : exact ? kFamExactFew : kFamScreen;
     }
   }
   if (!batch) {
@@ -577,10 +579,15 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
   uint8_t *sc = (uint8_t *)scratch;
   hipError_t e;
   const bool use_queue = ctx->queue == 1 || (ctx->queue == -1 && plan->batch);
-  // one text, one bucket with register targets: the single-bucket kernel,
+  // one text, one bucket with keys in registers: the single-bucket kernel,
   // which takes the text itself (the general kernel reads that of several
-  // instances through their descriptors, uploaded here for it and by a rescan)
-  const bool list = plan->list1 && !use_queue;
+  // instances through their descriptors, uploaded here for it and by a rescan).
+  // Three or four keys want a text of more sub-tiles than the chip takes waves:
+  // where a wave has one sub-tile at most, the time is that of one test pass
+  // alone, and the bitmap's is the shorter (4 keys, 1 MiB: 52 against 55 us a
+  // search, 8 MiB: 54 and 56, 16 MiB: 58 and 58, 64 MiB: 78 and 73).
+  const bool list = plan->list1 && !use_queue &&
+                    (plan->list_keys.nkeys <= 2 || L.T * L.parts[0].sub >= kTilesWanted);
   if (!list) {
     e = upload_insts(plan, L, sc, text, n, s);
     if (e != hipSuccess) return hip_err(ctx, e, "instance upload");
@@ -608,8 +615,9 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     lp.rot = (8u * plan->list_desc.m) % 61u;
     lp.slab_cap = r.S;
     lp.sub = r.sub;
-    memcpy(lp.tail, plan->list_tail, sizeof lp.tail);
-    lp.rec1 = plan->list_rec1;
+    lp.nkeys = plan->list_keys.nkeys;
+    memcpy(lp.tgt2, plan->list_keys.tgt2, sizeof lp.tgt2);
+    memcpy(lp.key, plan->list_keys.key, sizeof lp.key);
     lp.tile_counts = (uint32_t *)(sc + L.counts);
     lp.out = (uint64_t *)(sc + r.slabs);
     lp.ovf_count = (uint32_t *)(sc + L.ctr + kCtrOvf);
@@ -622,13 +630,13 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     uint32_t grid = ctx->grid;
     if (!grid) {
       int blocks = 0;
-      if (list_scan(plan->cfg, plan->fam, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
+      if (list_scan(plan->cfg, plan->list_fam, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
       grid = (uint32_t)ctx->num_cu * (uint32_t)blocks * kListGridMul;
     }
     grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, (L.T + kListBlock / 64 - 1) / (kListBlock / 64)));
     e = prof_begin(ctx, s, 0, &slot);
     if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
-    e = list_scan(plan->cfg, plan->fam, &lp, grid, s, nullptr);
+    e = list_scan(plan->cfg, plan->list_fam, &lp, grid, s, nullptr);
     if (e != hipSuccess) return hip_err(ctx, e, "scan launch");
     e = prof_end(ctx, s, slot);
     if (e != hipSuccess) return hip_err(ctx, e, "profiling event");

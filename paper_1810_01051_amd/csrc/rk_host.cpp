@@ -154,6 +154,7 @@ struct GroupBody {
   bool ids_lds = false;  // ids are in the LDS part
   bool pat_lds = false;  // pattern bytes are in the LDS part
   uint32_t npat = 0, max_m = 0;
+  FewKeys few;
 };
 constexpr uint32_t kIdsLds = 8 * 1024;   // most bytes of ids staged in LDS (a load for every hit of a pattern's 2nd id on)
 constexpr uint32_t kTabLds = 24 * 1024 + 512;  // largest record table staged in LDS (some 1,024 records)
@@ -194,15 +195,23 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
     // every lazy form the rolling state can take
     for (uint64_t s = H; s < (1ull << 62) + (1ull << 11); s += kQ) tkeys.push_back(table ? exact_mix(s) : (uint32_t)s);
   }
+  // exact: the lowest of three consecutive low words of key H times 2^(24-8j),
+  // by the window's place j in its four
+  auto target = [](uint64_t H, uint32_t j) {
+    const uint32_t rot = 24 - 8 * j;
+    return (uint32_t)(((H << rot) & kQ) | H >> (61 - rot)) - 2u;
+  };
+  FewKeys &F = out.few;
+  if (dist.size() <= (G.screen ? kFewScreen : kFewExact)) {
+    F.nkeys = (uint32_t)dist.size();
+    for (uint32_t j = 0; j < 4; ++j) {
+      F.tgt[j] = G.screen ? (uint32_t)dist[j < F.nkeys ? j : 0] : target(dist[0], j);
+      F.tgt2[j] = G.screen ? 0u : target(dist.back(), j);
+    }
+  }
   if (!table) {
     D.kind = G.screen ? kListScreen : kListExact;
-    for (int j = 0; j < 4; ++j) {
-      // exact: the lowest of three consecutive low words of the key times
-      // 2^(24-8j), by the window's place in its four
-      const uint32_t rot = 24 - 8 * j;
-      const uint64_t t = ((dist[0] << rot) & kQ) | dist[0] >> (61 - rot);
-      D.tgt[j] = G.screen ? tkeys[0] : (uint32_t)t - 2u;
-    }
+    memcpy(D.tgt, F.tgt, sizeof D.tgt);
     for (PatRef &r : P) r.at = 0;
   } else {
     D.kind = G.screen ? kTableScreen : kTableExact;
@@ -285,6 +294,16 @@ static bool emit_group(const GroupIn &G, bool tab_lds, GroupBody &out) {
     ++run;
     tab[i].rec = rec_run((uint32_t)tab.size(), (uint32_t)(hi - lo));
     for (size_t q = lo; q < hi; ++q) tab.push_back(ones[q]);
+  }
+  // the record of each of a few keys: that of its patterns' lookup bit
+  for (uint32_t j = 0; F.nkeys && j < kFewScreen; ++j) {
+    const uint64_t key = dist[j < F.nkeys ? j : 0];
+    const auto r = std::find_if(P.begin(), P.end(), [&](const PatRef &p) { return p.key == key; });
+    const auto t = std::find_if(tab.begin(), tab.begin() + nord, [&](const One &o) { return o.at == r->at; });
+    const uint32_t tail = std::min(t->p->m, 16u);
+    F.key[j].lk = r->lk;
+    memcpy((uint8_t *)F.key[j].tail + 16 - tail, t->p->p + t->p->m - tail, tail);
+    F.key[j].rec = t->rec;
   }
   D.ntab = (uint32_t)tab.size();
   std::vector<uint8_t> tb(24 * tab.size(), 0);
@@ -396,6 +415,7 @@ static rk_status build_images(rk_ctx *ctx, const std::vector<GroupIn> &groups, u
     v.max_m = max_m;
     v.npat = npat;
     v.only_one_list = only_one_list;
+    if (j == i + 1) v.few = bodies[i].few;
     blob.resize(v.img_off, 0);
     blob.insert(blob.end(), img.begin(), img.end());
     vinsts.push_back(v);

@@ -175,19 +175,37 @@ struct ScanParams {
   InstDesc one;               // inst == nullptr: the only instance
 };
 
-// Kernel parameters of the single-bucket scan (one text, one bucket whose set
-// sits in registers; count mode).
+// Most keys that the single-bucket scan compares in registers: a compare a
+// window each in screen mode, two operations in exact mode, against a probe of a
+// bitmap and the candidates that pass a small one by chance (1 GiB of letters,
+// patterns of 16 bytes, count and collect: two, three and four screen keys 238,
+// 278 and 319 us, with the bitmap 405; two exact keys 379 and 787.  Where the
+// keys recur, as on word text, four cost up to 515 us and the bitmap 440, three
+// as much as it and two less).
+constexpr uint32_t kFewScreen = 4, kFewExact = 2;
+
+// A key of the single-bucket scan.
+struct FewKey {
+  uint32_t lk;       // its lookup key (shift-add), which tells the candidates apart
+  uint32_t tail[4];  // its record's tail
+  uint32_t pad;
+  uint64_t rec;      // its record
+};
+
+// Kernel parameters of the single-bucket scan (one text, one bucket of a few
+// keys, which sit in registers; count mode).
 struct ListParams {
   const uint8_t *text;        // 16-byte aligned
   uint64_t n;
   uint64_t ntiles;
   const uint8_t *gimg;        // the instance image in device memory (verification tables)
-  BucketDesc D;               // the bucket (offsets relative to gimg)
+  BucketDesc D;               // the bucket (offsets relative to gimg), of a list kind
   uint32_t rot;               // 8 m mod 61
   uint32_t slab_cap;
   uint32_t sub;               // sub-tiles of 64 C bytes per tile
-  uint32_t tail[4];           // the record's tail
-  uint64_t rec1;              // record of the bucket's one key
+  uint32_t nkeys;             // keys (the ones after them repeat the first)
+  uint32_t tgt2[4];           // exact mode: what D.tgt is for the second key
+  FewKey key[kFewScreen];
   uint32_t *tile_counts;
   uint64_t *out;              // slabs [tile][slab_cap]
   uint32_t *ovf_count, *done; // set to zero
@@ -217,6 +235,7 @@ enum Family : int {
   kFamScreen1 = 0,  // list screen buckets only
   kFamScreen = 1,   // every screen kind
   kFamExact = 2,    // every exact kind and the hash dump
+  kFamExactFew = 3, // the single-bucket kernel of two exact keys (of several screen keys: kFamScreen's)
 };
 
 }  // namespace rk

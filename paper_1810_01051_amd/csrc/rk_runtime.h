@@ -31,11 +31,18 @@ struct CountMemo {
 // the length its stream hashes: 0: 1-3, 1: 4-7, 2: 8-15, 3: 16-31, 4: 32-64.
 constexpr int kNumMClass = 5;
 inline int m_class(uint32_t m) { return m < 4 ? 0 : m < 8 ? 1 : m < 16 ? 2 : m < 32 ? 3 : 4; }
-// Pattern-count class of an image: 0: one pattern, 1: 2-4 (register
-// targets), 2: 5-64, 3: more.
+// Pattern-count class of an image: 0: one pattern, 1: 2-4, 2: 5-64, 3: more.
 constexpr int kNumKClass = 4;
 inline int k_class(uint32_t k) { return k <= 1 ? 0 : k <= 4 ? 1 : k <= 64 ? 2 : 3; }
 constexpr int kMaxParts = kNumTileCfg;  // one persistent launch per scan geometry
+
+// The keys of a group of a few, as the single-bucket scan takes them
+// (ListParams); nkeys 0: the group has more.
+struct FewKeys {
+  uint32_t nkeys = 0;
+  uint32_t tgt[4] = {}, tgt2[4] = {};  // screen: the keys; exact: the first's and the second's, by a window's place in four
+  FewKey key[kFewScreen] = {};
+};
 
 struct VInst {
   uint32_t src;       // real instance index
@@ -47,6 +54,7 @@ struct VInst {
   uint32_t npat = 0;   // patterns in the image
   int cfg = 0;         // scan geometry
   bool only_one_list = true;  // every bucket is a list screen with one target
+  FewKeys few;                // of an image of one bucket
 };
 
 // The virtual instances of a plan that share one scan geometry, scanned by
@@ -108,10 +116,10 @@ struct rk_plan {
   int fam = rk::kFamScreen1;
   uint32_t k_total = 0;
   uint32_t img_cap = 0;       // LDS bytes reserved for images (max image size)
-  bool list1 = false;         // one text, one bucket with one key: single-bucket kernel
+  bool list1 = false;         // one text, one bucket with a few keys: single-bucket kernel
+  int list_fam = rk::kFamScreen1;  // its family
   rk::BucketDesc list_desc;   // that bucket
-  uint64_t list_rec1 = 0;     // its key's record
-  uint32_t list_tail[4] = {}; // and tail
+  rk::FewKeys list_keys;      // and its keys
   uint64_t text_bytes = 0;
   uint32_t max_m = 0;         // longest pattern
   std::vector<rk::RealInst> insts;

@@ -342,9 +342,9 @@ __device__ __forceinline__ void any_or(uint64_t &any, uint64_t b) {
   __asm__ volatile("" : "+s"(any));
 }
 
-// One key: the hash of every window compared with it.
-template <int C, int S, bool ANY>
-__device__ __forceinline__ void pass_list_screen(uint32_t mine, uint32_t msk, uint32_t tgt, uint64_t &any,
+// NT keys: the hash of every window compared with each.
+template <int C, int S, bool ANY, int NT>
+__device__ __forceinline__ void pass_list_screen(uint32_t mine, uint32_t msk, const uint32_t *tgt, uint64_t &any,
                                                  Bits<C> &bits) {
   uint32_t w[kWarm + C / 4];
   lds_read_words<kWarm + C / 4>(w, mine - 4 * kWarm);
@@ -352,7 +352,10 @@ __device__ __forceinline__ void pass_list_screen(uint32_t mine, uint32_t msk, ui
 #pragma unroll
   for (int i = 0; i < C; ++i) {
     h = (h << S) + byte_at(w, 4 * kWarm + i);
-    const uint64_t f = ballot(((S == 8) ? (h & msk) : h) == tgt);
+    const uint32_t v = (S == 8) ? (h & msk) : h;
+    uint64_t f = ballot(v == tgt[0]);
+#pragma unroll
+    for (int t = 1; t < NT; ++t) f |= ballot(v == tgt[t]);
     if (ANY) any_or(any, f);
     else put_mask<C>(bits, acc, i, f);
   }
@@ -534,24 +537,25 @@ __device__ __forceinline__ uint64_t rot61_word(uint32_t v, uint32_t r) {
   return rot61(v, r);
 }
 
-// One key of fewer than kStepM bytes: every window's state compared with the
-// key's lazy forms H, H + q, H + 2q, whose low words are consecutive from tg on
-// (q is -1 in 32 bits).
-template <int C, bool ANY, int OUTK>
+// NT keys of fewer than kStepM bytes: every window's state compared with each
+// key's lazy forms H, H + q, H + 2q, whose low words are consecutive from tg
+// (tg2) on (q is -1 in 32 bits).
+template <int C, bool ANY, int OUTK, int NT>
 __device__ __forceinline__ void pass_short_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, uint32_t tg,
-                                                 uint64_t &any, Bits<C> &bits) {
+                                                 uint32_t tg2, uint64_t &any, Bits<C> &bits) {
   uint32_t w[16 + C / 4], d[C / 4 + 1], acc = 0, low = ~0u;
   lds_read_words<16 + C / 4>(w, mine - 64);
   lds_read_words<C / 4 + 1>(d, os.d);
   roll_exact<C, OUTK>(w, d, os, m, r, [&](int i, uint64_t s) __attribute__((always_inline)) {
-    const uint32_t x = (uint32_t)s - tg;
+    uint32_t x = (uint32_t)s - tg;
+    if (NT == 2) x = min(x, (uint32_t)s - tg2);
     if (ANY) low = min(low, x);
     else put_mask<C>(bits, acc, i, ballot(x <= 2u));
   });
   if (ANY) any |= ballot(low <= 2u);
 }
 
-// One key: the hash of every window compared with it, four windows a step.
+// NT keys: the hash of every window compared with each, four windows a step.
 // With Y = 2^32 H for the hash H before the four, I and O the four entering and
 // leaving bytes (the first one on top) and R(x) = x * 256^m mod q, the hash
 // after j + 1 of them is, times 2^(24-8j),
@@ -560,7 +564,8 @@ __device__ __forceinline__ void pass_short_exact(uint32_t mine, OutStream os, ui
 // the rolling state moves once per four windows, and a window costs the low
 // word of X_j: one mask each for I and R(O), one three-way sum.  It is compared
 // with the low word of the key times 2^(24-8j): X_j + q is that plus 0, q or 2q
-// (Y < 2^61 + 2^35), whose low words are consecutive from tg[j] on.
+// (Y < 2^61 + 2^35), whose low words are consecutive from tg[j] (the second
+// key's: tg2[j]) on.
 // s < 2^62 + 2^35 after each step.
 // The low word of X_j is another 32 of the hash's 61 bits for each j, and of a
 // window of few bytes some of these are zero: more of its false matches go on
@@ -569,9 +574,9 @@ __device__ __forceinline__ void pass_short_exact(uint32_t mine, OutStream os, ui
 // and 728, 6 bytes 560 and 520, 8 bytes 560 and 420).
 // Bound by these operations: 8 a window where one 64-bit step per window
 // took 12 (1 GiB, m = 32: 316 us against 434).
-template <int C, bool ANY, int K>
+template <int C, bool ANY, int K, int NT>
 __device__ __forceinline__ void pass_list_exact(uint32_t mine, OutStream os, uint32_t m, uint32_t r, const uint32_t *tg,
-                                                uint64_t &any, Bits<C> &bits) {
+                                                const uint32_t *tg2, uint64_t &any, Bits<C> &bits) {
   uint32_t w[16 + C / 4], d[C / 4 + 1], acc = 0, low = ~0u;
   lds_read_words<16 + C / 4>(w, mine - 64);
   lds_read_words<C / 4 + 1>(d, os.d);
@@ -585,12 +590,16 @@ __device__ __forceinline__ void pass_list_exact(uint32_t mine, OutStream os, uin
     const uint32_t in = __builtin_bswap32(w[16 + i / 4]);
     const uint64_t neg = kQ ^ rot61_word<K>(__builtin_amdgcn_perm(d[i / 4 + 1], d[i / 4], osel), r);
     const uint64_t y = mul2p32_lazy(s);
-    uint32_t x[4];
+    uint32_t v[4], x[4];
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
-      x[j] = (uint32_t)y + (in & (0xFFFFFFFFu << (24 - 8 * j))) + ((uint32_t)neg | keep[j]) - tg[j];
+    for (int j = 0; j < 3; ++j) v[j] = (uint32_t)y + (in & (0xFFFFFFFFu << (24 - 8 * j))) + ((uint32_t)neg | keep[j]);
     s = y + in + neg;
-    x[3] = (uint32_t)s - tg[3];
+    v[3] = (uint32_t)s;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = v[j] - tg[j];
+      if (NT == 2) x[j] = min(x[j], v[j] - tg2[j]);
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (ANY) low = min(low, x[j]);
@@ -644,24 +653,54 @@ __device__ __forceinline__ void pass_dump(uint32_t mine, OutStream os, uint32_t 
 }
 
 // Runs the test pass of bucket D over the lane's windows: ANY=true ORs the
-// wave ballots into any (one-key buckets), ANY=false fills the lane's
-// candidate mask.  D.shift holds the screen shift in bits 0-7; base: LDS
-// address of the bucket's bitmap.
+// wave ballots into any (list kinds), ANY=false fills the lane's candidate
+// mask.  D.shift holds the screen shift in bits 0-7; base: LDS address of the
+// bucket's bitmap.  run_few: a few keys, two to four in kFamScreen and two, the
+// second with tgt2, in kFamExactFew.
+template <int C, bool ANY, int NT>
+__device__ __forceinline__ void run_list_screen(const BucketDesc &D, uint32_t mine, uint64_t &any, Bits<C> &bits) {
+  const uint32_t sh = D.shift & 0xFFu;
+  if (sh == 2) pass_list_screen<C, 2, ANY, NT>(mine, D.mask, D.tgt, any, bits);
+  else if (sh == 3) pass_list_screen<C, 3, ANY, NT>(mine, D.mask, D.tgt, any, bits);
+  else if (sh == 4) pass_list_screen<C, 4, ANY, NT>(mine, D.mask, D.tgt, any, bits);
+  else pass_list_screen<C, 8, ANY, NT>(mine, D.mask, D.tgt, any, bits);
+}
+
+template <int C, bool ANY, int NT>
+__device__ __forceinline__ void run_list_exact(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r,
+                                               const uint32_t *tgt2, uint64_t &any, Bits<C> &bits) {
+  if (D.m < kStepM) {
+    const int k = out_kind(r);
+    if (k == 0) pass_short_exact<C, ANY, 0, NT>(mine, os, D.m, r, D.tgt[3], tgt2[3], any, bits);
+    else if (k == 1) pass_short_exact<C, ANY, 1, NT>(mine, os, D.m, r, D.tgt[3], tgt2[3], any, bits);
+    else pass_short_exact<C, ANY, 2, NT>(mine, os, D.m, r, D.tgt[3], tgt2[3], any, bits);
+  } else {
+    const int k = rot_kind(r);
+    if (k == 0) pass_list_exact<C, ANY, 0, NT>(mine, os, D.m, r, D.tgt, tgt2, any, bits);
+    else if (k == 1) pass_list_exact<C, ANY, 1, NT>(mine, os, D.m, r, D.tgt, tgt2, any, bits);
+    else pass_list_exact<C, ANY, 2, NT>(mine, os, D.m, r, D.tgt, tgt2, any, bits);
+  }
+}
+
+template <int C, bool ANY, int FAM>
+__device__ __forceinline__ void run_few(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r, uint32_t nkeys,
+                                        const uint32_t *tgt2, uint64_t &any, Bits<C> &bits) {
+  if constexpr (FAM == kFamScreen) {
+    if (nkeys == 2) run_list_screen<C, ANY, 2>(D, mine, any, bits);
+    else if (nkeys == 3) run_list_screen<C, ANY, 3>(D, mine, any, bits);
+    else run_list_screen<C, ANY, 4>(D, mine, any, bits);
+  } else {
+    run_list_exact<C, ANY, 2>(D, mine, os, r, tgt2, any, bits);
+  }
+}
+
 template <int C, bool ANY, int FAM>
 __device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r,
                                          uint32_t base, uint64_t &any, Bits<C> &bits) {
   const uint32_t sh = D.shift & 0xFFu;
   if constexpr (FAM == kFamExact) {
-    if ((ANY || D.kind == kListExact) && D.m < kStepM) {
-      const int k = out_kind(r);
-      if (k == 0) pass_short_exact<C, ANY, 0>(mine, os, D.m, r, D.tgt[3], any, bits);
-      else if (k == 1) pass_short_exact<C, ANY, 1>(mine, os, D.m, r, D.tgt[3], any, bits);
-      else pass_short_exact<C, ANY, 2>(mine, os, D.m, r, D.tgt[3], any, bits);
-    } else if (ANY || D.kind == kListExact) {
-      const int k = rot_kind(r);
-      if (k == 0) pass_list_exact<C, ANY, 0>(mine, os, D.m, r, D.tgt, any, bits);
-      else if (k == 1) pass_list_exact<C, ANY, 1>(mine, os, D.m, r, D.tgt, any, bits);
-      else pass_list_exact<C, ANY, 2>(mine, os, D.m, r, D.tgt, any, bits);
+    if (ANY || D.kind == kListExact) {
+      run_list_exact<C, ANY, 1>(D, mine, os, r, D.tgt, any, bits);
     } else {
       const int k = out_kind(r);
       if (k == 0) pass_filter_exact<C, 0>(mine, os, D.m, r, base, D.test_sh, bits);
@@ -670,10 +709,7 @@ __device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, Out
     }
   } else {
     if (ANY || FAM == kFamScreen1 || D.kind == kListScreen) {
-      if (sh == 2) pass_list_screen<C, 2, ANY>(mine, D.mask, D.tgt[0], any, bits);
-      else if (sh == 3) pass_list_screen<C, 3, ANY>(mine, D.mask, D.tgt[0], any, bits);
-      else if (sh == 4) pass_list_screen<C, 4, ANY>(mine, D.mask, D.tgt[0], any, bits);
-      else pass_list_screen<C, 8, ANY>(mine, D.mask, D.tgt[0], any, bits);
+      run_list_screen<C, ANY, 1>(D, mine, any, bits);
     } else {
       if (sh == 2) pass_filter_screen<C, 2, false>(mine, 0, base, D.test_sh, bits);
       else if (sh == 3) pass_filter_screen<C, 3, false>(mine, 0, base, D.test_sh, bits);
@@ -839,16 +875,18 @@ struct Looked {
   rk_u32x4 tail;
 };
 
-// Where a bucket's records are: in the LDS image, in device memory, or only
-// one, held in registers.  The candidate phase is compiled for each, so that
+// Where a bucket's records are: in the LDS image, in device memory, or held in
+// registers: one of one pattern, or those of a few keys (the records of their
+// runs in device memory).  The candidate phase is compiled for each, so that
 // the LDS one holds no load from memory that could be under way: a wait for
 // one would be a wait for every hit stored before it.
-enum RecordPlace { kRecLds, kRecGlobal, kRecOne };
+enum RecordPlace { kRecLds, kRecGlobal, kRecOne, kRecKeys };
 
 struct Records {
   uint32_t img;         // LDS address of the image
   const uint8_t *gimg;  // device image
-  Looked one;
+  uint32_t lk[kFewScreen];  // kRecKeys: lookup keys (those not used repeat the first)
+  Looked held[kFewScreen];  // and their records; kRecOne: the first
 };
 
 // Record i of a bucket's table.
@@ -859,21 +897,32 @@ __device__ __forceinline__ Looked table_record(const BucketDesc &D, const Record
     const uint32_t r = R.img + D.tab_off + 16u * D.ntab + 8u * i;
     L.tail = *(lds_quad *)(uintptr_t)(R.img + D.tab_off + 16u * i);
     L.rec = (uint64_t)lds32(r + 4) << 32 | lds32(r);
-  } else if constexpr (AT == kRecGlobal) {
+  } else {
     L.tail = *(const rk_u32x4 *)(R.gimg + D.tab_off + 16u * i);
     L.rec = *(const uint64_t *)(R.gimg + D.tab_off + 16u * D.ntab + 8u * i);
-  } else {
-    L = R.one;
   }
   return L;
 }
 
 // The record of a bucket for the window whose last 16 bytes are raw: the rank
 // of the window key's bit in the lookup bitmap (rec 0: the bit is not set).
-// One-key buckets hold one record.
+// One-key buckets hold one record; of a few keys in registers a window whose
+// key is none of them gets the first one's, which its bytes do not match.
 template <RecordPlace AT>
 __device__ __forceinline__ Looked bucket_lookup(const BucketDesc &D, const Records &R, const uint32_t (&raw)[4]) {
-  if constexpr (AT == kRecOne) return R.one;
+  if constexpr (AT == kRecOne) return R.held[0];
+  if constexpr (AT == kRecKeys) {
+    const uint32_t v = screen_key(raw, D.shift & 0xFFu, D.mask);
+    Looked L = R.held[0];
+#pragma unroll
+    for (uint32_t j = 1; j < kFewScreen; ++j) {
+      const bool is = v == R.lk[j];
+      L.rec = is ? R.held[j].rec : L.rec;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) L.tail[i] = is ? R.held[j].tail[i] : L.tail[i];
+    }
+    return L;
+  }
   uint32_t ord = 0;
   bool in = true;
   if (D.kind == kTableScreen || D.kind == kTableExact) {
@@ -1114,7 +1163,7 @@ __device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketD
     }
     if constexpr (AT != kRecOne) {
       if (nd) wave_lds_fence();
-      if constexpr (AT == kRecGlobal) {
+      if constexpr (AT == kRecGlobal || AT == kRecKeys) {
         for (uint32_t i0 = 0; i0 < nd; i0 += 64) {
           // pairs of a candidate and a pattern of its run, 64 Q at a time, in
           // the candidates' order
@@ -1346,7 +1395,7 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
         for (int j = 0; j < NB; ++j) bits.b[j] = 0;
         uint64_t dummy = 0;
         run_pass<C, false, FAM>(D, mine, os, r, img + D.test_off, dummy, bits);
-        const Records R{img, gimg, Looked{}};
+        const Records R{img, gimg, {}, {}};
         unsigned long long *const pc = p.direct ? nullptr : p.pid_counts;
         if (D.shift & (1u << 16))
           wave_candidates<C, kRecLds>(bits, D, sub, start, cur.n, R, cand, slab, cap, tile_hits, cur.text, pc);
@@ -1363,16 +1412,17 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
 }
 
 // ------------------------------------------------- single-bucket scan kernel
-// The same scan for the most common plan shape: one text and one bucket with
-// one key (one pattern, or one pattern under several ids).  The bucket
-// descriptor, the text and the key's record come as kernel arguments, tiles
+// The same scan for the most common plan shapes: one text and one bucket with
+// one key (one pattern, or one pattern under several ids) or a few (up to
+// kFewScreen in screen mode, kFewExact in exact mode).  The bucket
+// descriptor, the text and the keys' records come as kernel arguments, tiles
 // are strided statically over the waves of the grid, and there is no image
 // staging, work list or instance lookup, so a sub-tile costs little beyond its
 // hash pass.  Count mode only (hits into per-tile slabs); a tile whose slab
-// overflows is rescanned by the general kernel.
+// overflows is rescanned by the general kernel, from the image's tables.
 //
 // A sub-tile without a candidate is decided by the test pass alone (a compare
-// and a scalar OR per window); after one with candidates the wave runs the
+// and a scalar OR per window and key); after one with candidates the wave runs the
 // mask pass straight away, until a sub-tile has none.  Two slots: the next
 // sub-tile loads while this one is tested.
 //
@@ -1413,23 +1463,32 @@ __global__ __launch_bounds__(kListBlock) void scan_list_kernel(ListParams p) {
           continue;
         }
       }
+      constexpr bool FEW = FAM == kFamScreen || FAM == kFamExactFew;
       uint64_t any = 0;
       if (!dense) {
-        run_pass<C, true, FAM>(D, mine, os, r, 0, any, bits);
+        if constexpr (FEW) run_few<C, true, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
+        else run_pass<C, true, FAM>(D, mine, os, r, 0, any, bits);
         if (any == 0) continue;
       }
 #pragma unroll
       for (int j = 0; j < NB; ++j) bits.b[j] = 0;
-      run_pass<C, false, FAM>(D, mine, os, r, 0, any, bits);
-      const Records R{0, p.gimg, Looked{p.rec1, {p.tail[0], p.tail[1], p.tail[2], p.tail[3]}}};
+      if constexpr (FEW) run_few<C, false, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
+      else run_pass<C, false, FAM>(D, mine, os, r, 0, any, bits);
+      Records R{0, p.gimg, {}, {}};
+#pragma unroll
+      for (uint32_t j = 0; j < (FEW ? kFewScreen : 1); ++j) {
+        R.lk[j] = p.key[j].lk;
+        R.held[j] = Looked{p.key[j].rec, {p.key[j].tail[0], p.key[j].tail[1], p.key[j].tail[2], p.key[j].tail[3]}};
+      }
       uint64_t *const slab = p.out + t * (uint64_t)p.slab_cap;
+      constexpr RecordPlace MANY = FEW ? kRecKeys : kRecGlobal;
       uint32_t nc;
-      if (rec_one_pattern(p.rec1))
+      if (!FEW && rec_one_pattern(p.key[0].rec))
         nc = wave_candidates<C, kRecOne>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
                                          p.pid_counts);
       else
-        nc = wave_candidates<C, kRecGlobal>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
-                                            p.pid_counts);
+        nc = wave_candidates<C, MANY>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
+                                      p.pid_counts);
       dense = nc != 0;
     }
     if (lane == 0 && D.kind != kDump) p.tile_counts[t] = tile_hits;
