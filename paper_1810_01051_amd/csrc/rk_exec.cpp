@@ -694,20 +694,24 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
   return RK_OK;
 }
 
-// The total is read as soon as it is there, which costs less than asking for
-// the stream (the count of a 1 MiB text: 18 against 32 us).  Beyond kSpinUs, far
+// Waits for the pass that was enqueued last on s: for its total, which the host
+// sees in its own memory as soon as it is there, then for the stream, as a call
+// that returns a value leaves it idle.  The event is recorded while the pass
+// runs, so that the stream has its end signalled without another packet after
+// the total (the count of a 1 MiB text: 26.5 us, with the stream's wait alone
+// 29.6, polling hipStreamQuery 46, without the wait 21.3).  Beyond kSpinUs, far
 // more than a count pass of a few GiB takes and no less than a blocking wait
-// adds in wake-up latency, the stream is waited for.
+// adds in wake-up latency, the stream is waited for at once.
 hipError_t wait_total(rk_ctx *ctx, hipStream_t s) {
   constexpr int64_t kSpinUs = 4000;
+  hipError_t e = hipEventRecord(ctx->counted, s);
+  if (e != hipSuccess) return e;
   const auto t0 = std::chrono::steady_clock::now();
   while (__atomic_load_n(&ctx->pinned[kHostTotal], __ATOMIC_ACQUIRE) == kNoTotal)
-    if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) {
-      const hipError_t e = hipStreamSynchronize(s);
-      if (e != hipSuccess) return e;
-      return ctx->pinned[kHostTotal] == kNoTotal ? hipErrorUnknown : hipSuccess;
-    }
-  return hipSuccess;
+    if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) break;
+  e = hipStreamSynchronize(s);
+  if (e == hipSuccess && ctx->pinned[kHostTotal] == kNoTotal) e = hipErrorUnknown;
+  return e;
 }
 
 rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total) {

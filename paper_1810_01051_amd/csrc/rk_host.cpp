@@ -547,6 +547,12 @@ rk_status rk_ctx_create(int device, uint64_t d, uint64_t q, rk_ctx **out) {
     delete c;
     return RK_EDEVICE;
   }
+  if (hipEventCreateWithFlags(&c->counted, hipEventDisableTiming) != hipSuccess) {
+    hipStreamDestroy(c->aux);
+    hipHostFree(c->pinned);
+    delete c;
+    return RK_EDEVICE;
+  }
   for (int md = 0; md < 3; ++md) {
     for (int m = 0; m <= RK_MAX_M; ++m) c->tune[md][m] = -1;
     for (int a = 0; a < kNumMClass; ++a)
@@ -557,6 +563,7 @@ rk_status rk_ctx_create(int device, uint64_t d, uint64_t q, rk_ctx **out) {
   }
   prepare_scan_kernels();
   if (static_scratch_setup(c) != RK_OK) {
+    hipEventDestroy(c->counted);
     hipStreamDestroy(c->aux);
     hipHostFree(c->pinned);
     delete c;
@@ -573,6 +580,7 @@ void rk_ctx_destroy(rk_ctx *ctx) {
     hipEventDestroy(ev.a);
     hipEventDestroy(ev.b);
   }
+  if (ctx->counted) hipEventDestroy(ctx->counted);
   if (ctx->pinned) hipHostFree(ctx->pinned);
   if (ctx->stage) hipHostFree(ctx->stage);
   if (ctx->copy) hipStreamDestroy(ctx->copy);

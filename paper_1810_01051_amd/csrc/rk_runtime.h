@@ -92,6 +92,7 @@ struct rk_ctx {
   bool profile = false;
   int queue = -1;
   uint64_t *pinned = nullptr;  // 4 KiB of pinned host memory for small transfers
+  hipEvent_t counted = nullptr;  // recorded behind a pass whose total the host waits for
   hipStream_t aux = nullptr;   // the context's own non-blocking stream (plan uploads, streamed searches)
   uint8_t *stage = nullptr;    // pinned ring of the streamed searches, from the first one on
   hipStream_t copy = nullptr;  // and their copy stream
@@ -190,7 +191,8 @@ uint64_t work_bytes_for(const rk_plan *plan, uint64_t total);
 rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, uint64_t n, void *scratch,
                         uint64_t scratch_bytes, uint64_t *counts, uint64_t *host, hipStream_t s);
 // A total that a kernel writes to the context's pinned memory as the last
-// thing of its pass: reset before the pass is enqueued, waited for after.
+// thing of its pass: reset before the pass is enqueued, waited for after, with
+// the stream.
 constexpr uint64_t kNoTotal = ~0ull;  // (no count reaches it)
 hipError_t wait_total(rk_ctx *ctx, hipStream_t s);
 rk_status count_finish(rk_ctx *ctx, const rk_plan *plan, void *scratch, hipStream_t s, uint64_t *total);

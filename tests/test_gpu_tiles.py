@@ -138,3 +138,22 @@ def test_rescan_of_a_dictionary_of_several_images(rk, mode, k, cap):
     assert (pos.cpu().numpy().astype(np.uint64) == ref[1]).all()
     plan.close()
     ctx.close()
+
+
+def test_counts_leave_their_stream_idle(rk):
+    """Calls that return a value synchronise the stream they are given."""
+    ctx = rk.Context(0)
+    g = rkgen.rng(87, 0)
+    text = torch.from_numpy(rkgen.iid_text(g, 1 << 20, rkgen.LOWER)).to("cuda:0")
+    flags = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda:0")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for pats in ([b"abcd"], [b"abc", b"de", b"fghijklm"]):
+        plan = rk.Plan(ctx, pats, "screen")
+        for _ in range(20):
+            plan.count(text, stream=stream)
+            assert stream.query()
+            assert ctx.paper_positions(flags, stream=stream).numel() == 0
+            assert stream.query()
+        plan.close()
+    ctx.close()
