@@ -134,3 +134,39 @@ def test_streamed_searches_of_two_threads(rk):
     for t in th:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("source", ["memory", "file"])
+@pytest.mark.parametrize("n,piece", [
+    ((8 << 20) - 1, 256 << 20), (8 << 20, 256 << 20), ((8 << 20) + 1, 256 << 20),
+    # three and more pieces of three chunks, the last of 4 MiB and 16 bytes
+    ((70 << 20) + 11, (20 << 20) + 16),
+    # a whole number of chunks per piece
+    (3 * (16 << 20) + 5, 16 << 20),
+    # the piece before the last one is cut by the text's end: its last chunk of 16 bytes is empty
+    ((16 << 20) + 16 - 63 + (16 << 20) - 10, (16 << 20) + 16),
+    # and a first piece that is
+    ((16 << 20) - 20, (16 << 20) + 16)])
+def test_staging_ring_pieces_of_several_chunks(ctx, rk, tmp_path, source, n, piece):
+    """Chunks of 8 MiB: texts at a chunk's edges, pieces of several chunks and
+    texts of several such pieces, hits at the seams of chunks and pieces; twice,
+    as the ring outlives a call."""
+    pats = [b"ACGTTGCAACGGTACC", b"TTTTTTTTTTTT", rkgen.ACGT[rkgen.rng(95, 0).integers(0, 4, size=64)].tobytes()]
+    text = rkgen.iid_text(rkgen.rng(95, n % 97), n, rkgen.ACGT)
+    L = piece - 63
+    seams = [b + c for b in range(0, n, L) for c in range(0, piece, 8 << 20)] + list(range(L, n, L)) + [n]
+    for i, s in enumerate(seams):
+        for j, d in enumerate((-130, -20, 40)):
+            p = pats[(i + j) % 3]
+            if 0 <= s + d <= n - len(p):
+                text[s + d:s + d + len(p)] = np.frombuffer(p, np.uint8)
+    ro, rp = oracle.search(text, pats, threads=8)
+    if source == "file":
+        path = tmp_path / "text.bin"
+        path.write_bytes(text.tobytes())
+        text = str(path)
+    plan = rk.Plan(ctx, pats, "screen")
+    for _ in range(2):
+        off, pos = plan.search_host(text, piece)
+        assert off.tolist() == ro.tolist() and pos.tolist() == rp.tolist()
+    plan.close()
