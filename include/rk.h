@@ -64,7 +64,11 @@ typedef enum {
 
 /* Scan modes.  Both give identical results.
  *   RK_MODE_EXACT : every window's d=256 / q=2^61-1 hash is rolled and tested
- *                   against the pattern-hash set; equal hashes are byte-checked.
+ *                   against the pattern-hash set: by its low word for one or
+ *                   two hashes, else in a bitmap that a mix of its words
+ *                   addresses, so some other windows pass as well; those that
+ *                   pass are byte-checked against the patterns with their
+ *                   shift-add key (that of the group's shortest length).
  *                   A set whose lengths all agree (one pattern, say) hashes
  *                   whole windows.  Several lengths share one stream per
  *                   length class (1, 2, 3, 4..7, 8..15, 16 and more; a class of
@@ -80,7 +84,8 @@ typedef enum {
  *                   11..15 and 2 from 16 (so the hash covers the last 32/s
  *                   bytes of a window: every pattern of 16 bytes or more shares
  *                   one stream), tested against the set of the patterns' shift-add
- *                   hashes; windows in the set are byte-checked against the
+ *                   hashes (compared for up to four, else in a bitmap);
+ *                   windows that pass are byte-checked against the
  *                   patterns with that hash (the byte check stands in for the
  *                   exact hash, which can only pass what the bytes pass).  A
  *                   true occurrence always passes the test, so no occurrence
@@ -112,14 +117,17 @@ const char *rk_status_string(rk_status s);
 /* Options (rk_ctx_set_option).  Values are read when a plan is created or a
  * scan is launched. */
 typedef enum {
-  RK_OPT_SLAB_CAP = 1,  /* per-tile staging slots for hits (0 = default: tile bytes / 64 for
-                           one pattern, / 16 for pattern sets).  Tiles with more hits are
-                           rescanned by rk_collect. */
+  RK_OPT_SLAB_CAP = 1,  /* per-tile staging slots for hits (0 = default: rk_tile_cfg's tile
+                           bytes / 64 for one pattern, / 16 for pattern sets).  Tiles with more
+                           hits are rescanned by rk_collect.  Texts of fewer than 4,096 tiles
+                           are scanned in smaller ones (down to 64 * windows_per_thread bytes),
+                           each with as many slots; rk_search_static gives them their share. */
   RK_OPT_TILE_CFG = 2,  /* scan geometry index into the built-in table (see rk_tile_cfg);
                            -1 = autotuned / default */
   RK_OPT_GRID = 3,      /* workgroups of the scan, which strides over the tiles (0 = default:
                            32 times as many as are resident on every CU at once for the
-                           single-pattern scan, as many as are resident for the others) */
+                           scan of one pattern or a few, as many as are resident for the
+                           others) */
   RK_OPT_PROFILE = 4,   /* 1: time every scan launch with HIP events (rk_ctx_profile) */
   RK_OPT_QUEUE = 5      /* 1: scan pulls tiles from an atomic work queue; 0: static striding;
                            -1 (default): queue for multi-instance plans only */
@@ -127,7 +135,8 @@ typedef enum {
 rk_status rk_ctx_set_option(rk_ctx *ctx, int option, int64_t value);
 
 /* Scan geometry table entry i (0 <= i < rk_tile_cfg_count()): workgroup size,
- * windows per thread, and tile bytes = wg * windows. */
+ * windows per thread, and tile bytes = wg * windows (the tile of long texts;
+ * shorter ones have smaller tiles). */
 int rk_tile_cfg_count(void);
 rk_status rk_tile_cfg(int i, uint32_t *wg, uint32_t *windows_per_thread, uint32_t *tile_bytes);
 
@@ -158,7 +167,12 @@ uint32_t rk_plan_patterns(const rk_plan *plan);
 /* Bytes of device scratch that rk_count / rk_collect need for a text of n
  * (per-tile staging of hits, which replaces the dense result array of
  * Sec. 3.1)
- * bytes (a function of n, the plan and RK_OPT_SLAB_CAP). */
+ * bytes (a function of n, the plan and RK_OPT_SLAB_CAP): by default some n / 8
+ * for one pattern and n / 2 for a set (of more patterns than one scan of the
+ * text takes, tens of thousands: as much for each scan); for texts of fewer
+ * than 8,192 tiles, which are scanned in smaller ones, up to four (geometries of
+ * 512 threads: eight) times that, as far as 8,192 tiles' worth, 18 and 71 MB
+ * with the first geometry.  The scratch of n serves every shorter text. */
 rk_status rk_scratch_size(rk_ctx *ctx, const rk_plan *plan, uint64_t n, uint64_t *bytes);
 
 /* Count pass (the first half of Sec. 1's problem, "find all occurrences":

@@ -32,15 +32,9 @@ __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_re
 __device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
 
 // Workgroup barrier for LDS traffic only.  __syncthreads() would also wait for
-// every outstanding load-to-LDS of the next tile (the compiler's release fence
-// counts them), which would end the overlap of that tile's loads with the
-// current tile's work; the tile pipeline waits for them explicitly instead.
+// every outstanding load-to-LDS of the next sub-tile (the compiler's release
+// fence counts them), which would end the overlap of its loads with the current
+// one's work; the scans wait for them explicitly instead.
 __device__ __forceinline__ void wg_barrier() { __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// The same after this wave's loads-to-LDS have landed: after it, every wave's
-// share of the tile is visible.
-__device__ __forceinline__ void wg_barrier_loads() {
-  __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 
 }  // namespace rk

@@ -27,8 +27,8 @@ namespace rk {
 // TILES: the counts are a count pass's hits per tile; the total, the
 // overflowed tiles and whether there are any come with the scan (TileTotals),
 // so that a pass needs no counters of its own, no kernel to clear them and no
-// copy to read them back, and the collect finds its offsets there: 33 us for
-// count and collect of a 1 MiB text, 55 us with those.  The flag travels in
+// copy to read them back, and the collect finds its offsets there: 38 us for
+// count and collect of a 1 MiB text, 52 to 57 us with those.  The flag travels in
 // the top bit of a block's sum.
 constexpr int kScanWG = 256;
 constexpr int kScanPer = 16;

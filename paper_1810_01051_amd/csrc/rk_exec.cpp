@@ -699,9 +699,10 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
 // that returns a value leaves it idle.  The event is recorded while the pass
 // runs, so that the stream has its end signalled without another packet after
 // the total (the count of a 1 MiB text: 26.5 us, with the stream's wait alone
-// 29.6, polling hipStreamQuery 46, without the wait 21.3).  Beyond kSpinUs, far
-// more than a count pass of a few GiB takes and no less than a blocking wait
-// adds in wake-up latency, the stream is waited for at once.
+// 29.6, polling hipStreamQuery 46, without the wait 21.3; of a pass that left
+// the L2s full of records the wait includes their write-back, 20 to 30 us).
+// Beyond kSpinUs, far more than a count pass of a few GiB takes and no less than
+// a blocking wait adds in wake-up latency, the stream is waited for at once.
 hipError_t wait_total(rk_ctx *ctx, hipStream_t s) {
   constexpr int64_t kSpinUs = 4000;
   hipError_t e = hipEventRecord(ctx->counted, s);

@@ -12,7 +12,6 @@
 #include <map>
 #include <new>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "../../include/rk.h"

@@ -18,7 +18,6 @@ constexpr uint64_t kPosMask = (1ull << kPosBits) - 1;
 constexpr uint32_t kWaveCand = 256;         // candidate slots in LDS per wave (window index in the sub-tile, u16)
 constexpr uint32_t kListBlock = 256;       // threads of a single-bucket scan's block (its waves are independent)
 constexpr uint32_t kNoLink = 0xFFFFFFFFu;
-constexpr uint64_t kEmptyKey = ~0ull;      // empty exact-table slot (no canonical hash is >= q)
 
 // Screen/test variants of one bucket (one pattern length inside one instance).
 enum BucketKind : uint32_t {

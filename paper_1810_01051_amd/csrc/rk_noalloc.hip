@@ -8,8 +8,8 @@
 // The array is the same on every call on a GPU: each GPU holds one copy (its
 // own address, taken once per device with hipGetSymbolAddress at context
 // creation, with that device current), and it keeps the last call's contents.
-// Counters are cleared by a fill kernel at the start of every count, so no
-// state carries over between calls; calls that overlap on one GPU (two
+// Every count starts from cleared counters (its scan's first block clears them,
+// with a work queue a fill kernel), so no state carries over between calls; calls that overlap on one GPU (two
 // streams, two host threads) race on the array and must be serialised by the
 // caller.
 #include <hip/hip_runtime.h>

@@ -184,8 +184,9 @@ __device__ __forceinline__ uint32_t flag_mask(const uint8_t *flags, uint64_t i, 
 
 // Count of set flags per block of kFlagBlock.  Bound by the read of the
 // flags: 16 bytes per lane, a wave's loads contiguous, the last flags first, as
-// those written last are still in the cache behind the L2 (320 MB: 51 us, 75 us
-// with the first flags first, 0.29 ms with one byte per lane and load).
+// those written last are still in the cache behind the L2 (320 MB: 51 us right
+// after the search that wrote them, 75 us with the first flags first or after
+// other searches, 0.29 ms with one byte per lane and load).
 __global__ __launch_bounds__(kFlagWG) void flag_counts(const uint8_t *flags, uint64_t nf, uint32_t *counts,
                                                        uint32_t *done) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;  // of the scan that follows

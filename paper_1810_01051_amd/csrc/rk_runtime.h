@@ -96,7 +96,6 @@ struct rk_ctx {
   hipStream_t aux = nullptr;   // the context's own non-blocking stream (plan uploads, streamed searches)
   uint8_t *stage = nullptr;    // pinned ring of the streamed searches, from the first one on
   hipStream_t copy = nullptr;  // and their copy stream
-  std::vector<uint8_t> upload; // staging for instance descriptors
   std::vector<rk::ProfEvent> prof_events, free_events;
   int tune[3][RK_MAX_M + 1];
   uint8_t tune_measured[3][RK_MAX_M + 1] = {};
@@ -164,13 +163,6 @@ constexpr uint32_t kCtrBytes = kCtrQueue + kCursors * kCursorStride;
 // What a count pass leaves in pinned host memory: the total and whether any
 // tile overflowed its slab.
 constexpr uint32_t kHostTotal = 0, kHostOvf = 1;
-// Tiles that overflowed their slabs, summed over parts, from the counters.
-inline uint32_t ovf_total(const uint64_t *ctr) {
-  const uint32_t *w = (const uint32_t *)ctr;
-  uint32_t t = 0;
-  for (int p = 0; p < kMaxParts; ++p) t += w[kCtrOvf / 4 + p];
-  return t;
-}
 
 // What the static scratch array holds beside the limit that callers see: the
 // per-tile arrays of a short text's smaller tiles (Layout::extra: 20 bytes for each

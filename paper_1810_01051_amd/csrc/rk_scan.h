@@ -90,8 +90,8 @@ __device__ __forceinline__ uint32_t lds16(uint32_t a) { return *(lds_half *)(uin
 // end the overlap.  The tile words are therefore read by inline asm (pairs of
 // dwords, then one wait for all of them inside the same statement, so that no
 // word is used before it has arrived; the outputs are early-clobber, as the
-// address is still read after the first word is written); the explicit
-// barriers of the pipeline order these reads after the tile has landed.
+// address is still read after the first word is written); the scan's
+// wait_loads orders these reads after the tile has landed.
 typedef uint32_t rk_u32x2 __attribute__((ext_vector_type(2)));
 
 #define RK_DSP1 "ds_read2_b32 %0, %[a] offset0:0 offset1:1\n"
@@ -816,7 +816,7 @@ __device__ __forceinline__ bool quad_equals(uint32_t a, const rk_u32x4 p, int r)
 // every later LDS read wait for all such loads (vmcnt(0)), the reads of the
 // tile being tested included, so that the next tile's loads would no longer
 // overlap its test.  Every read of a slot is ordered after that slot's loads
-// by the tile pipeline's own waits (wg_barrier_loads).
+// by the scan's own waits (wait_loads, wait_lds).
 // (M0 holds the LDS address, placed there by the compiler; the s_nop is the
 // wait state required between a write of M0 and the load that uses it.)  The
 // loads are non-temporal (nt): the text is read once, and streaming it past
