@@ -987,14 +987,6 @@ hipError_t launch_window_hashes(const uint8_t *text, uint64_t n, uint32_t m, con
     case kFamExact * 16 + 3: return ScanGeom<kFamExact, 3>::CALL;     \
     default: return hipErrorInvalidValue;                      \
   }
-#define RK_LIST_DISPATCH(fam, cfg, CALL)                       \
-  switch (fam * 16 + cfg) {                                    \
-    case kFamExactFew * 16 + 0: return ScanGeom<kFamExactFew, 0>::CALL; \
-    case kFamExactFew * 16 + 1: return ScanGeom<kFamExactFew, 1>::CALL; \
-    case kFamExactFew * 16 + 2: return ScanGeom<kFamExactFew, 2>::CALL; \
-    case kFamExactFew * 16 + 3: return ScanGeom<kFamExactFew, 3>::CALL; \
-    default: RK_SCAN_DISPATCH(fam, cfg, CALL)                  \
-  }
 
 hipError_t scan_fit(int cfg, int fam, uint32_t img_cap, uint32_t block, ScanFit *f) {
   RK_SCAN_DISPATCH(fam, cfg, fit(img_cap, block, f))
@@ -1007,18 +999,18 @@ hipError_t launch_scan(int cfg, int fam, const ScanParams &p, uint32_t grid, uin
 // Launches (p != nullptr) or sizes (occupancy into *blocks) the single-bucket
 // scan of geometry cfg and family fam.
 hipError_t list_scan(int cfg, int fam, const ListParams *p, uint32_t grid, hipStream_t s, int *blocks) {
-  RK_LIST_DISPATCH(fam, cfg, list(p, grid, s, blocks))
+  RK_SCAN_DISPATCH(fam, cfg, list(p, grid, s, blocks))
 }
 
 static hipError_t prepare_scan_kernel(int fam, int cfg) { RK_SCAN_DISPATCH(fam, cfg, prepare()) }
-static hipError_t prepare_list_kernel(int fam, int cfg) { RK_LIST_DISPATCH(fam, cfg, list_prepare()) }
+static hipError_t prepare_list_kernel(int fam, int cfg) { RK_SCAN_DISPATCH(fam, cfg, list_prepare()) }
 
 // Raises the dynamic LDS limit of every scan kernel once, outside any stream
 // capture (a graph capture must not run first-time setup calls).
 void prepare_scan_kernels() {
-  for (int fam : {kFamScreen1, kFamScreen, kFamExact, kFamExactFew})
+  for (int fam : {kFamScreen1, kFamScreen, kFamExact})
     for (int cfg = 0; cfg < kNumTileCfg; ++cfg) {
-      if (fam != kFamExactFew) (void)prepare_scan_kernel(fam, cfg);
+      (void)prepare_scan_kernel(fam, cfg);
       (void)prepare_list_kernel(fam, cfg);
     }
 }

@@ -198,7 +198,6 @@ rk_status plan_build_host(rk_ctx *ctx, const rk_instance *inst, uint32_t count, 
       P->list_desc.kind = exact ? kListExact : kListScreen;
       memcpy(P->list_desc.tgt, P->list_keys.tgt, sizeof P->list_desc.tgt);
       P->list_desc.shift &= 0xFFFFu;  // (no image in LDS there)
-      P->list_fam = P->list_keys.nkeys == 1 ? P->fam : exact ? kFamExactFew : kFamScreen;
     }
   }
   if (!batch) {
@@ -630,13 +629,13 @@ rk_status count_enqueue(rk_ctx *ctx, const rk_plan *plan, const uint8_t *text, u
     uint32_t grid = ctx->grid;
     if (!grid) {
       int blocks = 0;
-      if (list_scan(plan->cfg, plan->list_fam, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
+      if (list_scan(plan->cfg, plan->fam, nullptr, 0, nullptr, &blocks) != hipSuccess || blocks < 1) blocks = 1;
       grid = (uint32_t)ctx->num_cu * (uint32_t)blocks * kListGridMul;
     }
     grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(grid, (L.T + kListBlock / 64 - 1) / (kListBlock / 64)));
     e = prof_begin(ctx, s, 0, &slot);
     if (e != hipSuccess) return hip_err(ctx, e, "profiling event");
-    e = list_scan(plan->cfg, plan->list_fam, &lp, grid, s, nullptr);
+    e = list_scan(plan->cfg, plan->fam, &lp, grid, s, nullptr);
     if (e != hipSuccess) return hip_err(ctx, e, "scan launch");
     e = prof_end(ctx, s, slot);
     if (e != hipSuccess) return hip_err(ctx, e, "profiling event");

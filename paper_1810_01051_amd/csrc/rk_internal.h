@@ -234,7 +234,6 @@ enum Family : int {
   kFamScreen1 = 0,  // list screen buckets only
   kFamScreen = 1,   // every screen kind
   kFamExact = 2,    // every exact kind and the hash dump
-  kFamExactFew = 3, // the single-bucket kernel of two exact keys (of several screen keys: kFamScreen's)
 };
 
 }  // namespace rk

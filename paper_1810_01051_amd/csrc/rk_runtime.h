@@ -117,7 +117,6 @@ struct rk_plan {
   uint32_t k_total = 0;
   uint32_t img_cap = 0;       // LDS bytes reserved for images (max image size)
   bool list1 = false;         // one text, one bucket with a few keys: single-bucket kernel
-  int list_fam = rk::kFamScreen1;  // its family
   rk::BucketDesc list_desc;   // that bucket
   rk::FewKeys list_keys;      // and its keys
   uint64_t text_bytes = 0;

@@ -652,11 +652,10 @@ __device__ __forceinline__ void pass_dump(uint32_t mine, OutStream os, uint32_t 
   else pass_dump_w<C, 2>(w, d, os, m, r, e0, n, dst);
 }
 
-// Runs the test pass of bucket D over the lane's windows: ANY=true ORs the
-// wave ballots into any (list kinds), ANY=false fills the lane's candidate
-// mask.  D.shift holds the screen shift in bits 0-7; base: LDS address of the
-// bucket's bitmap.  run_few: a few keys, two to four in kFamScreen and two, the
-// second with tgt2, in kFamExactFew.
+// Runs the test pass of bucket D over the lane's windows, filling the lane's
+// candidate mask; ANY=true (list kinds): the wave ballots ORed into any instead.  D.shift holds the screen shift in bits 0-7; base: LDS address of the
+// bucket's bitmap.  run_few: the single-bucket kernel's keys, two to four in
+// kFamScreen, one or two, the second with tgt2, in kFamExact.
 template <int C, bool ANY, int NT>
 __device__ __forceinline__ void run_list_screen(const BucketDesc &D, uint32_t mine, uint64_t &any, Bits<C> &bits) {
   const uint32_t sh = D.shift & 0xFFu;
@@ -685,22 +684,26 @@ __device__ __forceinline__ void run_list_exact(const BucketDesc &D, uint32_t min
 template <int C, bool ANY, int FAM>
 __device__ __forceinline__ void run_few(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r, uint32_t nkeys,
                                         const uint32_t *tgt2, uint64_t &any, Bits<C> &bits) {
-  if constexpr (FAM == kFamScreen) {
+  if constexpr (FAM == kFamScreen1) {
+    run_list_screen<C, ANY, 1>(D, mine, any, bits);
+  } else if constexpr (FAM == kFamScreen) {
     if (nkeys == 2) run_list_screen<C, ANY, 2>(D, mine, any, bits);
     else if (nkeys == 3) run_list_screen<C, ANY, 3>(D, mine, any, bits);
     else run_list_screen<C, ANY, 4>(D, mine, any, bits);
   } else {
-    run_list_exact<C, ANY, 2>(D, mine, os, r, tgt2, any, bits);
+    if (nkeys == 2) run_list_exact<C, ANY, 2>(D, mine, os, r, tgt2, any, bits);
+    else run_list_exact<C, ANY, 1>(D, mine, os, r, tgt2, any, bits);
   }
 }
 
-template <int C, bool ANY, int FAM>
+template <int C, int FAM>
 __device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, OutStream os, uint32_t r,
-                                         uint32_t base, uint64_t &any, Bits<C> &bits) {
+                                         uint32_t base, Bits<C> &bits) {
   const uint32_t sh = D.shift & 0xFFu;
+  uint64_t any = 0;  // (not used)
   if constexpr (FAM == kFamExact) {
-    if (ANY || D.kind == kListExact) {
-      run_list_exact<C, ANY, 1>(D, mine, os, r, D.tgt, any, bits);
+    if (D.kind == kListExact) {
+      run_list_exact<C, false, 1>(D, mine, os, r, D.tgt, any, bits);
     } else {
       const int k = out_kind(r);
       if (k == 0) pass_filter_exact<C, 0>(mine, os, D.m, r, base, D.test_sh, bits);
@@ -708,8 +711,8 @@ __device__ __forceinline__ void run_pass(const BucketDesc &D, uint32_t mine, Out
       else pass_filter_exact<C, 2>(mine, os, D.m, r, base, D.test_sh, bits);
     }
   } else {
-    if (ANY || FAM == kFamScreen1 || D.kind == kListScreen) {
-      run_list_screen<C, ANY, 1>(D, mine, any, bits);
+    if (FAM == kFamScreen1 || D.kind == kListScreen) {
+      run_list_screen<C, false, 1>(D, mine, any, bits);
     } else {
       if (sh == 2) pass_filter_screen<C, 2, false>(mine, 0, base, D.test_sh, bits);
       else if (sh == 3) pass_filter_screen<C, 3, false>(mine, 0, base, D.test_sh, bits);
@@ -908,14 +911,14 @@ __device__ __forceinline__ Looked table_record(const BucketDesc &D, const Record
 // of the window key's bit in the lookup bitmap (rec 0: the bit is not set).
 // One-key buckets hold one record; of a few keys in registers a window whose
 // key is none of them gets the first one's, which its bytes do not match.
-template <RecordPlace AT>
+template <RecordPlace AT, uint32_t KEYS>
 __device__ __forceinline__ Looked bucket_lookup(const BucketDesc &D, const Records &R, const uint32_t (&raw)[4]) {
   if constexpr (AT == kRecOne) return R.held[0];
   if constexpr (AT == kRecKeys) {
     const uint32_t v = screen_key(raw, D.shift & 0xFFu, D.mask);
     Looked L = R.held[0];
 #pragma unroll
-    for (uint32_t j = 1; j < kFewScreen; ++j) {
+    for (uint32_t j = 1; j < KEYS; ++j) {
       const bool is = v == R.lk[j];
       L.rec = is ? R.held[j].rec : L.rec;
 #pragma unroll
@@ -1041,7 +1044,7 @@ __device__ __forceinline__ void verify(const BucketDesc &D, const Records &R, co
 // memory latencies are covered by the other waves of the CU, whatever they
 // are doing; records and pattern bytes in memory are loaded for 128 candidates
 // at a time.
-template <int C, RecordPlace AT>
+template <int C, RecordPlace AT, uint32_t KEYS = 1>
 __device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketDesc &D, uint32_t sub, uint64_t start,
                                                     uint64_t n, const Records &R, uint32_t cand,
                                                     uint64_t *slab, uint32_t cap, uint32_t &tile_hits,
@@ -1098,7 +1101,7 @@ __device__ __forceinline__ uint32_t wave_candidates(Bits<C> &bits, const BucketD
         __attribute__((always_inline)) -> Looked {
       e_rel = lds16(cand + 2u * min(i + lane, count - 1));
       last_bytes(sub + kFront + e_rel, raw);
-      Looked L = bucket_lookup<AT>(D, R, raw);
+      Looked L = bucket_lookup<AT, KEYS>(D, R, raw);
       if (i + lane >= count) L.rec = 0;
       return L;
     };
@@ -1393,8 +1396,7 @@ __global__ __launch_bounds__(scan_block_max(C, FAM)) void scan_kernel(ScanParams
         Bits<C> bits;
 #pragma unroll
         for (int j = 0; j < NB; ++j) bits.b[j] = 0;
-        uint64_t dummy = 0;
-        run_pass<C, false, FAM>(D, mine, os, r, img + D.test_off, dummy, bits);
+        run_pass<C, FAM>(D, mine, os, r, img + D.test_off, bits);
         const Records R{img, gimg, {}, {}};
         unsigned long long *const pc = p.direct ? nullptr : p.pid_counts;
         if (D.shift & (1u << 16))
@@ -1463,32 +1465,29 @@ __global__ __launch_bounds__(kListBlock) void scan_list_kernel(ListParams p) {
           continue;
         }
       }
-      constexpr bool FEW = FAM == kFamScreen || FAM == kFamExactFew;
       uint64_t any = 0;
       if (!dense) {
-        if constexpr (FEW) run_few<C, true, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
-        else run_pass<C, true, FAM>(D, mine, os, r, 0, any, bits);
+        run_few<C, true, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
         if (any == 0) continue;
       }
 #pragma unroll
       for (int j = 0; j < NB; ++j) bits.b[j] = 0;
-      if constexpr (FEW) run_few<C, false, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
-      else run_pass<C, false, FAM>(D, mine, os, r, 0, any, bits);
+      run_few<C, false, FAM>(D, mine, os, r, p.nkeys, p.tgt2, any, bits);
+      constexpr uint32_t KEYS = FAM == kFamScreen ? kFewScreen : FAM == kFamExact ? kFewExact : 1;
       Records R{0, p.gimg, {}, {}};
 #pragma unroll
-      for (uint32_t j = 0; j < (FEW ? kFewScreen : 1); ++j) {
+      for (uint32_t j = 0; j < KEYS; ++j) {
         R.lk[j] = p.key[j].lk;
         R.held[j] = Looked{p.key[j].rec, {p.key[j].tail[0], p.key[j].tail[1], p.key[j].tail[2], p.key[j].tail[3]}};
       }
       uint64_t *const slab = p.out + t * (uint64_t)p.slab_cap;
-      constexpr RecordPlace MANY = FEW ? kRecKeys : kRecGlobal;
       uint32_t nc;
-      if (!FEW && rec_one_pattern(p.key[0].rec))
+      if (FAM != kFamScreen && p.nkeys == 1 && rec_one_pattern(p.key[0].rec))
         nc = wave_candidates<C, kRecOne>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
                                          p.pid_counts);
       else
-        nc = wave_candidates<C, MANY>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
-                                      p.pid_counts);
+        nc = wave_candidates<C, kRecKeys, KEYS>(bits, D, sub, start, p.n, R, cand, slab, p.slab_cap, tile_hits, p.text,
+                                                p.pid_counts);
       dense = nc != 0;
     }
     if (lane == 0 && D.kind != kDump) p.tile_counts[t] = tile_hits;
